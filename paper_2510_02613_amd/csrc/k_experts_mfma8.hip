@@ -12,11 +12,8 @@
 //    (also out of L2: a copy instruction that touches 16 half lines costs the issuing
 //    wavefront twice one that touches 8 whole lines).  Both operands therefore travel
 //    in steps of 64 k -- one full line per row: 32 KB of weight rows, up to 40 KB of
-//    token rows per step -- through a 2-deep ring each (144 of the 160 KB of LDS: a
-//    third weight step does not fit beside two token steps), with their own loader
-//    wavefronts.  The weight step is issued half way through a K-step's multiply,
-//    between two rounds of token copies (see k_loop: a compute unit returns copies in
-//    issue order).
+//    token rows per step -- through a ring each, as deep as LDS allows for the tile's
+//    number of token rows (see Ring), with their own loader wavefronts.
 //  * A compute unit pulls ~64 B/clk from L2 but retires 4096 bf16 flops/clk, so a
 //    tile must reuse staged bytes >= 64 times: up to 320 token rows x 256 weight
 //    rows gives 114-142 (a 128 x 128 tile gives exactly 64 and is bandwidth bound).
@@ -46,6 +43,8 @@
 // 8-byte writes meet two to a bank) and writes whole contiguous row segments, 16 bytes
 // per lane, so global stores are full cache lines.  The epilogue is instruction bound
 // (3 us of a workgroup): 16-byte rather than 8-byte copies out halve its longest loop.
+#include <type_traits>
+
 #include "moe_internal.h"
 
 namespace emoe {
@@ -62,21 +61,10 @@ constexpr int kMaxTT = 10;                 // token tiles (32 rows) per workgrou
 constexpr int kBM = kMaxTT * 32;           // 320: a whole group with its ragged tail in the usual case
 constexpr int kBKW = 64;                   // weight K-step: 128 bytes per row = one whole cache line
 constexpr int kWStage = kBN * kBKW * 2;    // 32 KB of weight rows per weight step
-constexpr int kXStage = kBM * kBK * 2;     // 40 KB of token rows per K-step
-#ifdef EMOE_TIMING_W3
-constexpr int kNW = 3;                     // TIMING ONLY: a third weight stage, two steps in flight (see kXBase)
-#else
-constexpr int kNW = 2;                     // weight ring depth: one step multiplied, one in flight
-#endif
-constexpr int kNX = 2;                     // token ring depth
+constexpr int kXTile = 32 * kBK * 2;       // 4 KB: a token tile's share of a K-step
 constexpr int kWPieces = kWStage / 1024 / 4;   // 8: 1 KB pieces (8 rows x 128 B) per weight-loader wavefront per weight step
-constexpr int kXPieces = kXStage / 1024 / 4;   // 10: 1 KB pieces (8 rows x 128 B) per token-loader wavefront per K-step
-#ifdef EMOE_TIMING_W3
-constexpr int kXBase = kNW * kWStage - 16384;   // the token stages overlap the third weight stage (it does not fit beside them): garbage results
-#else
-constexpr int kXBase = kNW * kWStage;      // the token ring follows the weight ring
-#endif
-constexpr int kRingBytes = kXBase + kNX * kXStage;
+constexpr int kXPieces = kMaxTT * kXTile / 1024 / 4;   // 10: 1 KB pieces (8 rows x 128 B) per token-loader wavefront per K-step
+constexpr int kLdsBytes = 160 * 1024;      // all of a compute unit's LDS: the rings below, then the epilogue's staging
 constexpr int kXcds = 8;
 constexpr int kMaxPartialSets = 256;        // partial-sum sets the workspace has room for: one round of a 256-unit chip
 constexpr int kTC = kMaxTT / 2;            // token tiles per wavefront
@@ -84,10 +72,8 @@ constexpr int kWT = 2;                     // weight tiles per wavefront
 constexpr int kEpiStride1 = 2 * kWT * 16 + 16;  // GEMM-1: 32 h columns per wavefront, bytes per staged row (rows stay 16-byte aligned)
 constexpr int kEpiStride2 = 2 * kWT * 32 + 16;  // GEMM-2: 64 y columns per wavefront
 constexpr int kEpiBytes = 32 * kEpiStride2;     // one token tile of one wavefront
-constexpr int kLdsBytes = kRingBytes;
-static_assert(kWaves * kEpiBytes <= kRingBytes, "epilogue staging reuses the ring");
-static_assert(kTC == 5, "the dispatch on token tiles per wavefront below lists cases 0..5");
-static_assert(kLdsBytes <= 160 * 1024, "LDS budget");
+static_assert(kWaves * kEpiBytes <= kLdsBytes, "epilogue staging reuses the ring");
+static_assert(kMaxTT == 10, "the dispatch on token tiles below lists 1..10");
 
 // Everything one wavefront needs for its K loop.
 struct WaveCtx {
@@ -95,7 +81,6 @@ struct WaveCtx {
     uint32_t off[kXPieces > kWPieces ? kXPieces : kWPieces];               // this lane's byte offset (from the matrix base) of each piece it stages, k = 0
     uint32_t woff[kBKW / 16], xoff[kBK / 16]; // LDS byte offsets (inside a stage) of this lane's operand rows per sub-step
     int wave, lane, wm, wn, n_tt;
-    uint32_t wkb;                         // EMOE_TIMING_KMAJOR: elements between the k-blocks of a slot
     bool stream_w;                        // this tile's weight rows are read by no other tile: copy them non-temporally
     int xlive;                            // token-loader wavefronts: how many of their pieces hold rows that exist
 };
@@ -136,21 +121,8 @@ __device__ __forceinline__ void dma_piece(const void *base, uint32_t byte_off, u
 // complete in order.
 __device__ __forceinline__ void issue_step(const WaveCtx &c, uint32_t slot_addr, int k0)
 {
-    // Timing-only builds (results are garbage): leave out the weight copies, the token copies or (below) the
-    // multiply, to time what is left; EMOE_TIMING_W3 and EMOE_TIMING_KMAJOR time a third weight stage and a
-    // k-block-major pool without building either.  Off unless the build defines the macro.
-#ifdef EMOE_TIMING_NO_W
-    if (c.wave < 4) return;
-#endif
-#ifdef EMOE_TIMING_NO_X
-    if (c.wave >= 4) return;
-#endif
     if (c.wave < 4) {
-#ifdef EMOE_TIMING_KMAJOR
-        const uint16_t *b = c.wbase + (size_t)(k0 / kBKW) * c.wkb;   // TIMING ONLY: the pool read as if it were [K/64][rows][64]
-#else
         const uint16_t *b = c.wbase + k0;
-#endif
         if (c.stream_w) {
 #pragma unroll
             for (int i = 0; i < kWPieces; ++i) dma_piece<true>(b, c.off[i], slot_addr + (c.wave * kWPieces + i) * 1024);
@@ -193,10 +165,6 @@ __device__ __forceinline__ void wait_loads()
 template <int NTC, typename Mid>
 __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x16 (&acc)[kWT][kTC], Mid mid)
 {
-#ifdef EMOE_TIMING_NO_MUL
-    mid();
-    return;
-#endif
     if constexpr (NTC > 0) {
         constexpr int KS = kBK / 16, STEPS = KS * NTC, D = 2;
         bf16x8 wf[2][kWT], xf[D + 1];
@@ -231,41 +199,71 @@ __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws,
     }
 }
 
-template <int NTC>
+// Ring geometry of a workgroup: NW stages of weight rows (32 KB each), then NX stages of TT token tiles (4 KB
+// each).  What bounds this kernel is how many bytes a compute unit has on their way: a step's copies come back a
+// memory latency after they were issued, so a ring that holds only the next step is a burst and a wait.  The
+// fewer token tiles a workgroup has, the more weight stages fit beside them, and the shorter its multiply --
+// which is what covers the wait -- so the ring is chosen by the tile's size:
+//   1-2 token tiles   4 weight + 4 token stages   three steps in flight
+//   3-4               3 + 4                       two
+//   5-8               3 + 2                       weights two steps ahead
+//   9-10              2 + 2                       one (a third weight stage does not fit)
+// kMid: a weight step is issued half way through a multiply instead of at its start.  A compute unit returns
+// copies in issue order and accepts about 64 KB of them before the issuing wavefronts stand still: with many
+// token tiles the token copies (L2 hits, needed one step later) go first and alone, and the weight copies follow
+// when those have landed.
+// Measured against two stages of each for every size (whole pass, us): Qwen3 shape 333 tokens 279 -> 238, 1000
+// tokens 298 -> 274, 3500 tokens 367 -> 362; DeepSeek-V3-shaped rank 512 tokens 600 -> 517, 2000 tokens
+// 674 -> 597, 6500 tokens 885 -> 839; 1777 routed tokens of the DeepSeek-V2-Lite shape 367 -> 340.
+template <int NW_, int NX_, int TT_, bool kMid_>
+struct Ring {
+    static constexpr int NW = NW_, NX = NX_, XStage = TT_ * kXTile, XBase = NW_ * kWStage;
+    static constexpr bool kMid = kMid_;
+    static_assert(NW_ >= 2 && NX_ >= 2 && XBase + NX_ * XStage <= kLdsBytes, "LDS budget");
+};
+using Ring2 = Ring<4, 4, 2, false>;
+using Ring4 = Ring<3, 4, 4, false>;
+using Ring8 = Ring<3, 2, 8, true>;
+using Ring10 = Ring<2, 2, kMaxTT, true>;
+
+// Wait until at most n of this wavefront's copies are in flight.  n: steps that may stay in flight times copies
+// per step (8 for a weight loader, the token tiles that exist for a token loader); the count is an immediate of
+// the instruction, and a count not listed waits for everything.
+__device__ __forceinline__ void wait_copies(int n)
+{
+    switch (n) {
+    case 1: wait_loads<1>(); break;
+    case 2: wait_loads<2>(); break;
+    case 3: wait_loads<3>(); break;
+    case 4: wait_loads<4>(); break;
+    case 6: wait_loads<6>(); break;
+    case 8: wait_loads<8>(); break;
+    case 16: wait_loads<16>(); break;
+    default: wait_loads<0>(); break;
+    }
+}
+
+// KT K-steps of 64 of this wavefront.  The caller issued the first depth - 1 steps of the ring this wavefront loads.
+template <int NTC, typename R>
 __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, f32x16 (&acc)[kWT][kTC])
 {
-    // KT K-steps of 64.  Both rings are two deep: step kt+1 is copied while step kt is multiplied.  The
-    // caller issued step 0.  Token copies go out right after the barrier, the weight copies half way
-    // through the multiply: a compute unit returns copies in issue order, and token copies (L2 hits)
-    // issued just behind a burst of weight copies would wait out that burst's HBM latency.
     const bool wloader = c.wave < 4;
-    const uint32_t wring = lds_addr(ring), xring = wring + kXBase;
-    int slot = 0;
-#ifdef EMOE_TIMING_W3
-    // TIMING ONLY: weight step kt+2 goes out half way through step kt (the caller issued steps 0 and 1)
-    int ws = 0;
+    const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
+    const int depth = wloader ? R::NW : R::NX, per_step = wloader ? kWPieces : c.xlive;
+    int ws = 0, xs = 0, fill = depth - 1;
     for (int kt = 0; kt < KT; ++kt) {
-        const bool more = kt + 1 < KT;
-        if (wloader && more) wait_loads<kWPieces>(); else wait_loads<0>();   // step kt has landed; kt+1 may be in flight
-        __syncthreads();
-        if (!wloader && more) issue_step(c, xring + (slot ^ 1) * kXStage, (kt + 1) * kBK);
-        const int w2 = ws == 0 ? 2 : ws - 1;    // stage of step kt+2 = stage of step kt-1
-        multiply_stage<NTC>(c, ring + ws * kWStage, ring + kXBase + slot * kXStage, acc,
-                            [&]() { if (wloader && kt + 2 < KT) issue_step(c, wring + w2 * kWStage, (kt + 2) * kBKW); });
-        slot ^= 1;
-        ws = ws == 2 ? 0 : ws + 1;
-    }
-#else
-    for (int kt = 0; kt < KT; ++kt) {
-        wait_loads<0>();   // this wavefront's share of step kt has landed (nothing younger is in flight)
+        wait_copies(min(depth - 2, KT - 1 - kt) * per_step);   // this wavefront's share of step kt has landed
         __syncthreads();   // everyone's share of step kt is in LDS; everyone is done reading step kt-1
-        const bool more = kt + 1 < KT;
-        if (!wloader && more) issue_step(c, xring + (slot ^ 1) * kXStage, (kt + 1) * kBK);
-        multiply_stage<NTC>(c, ring + slot * kWStage, ring + kXBase + slot * kXStage, acc,
-                            [&]() { if (wloader && more) issue_step(c, wring + (slot ^ 1) * kWStage, (kt + 1) * kBKW); });
-        slot ^= 1;
+        auto issue = [&]() {
+            if (kt + depth - 1 >= KT) return;
+            issue_step(c, wloader ? wring + fill * kWStage : xring + fill * R::XStage, (kt + depth - 1) * kBK);
+            fill = fill + 1 == depth ? 0 : fill + 1;
+        };
+        if (!wloader || !R::kMid) issue();
+        multiply_stage<NTC>(c, ring + ws * kWStage, ring + R::XBase + xs * R::XStage, acc, [&]() { if (wloader && R::kMid) issue(); });
+        ws = ws + 1 == R::NW ? 0 : ws + 1;
+        xs = xs + 1 == R::NX ? 0 : xs + 1;
     }
-#endif
 }
 
 // Partial sums of a tile whose contraction is shared out over several workgroups (the tail of a
@@ -328,7 +326,7 @@ __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c,
 // p.partials (phase 2, sum_body below, adds them up).
 // (Letting the last of a tile's workgroups to finish do the adding, in the same launch, was
 // measured and is slower: the device-wide fence it needs costs more than the third launch.)
-template <bool kFirst, int NTC, int kPhase>
+template <bool kFirst, int NTC, int kPhase, typename R>
 __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, char *ring,
                                           float *tile_sets, int part)
 {
@@ -339,7 +337,7 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
         for (int t = 0; t < kTC; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
-    k_loop<NTC>(c, ring, KT, acc);
+    k_loop<NTC, R>(c, ring, KT, acc);
     __syncthreads();  // all operand reads are done: the ring becomes the epilogue staging area
     if (kPhase == 1) {
         float *mine = tile_sets + (size_t)part * kPartialFloats;
@@ -473,12 +471,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     const int w1 = kPhase == 1 ? (int)((long long)(part + 1) * wsteps / n_parts) : wsteps;
     const uint16_t *W = (const uint16_t *)(kFirst ? p.w13 : p.w2) + (size_t)mt.slot * (kFirst ? 2 : 1) * (size_t)p.I * p.H;
     const uint16_t *A = (const uint16_t *)(kFirst ? p.x : p.h);
-#ifdef EMOE_TIMING_KMAJOR
-    c.wkb = (uint32_t)(kFirst ? 2 * p.I : p.H) * kBKW;
-    c.wbase = W + (size_t)w0 * c.wkb;
-#else
     c.wbase = W + w0 * kBKW;      // rows are K-contiguous: the piece offsets below are relative to the range's first k
-#endif
     c.abase = A + w0 * kBKW;
     if (c.wave < 4) {
 #pragma unroll
@@ -495,13 +488,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
             } else {
                 g = min(n0 + row, N - 1);
             }
-#ifdef EMOE_TIMING_KMAJOR
-            // the workgroup's 256 weight rows as one contiguous 32 KB block per k-block (stays inside the slot)
-            (void)g; (void)chunk;
-            c.off[i] = ((uint32_t)min((n0 / BNO) * kBN + row, (kFirst ? 2 * p.I : p.H) - 1) * kBKW + (c.lane & 7) * 8) * 2;
-#else
             c.off[i] = ((uint32_t)g * K + chunk * 8) * 2;
-#endif
         }
     } else {
 #pragma unroll
@@ -525,13 +512,6 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     }
 
     const int KT = w1 - w0;
-    if (kPhase != 2) {
-        const uint32_t wring = lds_addr(ring), xring = wring + kXBase;
-        if (KT > 0) issue_step(c, c.wave < 4 ? wring : xring, 0);
-#ifdef EMOE_TIMING_W3
-        if (KT > 1 && c.wave < 4) issue_step(c, wring + kWStage, kBKW);
-#endif
-    }
     // token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
     // wavefront's work is specialised on that count so that its K loop is straight-line code.
     const int ntc = (c.n_tt - c.wm + 1) >> 1;
@@ -539,14 +519,18 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
         // phase 2 is spread over the token tiles too: a workgroup adds up one per wavefront
         if ((int)blockIdx.y < ntc) sum_body<kFirst>(p, c, mt, n0, N, ring, tile_sets, n_parts, (int)blockIdx.y);
     } else {
-        switch (ntc) {
-        case 5: wave_body<kFirst, 5, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        case 4: wave_body<kFirst, 4, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        case 3: wave_body<kFirst, 3, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        case 2: wave_body<kFirst, 2, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        case 1: wave_body<kFirst, 1, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        default: wave_body<kFirst, 0, kPhase>(p, c, mt, n0, N, KT, ring, tile_sets, part); break;
-        }
+        auto run = [&](auto geometry, auto tiles) {
+            using R = decltype(geometry);
+            const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
+            const int depth = c.wave < 4 ? R::NW : R::NX;
+            for (int s = 0; s < depth - 1 && s < KT; ++s) issue_step(c, c.wave < 4 ? wring + s * kWStage : xring + s * R::XStage, s * kBK);
+            wave_body<kFirst, decltype(tiles)::value, kPhase, R>(p, c, mt, n0, N, KT, ring, tile_sets, part);
+        };
+        using std::integral_constant;
+        if (c.n_tt <= 2)      { if (ntc == 1) run(Ring2{}, integral_constant<int, 1>{}); else run(Ring2{}, integral_constant<int, 0>{}); }
+        else if (c.n_tt <= 4) { if (ntc == 2) run(Ring4{}, integral_constant<int, 2>{}); else run(Ring4{}, integral_constant<int, 1>{}); }
+        else if (c.n_tt <= 8) { if (ntc == 4) run(Ring8{}, integral_constant<int, 4>{}); else if (ntc == 3) run(Ring8{}, integral_constant<int, 3>{}); else run(Ring8{}, integral_constant<int, 2>{}); }
+        else                  { if (ntc == 5) run(Ring10{}, integral_constant<int, 5>{}); else run(Ring10{}, integral_constant<int, 4>{}); }
     }
 }
 

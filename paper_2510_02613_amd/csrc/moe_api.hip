@@ -116,7 +116,7 @@ Layout make_layout(const moe_config_t &c)
     L.n_tiles = take(4);
     // unit lists of the large-tile GEMMs (layers they can serve): one entry per (tile, run of N-slices), in rows of 8
     L.unit_cap = 0;
-    if (c.act_dtype == MOE_BF16 && c.hidden % 64 == 0 && c.inter % 64 == 0 && A >= 48 * S) {
+    if (c.act_dtype == MOE_BF16 && c.hidden % 64 == 0 && c.inter % 64 == 0) {
         const size_t big_tiles = (A + mfma8_tile_rows() - 1) / mfma8_tile_rows() + S;
         const int ns0 = mfma8_n_slices(c.hidden, c.inter, 0), ns1 = mfma8_n_slices(c.hidden, c.inter, 1);
         L.unit_cap = 8 * (size_t)mfma8_grid_rows((int)big_tiles, ns0 > ns1 ? ns0 : ns1);
@@ -596,10 +596,13 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = p.act_bf16 && !routed_ids && T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // large tiles once groups average at least a few MFMA tiles of rows
-    const bool big = mfma && mfma8_supports(p) && (long long)T * p.kk >= 48ll * p.S;
-    // weight streaming when a slot expects only a handful of rows (routed: T*k/E on average)
-    const bool tiny = mfma && !big && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
+    // Weight streaming without LDS when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
+    // large-tile kernels, which stream the weights through deep LDS rings while groups are small.  The 128 x 128
+    // kernels take what those cannot address (contractions that are no whole K-steps).
+    const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
+    const bool tiny = mfma && !(can_big && (long long)T * p.kk >= 48ll * p.S) &&
+                      (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
+    const bool big = can_big && !tiny;
     const int tile_rows = big ? mfma8_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : kGenericTileRows;
     p.max_tiles = (int)(((long long)T * p.kk + tile_rows - 1) / tile_rows) + p.S;
     if (big) {   // the tile-list workgroup also deals the tiles' N-slices to the XCDs, per GEMM
