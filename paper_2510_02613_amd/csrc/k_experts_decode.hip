@@ -51,13 +51,14 @@ constexpr int kBlocks2 = 2;   // 16-row weight blocks per task in GEMM-2
 constexpr int kSplit1 = 4;
 constexpr int kSplit2 = 4;
 
-// Self-derived tiles (GEMM-1 of passes with at most 64 tokens and 64 slots whose selection kernel left per-block
+// Self-derived tiles (GEMM-1 of passes with at most 64 tokens and 256 slots whose selection kernel left per-block
 // slot masks): with so few tokens the offsets / permutation / tile-list kernel is pure latency in front of the
 // weight stream, and everything a GEMM-1 workgroup needs from it follows from 4 count bytes per slot.  So that
-// kernel is not launched: every wavefront adds up the counts itself (lane s = slot s), finds the slot and chunk
-// of its tile with a wavefront scan, and reads its rows' tokens off the slot's block masks; workgroup 0 of the
-// same launch writes the tables that GEMM-2, the combine and the workspace view read, while the others stream.
-constexpr int kSelfMaxSlots = 64, kSelfMaxBlocks = 4;
+// kernel is not launched: every wavefront adds up the counts itself (lane l = up to four consecutive slots), finds
+// the slot and chunk of its tile with a wavefront scan, and reads its rows' tokens off the slot's block masks;
+// workgroup 0 of the same launch writes the tables that GEMM-2, the combine and the workspace view read, while the
+// others stream.
+constexpr int kSelfLaneSlots = 4, kSelfMaxSlots = 64 * kSelfLaneSlots, kSelfMaxBlocks = 4;
 
 // position of the r-th (0-based) set bit of m; m has more than r bits set
 __device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
@@ -78,37 +79,68 @@ __device__ __forceinline__ uint32_t self_counts(const Pass &p, int s, int nb)
     return nb >= 4 ? w : w & ((1u << (8 * nb)) - 1u);
 }
 
+// Lane l of a wavefront: the count bytes of its slots l * spl + i, i < spl = ceil(S / 64), and the sums over all
+// slots up to and including its own (rows in the high half, tiles in the low one).
+struct SelfScan {
+    uint32_t w[kSelfLaneSlots];   // count bytes (one per block of 16 tokens)
+    int own, incl, spl;
+};
+__device__ __forceinline__ int rows_of(uint32_t count_bytes) { return (int)__builtin_amdgcn_sad_u8(count_bytes, 0u, 0u); }
+__device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb)
+{
+    SelfScan r;
+    r.spl = (p.S + 63) >> 6;
+    r.own = 0;
+#pragma unroll
+    for (int i = 0; i < kSelfLaneSlots; ++i) {
+        const int s = lane * r.spl + i;
+        r.w[i] = i < r.spl && s < p.S ? self_counts(p, s, nb) : 0u;
+    }
+#pragma unroll
+    for (int i = 0; i < kSelfLaneSlots; ++i) {
+        const int c = rows_of(r.w[i]);
+        r.own += (c << 16) | ((c + kTileRows - 1) / kTileRows);
+    }
+    r.incl = r.own;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(r.incl, off, 64);
+        if (lane >= off) r.incl += o;
+    }
+    return r;
+}
+
 // Workgroup 0: counts, offsets, tile list (slot order, chunks of kTileRows), permutation and its inverse --
 // the tables of the bookkeeping kernels, for the few-token case.  256 threads.
 __device__ void self_tables(const Pass &p)
 {
-    __shared__ int32_t s_cb[kSelfMaxSlots][kSelfMaxBlocks];   // rows of slot s in block b
+    __shared__ uint32_t s_cb[kSelfMaxSlots];   // count bytes of slot s
     __shared__ int32_t s_off[kSelfMaxSlots];
-    const int tid = threadIdx.x, S = p.S, nb = (p.T + kFusedTokens - 1) / kFusedTokens;
-    if (tid < S) {
-        const uint32_t w = self_counts(p, tid, nb);
+    const int tid = threadIdx.x, nb = (p.T + kFusedTokens - 1) / kFusedTokens;
+    if (tid < 64) {
+        const SelfScan sc = self_scan(p, tid, nb);
+        int row = (sc.incl - sc.own) >> 16, tl = (sc.incl - sc.own) & 0xffff;
 #pragma unroll
-        for (int b = 0; b < kSelfMaxBlocks; ++b) s_cb[tid][b] = (int)((w >> (8 * b)) & 0xffu);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int row = 0, tl = 0;
-        for (int s = 0; s < S; ++s) {
-            const int c = s_cb[s][0] + s_cb[s][1] + s_cb[s][2] + s_cb[s][3];
+        for (int i = 0; i < kSelfLaneSlots; ++i) {
+            const int s = tid * sc.spl + i, c = rows_of(sc.w[i]);
+            if (i >= sc.spl || s >= p.S) continue;
             const int nt = (c + kTileRows - 1) / kTileRows;
+            s_cb[s] = sc.w[i];
+            s_off[s] = row;
             p.counts[s] = c;
             p.offs[s] = row;
-            s_off[s] = row;
-            for (int i = 0; i < nt; ++i, ++tl)
+            for (int j = 0; j < nt; ++j, ++tl)
                 if (tl < p.max_tiles) {
                     MTile mt;
-                    mt.slot = s; mt.row_begin = row + i * kTileRows; mt.rows = min(kTileRows, c - i * kTileRows); mt.single = nt == 1;
+                    mt.slot = s; mt.row_begin = row + j * kTileRows; mt.rows = min(kTileRows, c - j * kTileRows); mt.single = nt == 1;
                     p.tiles[tl] = mt;
                 }
             row += c;
         }
-        p.offs[S] = row;
-        *p.n_tiles = min(tl, p.max_tiles);
+        if (tid == 63) {
+            p.offs[p.S] = sc.incl >> 16;
+            *p.n_tiles = min(sc.incl & 0xffff, p.max_tiles);
+        }
     }
     __syncthreads();
     for (int a = tid; a < p.T * p.kk; a += blockDim.x) {
@@ -116,8 +148,8 @@ __device__ void self_tables(const Pass &p)
         int row = -1;
         if (sr >= 0) {
             const int slot = sr >> 12, rank = sr & 0xfff, t = a / p.kk, b = t / kFusedTokens;
-            row = s_off[slot] + rank;
-            for (int b2 = 0; b2 < b; ++b2) row += s_cb[slot][b2];
+            // rows of the slot in the blocks before the token's
+            row = s_off[slot] + rank + rows_of(s_cb[slot] & ((1u << (8 * b)) - 1u));
             p.perm[row] = t;
         }
         p.inv[a] = row;
@@ -147,20 +179,19 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     int self_token = 0;                                     // kSelf: the token of this lane's row
     if (kSelf) {
         const int nb = (p.T + kFusedTokens - 1) / kFusedTokens, stride = fused_row_stride(nb);
-        // lane s: rows and tiles of slot s, then inclusive sums over the slots (rows in the high half)
-        int c = 0;
-        if (lane < p.S) c = (int)__builtin_amdgcn_sad_u8(self_counts(p, lane, nb), 0u, 0u);
-        const int nt = (c + kTileRows - 1) / kTileRows;
-        int incl = (c << 16) | nt;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(incl, off, 64);
-            if (lane >= off) incl += o;
-        }
-        const unsigned long long owners = __ballot((incl & 0xffff) > tile);
+        const SelfScan sc = self_scan(p, lane, nb);
+        const unsigned long long owners = __ballot((sc.incl & 0xffff) > tile);
         if (owners == 0) return;                            // past the last tile (the same in every wavefront)
-        const int s = __ffsll((long long)owners) - 1;
-        const int before = __shfl(incl - ((c << 16) | nt), s, 64), cs = __shfl(c, s, 64);
+        const int l = __ffsll((long long)owners) - 1;
+        int before = __builtin_amdgcn_readlane(sc.incl - sc.own, l), cs = 0, s = l * sc.spl;
+#pragma unroll
+        for (int i = 0; i < kSelfLaneSlots; ++i) {          // which of the lane's slots (uniform)
+            const int c = rows_of((uint32_t)__builtin_amdgcn_readlane((int)sc.w[i], l)), nt = (c + kTileRows - 1) / kTileRows;
+            if (cs == 0) {
+                if ((before & 0xffff) + nt > tile) { cs = c; s += i; }
+                else before += (c << 16) | nt;
+            }
+        }
         const int chunk = tile - (before & 0xffff);
         mt.slot = s;
         mt.row_begin = (before >> 16) + chunk * kTileRows;
@@ -246,7 +277,7 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
 
 int decode_tile_rows() { return kTileRows; }
 
-// GEMM-1 can derive its tiles itself when the selection kernel left per-block masks for at most 4 blocks and 64 slots
+// GEMM-1 can derive its tiles itself when the selection kernel left per-block masks for at most 4 blocks and 256 slots
 bool decode_self_tiles(const Pass &p)
 {
     return p.fused_hist && p.S <= kSelfMaxSlots && p.T <= kSelfMaxBlocks * kFusedTokens && kSplit1 * kThreads >= 64;

@@ -604,7 +604,13 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
                       (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool big = can_big && !tiny;
     const int tile_rows = big ? mfma8_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : kGenericTileRows;
-    p.max_tiles = (int)(((long long)T * p.kk + tile_rows - 1) / tile_rows) + p.S;
+    // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
+    // tile.  With a token or two most slots have none, and thousands of workgroups that only find out that their
+    // tile does not exist take longer to dispatch than one token's experts take to stream.
+    const long long assigned = (long long)T * p.k + (long long)(shared_end - shared_begin) * p.n_shared;
+    const long long nonempty = assigned < p.S ? assigned : p.S;
+    const long long tiles_most = (assigned + tile_rows - 1) / tile_rows + nonempty;
+    p.max_tiles = (int)(tiles_most < assigned ? tiles_most : assigned);
     if (big) {   // the tile-list workgroup also deals the tiles' N-slices to the XCDs, per GEMM
         p.units[0] = (MUnit *)(ws + l->lay.units[0]);
         p.units[1] = (MUnit *)(ws + l->lay.units[1]);
@@ -622,7 +628,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     mark(MOE_PHASE_GATE);
     if (e == hipSuccess && !routed_ids) e = launch_gate(p, st);
     mark(MOE_PHASE_PERMUTE);
-    // few tokens, few slots: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
+    // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
     p.self_tiles = tiny && !identity && decode_self_tiles(p);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
     mark(MOE_PHASE_GEMM1);

@@ -1,0 +1,49 @@
+"""Expert kernels at the sizes where their dispatch changes: ring geometries of the large-tile kernels by the number
+of token tiles and K-steps, and the few-token path with more slots than a wavefront has lanes."""
+import numpy as np
+import pytest
+
+from workloads import MoEWorkload, block_expert_map
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 192), (192, 128), (320, 256), (512, 320)])
+def test_large_tile_rings_at_every_token_tile_count(hidden, inter):
+    """Slots with 1, 2, 3 ... 10 token tiles of 32 rows, full and with one row in the last, on contractions of 1 to 8
+    K-steps (shorter and longer than every ring is deep): each token has one expert, so the counts are exact."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    counts = [1, 32, 33, 64, 65, 97, 128, 129, 160, 161, 193, 225, 256, 257, 288, 289, 320]
+    tokens = sum(counts)
+    wl = MoEWorkload(name="rings", tokens=tokens, hidden=hidden, inter=inter, n_experts=len(counts), top_k=1, n_slots=len(counts),
+                     n_local=len(counts), act_dtype="bf16", router_dtype="f32", gate="softmax", seed=300 + hidden)
+    g = np.random.Generator(np.random.PCG64(hidden))
+    ids = g.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)[:, None]
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    rows = np.sort(case.layer.view(tokens)["tiles"][:, 2])
+    np.testing.assert_array_equal(rows, np.sort(counts))      # the large-tile kernels ran: a tile per slot
+
+
+@pytest.mark.parametrize("tokens", [1, 17, 64])
+@pytest.mark.parametrize("local", [64, 65, 127, 130, 255])
+def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
+    """1 to 4 slots per lane in the few-token GEMM-1 that derives its tiles itself: output and tables as in the pass
+    with separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="few_many", tokens=tokens, hidden=136, inter=72, n_experts=256, top_k=4, n_slots=local + 1, n_local=local,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", n_shared=1, shared_range=(0, min(tokens, 20)), seed=900 + local)
+    g = np.random.Generator(np.random.PCG64(local))
+    case = Case(wl, expert_map=block_expert_map(256, 0, local, g.permutation(local)))
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
