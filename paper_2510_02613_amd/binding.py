@@ -5,6 +5,7 @@ fails it raises.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional, Sequence
@@ -169,11 +170,22 @@ def moe_layer_create(cfg: MoEConfig, buf: MoEBuffers) -> ctypes.c_void_p:
     return h
 
 
+def i32_array(vals: Sequence[int]):
+    """A sequence of whole numbers as the int32 array the calls take (such an array: unchanged)."""
+    if isinstance(vals, ctypes.Array):
+        return vals
+    try:
+        a = array.array("i", vals)
+    except TypeError:
+        a = array.array("i", [int(v) for v in vals])
+    return (ctypes.c_int32 * len(a)).from_buffer(a)
+
+
 def _i32_array(vals: Optional[Sequence[int]]):
     if vals is None:
         return None, 0
-    vals = [int(v) for v in vals]
-    return (ctypes.c_int32 * len(vals))(*vals), len(vals)
+    a = i32_array(vals)
+    return a, len(a)
 
 
 def moe_set_expert_map(layer, host_map: Sequence[int], host_shared_slots: Optional[Sequence[int]] = None,
@@ -182,7 +194,7 @@ def moe_set_expert_map(layer, host_map: Sequence[int], host_shared_slots: Option
     s, ns = _i32_array(host_shared_slots)
     if ns == 0:
         s = None
-    _check(lib().moe_set_expert_map(layer, m, n, s, ctypes.c_void_p(stream)))
+    _check(lib().moe_set_expert_map(layer, m, n, s, stream))
 
 
 def moe_set_expert_replicas(layer, host_rep_offsets: Sequence[int], host_rep_slots: Sequence[int],
@@ -190,19 +202,19 @@ def moe_set_expert_replicas(layer, host_rep_offsets: Sequence[int], host_rep_slo
     o, no = _i32_array(host_rep_offsets)
     r, nr = _i32_array(host_rep_slots)
     s, ns = _i32_array(host_shared_slots)
-    _check(lib().moe_set_expert_replicas(layer, o, r if nr else None, no - 1, s if ns else None, ctypes.c_void_p(stream)))
+    _check(lib().moe_set_expert_replicas(layer, o, r if nr else None, no - 1, s if ns else None, stream))
 
 
 def moe_forward(layer, x_ptr: int, T: int, out_ptr: int, shared_begin: int = 0, shared_end: int = 0,
                 stream: int = 0, flags: int = 0) -> None:
-    _check(lib().moe_forward(layer, ctypes.c_void_p(x_ptr), T, shared_begin, shared_end,
-                             ctypes.c_void_p(out_ptr), ctypes.c_void_p(stream), flags))
+    _check(lib().moe_forward(layer, x_ptr, T, shared_begin, shared_end,
+                             out_ptr, stream, flags))
 
 
 def moe_forward_routed(layer, x_ptr: int, T: int, ids_ptr: int, w_ptr: int, out_ptr: int,
                        shared_begin: int = 0, shared_end: int = 0, stream: int = 0, flags: int = 0) -> None:
-    _check(lib().moe_forward_routed(layer, ctypes.c_void_p(x_ptr), T, ctypes.c_void_p(ids_ptr), ctypes.c_void_p(w_ptr),
-                                    shared_begin, shared_end, ctypes.c_void_p(out_ptr), ctypes.c_void_p(stream), flags))
+    _check(lib().moe_forward_routed(layer, x_ptr, T, ids_ptr, w_ptr,
+                                    shared_begin, shared_end, out_ptr, stream, flags))
 
 
 def moe_forward_static(cfg: MoEConfig, buf: MoEBuffers, host_map: Sequence[int], host_shared_slots: Optional[Sequence[int]],
@@ -210,14 +222,14 @@ def moe_forward_static(cfg: MoEConfig, buf: MoEBuffers, host_map: Sequence[int],
                        stream: int = 0, flags: int = 0) -> None:
     m, n = _i32_array(host_map)
     s, ns = _i32_array(host_shared_slots)
-    _check(lib().moe_forward_static(ctypes.byref(cfg), ctypes.byref(buf), m, n, s if ns else None, ctypes.c_void_p(x_ptr), T,
-                                    shared_begin, shared_end, ctypes.c_void_p(out_ptr), ctypes.c_void_p(stream), flags))
+    _check(lib().moe_forward_static(ctypes.byref(cfg), ctypes.byref(buf), m, n, s if ns else None, x_ptr, T,
+                                    shared_begin, shared_end, out_ptr, stream, flags))
 
 
 def moe_load_expert(layer, slot: int, src_w13_ptr: int, src_w2_ptr: int, copy_stream: int, serve_stream: int,
                     copy_blocks: int = 0) -> None:
-    _check(lib().moe_load_expert(layer, slot, ctypes.c_void_p(src_w13_ptr), ctypes.c_void_p(src_w2_ptr),
-                                 ctypes.c_void_p(copy_stream), ctypes.c_void_p(serve_stream), copy_blocks))
+    _check(lib().moe_load_expert(layer, slot, src_w13_ptr, src_w2_ptr,
+                                 copy_stream, serve_stream, copy_blocks))
 
 
 def moe_vpool_create(slot_bytes: int, n_vslots: int):

@@ -152,8 +152,10 @@ struct moe_layer {
     Layout lay;
     bool has_map;
     std::vector<int32_t> slot_owner;  // per slot: entry (expert, or E + shared expert) of the active table that uses it, or -1
-    // slot fills that the next map switch has to wait for (one event per fill, reused after the switch)
-    std::vector<hipEvent_t> load_ev;
+    // slot fills that the next map switch has to wait for: one event per copy stream, recorded again by every fill
+    // on that stream (a stream runs its fills in order), the entries reused after the switch
+    struct Fill { hipEvent_t ev; void *stream; };
+    std::vector<Fill> load_ev;
     int n_pending = 0;
     hipEvent_t serve_ev = nullptr;  // "work enqueued on the serving stream so far", recorded per fill
     moe_vpool *vpool[2] = {nullptr, nullptr};  // the page pools under w13 and w2 when the layer was told (moe_layer_bind_vpools)
@@ -258,7 +260,7 @@ void moe_layer_destroy(moe_layer_t *layer)
 {
     if (!layer) return;
     if (layer->prof_on) moe_profile_enable(layer, 0);
-    for (hipEvent_t ev : layer->load_ev) (void)hipEventDestroy(ev);
+    for (const moe_layer::Fill &f : layer->load_ev) (void)hipEventDestroy(f.ev);
     if (layer->serve_ev) (void)hipEventDestroy(layer->serve_ev);
     for (int i = 0; i < 2; ++i)
         if (layer->vpool[i]) vpool_unbind(layer->vpool[i], layer);
@@ -340,7 +342,7 @@ moe_status_t install_table(moe_layer_t *l, std::vector<int32_t> &table, std::vec
     if (backed != MOE_OK) return backed;
     hipError_t e = hipSuccess;
     // slot fills enqueued by moe_load_expert: everything after this switch on hip_stream sees them complete
-    for (int i = 0; i < l->n_pending && e == hipSuccess; ++i) e = hipStreamWaitEvent((hipStream_t)hip_stream, l->load_ev[i], 0);
+    for (int i = 0; i < l->n_pending && e == hipSuccess; ++i) e = hipStreamWaitEvent((hipStream_t)hip_stream, l->load_ev[i].ev, 0);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "waiting for slot fills failed: %s", hipGetErrorString(e));
     l->n_pending = 0;
     e = launch_write_map(dst, table.data(), (int)table.size(), (hipStream_t)hip_stream);
@@ -496,10 +498,12 @@ moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, 
     if (backed != MOE_OK) return backed;
     hipError_t e = hipSuccess;
     if (!l->serve_ev) e = hipEventCreateWithFlags(&l->serve_ev, hipEventDisableTiming);
-    if (e == hipSuccess && (int)l->load_ev.size() == l->n_pending) {
-        hipEvent_t ev = nullptr;
-        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e == hipSuccess) l->load_ev.push_back(ev);
+    int at = 0;
+    while (at < l->n_pending && l->load_ev[at].stream != copy_stream) ++at;
+    if (e == hipSuccess && at == (int)l->load_ev.size()) {
+        moe_layer::Fill f = {nullptr, nullptr};
+        e = hipEventCreateWithFlags(&f.ev, hipEventDisableTiming);
+        if (e == hipSuccess) l->load_ev.push_back(f);
     }
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "hipEventCreate: %s", hipGetErrorString(e));
     // a forward already enqueued on the serving stream may still read the slot under an older map
@@ -508,11 +512,13 @@ moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, 
     const size_t es = esize(c.act_dtype);
     const size_t b13 = 2 * (size_t)c.inter * c.hidden * es, b2 = (size_t)c.hidden * c.inter * es;
     const int blocks = copy_blocks ? copy_blocks : 32;
-    if (e == hipSuccess) e = launch_copy((char *)const_cast<void *>(l->buf.w13) + (size_t)slot * b13, src_w13, b13, blocks, (hipStream_t)copy_stream);
-    if (e == hipSuccess) e = launch_copy((char *)const_cast<void *>(l->buf.w2) + (size_t)slot * b2, src_w2, b2, blocks, (hipStream_t)copy_stream);
-    if (e == hipSuccess) e = hipEventRecord(l->load_ev[l->n_pending], (hipStream_t)copy_stream);
+    if (e == hipSuccess)
+        e = launch_fill_slot((char *)const_cast<void *>(l->buf.w13) + (size_t)slot * b13, src_w13, b13,
+                             (char *)const_cast<void *>(l->buf.w2) + (size_t)slot * b2, src_w2, b2, blocks, (hipStream_t)copy_stream);
+    if (e == hipSuccess) e = hipEventRecord(l->load_ev[at].ev, (hipStream_t)copy_stream);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "slot fill failed: %s", hipGetErrorString(e));
-    l->n_pending++;
+    l->load_ev[at].stream = copy_stream;
+    if (at == l->n_pending) l->n_pending++;
     return MOE_OK;
 }
 

@@ -21,6 +21,12 @@ def _dev(a: np.ndarray, device) -> torch.Tensor:
     return torch.from_numpy(a).to(device)
 
 
+def _stream_ptr(stream: Optional[torch.cuda.Stream], device: torch.device) -> int:
+    """hipStream_t of `stream`, or of the device's current stream (read as a plain handle: building a Stream object
+    costs more than enqueueing a kernel)."""
+    return torch._C._cuda_getCurrentRawStream(device.index) if stream is None else stream.cuda_stream
+
+
 class _DeviceSpan:
     """Names a span of device memory for torch.as_tensor (no copy, no ownership)."""
 
@@ -104,6 +110,8 @@ class MoELayer:
                  select_bias=None, device="cuda:0", w13_pool: Optional[VirtualPool] = None,
                  w2_pool: Optional[VirtualPool] = None):
         self.device = torch.device(device)
+        if self.device.index is None:
+            self.device = torch.device("cuda", torch.cuda.current_device())
         dt = {"f32": B.MOE_F32, "bf16": B.MOE_BF16}
         self.cfg = B.MoEConfig(hidden, inter, n_experts, top_k, n_slots, max_tokens, dt[act_dtype],
                                dt[router_dtype], B.MOE_GATE_SOFTMAX_TOPK if gate == "softmax"
@@ -125,6 +133,7 @@ class MoELayer:
         else:
             assert w2_pool.n_vslots == n_slots and w2_pool.slot_shape == (hidden, inter) and w2_pool.elt == self.elt
             self.w2 = w2_pool.tensor
+        self.slot13, self.slot2 = self.w13.shape[1:], self.w2.shape[1:]   # one expert's tensors
         ws_bytes = B.moe_workspace_bytes(self.cfg)
         self.workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=self.device)
         self.buf = B.MoEBuffers(self.router_w.data_ptr(),
@@ -164,29 +173,31 @@ class MoELayer:
                           serve_stream: Optional[torch.cuda.Stream] = None, copy_blocks: int = 0) -> None:
         """Background fill of a slot that the active map does not use, from device tensors, on copy_stream;
         the next set_expert_map waits for it."""
-        assert w13.dtype == self.elt and w13.is_contiguous() and tuple(w13.shape) == tuple(self.w13.shape[1:])
-        assert w2.dtype == self.elt and w2.is_contiguous() and tuple(w2.shape) == tuple(self.w2.shape[1:])
-        s = torch.cuda.current_stream(self.device) if serve_stream is None else serve_stream
-        B.moe_load_expert(self.handle, slot, w13.data_ptr(), w2.data_ptr(), copy_stream.cuda_stream, s.cuda_stream,
+        assert w13.dtype == self.elt and w13.is_contiguous() and w13.shape == self.slot13
+        assert w2.dtype == self.elt and w2.is_contiguous() and w2.shape == self.slot2
+        s = _stream_ptr(serve_stream, self.device)
+        B.moe_load_expert(self.handle, slot, w13.data_ptr(), w2.data_ptr(), copy_stream.cuda_stream, s,
                           copy_blocks)
 
     # -- placement -----------------------------------------------------------
     def set_expert_map(self, expert_map: Sequence[int], shared_slots: Optional[Sequence[int]] = None,
                        stream: Optional[torch.cuda.Stream] = None) -> None:
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
-        B.moe_set_expert_map(self.handle, list(expert_map),
-                             None if shared_slots is None or len(shared_slots) == 0 else list(shared_slots), s.cuda_stream)
-        self.plain_map = ([int(v) for v in expert_map], None if shared_slots is None or len(shared_slots) == 0 else [int(v) for v in shared_slots])
+        s = _stream_ptr(stream, self.device)
+        # the placement as arrays of the call's type, kept for forward_static
+        m = B.i32_array(expert_map)
+        sh = None if shared_slots is None or len(shared_slots) == 0 else B.i32_array(shared_slots)
+        B.moe_set_expert_map(self.handle, m, sh, s)
+        self.plain_map = (m, sh)
 
     def set_expert_replicas(self, replicas: Sequence[Sequence[int]], shared_slots: Optional[Sequence[int]] = None,
                             stream: Optional[torch.cuda.Stream] = None) -> None:
         """Placement with copies: replicas[e] lists the slots holding expert e (empty: on another rank)."""
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
+        s = _stream_ptr(stream, self.device)
         offs = [0]
         for r in replicas:
             offs.append(offs[-1] + len(r))
         B.moe_set_expert_replicas(self.handle, offs, [int(v) for r in replicas for v in r],
-                                  None if shared_slots is None or len(shared_slots) == 0 else list(shared_slots), s.cuda_stream)
+                                  None if shared_slots is None or len(shared_slots) == 0 else list(shared_slots), s)
 
     # -- forward -------------------------------------------------------------
     def upload(self, x: np.ndarray) -> torch.Tensor:
@@ -198,9 +209,9 @@ class MoELayer:
         T = x.shape[0]
         if out is None:
             out = torch.empty_like(x)
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
+        s = _stream_ptr(stream, self.device)
         B.moe_forward(self.handle, x.data_ptr(), T, out.data_ptr(), int(shared_range[0]),
-                      int(shared_range[1]), s.cuda_stream, flags)
+                      int(shared_range[1]), s, flags)
         return out
 
     def forward_static(self, x: torch.Tensor, out: Optional[torch.Tensor] = None, shared_range=(0, 0),
@@ -210,10 +221,10 @@ class MoELayer:
         assert x.dtype == self.elt and x.is_contiguous() and x.shape[1] == self.cfg.hidden
         if out is None:
             out = torch.empty_like(x)
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
+        s = _stream_ptr(stream, self.device)
         buf = B.MoEBuffers(self.buf.router_w, self.buf.logit_bias, self.buf.select_bias, self.buf.w13, self.buf.w2, 0, 0)
         B.moe_forward_static(self.cfg, buf, self.plain_map[0], self.plain_map[1], x.data_ptr(), x.shape[0], out.data_ptr(),
-                             int(shared_range[0]), int(shared_range[1]), s.cuda_stream, flags)
+                             int(shared_range[0]), int(shared_range[1]), s, flags)
         return out
 
     def forward_routed(self, x: torch.Tensor, topk_ids: torch.Tensor, topk_w: torch.Tensor,
@@ -227,9 +238,9 @@ class MoELayer:
         assert topk_ids.device == x.device and topk_w.device == x.device
         if out is None:
             out = torch.empty_like(x)
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
+        s = _stream_ptr(stream, self.device)
         B.moe_forward_routed(self.handle, x.data_ptr(), T, topk_ids.data_ptr(), topk_w.data_ptr(), out.data_ptr(),
-                             int(shared_range[0]), int(shared_range[1]), s.cuda_stream, flags)
+                             int(shared_range[0]), int(shared_range[1]), s, flags)
         return out
 
     # -- intermediates (tests) -------------------------------------------------
