@@ -19,6 +19,7 @@
 // The next chunk's loads are in flight during the current chunk's MFMAs; with 4
 // wavefronts per SIMD that keeps more than 128 KB per compute unit on its way from HBM.
 #include "moe_internal.h"
+#include "self_tiles.h"
 
 namespace emoe {
 namespace {
@@ -51,111 +52,6 @@ constexpr int kBlocks2 = 2;   // 16-row weight blocks per task in GEMM-2
 constexpr int kSplit1 = 4;
 constexpr int kSplit2 = 4;
 
-// Self-derived tiles (GEMM-1 of passes with at most 64 tokens and 256 slots whose selection kernel left per-block
-// slot masks): with so few tokens the offsets / permutation / tile-list kernel is pure latency in front of the
-// weight stream, and everything a GEMM-1 workgroup needs from it follows from 4 count bytes per slot.  So that
-// kernel is not launched: every wavefront adds up the counts itself (lane l = up to four consecutive slots), finds
-// the slot and chunk of its tile with a wavefront scan, and reads its rows' tokens off the slot's block masks;
-// workgroup 0 of the same launch writes the tables that GEMM-2, the combine and the workspace view read, while the
-// others stream.
-constexpr int kSelfLaneSlots = 4, kSelfMaxSlots = 64 * kSelfLaneSlots, kSelfMaxBlocks = 4;
-
-// position of the r-th (0-based) set bit of m; m has more than r bits set
-__device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
-{
-    int pos = 0;
-#pragma unroll
-    for (int w = 32; w >= 1; w >>= 1) {
-        const int cnt = __popcll(m & ((1ull << w) - 1ull));
-        if (r >= cnt) { r -= cnt; m >>= w; pos += w; }
-    }
-    return pos;
-}
-
-// the count bytes of slot s that exist (blocks past nb hold nothing defined)
-__device__ __forceinline__ uint32_t self_counts(const Pass &p, int s, int nb)
-{
-    const uint32_t w = *(const uint32_t *)(p.blk_cnt + (size_t)s * fused_row_stride(nb));
-    return nb >= 4 ? w : w & ((1u << (8 * nb)) - 1u);
-}
-
-// Lane l of a wavefront: the count bytes of its slots l * spl + i, i < spl = ceil(S / 64), and the sums over all
-// slots up to and including its own (rows in the high half, tiles in the low one).
-struct SelfScan {
-    uint32_t w[kSelfLaneSlots];   // count bytes (one per block of 16 tokens)
-    int own, incl, spl;
-};
-__device__ __forceinline__ int rows_of(uint32_t count_bytes) { return (int)__builtin_amdgcn_sad_u8(count_bytes, 0u, 0u); }
-__device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb)
-{
-    SelfScan r;
-    r.spl = (p.S + 63) >> 6;
-    r.own = 0;
-#pragma unroll
-    for (int i = 0; i < kSelfLaneSlots; ++i) {
-        const int s = lane * r.spl + i;
-        r.w[i] = i < r.spl && s < p.S ? self_counts(p, s, nb) : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < kSelfLaneSlots; ++i) {
-        const int c = rows_of(r.w[i]);
-        r.own += (c << 16) | ((c + kTileRows - 1) / kTileRows);
-    }
-    r.incl = r.own;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int o = __shfl_up(r.incl, off, 64);
-        if (lane >= off) r.incl += o;
-    }
-    return r;
-}
-
-// Workgroup 0: counts, offsets, tile list (slot order, chunks of kTileRows), permutation and its inverse --
-// the tables of the bookkeeping kernels, for the few-token case.  256 threads.
-__device__ void self_tables(const Pass &p)
-{
-    __shared__ uint32_t s_cb[kSelfMaxSlots];   // count bytes of slot s
-    __shared__ int32_t s_off[kSelfMaxSlots];
-    const int tid = threadIdx.x, nb = (p.T + kFusedTokens - 1) / kFusedTokens;
-    if (tid < 64) {
-        const SelfScan sc = self_scan(p, tid, nb);
-        int row = (sc.incl - sc.own) >> 16, tl = (sc.incl - sc.own) & 0xffff;
-#pragma unroll
-        for (int i = 0; i < kSelfLaneSlots; ++i) {
-            const int s = tid * sc.spl + i, c = rows_of(sc.w[i]);
-            if (i >= sc.spl || s >= p.S) continue;
-            const int nt = (c + kTileRows - 1) / kTileRows;
-            s_cb[s] = sc.w[i];
-            s_off[s] = row;
-            p.counts[s] = c;
-            p.offs[s] = row;
-            for (int j = 0; j < nt; ++j, ++tl)
-                if (tl < p.max_tiles) {
-                    MTile mt;
-                    mt.slot = s; mt.row_begin = row + j * kTileRows; mt.rows = min(kTileRows, c - j * kTileRows); mt.single = nt == 1;
-                    p.tiles[tl] = mt;
-                }
-            row += c;
-        }
-        if (tid == 63) {
-            p.offs[p.S] = sc.incl >> 16;
-            *p.n_tiles = min(sc.incl & 0xffff, p.max_tiles);
-        }
-    }
-    __syncthreads();
-    for (int a = tid; a < p.T * p.kk; a += blockDim.x) {
-        const int sr = p.slot_rank[a];
-        int row = -1;
-        if (sr >= 0) {
-            const int slot = sr >> 12, rank = sr & 0xfff, t = a / p.kk, b = t / kFusedTokens;
-            // rows of the slot in the blocks before the token's
-            row = s_off[slot] + rank + rows_of(s_cb[slot] & ((1u << (8 * b)) - 1u));
-            p.perm[row] = t;
-        }
-        p.inv[a] = row;
-    }
-}
-
 template <bool kFirst, bool kSelf = false>
 __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) void k_expert_decode(Pass p)
 {
@@ -170,7 +66,7 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     const int ks = NS > 1 ? (int)(threadIdx.x >> 6) : 0;    // which part of the contraction
     int task = blockIdx.x;
     if (kSelf) {
-        if (task == 0) { self_tables(p); return; }
+        if (task == 0) { self_tables(p, kTileRows); return; }
         task -= 1;
     }
     const int tile = task / groups;
@@ -178,29 +74,10 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     MTile mt;
     int self_token = 0;                                     // kSelf: the token of this lane's row
     if (kSelf) {
-        const int nb = (p.T + kFusedTokens - 1) / kFusedTokens, stride = fused_row_stride(nb);
-        const SelfScan sc = self_scan(p, lane, nb);
-        const unsigned long long owners = __ballot((sc.incl & 0xffff) > tile);
-        if (owners == 0) return;                            // past the last tile (the same in every wavefront)
-        const int l = __ffsll((long long)owners) - 1;
-        int before = __builtin_amdgcn_readlane(sc.incl - sc.own, l), cs = 0, s = l * sc.spl;
-#pragma unroll
-        for (int i = 0; i < kSelfLaneSlots; ++i) {          // which of the lane's slots (uniform)
-            const int c = rows_of((uint32_t)__builtin_amdgcn_readlane((int)sc.w[i], l)), nt = (c + kTileRows - 1) / kTileRows;
-            if (cs == 0) {
-                if ((before & 0xffff) + nt > tile) { cs = c; s += i; }
-                else before += (c << 16) | nt;
-            }
-        }
-        const int chunk = tile - (before & 0xffff);
-        mt.slot = s;
-        mt.row_begin = (before >> 16) + chunk * kTileRows;
-        mt.rows = min(kTileRows, cs - chunk * kTileRows);
-        mt.single = cs <= kTileRows;
-        // the slot's tokens, ascending: bit t of the block masks side by side
-        unsigned long long m = 0;
-        for (int b = 0; b < nb; ++b) m |= (unsigned long long)((uint32_t)p.blk_hist[(size_t)s * stride + b] & 0xffffu) << (16 * b);
-        self_token = nth_set_bit(m, chunk * kTileRows + min(n, mt.rows - 1));
+        unsigned long long tokens;
+        int first;
+        if (!self_tile(p, lane, tile, kTileRows, &mt, &tokens, &first)) return;
+        self_token = nth_set_bit(tokens, first + min(n, mt.rows - 1));
     } else {
         if (tile >= *p.n_tiles) return;
         mt = p.tiles[tile];
@@ -276,12 +153,6 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
 }  // namespace
 
 int decode_tile_rows() { return kTileRows; }
-
-// GEMM-1 can derive its tiles itself when the selection kernel left per-block masks for at most 4 blocks and 256 slots
-bool decode_self_tiles(const Pass &p)
-{
-    return p.fused_hist && p.S <= kSelfMaxSlots && p.T <= kSelfMaxBlocks * kFusedTokens && kSplit1 * kThreads >= 64;
-}
 
 hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
 {

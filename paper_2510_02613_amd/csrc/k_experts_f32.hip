@@ -1,0 +1,184 @@
+// Grouped SwiGLU expert GEMMs of fp32 layers on the fp32 matrix cores.
+//
+// The same computation as the bf16 kernels (the expert FFN of Sec. 2.1 of the paper over slot-grouped rows; the
+// slot comes from the M-tile list or, for few tokens, from the selection kernel's block masks), every product a
+// true fp32 product, fp32 accumulation.
+//
+// What bounds it: a layer of a few megabytes is latency, a chain of memory round trips per launch, so as many of a
+// task's loads as possible go out together; large batches are bound by the fp32 matrix rate.  A task is 16 gate rows
+// and the 16 matching up rows (GEMM-1) or 32 W2 rows (GEMM-2) of one M-tile, one workgroup of four wavefronts that
+// each walk a quarter of the contraction; the four sums are added in K order through LDS.  Operands go straight from
+// global memory into the layout of v_mfma_f32_16x16x4_f32: lane (n = l % 16, q = l / 16) reads 16 bytes, k = 4q .. 4q+3,
+// of row n per 16 k, and the contraction does not care that MFMA i takes element i of every lane as long as weight
+// and token rows agree.  A tile has up to 64 token rows, which a weight row read once serves; the next 32 k are
+// in flight while 32 are multiplied.
+// Measured against 32 x 64 tiles staged through LDS without overlap: 64 tokens of the 128 x 64 layer, GEMM-1 21 -> 5 us;
+// 1500 tokens of a 264 x 264 layer, GEMM-1 99 -> 18 us, GEMM-2 65 -> 12 us.
+#include "moe_internal.h"
+#include "self_tiles.h"
+
+namespace emoe {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kSplit = 4;         // wavefronts that share a task's contraction
+constexpr int kKC = 32;           // k per chunk: 128 bytes of every row
+constexpr int kWRows = 32;        // weight rows per task
+
+struct Run { f32x4 v[kKC / 16]; };   // a lane's share of one row of a chunk
+
+__device__ __forceinline__ void load_run(Run &r, const float *row, int k0, int q, int K)
+{
+#pragma unroll
+    for (int j = 0; j < kKC / 16; ++j) {
+        const int k = k0 + j * 16 + q * 4;
+        r.v[j] = k < K ? *(const f32x4 *)(row + k) : (f32x4){0.f, 0.f, 0.f, 0.f};   // K % 8 == 0
+    }
+}
+
+// The part of a task behind the tile lookup, for a tile with up to NT groups of 16 rows; src: this lane's row of x or h
+// per group.
+template <bool kFirst, int NT, int TT>
+__device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int n0, const int (&src)[TT], f32x4 *part)
+{
+    const int K = kFirst ? p.H : p.I, N = kFirst ? p.I : p.H;
+    const int lane = threadIdx.x & 63, ks = (int)(threadIdx.x >> 6), n = lane & 15, q = lane >> 4;
+    const float *W = (const float *)(kFirst ? p.w13 : p.w2) + (size_t)mt.slot * (kFirst ? 2 : 1) * (size_t)p.I * p.H;
+    const float *A = (const float *)(kFirst ? p.x : p.h);
+    const int ra = min(n0 + n, N - 1), rb = kFirst ? p.I + ra : min(n0 + 16 + n, N - 1);
+    const float *wa = W + (size_t)ra * K, *wb = W + (size_t)rb * K;
+    const float *xr[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) xr[c] = A + (size_t)src[c] * K;
+    const int chunks = (K + kKC - 1) / kKC, per = (chunks + kSplit - 1) / kSplit;
+    const int kbeg = min(ks * per, chunks) * kKC, kend = min(min((ks + 1) * per, chunks) * kKC, K);
+    f32x4 aa[NT], ab[NT];
+#pragma unroll
+    for (int c = 0; c < NT; ++c) aa[c] = ab[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    Run ca, cb, na, nb, cx[NT], nx[NT];
+    auto load = [&](int k0, Run &a, Run &b, Run (&x)[NT]) {
+        load_run(a, wa, k0, q, K);
+        load_run(b, wb, k0, q, K);
+#pragma unroll
+        for (int c = 0; c < NT; ++c) load_run(x[c], xr[c], k0, q, K);
+    };
+    if (kbeg < kend) load(kbeg, ca, cb, cx);
+    for (int k0 = kbeg; k0 < kend; k0 += kKC) {
+        if (k0 + kKC < kend) load(k0 + kKC, na, nb, nx);
+        __builtin_amdgcn_sched_barrier(0);   // the prefetch goes out before this chunk's MFMAs, not after
+#pragma unroll
+        for (int j = 0; j < kKC / 16; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < NT; ++c) {
+                    aa[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(ca.v[j][i], cx[c].v[j][i], aa[c], 0, 0, 0);
+                    ab[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(cb.v[j][i], cx[c].v[j][i], ab[c], 0, 0, 0);
+                }
+        ca = na; cb = nb;
+#pragma unroll
+        for (int c = 0; c < NT; ++c) cx[c] = nx[c];
+    }
+    // the parts' sums meet in LDS; wavefront c adds those of row group c in K order and stores them
+#pragma unroll
+    for (int c = 0; c < NT; ++c) {
+        part[((ks * NT + c) * 2) * 64 + lane] = aa[c];
+        part[((ks * NT + c) * 2 + 1) * 64 + lane] = ab[c];
+    }
+    __syncthreads();
+    const int m = ks * 16 + n;                    // the lane's row of the tile, weight rows 4q .. 4q+3 of both blocks
+    if (ks >= NT || m >= mt.rows) return;
+    f32x4 sa = part[(ks * 2) * 64 + lane], sb = part[(ks * 2 + 1) * 64 + lane];
+#pragma unroll
+    for (int s = 1; s < kSplit; ++s) {
+        sa += part[((s * NT + ks) * 2) * 64 + lane];
+        sb += part[((s * NT + ks) * 2 + 1) * 64 + lane];
+    }
+    float *O = (float *)(kFirst ? p.h : p.y) + (size_t)(mt.row_begin + m) * N;
+    const int c0 = n0 + 4 * q, c1 = n0 + 16 + 4 * q;
+    if (kFirst) {
+        f32x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = sa[r] / (1.f + expf(-sa[r])) * sb[r];
+        if (c0 < N) *(f32x4 *)(O + c0) = h;
+    } else {
+        if (c0 < N) *(f32x4 *)(O + c0) = sa;
+        if (c1 < N) *(f32x4 *)(O + c1) = sb;
+    }
+}
+
+template <bool kFirst, int TT, bool kSelf>
+__global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
+{
+    static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
+    constexpr int TR = 16 * TT, COLS = kFirst ? kWRows / 2 : kWRows;
+    __shared__ f32x4 part[kSplit * TT * 2 * 64];
+    const int N = kFirst ? p.I : p.H;
+    const int groups = (N + COLS - 1) / COLS;               // tasks per M-tile
+    const int lane = threadIdx.x & 63, n = lane & 15;
+    int task = blockIdx.x;
+    if (kSelf) {
+        if (task == 0) { self_tables(p, TR); return; }
+        task -= 1;
+    }
+    const int tile = task / groups, n0 = task % groups * COLS;
+    MTile mt;
+    int src[TT];                                            // rows past the tile's end re-read its last row; their outputs are dropped
+    if (kSelf) {
+        unsigned long long tokens;
+        int first;
+        if (!self_tile(p, lane, tile, TR, &mt, &tokens, &first)) return;
+#pragma unroll
+        for (int c = 0; c < TT; ++c) src[c] = nth_set_bit(tokens, first + min(c * 16 + n, mt.rows - 1));
+    } else {
+        if (tile >= *p.n_tiles) return;
+        mt = p.tiles[tile];
+#pragma unroll
+        for (int c = 0; c < TT; ++c) {
+            const int r = mt.row_begin + min(c * 16 + n, mt.rows - 1);
+            src[c] = kFirst ? p.perm[r] : r;
+        }
+    }
+    if constexpr (TT >= 4) {
+        if (mt.rows > 32) { task_body<kFirst, 4>(p, mt, n0, src, part); return; }
+    }
+    if constexpr (TT >= 2) {
+        if (mt.rows > 16) { task_body<kFirst, 2>(p, mt, n0, src, part); return; }
+    }
+    task_body<kFirst, 1>(p, mt, n0, src, part);
+}
+
+template <int TT>
+void launch_tt(const Pass &p, int which, hipStream_t st)
+{
+    const dim3 block(64 * kSplit);
+    if (which == 0) {
+        const int blocks = p.max_tiles * ((p.I + kWRows / 2 - 1) / (kWRows / 2));
+        if (p.self_tiles) hipLaunchKernelGGL((k_expert_f32<true, TT, true>), dim3(blocks + 1), block, 0, st, p);
+        else              hipLaunchKernelGGL((k_expert_f32<true, TT, false>), dim3(blocks), block, 0, st, p);
+    } else {
+        const int blocks = p.max_tiles * ((p.H + kWRows - 1) / kWRows);
+        hipLaunchKernelGGL((k_expert_f32<false, TT, false>), dim3(blocks), block, 0, st, p);
+    }
+}
+
+}  // namespace
+
+// Rows per M-tile: what a slot can expect (its share of the routed assignments), so that a weight row read once
+// serves the slot's rows and small groups are not multiplied with padding.
+int f32_tile_rows(const Pass &p)
+{
+    const long long r = ((long long)p.T * p.k + p.E - 1) / p.E;
+    return r <= 16 ? 16 : r <= 32 ? 32 : 64;
+}
+
+hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st)
+{
+    if (tile_rows == 16)      launch_tt<1>(p, which, st);
+    else if (tile_rows == 32) launch_tt<2>(p, which, st);
+    else                      launch_tt<4>(p, which, st);
+    return hipGetLastError();
+}
+
+}  // namespace emoe

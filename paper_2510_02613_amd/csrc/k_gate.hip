@@ -6,11 +6,9 @@
 // top-k (group score = sum of the group's two best), both with optional
 // renormalisation over the k selected and a constant scale.
 //
-// One workgroup owns kTokens tokens.  Phase 1 accumulates their logits in fp32
-// (activations and router rows staged through LDS in K-chunks).  Phase 2 gives
-// each token to one 64-lane wavefront: scores live in LDS, every arg-max is a
-// wavefront reduction over a 64-bit (score, inverted index) key, so ties go to
-// the lower index exactly as the ordering rule demands.
+// Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token: scores
+// live in LDS, every arg-max is a wavefront reduction in which ties go to the lower index exactly as the ordering
+// rule demands.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -20,10 +18,7 @@ namespace emoe {
 
 namespace {
 
-constexpr int kTokens = 8;     // tokens per workgroup
 constexpr int kThreads = 256;  // 4 wavefronts
-constexpr int kET = 128;       // experts per logit tile
-constexpr int kKC = 32;        // K chunk
 
 // Monotone map float -> uint32 (larger float <-> larger integer).
 __device__ __forceinline__ uint32_t orderable(float f)
@@ -39,7 +34,7 @@ __device__ __forceinline__ unsigned long long make_key(float score, int idx)
 }
 __device__ __forceinline__ int key_index(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull)); }
 
-// Phase 2 for one token, run by one wavefront.
+// Selection for one token, run by one wavefront.
 //   lg   : LDS [E] logits in, scores out
 //   cs   : LDS [E] selection scores (biased), destroyed (taken entries -> -inf)
 // Returns the expert this lane holds (lane j < k: the j-th selected), which is also written to p.ids.
@@ -171,87 +166,20 @@ __device__ int select_token(const Pass &p, int t, float *lg, float *cs, int lane
     return my_id;
 }
 
-template <typename XT, typename WT>
-__global__ __launch_bounds__(kThreads) void k_gate(Pass p)
-{
-    extern __shared__ float smem[];
-    float *xs = smem;                        // [kTokens][kKC]
-    float *ws = xs + kTokens * kKC;          // [kET][kKC+1]
-    float *lg = ws + kET * (kKC + 1);        // [kTokens][E]
-    float *cs = lg + kTokens * p.E;          // [4 waves][E]
-
-    const int tid = threadIdx.x;
-    const int t0 = blockIdx.x * kTokens;
-    const XT *x = (const XT *)p.x;
-    const WT *wr = (const WT *)p.router_w;
-    const int H = p.H, E = p.E;
-
-    // phase 1: logits.  thread -> expert (tid % 128) of the tile, tokens (tid / 128) * 4 .. +4
-    const int el = tid & (kET - 1);
-    const int th = (tid >> 7) * (kTokens / 2);
-    for (int e0 = 0; e0 < E; e0 += kET) {
-        float acc[kTokens / 2];
-#pragma unroll
-        for (int i = 0; i < kTokens / 2; ++i) acc[i] = 0.f;
-        for (int k0 = 0; k0 < H; k0 += kKC) {
-            __syncthreads();
-            {   // stage x chunk: kTokens*kKC = 256 values, one per thread
-                int tt = tid / kKC, kc = tid % kKC;
-                int t = t0 + tt, kx = k0 + kc;
-                xs[tt * kKC + kc] = (t < p.T && kx < H) ? load_f32<XT>(x, (size_t)t * H + kx) : 0.f;
-            }
-            for (int idx = tid; idx < kET * kKC; idx += kThreads) {
-                int er = idx / kKC, kc = idx % kKC;
-                int e = e0 + er, kx = k0 + kc;
-                ws[er * (kKC + 1) + kc] = (e < E && kx < H) ? load_f32<WT>(wr, (size_t)e * H + kx) : 0.f;
-            }
-            __syncthreads();
-#pragma unroll 8
-            for (int kc = 0; kc < kKC; ++kc) {
-                float wv = ws[el * (kKC + 1) + kc];
-#pragma unroll
-                for (int i = 0; i < kTokens / 2; ++i) acc[i] = fmaf(xs[(th + i) * kKC + kc], wv, acc[i]);
-            }
-        }
-        int e = e0 + el;
-        if (e < E) {
-            float b = p.logit_bias ? p.logit_bias[e] : 0.f;
-#pragma unroll
-            for (int i = 0; i < kTokens / 2; ++i) lg[(th + i) * E + e] = acc[i] + b;
-        }
-    }
-    __syncthreads();
-
-    // phase 2: one wavefront per token
-    const int wave = tid >> 6, lane = tid & 63;
-    for (int tt = wave; tt < kTokens; tt += 4) {
-        int t = t0 + tt;
-        if (t < p.T) select_token(p, t, lg + tt * E, cs + wave * E, lane);
-    }
-}
-
-
 // ---------------------------------------------------------------------------------
-// Matrix-core path for bf16 activations: a logits kernel and a selection kernel.
-//
-// k_gate_logits.  A workgroup owns 16*TT tokens x a block of experts and writes their
-// fp32 logits to the workspace.  Both MFMA operands are read straight from global
-// memory in operand layout (no LDS): for a K-chunk of 128, lane (n = l%16, q = l/16)
-// reads 32 of the 128 k of row n, interleaved with the other three lanes of the row
-// in units of 8, and feeds them to the matrix core 8 (bf16) or 1 (fp32) at a time.
-// The contraction does not care which k a lane group carries as long as the router
-// row and the token row use the same assignment, which they do.
-//   bf16 router: v_mfma_f32_16x16x32_bf16, fp32 accumulate.
-//   fp32 router: tokens widened to fp32 (exact), v_mfma_f32_16x16x4_f32: every
-//                product is a true fp32 product ("fp32 gate").
-// The next chunk's loads are issued before the current chunk's MFMAs.
-// Two ways to split a workgroup's work over its 4 wavefronts:
-//   expert split (KSPLIT = false): wavefront w owns ET expert tiles of the workgroup's
-//       4*ET tiles; used when there are enough tokens to fill the chip;
-//   K split (KSPLIT = true): all wavefronts own the same ET expert tiles and a quarter
-//       of K each; partial sums meet in LDS and are added in wavefront order
-//       (deterministic).  Used for decode-sized batches, where the router matrix
-//       must be streamed by many workgroups at once.
+// k_gate_logits.  A workgroup owns 16 tokens x 16 experts (its logits go to the workspace in fp32).  Both MFMA
+// operands are read straight from global memory in operand layout (no LDS): for a K-chunk of 128, lane (n = l%16,
+// q = l/16) reads 32 of the 128 k of row n, interleaved with the other three lanes of the row in units of 8, and
+// feeds them to the matrix core 8 (bf16) or 1 (fp32) at a time.  The contraction does not care which k a lane group
+// carries as long as the router row and the token row use the same assignment, which they do.
+//   bf16 x bf16:      v_mfma_f32_16x16x32_bf16, fp32 accumulate.
+//   otherwise:        bf16 operands widened to fp32 (exact), v_mfma_f32_16x16x4_f32: every product is a true fp32
+//                     product.
+// The next chunk's loads are issued before the current chunk's MFMAs.  The contraction is shared out over the
+// workgroup's 4 wavefronts (partial sums meet in LDS, added in wavefront order) and, for few tokens, over gridDim.z
+// workgroups (partial-sum planes): the router matrix must be streamed by many workgroups at once.
+// fp32 layers run it at every batch size (64 tokens of a 128-wide layer: 14 us in a kernel that staged both operands
+// through LDS -> 4 us; 1500 tokens of a 264-wide layer with 40 experts: 32 -> 7 us).
 //
 // k_gate_select.  One wavefront per token: scores, group limiting, top-k, weights
 // (select_token above).  Its reductions are latency chains, so it runs as many small
@@ -281,128 +209,84 @@ __device__ __forceinline__ void load_run(RouterRun<WT> &r, const WT *row, int k0
     }
 }
 
-template <typename WT, int TT, int ET, bool KSPLIT>
+__device__ __forceinline__ void widen(const RouterRun<uint16_t> &r, float (&f)[32])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t *u = (const uint32_t *)&r.v[j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            f[j * 8 + 2 * e] = __uint_as_float(u[e] << 16);
+            f[j * 8 + 2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+        }
+    }
+}
+__device__ __forceinline__ void widen(const RouterRun<float> &r, float (&f)[32])
+{
+#pragma unroll
+    for (int e = 0; e < 32; ++e) f[e] = ((const float *)&r.v[0])[e];
+}
+
+template <typename XT, typename WT>
 __global__ __launch_bounds__(kThreads) void k_gate_logits(Pass p)
 {
-    __shared__ float part[KSPLIT ? 4 * TT * ET * 256 : 1];
+    constexpr bool kBf16 = sizeof(XT) == 2 && sizeof(WT) == 2;
+    __shared__ float part[4 * 256];
     const int E = p.E, H = p.H;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, q = lane >> 4;
-    const int t0 = blockIdx.x * 16 * TT;
-    const int et0 = KSPLIT ? blockIdx.y * ET : (blockIdx.y * 4 + wave) * ET;   // first expert tile of this wavefront
-    if (!KSPLIT && et0 * 16 >= E) return;
-    const uint16_t *x = (const uint16_t *)p.x;
-    const WT *wr = (const WT *)p.router_w;
-    // K range of this wavefront (whole chunks of 128)
-    int kbeg = 0, kend = H;
-    if (KSPLIT) {
-        // workgroup z of gridDim.z takes an equal share of the chunks (its sums go to plane z of the
-        // logits buffer), its wavefronts a quarter of that each
-        const int chunks = (H + 127) / 128;
-        const int c0 = (int)((long long)blockIdx.z * chunks / gridDim.z), c1 = (int)((long long)(blockIdx.z + 1) * chunks / gridDim.z);
-        const int per = (c1 - c0 + 3) / 4;
-        kbeg = min(H, min(c1, c0 + wave * per) * 128);
-        kend = min(H, min(c1, c0 + (wave + 1) * per) * 128);
+    const int t0 = blockIdx.x * 16, e0 = blockIdx.y * 16;
+    // K range of this wavefront (whole chunks of 128): workgroup z of gridDim.z takes an equal share of the chunks
+    // (its sums go to plane z of the logits buffer), its wavefronts a quarter of that each
+    const int chunks = (H + 127) / 128;
+    const int c0 = (int)((long long)blockIdx.z * chunks / gridDim.z), c1 = (int)((long long)(blockIdx.z + 1) * chunks / gridDim.z);
+    const int per = (c1 - c0 + 3) / 4;
+    const int kbeg = min(H, min(c1, c0 + wave * per) * 128), kend = min(H, min(c1, c0 + (wave + 1) * per) * 128);
+
+    const XT *xrow = (const XT *)p.x + (size_t)min(t0 + n, p.T - 1) * H;
+    const WT *wrow = (const WT *)p.router_w + (size_t)min(e0 + n, E - 1) * H;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    RouterRun<XT> xc, xn;
+    RouterRun<WT> wc, wn;
+    if (kbeg < kend) {
+        load_run<XT>(xc, xrow, kbeg, q, kend);
+        load_run<WT>(wc, wrow, kbeg, q, kend);
     }
-
-    const uint16_t *xrow[TT];
-    const WT *wrow[ET];
-#pragma unroll
-    for (int tb = 0; tb < TT; ++tb) xrow[tb] = x + (size_t)min(t0 + tb * 16 + n, p.T - 1) * H;
-#pragma unroll
-    for (int a = 0; a < ET; ++a) wrow[a] = wr + (size_t)min((et0 + a) * 16 + n, E - 1) * H;
-
-    f32x4 acc[ET][TT];
-#pragma unroll
-    for (int a = 0; a < ET; ++a)
-#pragma unroll
-        for (int tb = 0; tb < TT; ++tb) acc[a][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-    RouterRun<uint16_t> xc[TT], xn[TT];
-    RouterRun<WT> wc[ET], wn[ET];
-    auto load_chunk = [&](int k0, RouterRun<uint16_t> *xd, RouterRun<WT> *wd) {
-#pragma unroll
-        for (int tb = 0; tb < TT; ++tb) load_run<uint16_t>(xd[tb], xrow[tb], k0, q, kend);
-#pragma unroll
-        for (int a = 0; a < ET; ++a) load_run<WT>(wd[a], wrow[a], k0, q, kend);
-    };
-    if (kbeg < kend) load_chunk(kbeg, xc, wc);
     for (int k0 = kbeg; k0 < kend; k0 += 128) {
-        if (k0 + 128 < kend) load_chunk(k0 + 128, xn, wn);
-        __builtin_amdgcn_sched_barrier(0);  // the prefetch must be issued before this chunk's MFMAs, not after
-        if constexpr (sizeof(WT) == 2) {
-#pragma unroll
-            for (int a = 0; a < ET; ++a)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int tb = 0; tb < TT; ++tb)
-                        acc[a][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&wc[a].v[j], *(bf16x8 *)&xc[tb].v[j], acc[a][tb], 0, 0, 0);
-        } else {
-            float xf[TT][32];
-#pragma unroll
-            for (int tb = 0; tb < TT; ++tb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t *u = (const uint32_t *)&xc[tb].v[j];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        xf[tb][j * 8 + 2 * e] = __uint_as_float(u[e] << 16);
-                        xf[tb][j * 8 + 2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
-                    }
-                }
-#pragma unroll
-            for (int a = 0; a < ET; ++a) {
-                const float *wf = (const float *)&wc[a].v[0];
-#pragma unroll
-                for (int e = 0; e < 32; ++e)
-#pragma unroll
-                    for (int tb = 0; tb < TT; ++tb)
-                        acc[a][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], xf[tb][e], acc[a][tb], 0, 0, 0);
-            }
+        if (k0 + 128 < kend) {
+            load_run<XT>(xn, xrow, k0 + 128, q, kend);
+            load_run<WT>(wn, wrow, k0 + 128, q, kend);
         }
+        __builtin_amdgcn_sched_barrier(0);  // the prefetch must be issued before this chunk's MFMAs, not after
+        if constexpr (kBf16) {
 #pragma unroll
-        for (int tb = 0; tb < TT; ++tb) xc[tb] = xn[tb];
+            for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&wc.v[j], *(bf16x8 *)&xc.v[j], acc, 0, 0, 0);
+        } else {
+            float xf[32], wf[32];
+            widen(xc, xf);
+            widen(wc, wf);
 #pragma unroll
-        for (int a = 0; a < ET; ++a) wc[a] = wn[a];
+            for (int e = 0; e < 32; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], xf[e], acc, 0, 0, 0);
+        }
+        xc = xn;
+        wc = wn;
     }
-
-    if (KSPLIT) {  // partial sums of the 4 K-quarters meet in LDS, added in wavefront order
 #pragma unroll
-        for (int a = 0; a < ET; ++a)
-#pragma unroll
-            for (int tb = 0; tb < TT; ++tb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) part[((wave * ET + a) * TT + tb) * 256 + r * 64 + lane] = acc[a][tb][r];
-        __syncthreads();
-        if (wave != 0) return;
-#pragma unroll
-        for (int a = 0; a < ET; ++a)
-#pragma unroll
-            for (int tb = 0; tb < TT; ++tb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float s = 0.f;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) s += part[((w * ET + a) * TT + tb) * 256 + r * 64 + lane];
-                    acc[a][tb][r] = s;
-                }
-    }
-    // lane holds token n of each token tile, experts 4q + r of each of its expert tiles
+    for (int r = 0; r < 4; ++r) part[wave * 256 + r * 64 + lane] = acc[r];
+    __syncthreads();
+    if (wave != 0) return;
+    // lane holds token n, experts 4q + r
     float *plane = p.logits + (size_t)blockIdx.z * p.T * E;
     const float *bias = blockIdx.z == 0 ? p.logit_bias : nullptr;   // added once
+    const int t = t0 + n, e = e0 + 4 * q;   // E may be any size: guard each of the 4
+    if (t >= p.T) return;
 #pragma unroll
-    for (int a = 0; a < ET; ++a)
+    for (int r = 0; r < 4; ++r) {
+        float s = 0.f;
 #pragma unroll
-        for (int tb = 0; tb < TT; ++tb) {
-            const int t = t0 + tb * 16 + n;
-            const int e = (et0 + a) * 16 + 4 * q;   // E may be any size: guard each of the 4
-            if (t < p.T) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (e + r < E) plane[(size_t)t * E + e + r] = acc[a][tb][r] + (bias ? bias[e + r] : 0.f);
-            }
-        }
+        for (int w = 0; w < 4; ++w) s += part[w * 256 + r * 64 + lane];
+        if (e + r < E) plane[(size_t)t * E + e + r] = s + (bias ? bias[e + r] : 0.f);
+    }
 }
 
 // LDS-tiled logits kernel for prefill-sized batches.  A workgroup owns 16*TBT tokens x 64*EBT
@@ -649,42 +533,47 @@ __global__ __launch_bounds__(kFusedTokens * 64) void k_gate_select_hist(Pass p, 
     }
 }
 
-template <typename WT, int TT, int ET, bool KSPLIT>
-hipError_t launch_gate_logits_t(const Pass &p, int planes, hipStream_t st)
+template <typename XT, typename WT>
+hipError_t launch_gate_logits(const Pass &p, int planes, hipStream_t st)
 {
-    const int eb = (KSPLIT ? 1 : 4) * ET * 16;
-    dim3 grid((p.T + 16 * TT - 1) / (16 * TT), (p.E + eb - 1) / eb, planes);
-    hipLaunchKernelGGL((k_gate_logits<WT, TT, ET, KSPLIT>), grid, dim3(kThreads), 0, st, p);
+    hipLaunchKernelGGL((k_gate_logits<XT, WT>), dim3((p.T + 15) / 16, (p.E + 15) / 16, planes), dim3(kThreads), 0, st, p);
     return hipGetLastError();
 }
 
-template <typename WT>
-hipError_t launch_gate_mfma(const Pass &p0, hipStream_t st)
+// planes for the few-token logits kernel: 4 chunks of 128 (one per wavefront) or more per workgroup
+int few_token_planes(int T, int H)
 {
-    Pass p = p0;
-    int planes = 1;
-    hipError_t e;
+    if (T > kGateFewTokens) return 1;
+    const int z = (H + 127) / 128 / 4;
+    return z < 1 ? 1 : z > kGatePlanes ? kGatePlanes : z;
+}
+
+template <typename WT>
+hipError_t launch_logits_bf16(const Pass &p, int *planes, hipStream_t st)
+{
     // Up to a hundred or so tokens there are too few (token, expert) tiles for the LDS-tiled kernels: the
     // K-split kernel reads both operands straight into registers, 16 tokens x 16 experts per workgroup, and
     // shares the contraction out over its wavefronts and over workgroups.  (Without the direct-to-LDS
     // kernel -- H not a multiple of 64 -- it stays ahead until the router re-reads reach about 128 MB.)
     const size_t router_rereads = (size_t)((p.T + 15) / 16) * p.E * p.H * (p.router_bf16 ? 2 : 4);
-    const bool small = gate_dma_supports(p) ? p.T <= 128 : (p.T <= 256 || router_rereads <= (size_t)128 << 20);
+    const bool small = gate_dma_supports(p) ? p.T <= 128 : (p.T <= kGateFewTokens || router_rereads <= (size_t)128 << 20);
+    *planes = 1;
     if (!p.gate_tiled && small) {
-        // 4 chunks of 128 (one per wavefront) or more per workgroup
-        if (p.T <= 256) planes = min(kGatePlanes, max(1, (p.H + 127) / 128 / 4));
-        e = launch_gate_logits_t<WT, 1, 1, true>(p, planes, st);
+        *planes = few_token_planes(p.T, p.H);
+        return launch_gate_logits<uint16_t, WT>(p, *planes, st);
     }
-    else if (gate_dma_supports(p))      e = launch_gate_logits_dma(p, &planes, st);    // LDS ring filled by direct copies
-    else if (p.E > 64 && p.T >= 8192)   e = launch_gate_logits_lds<WT, 4, 2>(p, st);   // 64 tokens x 128 experts
-    else                                e = launch_gate_logits_lds<WT, 2, 1>(p, st);   // 32 tokens x 64 experts
-    if (e != hipSuccess) return e;
-    p.logit_planes = planes;
+    if (gate_dma_supports(p))      return launch_gate_logits_dma(p, planes, st);    // LDS ring filled by direct copies
+    if (p.E > 64 && p.T >= 8192)   return launch_gate_logits_lds<WT, 4, 2>(p, st);   // 64 tokens x 128 experts
+    return launch_gate_logits_lds<WT, 2, 1>(p, st);                                  // 32 tokens x 64 experts
+}
+
+hipError_t launch_select(const Pass &p, hipStream_t st)
+{
     if (p.fused_hist) {
         const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
         const size_t smem = sizeof(float) * kFusedTokens * 2 * (size_t)p.E + sizeof(uint32_t) * p.S;
         if (smem > 64 * 1024) {
-            e = hipFuncSetAttribute((const void *)k_gate_select_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            const hipError_t e = hipFuncSetAttribute((const void *)k_gate_select_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(k_gate_select_hist, dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb);
@@ -697,28 +586,19 @@ hipError_t launch_gate_mfma(const Pass &p0, hipStream_t st)
 
 }  // namespace
 
-hipError_t launch_gate(const Pass &p, hipStream_t st)
+int gate_f32_planes(int T, int H) { return few_token_planes(T, H); }
+
+hipError_t launch_gate(const Pass &p0, hipStream_t st)
 {
-    if (p.act_bf16) return p.router_bf16 ? launch_gate_mfma<uint16_t>(p, st) : launch_gate_mfma<float>(p, st);
-    const int blocks = (p.T + kTokens - 1) / kTokens;
-    const size_t smem = sizeof(float) * (kTokens * kKC + kET * (kKC + 1) + (size_t)kTokens * p.E + 4 * (size_t)p.E);
-    dim3 grid(blocks), block(kThreads);
-    if (smem > 64 * 1024) {  // opt in to the large-LDS launch once per kernel variant is cheap enough
-        hipError_t e = hipSuccess;
-        if (p.act_bf16 && p.router_bf16) e = hipFuncSetAttribute((const void *)k_gate<uint16_t, uint16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        else if (p.act_bf16)             e = hipFuncSetAttribute((const void *)k_gate<uint16_t, float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        else if (p.router_bf16)          e = hipFuncSetAttribute((const void *)k_gate<float, uint16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        else                             e = hipFuncSetAttribute((const void *)k_gate<float, float>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-    }
+    Pass p = p0;
+    hipError_t e;
     if (p.act_bf16) {
-        if (p.router_bf16) hipLaunchKernelGGL((k_gate<uint16_t, uint16_t>), grid, block, smem, st, p);
-        else               hipLaunchKernelGGL((k_gate<uint16_t, float>), grid, block, smem, st, p);
+        e = p.router_bf16 ? launch_logits_bf16<uint16_t>(p, &p.logit_planes, st) : launch_logits_bf16<float>(p, &p.logit_planes, st);
     } else {
-        if (p.router_bf16) hipLaunchKernelGGL((k_gate<float, uint16_t>), grid, block, smem, st, p);
-        else               hipLaunchKernelGGL((k_gate<float, float>), grid, block, smem, st, p);
+        p.logit_planes = gate_f32_planes(p.T, p.H);
+        e = p.router_bf16 ? launch_gate_logits<float, uint16_t>(p, p.logit_planes, st) : launch_gate_logits<float, float>(p, p.logit_planes, st);
     }
-    return hipGetLastError();
+    return e == hipSuccess ? launch_select(p, st) : e;
 }
 
 }  // namespace emoe

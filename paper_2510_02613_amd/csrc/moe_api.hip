@@ -99,7 +99,13 @@ Layout make_layout(const moe_config_t &c)
     // a table: E + n_shared entries, then the copy lists of replicated experts (count, slots...:
     // at most S slots in lists of at least two, so 3S/2 entries)
     L.map = take(4 * (c.n_experts + c.n_shared + 2 * S));
-    L.logits = take(c.act_dtype == MOE_BF16 ? 4 * T * c.n_experts * kGatePlanes : 0);   // partial-sum planes of the K-split logits kernels
+    // partial-sum planes of the K-split logits kernels (fp32 layers: only few tokens have several)
+    size_t planes_of_tokens = T * kGatePlanes;
+    if (c.act_dtype == MOE_F32) {
+        const size_t few = T < (size_t)kGateFewTokens ? T : (size_t)kGateFewTokens;
+        planes_of_tokens = few * gate_f32_planes((int)few, c.hidden) > T ? few * gate_f32_planes((int)few, c.hidden) : T;
+    }
+    L.logits = take(4 * planes_of_tokens * c.n_experts);
     L.ids = take(4 * T * k);
     L.w = take(4 * T * k);
     L.slot_rank = take(4 * A);
@@ -598,8 +604,8 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.partials = l->lay.has_partials ? (float *)(ws + l->lay.partials) : nullptr;
 
     p.gate_tiled = (flags & MOE_FLAG_GATE_TILED) != 0;
-    // gated bf16 passes up to kFusedMaxTokens tokens: the selection kernel ranks the assignments, one more kernel places them
-    p.fused_hist = p.act_bf16 && !routed_ids && T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
+    // gated passes up to kFusedMaxTokens tokens: the selection kernel ranks the assignments, one more kernel places them
+    p.fused_hist = !routed_ids && T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
     // Weight streaming without LDS when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
@@ -609,7 +615,8 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const bool tiny = mfma && !(can_big && (long long)T * p.kk >= 48ll * p.S) &&
                       (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool big = can_big && !tiny;
-    const int tile_rows = big ? mfma8_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : kGenericTileRows;
+    const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
+    const int tile_rows = big ? mfma8_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
     // tile.  With a token or two most slots have none, and thousands of workgroups that only find out that their
     // tile does not exist take longer to dispatch than one token's experts take to stream.
@@ -635,7 +642,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     if (e == hipSuccess && !routed_ids) e = launch_gate(p, st);
     mark(MOE_PHASE_PERMUTE);
     // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
-    p.self_tiles = tiny && !identity && decode_self_tiles(p);
+    p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
     mark(MOE_PHASE_GEMM1);
     if (e == hipSuccess) {
@@ -643,11 +650,13 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
         else if (big)  e = launch_experts_mfma8(p, 0, st);
         else if (tiny) e = launch_experts_decode(p, 0, st);
         else if (mfma) e = launch_experts_mfma(p, 0, st);
+        else if (f32)  e = launch_experts_f32(p, tile_rows, 0, st);
         else           e = launch_experts_generic(p, 0, st);
     }
     mark(MOE_PHASE_GEMM2);
     if (e == hipSuccess && !identity)
-        e = big ? launch_experts_mfma8(p, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) : launch_experts_generic(p, 1, st);
+        e = big ? launch_experts_mfma8(p, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
+            f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
     mark(MOE_PHASE_COMBINE);
     if (e == hipSuccess) e = launch_combine(p, st);
     mark(MOE_N_PHASES);

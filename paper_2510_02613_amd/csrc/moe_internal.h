@@ -64,7 +64,7 @@ struct Pass {
     const void *w13, *w2;
     // workspace
     const int32_t *map;  // [E + n_shared] active table, shared slots last
-    float *logits;       // [logit_planes][T,E] gate logits (bf16-activation path): the planes are partial sums over K ranges
+    float *logits;       // [logit_planes][T,E] gate logits: the planes are partial sums over K ranges
     int32_t logit_planes;
     int32_t *ids;        // [T,k]
     float *w;            // [T,k]
@@ -94,7 +94,8 @@ struct Pass {
     int32_t k_split;     // this launch may share the contraction of its last round's tiles out (set by the launcher)
 };
 
-constexpr int kGatePlanes = 8;         // partial-sum planes of the gate logits the workspace has room for
+constexpr int kGatePlanes = 8;         // most partial-sum planes of the gate logits
+constexpr int kGateFewTokens = 256;    // up to here the few-token logits kernel shares the contraction out over workgroups
 constexpr int kAssignPerBlock = 1024;  // assignments ranked by one block of the slot histogram kernel
 constexpr int kFusedTokens = 16;       // tokens per workgroup of the fused selection + ranking kernel (one per wavefront)
 constexpr int kFusedMaxTokens = 8192;  // largest batch the fused bookkeeping serves: every placing workgroup reads all block masks
@@ -104,6 +105,7 @@ __host__ __device__ constexpr int fused_row_stride(int n_blocks) { return (n_blo
 hipError_t launch_write_map(int32_t *dst, const int32_t *host_vals, int n, hipStream_t st);
 hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st);  // bytes % 16 == 0
 hipError_t launch_gate(const Pass &p, hipStream_t st);
+int gate_f32_planes(int T, int H);   // partial-sum planes of the gate logits of fp32 layers
 hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st);   // logits only, bf16 activations
 bool gate_dma_supports(const Pass &p);
 hipError_t launch_permute(const Pass &p, int tile_rows, bool sort_tiles, hipStream_t st);
@@ -125,7 +127,12 @@ hipError_t launch_ceiling_tile_stream(const void *buf, int n_tiles, size_t row_b
 // weight-streaming variant for decode-sized batches (M-tiles of 16 rows)
 hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st);
 int decode_tile_rows();
-bool decode_self_tiles(const Pass &p);   // GEMM-1 needs no bookkeeping kernel in front of it (Pass::self_tiles)
+// fp32 layers, M-tiles of 16, 32 or 64 rows
+hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st);
+int f32_tile_rows(const Pass &p);
+// GEMM-1 of those two can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
+// at most 4 blocks of tokens and 256 slots: no bookkeeping kernel in front of it
+inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 256 && p.T <= 4 * 16; }
 hipError_t launch_identity_experts(const Pass &p, hipStream_t st);
 hipError_t launch_combine(const Pass &p, hipStream_t st);
 

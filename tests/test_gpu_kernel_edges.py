@@ -47,3 +47,20 @@ def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
     np.testing.assert_array_equal(runs[0][0], runs[1][0])
     for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
         np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
+@pytest.mark.parametrize("tokens", [1, 16, 33, 64, 65, 257, 700])
+@pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32")])
+def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
+    """fp32 layers on both sides of the self-derived tiles (64 tokens) and of every tile height (16, 32, 64 rows), with
+    contractions that leave wavefronts of a task without a chunk, and both router types."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    wl = MoEWorkload(name="f32_edges", tokens=tokens, hidden=hidden, inter=inter, n_experts=24, top_k=3, n_slots=22, n_local=20,
+                     act_dtype="f32", router_dtype=router, gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,
+                     n_shared=1, shared_range=(tokens // 3, tokens), seed=400 + tokens)
+    case = Case(wl)
+    out = case.run()
+    v = case.layer.view(tokens)
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
