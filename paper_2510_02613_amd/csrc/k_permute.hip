@@ -15,6 +15,7 @@
 //                sum over slots (LDS scan), and the M-tile list for the GEMMs.
 //   k_slot_place row = offsets[slot] + block base + rank; perm[row] = token,
 //                inv[assignment] = row (or -1 when the expert is not local).
+//   k_hist_place the last two in one launch, up to 64 blocks.
 //
 // Rows of one slot end up ordered by (token, selection position); nothing depends
 // on atomics ordering, so two passes over the same input give the same layout.
@@ -132,12 +133,7 @@ template <int NT = kThreads>
 __device__ __forceinline__ int block_exclusive_scan(int v, int32_t *scratch, int *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        int o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
+    const int incl = wave_incl_scan_i32(v);
     if (lane == 63) scratch[wave] = incl;
     __syncthreads();
     int base = 0, tot = 0;
@@ -152,12 +148,21 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int32_t *scratch, int
     return base + incl - v;
 }
 
-// The M-tiles of one slot: its c rows split into nt nearly equal chunks (multiples of 32 rows, or of
-// tile_rows when that is smaller) so that no chunk is a sliver.
-__device__ __forceinline__ void emit_tiles(const Pass &p, int s, int c, int nt, int row_off, int tile_off, int tile_rows, MTile *dst)
+// M-tiles of a slot with c rows
+__device__ __forceinline__ int tiles_of(int c, int tile_rows) { return c <= tile_rows ? (c > 0) : (c + tile_rows - 1) / tile_rows; }
+
+// Rows per M-tile of a slot: its c rows split into nt nearly equal chunks (multiples of 32 rows, or of tile_rows when
+// that is smaller: both powers of two) so that no chunk is a sliver.
+__device__ __forceinline__ int rows_per_tile(int c, int nt, int tile_rows)
 {
     const int gran = tile_rows < 32 ? tile_rows : 32;
-    const int per = nt ? min(tile_rows, ((c + nt - 1) / nt + gran - 1) / gran * gran) : 0;
+    const int even = nt > 1 ? (c + nt - 1) / nt : c;
+    return min(tile_rows, (even + gran - 1) & -gran);
+}
+
+// The M-tiles of one slot
+__device__ __forceinline__ void emit_tiles(const Pass &p, int s, int c, int nt, int per, int row_off, int tile_off, MTile *dst)
+{
     for (int i = 0; i < nt; ++i) {
         const int idx = tile_off + i;
         if (idx < p.max_tiles) {
@@ -176,17 +181,18 @@ constexpr int kSizeBins = 12;    // size classes: 32-row token tiles of a chunk,
 
 constexpr int kMaxSlots = 2048;  // n_slots <= 2047
 
+// inclusive wavefront sums of two counters side by side (no carry between them)
+__device__ __forceinline__ unsigned long long wave_incl_scan_2x32(unsigned long long v)
+{
+    const uint32_t lo = (uint32_t)wave_incl_scan_i32((int)(uint32_t)v), hi = (uint32_t)wave_incl_scan_i32((int)(uint32_t)(v >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
 // exclusive scan of a 64-bit value over the NT threads of the block (two 32-bit counters side by side)
 template <int NT>
 __device__ __forceinline__ unsigned long long block_exclusive_scan_u64(unsigned long long v, unsigned long long *scratch, unsigned long long *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
+    const unsigned long long incl = wave_incl_scan_2x32(v);
     if (lane == 63) scratch[wave] = incl;
     __syncthreads();
     unsigned long long base = 0, tot = 0;
@@ -212,7 +218,7 @@ __device__ void deal_units(const Pass &p, const MTile *src, const int32_t *order
     MUnit *units = p.units[which];
     const int n_units = min((n * runs + 7) / 8 * 8, p.unit_cap);
     for (int at = t; at < n * runs && at < p.unit_cap; at += threads) {
-        const int q = at / runs, r = at - q * runs;
+        const int q = runs == 1 ? at : at / runs, r = at - q * runs;
         const MTile mt = src[order ? order[q] : q];
         MUnit u;
         u.slot = mt.slot; u.row_begin = mt.row_begin; u.rows = mt.rows;
@@ -243,12 +249,7 @@ __device__ __forceinline__ unsigned long long half_exclusive_scan_u64(unsigned l
 {
     constexpr int HW = NT / 128;                            // wavefronts per half
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = wave / HW;
-    unsigned long long incl = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const unsigned long long o = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += o;
-    }
+    const unsigned long long incl = wave_incl_scan_2x32(v);
     if (lane == 63) scratch[wave] = incl;
     __syncthreads();
     unsigned long long base = 0, tot = 0;
@@ -288,7 +289,7 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
     const int pm = max(2, target / 2);                     // largest piece
     MUnit *units = p.units[which];
     if (t < 8) colF[t] = 0;
-    const bool ok = total <= kSortMax / 2 && runs <= 64;
+    const bool ok = total <= kSortMax / 2 && runs <= 64;   // pieces from the front of tmp, single tiles from its end
     // pieces and single tiles per group -> each group's start in the two numberings (one scan, two counters)
     auto shape = [&](int g, int &m, int &np, int &singles) {
         m = (g + 1 < ng ? gq0[g + 1] : n) - gq0[g];
@@ -305,7 +306,7 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
         int m = 0, np = 0, singles = 0;
         if (g < ng) shape(g, m, np, singles);
         unsigned long long tot;
-        const unsigned long long at = carry + half_exclusive_scan_u64<NT>(((unsigned long long)(np * runs) << 32) | (unsigned)(singles * runs), scratch, &tot);
+        const unsigned long long at = carry + half_exclusive_scan_u64<NT>(((unsigned long long)(np * runs) << 32) | (unsigned)singles, scratch, &tot);
         if (g < ng && ok) {
             const int k0 = (int)(at >> 32);
             for (int pi = 0; pi < np; ++pi) {
@@ -313,12 +314,14 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
                 for (int r = 0; r < runs; ++r)              // first place in the order (11 bits) | tiles (11) | run (6)
                     tmp[k0 + pi * runs + r] = (gq0[g] + pi * pm) | (size << 11) | (r << 22);
             }
-            // the group's single tile starts at this number among the single units (kept for the second pass)
+            // the group's single tile: its place in the order, by number among the single tiles, from the end of tmp
+            if (singles) tmp[kSortMax / 2 - 1 - (int)(at & 0xffffffffu)] = gq0[g] + m - 1;
         }
         carry += tot;
     }
     const int P = (int)(carry >> 32);
-    int R = (int)(carry & 0xffffffffu);                     // single units (later: those dealt unit by unit)
+    const int n_single = (int)(carry & 0xffffffffu);        // single tiles (a group has at most one)
+    int R = n_single * runs;                                // their units (later: those dealt unit by unit)
     __syncthreads();
     // piece k sits in column k mod 8 behind the earlier pieces of that column
     if (ok) {
@@ -424,17 +427,11 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
             p.unit_hdr[which] = h;
         }
     }
-    // single units, numbered group by group in the order (a group has at most one single tile), run by run
-    unsigned long long carry2 = 0;
-    for (int g0 = 0; g0 < ng; g0 += HT) {
-        const int g = g0 + t;
-        int m = 0, np = 0, has = 0;
-        if (g < ng) shape(g, m, np, has);
-        unsigned long long tot;
-        const int i0 = (int)(carry2 + half_exclusive_scan_u64<NT>((unsigned long long)(has * runs), scratch, &tot));
-        if (has && grouped) {
-            const MTile tl = src[order[gq0[g] + m - 1]];      // the group's last tile
-            const int j = i0 / runs;                         // its number among the single tiles
+    // single units, tile by tile in the order, run by run: a thread per unit
+    if (grouped)
+        for (int u = t; u < n_single * runs; u += HT) {
+            const int j = runs == 1 ? u : u / runs, r = u - j * runs;   // the tile's number among the single tiles, the run
+            const MTile tl = src[order[tmp[kSortMax / 2 - 1 - j]]];
             if (j < NA) {                                    // whole: block level k of the rank-th column that reaches it
                 const int k = levelA(j), rank = j - belowA(k);
                 int x = 0, base = 0;
@@ -445,10 +442,9 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
                     for (int y = 0; y < 8; ++y) before += (y < xx && cap[y] > k);
                     if (cap[xx] > k && before == rank) { x = xx; base = colF[xx]; }   // the column's pieces end there
                 }
-                for (int r = 0; r < runs; ++r) put(base + k * runs + r, x, tl, r);
-            } else
-            for (int r = 0; r < runs; ++r) {
-                const int i = i0 - NA * runs + r, l = level_of(i);
+                put(base + k * runs + r, x, tl, r);
+            } else {
+                const int i = u - NA * runs, l = level_of(i);
                 const int rank = i - below(l);
                 int x = 0;
 #pragma unroll
@@ -461,8 +457,6 @@ __device__ void deal_units_grouped(const Pass &p, const MTile *src, const int32_
                 put(l, x, tl, r);
             }
         }
-        carry2 += tot;
-    }
     if (!grouped) deal_units(p, src, order, n, which, which * HT, HT);
 }
 
@@ -495,18 +489,16 @@ __device__ void offsets_and_tiles(const Pass &p, int tile_rows, bool staging, co
     for (int s0 = 0; s0 < S; s0 += NT) {
         const int s = s0 + tid;
         const int c = s < S ? cnt[s] : 0;
-        const int nt = (c + tile_rows - 1) / tile_rows;
+        const int nt = tiles_of(c, tile_rows), per = rows_per_tile(c, nt, tile_rows);
         unsigned long long tot;
         const unsigned long long off = carry + block_exclusive_scan_u64<NT>(((unsigned long long)c << 32) | (unsigned)nt, scratch, &tot);
         if (s < S) {
             const int row_off = (int)(off >> 32), tile_off = (int)(off & 0xffffffffu);
             p.counts[s] = c;
             p.offs[s] = row_off;
-            emit_tiles(p, s, c, nt, row_off, tile_off, tile_rows, staging ? staged : p.tiles);
+            emit_tiles(p, s, c, nt, per, row_off, tile_off, staging ? staged : p.tiles);
             if (nt > 1) any_multi = 1;
             if (staging) {
-                const int gran = tile_rows < 32 ? tile_rows : 32;
-                const int per = nt ? min(tile_rows, ((c + nt - 1) / nt + gran - 1) / gran * gran) : 0;
                 for (int i = 0; i < nt && tile_off + i < p.max_tiles; ++i) {
                     const int rows = max(0, min(per, c - i * per));
                     const int cls = min(kSizeBins - 1, (rows + 31) >> 5);
@@ -626,11 +618,13 @@ __global__ __launch_bounds__(kThreads) void k_slot_scan(Pass p, int n_blocks, in
 // [16 b, 16 b + 16).  Nobody waits for anybody: every workgroup adds up, for itself, the block masks of all
 // slots (a quarter wavefront per slot, row-wise reductions) -- rows per slot in the whole
 // pass and in the blocks before its own -- and scans the totals; at most 512 blocks x S words, out of L2.
-// 64 registers at most: two workgroups of 16 wavefronts per compute unit, 512 on the chip.  The tile list's
+// kMany (more placing workgroups than compute units): 64 registers at most, two workgroups of 16 wavefronts per compute
+// unit, 512 on the chip.  The tile list's
 // workgroup is the longest of the launch (2 to 3 times a placing one) and therefore the first of the grid: at
 // 8192 tokens the launch has 513 workgroups, and the one that has to wait for a place should be a short one
 // (measured at 8192 tokens: the kernel 3 us shorter than with the tile list's workgroup last).
-__global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_scan_place(Pass p, int n_blocks, int tile_rows, int sort_tiles)
+template <bool kMany>
+__global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_eu(kMany ? 8 : 4))) void k_scan_place(Pass p, int n_blocks, int tile_rows, int sort_tiles)
 {
     constexpr int NT = kFusedTokens * 64;
     __shared__ int32_t total[kMaxSlots];   // rows per slot, then (placing workgroups) the slot's first row
@@ -651,15 +645,12 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
     const int sub = lane & 15, qrow = lane >> 4;
     // byte masks of this lane's words: blocks that exist, blocks before this workgroup's
     uint32_t mv[8], mb[8];
+    auto first_bytes = [](int n) { return n >= 4 ? 0xffffffffu : n <= 0 ? 0u : (1u << (8 * n)) - 1u; };
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        mv[i] = mb[i] = 0u;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int blk = sub * lb + 4 * i + e;
-            if (blk < n_blocks) mv[i] |= 0xffu << (8 * e);
-            if (blk < b) mb[i] |= 0xffu << (8 * e);        // b <= n_blocks
-        }
+        const int blk = sub * lb + 4 * i;
+        mv[i] = first_bytes(n_blocks - blk);
+        mb[i] = first_bytes(b - blk);                      // b <= n_blocks
     }
     auto load_row = [&](int s0, uint32_t (&v)[8]) {
         const uint32_t *row = (const uint32_t *)(p.blk_cnt + (size_t)min(s0 + qrow, S - 1) * row_stride + sub * lb);
@@ -695,16 +686,7 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
         }
         if (sub == 15 && s < S) {
             total[s] = both & 0xffff;
-            int v = both >> 16;
-            if (tiles_wg) {
-                // the group's first assignment: its first block with a row, that block's lowest token, that row's position
-                v = 0x7fffffff;
-                if (first != 0x7fffffff) {
-                    const uint32_t m = (uint32_t)p.blk_hist[(size_t)s * row_stride + first];
-                    v = (((first * kFusedTokens + (__ffs(m & 0xffffu) - 1)) << 6) | (int)(m >> 16));
-                }
-            }
-            base[s] = v;
+            base[s] = tiles_wg ? first : both >> 16;
         }
         if (more) {
 #pragma unroll
@@ -713,8 +695,18 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
     }
     __syncthreads();
     if (tiles_wg) {
-        // four wavefronts carry on (the barriers below count the wavefronts still running): that keeps the
-        // kernel's LDS at two workgroups per compute unit, so that the placing workgroups all run at once
+        // the groups' first assignments, all looked up together: the first block with a row (base), that block's
+        // lowest token, that row's position
+        for (int s = tid; s < S; s += NT) {
+            const int first = base[s];
+            if (first != 0x7fffffff) {
+                const uint32_t m = (uint32_t)p.blk_hist[(size_t)s * row_stride + first];
+                base[s] = (((first * kFusedTokens + (__ffs(m & 0xffffu) - 1)) << 6) | (int)(m >> 16));
+            }
+        }
+        __syncthreads();
+        // four wavefronts carry on (the barriers below count the wavefronts still running): the steps are short and
+        // many, sixteen wavefronts meet at each of them too slowly (measured: 1 to 4 us more)
         if (tid >= kThreads) return;
         offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && p.max_tiles <= kSortMax, total, base);
         return;
@@ -746,6 +738,64 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
     }
 }
 
+// Scan and placement of the separate path in one launch, for batches of up to kScanPlaceBlocks histogram blocks: like
+// k_scan_place, every workgroup adds up the block histograms for itself (a thread per slot, 16 blocks' words in flight),
+// workgroup 0 writes the tile list, workgroup b + 1 places the assignments of histogram block b.
+// 1777 routed tokens, 6 of 64 experts each: scan and placement as two launches 18 us -> 10 us.
+constexpr int kScanPlaceBlocks = 64;
+__global__ __launch_bounds__(kHistThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_hist_place(Pass p, int n_blocks, int tile_rows, int sort_tiles)
+{
+    __shared__ int32_t total[kMaxSlots];   // rows per slot, then (placing workgroups) the slot's first row
+    __shared__ int32_t base[kMaxSlots];    // rows of the slot in earlier blocks; the tile workgroup: the group's first assignment
+    __shared__ int32_t scratch[kHistThreads / 64];
+    const int tid = threadIdx.x, S = p.S;
+    const bool tiles_wg = blockIdx.x == 0;
+    const int b = tiles_wg ? n_blocks : (int)blockIdx.x - 1;
+    const int a = b * kHistThreads + tid;
+    const bool mine = !tiles_wg && a < p.T * p.kk;
+    const int sr = mine ? p.slot_rank[a] : -1;
+    for (int s = tid; s < S; s += kHistThreads) {
+        int run = 0, before = 0, key = 0x7fffffff;
+        for (int b0 = 0; b0 < n_blocks; b0 += 16) {
+            int c[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) c[i] = b0 + i < n_blocks ? p.blk_hist[(size_t)(b0 + i) * S + s] : 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (c[i] && key == 0x7fffffff) key = (b0 + i) * kAssignPerBlock + (c[i] >> 16);
+                if (b0 + i == b) before = run;
+                run += c[i] & 0xffff;
+            }
+        }
+        total[s] = run;
+        base[s] = tiles_wg ? key : before;
+    }
+    __syncthreads();
+    if (tiles_wg) {
+        if (tid >= kThreads) return;
+        offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && p.max_tiles <= kSortMax, total, base);
+        return;
+    }
+    int carry = 0;
+    for (int s0 = 0; s0 < S; s0 += kHistThreads) {
+        const int s = s0 + tid;
+        const int c = s < S ? total[s] : 0;
+        int tot;
+        const int off = carry + block_exclusive_scan<kHistThreads>(c, scratch, &tot);
+        if (s < S) total[s] = off;
+        carry += tot;
+    }
+    __syncthreads();
+    if (!mine) return;
+    int row = -1;
+    if (sr >= 0) {
+        const int slot = sr >> 12;
+        row = total[slot] + base[slot] + (sr & 0xfff);
+        p.perm[row] = a / p.kk;
+    }
+    p.inv[a] = row;
+}
+
 __global__ __launch_bounds__(kThreads) void k_slot_place(Pass p)
 {
     const int a = blockIdx.x * kThreads + threadIdx.x;
@@ -775,7 +825,7 @@ __global__ __launch_bounds__(kHistThreads) void k_permute_one_block(Pass p, int 
     for (int s0 = 0; s0 < S; s0 += kHistThreads) {
         const int s = s0 + tid;
         const int c = s < S ? hist[s] : 0;
-        const int nt = (c + tile_rows - 1) / tile_rows;
+        const int nt = tiles_of(c, tile_rows);
         int row_tot, tile_tot;
         const int row_off = row_carry + block_exclusive_scan<kHistThreads>(c, scratch, &row_tot);
         const int tile_off = tile_carry + block_exclusive_scan<kHistThreads>(nt, scratch, &tile_tot);
@@ -783,7 +833,7 @@ __global__ __launch_bounds__(kHistThreads) void k_permute_one_block(Pass p, int 
             p.counts[s] = c;
             p.offs[s] = row_off;
             offs[s] = row_off;
-            emit_tiles(p, s, c, nt, row_off, tile_off, tile_rows, p.tiles);
+            emit_tiles(p, s, c, nt, rows_per_tile(c, nt, tile_rows), row_off, tile_off, p.tiles);
         }
         row_carry += row_tot;
         tile_carry += tile_tot;
@@ -809,7 +859,8 @@ hipError_t launch_permute(const Pass &p, int tile_rows, bool sort_tiles, hipStre
 {
     if (p.fused_hist) {   // the selection kernel has ranked the assignments already
         const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
-        hipLaunchKernelGGL(k_scan_place, dim3(nb + 1), dim3(kFusedTokens * 64), 0, st, p, nb, tile_rows, sort_tiles ? 1 : 0);
+        if (nb > 224) hipLaunchKernelGGL((k_scan_place<true>), dim3(nb + 1), dim3(kFusedTokens * 64), 0, st, p, nb, tile_rows, sort_tiles ? 1 : 0);
+        else          hipLaunchKernelGGL((k_scan_place<false>), dim3(nb + 1), dim3(kFusedTokens * 64), 0, st, p, nb, tile_rows, sort_tiles ? 1 : 0);
         return hipGetLastError();
     }
     const int n_assign = p.T * p.kk;
@@ -821,6 +872,10 @@ hipError_t launch_permute(const Pass &p, int tile_rows, bool sort_tiles, hipStre
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_slot_hist, dim3(nb), dim3(kHistThreads), sizeof(int32_t) * (rank_lds_ints(p.S) + p.S), st, p);
+    if (nb <= kScanPlaceBlocks) {
+        hipLaunchKernelGGL(k_hist_place, dim3(nb + 1), dim3(kHistThreads), 0, st, p, nb, tile_rows, sort_tiles ? 1 : 0);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_slot_scan, dim3(1), dim3(kThreads), 0, st, p, nb, tile_rows, sort_tiles ? 1 : 0);
     hipLaunchKernelGGL(k_slot_place, dim3(nbp), dim3(kThreads), 0, st, p);
     return hipGetLastError();

@@ -65,6 +65,14 @@ __device__ __forceinline__ float wave_max_f32(float v)
 #undef STEP
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
+// inclusive sum over the lanes up to this one: inside rows of 16 by row_shr, then each row's total to the rows behind it
+__device__ __forceinline__ int wave_incl_scan_i32(int v)
+{
+#define STEP(CTRL, MASK) v += dpp_i32<CTRL, MASK>(0, v);
+    EMOE_DPP_REDUCE(STEP)
+#undef STEP
+    return v;
+}
 // Orders this wavefront's LDS traffic: writes before it are visible to every lane after it.
 __device__ __forceinline__ void wave_sync()
 {
