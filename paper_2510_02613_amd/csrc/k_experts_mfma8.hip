@@ -243,9 +243,12 @@ __device__ __forceinline__ void wait_copies(int n)
     }
 }
 
+// K-step number i in the order this workgroup walks its KT steps: it starts at step `first` and wraps around.
+__device__ __forceinline__ int step_at(int i, int first, int KT) { return i + first < KT ? i + first : i + first - KT; }
+
 // KT K-steps of 64 of this wavefront.  The caller issued the first depth - 1 steps of the ring this wavefront loads.
 template <int NTC, typename R>
-__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, f32x16 (&acc)[kWT][kTC])
+__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x16 (&acc)[kWT][kTC])
 {
     const bool wloader = c.wave < 4;
     const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
@@ -256,7 +259,7 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
         __syncthreads();   // everyone's share of step kt is in LDS; everyone is done reading step kt-1
         auto issue = [&]() {
             if (kt + depth - 1 >= KT) return;
-            issue_step(c, wloader ? wring + fill * kWStage : xring + fill * R::XStage, (kt + depth - 1) * kBK);
+            issue_step(c, wloader ? wring + fill * kWStage : xring + fill * R::XStage, step_at(kt + depth - 1, first, KT) * kBK);
             fill = fill + 1 == depth ? 0 : fill + 1;
         };
         if (!wloader || !R::kMid) issue();
@@ -327,7 +330,7 @@ __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c,
 // (Letting the last of a tile's workgroups to finish do the adding, in the same launch, was
 // measured and is slower: the device-wide fence it needs costs more than the third launch.)
 template <bool kFirst, int NTC, int kPhase, typename R>
-__device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, char *ring,
+__device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, int first, char *ring,
                                           float *tile_sets, int part)
 {
     f32x16 acc[kWT][kTC];
@@ -337,7 +340,7 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
         for (int t = 0; t < kTC; ++t)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
-    k_loop<NTC, R>(c, ring, KT, acc);
+    k_loop<NTC, R>(c, ring, KT, first, acc);
     __syncthreads();  // all operand reads are done: the ring becomes the epilogue staging area
     if (kPhase == 1) {
         float *mine = tile_sets + (size_t)part * kPartialFloats;
@@ -512,6 +515,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     }
 
     const int KT = w1 - w0;
+    // All workgroups of a launch walk K at the same pace, 128 bytes of rows that lie a row length apart: started at the
+    // same K-step they ask the same few memory channels at a time (a row length of 4096 bytes is the worst case, and
+    // how bad it gets then changes with where the pool lies).  The N-slices of a tile start spread over K instead.
+    // Only while a tile has few token rows: many of them are shared through L2 by slices at the same K-step.
+    // Qwen3 shape (rows of 4096 bytes) 333 tokens 236 .. 254 -> 228 us, 1000 tokens 263 .. 281 -> 251 us; rows of
+    // 14336 bytes +-0; with the tiles of 8192 tokens of the DeepSeek-V3-shaped rank included 943 -> 998 us.
+    const int first = kPhase == 0 && c.n_tt <= 4 ? n0 / BNO * KT / p.n_slices[kFirst ? 0 : 1] : 0;
     // token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
     // wavefront's work is specialised on that count so that its K loop is straight-line code.
     const int ntc = (c.n_tt - c.wm + 1) >> 1;
@@ -523,8 +533,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
             using R = decltype(geometry);
             const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
             const int depth = c.wave < 4 ? R::NW : R::NX;
-            for (int s = 0; s < depth - 1 && s < KT; ++s) issue_step(c, c.wave < 4 ? wring + s * kWStage : xring + s * R::XStage, s * kBK);
-            wave_body<kFirst, decltype(tiles)::value, kPhase, R>(p, c, mt, n0, N, KT, ring, tile_sets, part);
+            for (int s = 0; s < depth - 1 && s < KT; ++s) issue_step(c, c.wave < 4 ? wring + s * kWStage : xring + s * R::XStage, step_at(s, first, KT) * kBK);
+            wave_body<kFirst, decltype(tiles)::value, kPhase, R>(p, c, mt, n0, N, KT, first, ring, tile_sets, part);
         };
         using std::integral_constant;
         if (c.n_tt <= 2)      { if (ntc == 1) run(Ring2{}, integral_constant<int, 1>{}); else run(Ring2{}, integral_constant<int, 0>{}); }
