@@ -1,4 +1,5 @@
-// Weight-streaming expert kernels for decode-sized batches (bf16).
+// Weight-streaming expert kernels for decode-sized batches (bf16): operands in registers, small tasks; a token or two, and
+// contractions that are no whole K-steps (the LDS-ring kernels take the rest).
 //
 // With a few tokens per step most resident experts receive 0-4 rows (the
 // memory-bound regime of the layer of Sec. 2.1 of the paper under expert
@@ -66,7 +67,8 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     const int ks = NS > 1 ? (int)(threadIdx.x >> 6) : 0;    // which part of the contraction
     int task = blockIdx.x;
     if (kSelf) {
-        if (task == 0) { self_tables(p, kTileRows); return; }
+        __shared__ int32_t lds[kSelfTableBytes / 4];
+        if (task == 0) { self_tables(p, kTileRows, lds); return; }
         task -= 1;
     }
     const int tile = task / groups;

@@ -114,12 +114,13 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
     constexpr int TR = 16 * TT, COLS = kFirst ? kWRows / 2 : kWRows;
     __shared__ f32x4 part[kSplit * TT * 2 * 64];
+    static_assert(sizeof part >= kSelfTableBytes, "the table workgroup borrows the partial sums' LDS");
     const int N = kFirst ? p.I : p.H;
     const int groups = (N + COLS - 1) / COLS;               // tasks per M-tile
     const int lane = threadIdx.x & 63, n = lane & 15;
     int task = blockIdx.x;
     if (kSelf) {
-        if (task == 0) { self_tables(p, TR); return; }
+        if (task == 0) { self_tables(p, TR, part); return; }
         task -= 1;
     }
     const int tile = task / groups, n0 = task % groups * COLS;

@@ -608,15 +608,22 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = !routed_ids && T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // Weight streaming without LDS when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
+    // Small weight-streaming tasks when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
     // large-tile kernels, which stream the weights through deep LDS rings while groups are small.  The 128 x 128
     // kernels take what those cannot address (contractions that are no whole K-steps).
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const bool tiny = mfma && !(can_big && (long long)T * p.kk >= 48ll * p.S) &&
                       (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool big = can_big && !tiny;
+    // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
+    // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416); with a token or two there are too few of its 128-row tasks for
+    // the chip (Qwen3 shape: 1 token, 96 tasks, 34 -> 39; 2 tokens, 192 tasks, 47 -> 43), and the register kernel
+    // with its 32-row tasks takes them, as it takes contractions that are no whole K-steps.
+    const long long resident = p.S - p.n_shared < p.E ? p.S - p.n_shared : p.E;
+    const long long tiles_expected = (long long)T * p.k * resident / p.E + (shared_end > shared_begin ? p.n_shared : 0);
+    const bool ring = tiny && can_big && tiles_expected * (p.I / 64) >= 128;
     const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    const int tile_rows = big ? mfma8_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
+    const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
     // tile.  With a token or two most slots have none, and thousands of workgroups that only find out that their
     // tile does not exist take longer to dispatch than one token's experts take to stream.
@@ -648,6 +655,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     if (e == hipSuccess) {
         if (identity)  e = launch_identity_experts(p, st);
         else if (big)  e = launch_experts_mfma8(p, 0, st);
+        else if (ring) e = launch_experts_ring(p, 0, st);
         else if (tiny) e = launch_experts_decode(p, 0, st);
         else if (mfma) e = launch_experts_mfma(p, 0, st);
         else if (f32)  e = launch_experts_f32(p, tile_rows, 0, st);
@@ -655,7 +663,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     }
     mark(MOE_PHASE_GEMM2);
     if (e == hipSuccess && !identity)
-        e = big ? launch_experts_mfma8(p, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
+        e = big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
             f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
     mark(MOE_PHASE_COMBINE);
     if (e == hipSuccess) e = launch_combine(p, st);

@@ -127,10 +127,13 @@ hipError_t launch_ceiling_tile_stream(const void *buf, int n_tiles, size_t row_b
 // weight-streaming variant for decode-sized batches (M-tiles of 16 rows)
 hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st);
 int decode_tile_rows();
+// the same for contractions that are whole K-steps (H and I multiples of 64)
+hipError_t launch_experts_ring(const Pass &p, int which, hipStream_t st);
+int ring_tile_rows();
 // fp32 layers, M-tiles of 16, 32 or 64 rows
 hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st);
 int f32_tile_rows(const Pass &p);
-// GEMM-1 of those two can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
+// GEMM-1 of these can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
 // at most 4 blocks of tokens and 256 slots: no bookkeeping kernel in front of it
 inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 256 && p.T <= 4 * 16; }
 hipError_t launch_identity_experts(const Pass &p, hipStream_t st);

@@ -65,11 +65,12 @@ __device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, i
 }
 
 // Workgroup 0: counts, offsets, tile list (slot order, chunks of tile_rows), permutation and its inverse --
-// the tables of the bookkeeping kernels, for the few-token case.  256 threads.
-__device__ inline void self_tables(const Pass &p, int tile_rows)
+// the tables of the bookkeeping kernels, for the few-token case.  256 threads; lds: kSelfTableBytes of LDS.
+constexpr int kSelfTableBytes = kSelfMaxSlots * 8;
+__device__ inline void self_tables(const Pass &p, int tile_rows, void *lds)
 {
-    __shared__ uint32_t s_cb[kSelfMaxSlots];   // count bytes of slot s
-    __shared__ int32_t s_off[kSelfMaxSlots];
+    uint32_t *s_cb = (uint32_t *)lds;                        // count bytes of slot s
+    int32_t *s_off = (int32_t *)(s_cb + kSelfMaxSlots);
     const int tid = threadIdx.x, nb = (p.T + kFusedTokens - 1) / kFusedTokens;
     if (tid < 64) {
         const SelfScan sc = self_scan(p, tid, nb, tile_rows);

@@ -49,6 +49,43 @@ def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
         np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
 
 
+@pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
+@pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
+def test_decode_ring_kernels(tokens, hidden, inter):
+    """The LDS-ring decode kernels: contractions shorter and longer than the ring, output widths that end inside a task's
+    128 columns, shared rows; tables and output as in
+    the pass with separate bookkeeping kernels, bit for bit."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="ring", tokens=tokens, hidden=hidden, inter=inter, n_experts=96, top_k=4, n_slots=93, n_local=90,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, min(tokens, 30)), seed=700 + tokens)
+    case = Case(wl, expert_map=block_expert_map(96, 0, 90, np.random.Generator(np.random.PCG64(3)).permutation(92)[:90]))
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
+def test_decode_ring_kernels_with_a_crowded_expert():
+    """Every token takes the same expert: its 64 rows are two tiles of the ring kernels."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="crowd", tokens=64, hidden=256, inter=512, n_experts=64, top_k=4, n_slots=64, n_local=64,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", seed=77)
+    g = np.random.Generator(np.random.PCG64(5))
+    ids = np.stack([np.concatenate([[7], 8 + g.permutation(56)[:3]]) for _ in range(64)]).astype(np.int32)
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    tiles = case.layer.view(64)["tiles"]
+    assert (tiles[tiles[:, 0] == 7][:, 2] == 32).all() and (tiles[:, 0] == 7).sum() == 2
+
+
 @pytest.mark.parametrize("tokens", [1, 16, 33, 64, 65, 257, 700])
 @pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32")])
 def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
