@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void k_combine(Pass p)
     }
 }
 
-struct MapChunk { int32_t v[256]; };
+struct MapChunk { int32_t v[kTableArg]; };
 
 __global__ void k_write_map(int32_t *dst, MapChunk c, int n)
 {
@@ -204,11 +204,11 @@ hipError_t launch_combine(const Pass &p, hipStream_t st)
 // like any other kernel; no staging buffer, no memcpy node.
 hipError_t launch_write_map(int32_t *dst, const int32_t *host_vals, int n, hipStream_t st)
 {
-    for (int o = 0; o < n; o += 256) {
+    for (int o = 0; o < n; o += kTableArg) {
         MapChunk c;
-        const int m = n - o < 256 ? n - o : 256;
-        for (int i = 0; i < 256; ++i) c.v[i] = i < m ? host_vals[o + i] : -1;
-        hipLaunchKernelGGL(k_write_map, dim3(1), dim3(256), 0, st, dst + o, c, m);
+        const int m = n - o < kTableArg ? n - o : kTableArg;
+        for (int i = 0; i < kTableArg; ++i) c.v[i] = i < m ? host_vals[o + i] : -1;
+        hipLaunchKernelGGL(k_write_map, dim3(1), dim3(kTableArg), 0, st, dst + o, c, m);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -341,6 +341,29 @@ __device__ __forceinline__ void widen(const RouterRun<float> &r, float (&f)[32])
     for (int e = 0; e < 32; ++e) f[e] = ((const float *)&r.v[0])[e];
 }
 
+// 8 consecutive elements of a row (zeros past the end)
+template <typename T> struct Run8 { uint4 v[sizeof(T) / 2]; };
+template <typename T>
+__device__ __forceinline__ void load_run8(Run8<T> &r, const T *row, int k, int H)
+{
+#pragma unroll
+    for (int h = 0; h < (int)sizeof(T) / 2; ++h) r.v[h] = k < H ? *(const uint4 *)(row + k + h * (16 / sizeof(T))) : make_uint4(0, 0, 0, 0);
+}
+__device__ __forceinline__ void widen8(const Run8<uint16_t> &r, float (&f)[8])
+{
+    const uint32_t *u = (const uint32_t *)&r.v[0];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        f[2 * e] = __uint_as_float(u[e] << 16);
+        f[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
+    }
+}
+__device__ __forceinline__ void widen8(const Run8<float> &r, float (&f)[8])
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) f[e] = ((const float *)&r.v[0])[e];
+}
+
 template <typename XT, typename WT>
 __global__ __launch_bounds__(kThreads) void k_gate_logits(Pass p)
 {
@@ -626,35 +649,40 @@ __global__ __launch_bounds__(kThreads) void k_gate_select(Pass p)
 // Word [slot][block] of blk_hist: the mask, and above it (bits 16..21) the selection position of the
 // block's first row in the slot (with the token it makes the group's first-assignment key); byte
 // [slot][block] of blk_cnt: the number of rows, i.e. of mask bits.
-// kMany: batches that fill the chip; two workgroups per compute unit then matter more than a token's latency.
-template <bool kMany>
-__global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_eu(kMany ? 8 : 4))) void k_gate_select_hist(Pass p, int n_blocks)
+// The expert table's entries [0, E + n_shared) -> LDS: from the workspace, or from the kernel's argument (a pass that
+// brings its placement along: the first workgroup then leaves it in the workspace too).
+struct NoTable {};
+struct TableArg { int32_t v[kTableArg]; };
+__device__ __forceinline__ void stage_table(const Pass &p, const NoTable &, int32_t *map)
 {
-    extern __shared__ float smem[];
-    const int S = p.S, stride = select_stride(p.E);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float *lg = smem + wave * 2 * stride;
-    uint32_t *blkmask = (uint32_t *)(smem + kFusedTokens * 2 * stride);   // [S]
-    int32_t *map = (int32_t *)(blkmask + S);                              // [E + n_shared] of the expert table: looked up right after the selection
-    for (int s = threadIdx.x; s < S; s += kFusedTokens * 64) blkmask[s] = 0u;
     for (int e = threadIdx.x; e < p.E + p.n_shared; e += kFusedTokens * 64) map[e] = p.map[e];
-    __syncthreads();
-    const int t = blockIdx.x * kFusedTokens + wave;
-    int slot = -1;
-    if (t < p.T) {
-        const int id = select_one<kMany ? 4 : kGatePlanes>(p, t, lg, lg + stride, lane);
-        if (lane < p.k) {
-            const int m = map[id];
-            if (m >= -1) {
-                slot = m;
-            } else {   // an expert with several copies: token t uses copy t mod R of the list behind the table's entries
-                const int32_t *copies = p.map + p.E + p.n_shared + (-2 - m);
-                slot = copies[1 + t % copies[0]];
-            }
-        } else if (lane < p.kk && t >= p.shared_begin && t < p.shared_end) {
-            slot = map[p.E + (lane - p.k)];
-        }
+}
+__device__ __forceinline__ void stage_table(const Pass &p, const TableArg &tab, int32_t *map)
+{
+    for (int e = threadIdx.x; e < p.E + p.n_shared; e += kFusedTokens * 64) {
+        const int32_t v = tab.v[e];
+        map[e] = v;
+        if (blockIdx.x == 0) const_cast<int32_t *>(p.map)[e] = v;
     }
+}
+
+// Slot of this lane's assignment of token t (lane j < k: the j-th selected expert `id`, then the shared experts), or -1.
+__device__ __forceinline__ int slot_of_lane(const Pass &p, const int32_t *map, int t, int lane, int id)
+{
+    if (lane < p.k) {
+        const int m = map[id];
+        if (m >= -1) return m;
+        // an expert with several copies: token t uses copy t mod R of the list behind the table's entries
+        const int32_t *copies = p.map + p.E + p.n_shared + (-2 - m);
+        return copies[1 + t % copies[0]];
+    }
+    if (lane < p.kk && t >= p.shared_begin && t < p.shared_end) return map[p.E + (lane - p.k)];
+    return -1;
+}
+
+// The block's token masks from its assignments' slots, and every assignment's rank.  All threads call it.
+__device__ __forceinline__ void rank_block(const Pass &p, int n_blocks, uint32_t *blkmask, int t, int slot, int lane, int wave)
+{
     if (slot >= 0) atomicOr(&blkmask[slot], 1u << wave);
     __syncthreads();
     int rank = 0;
@@ -664,11 +692,96 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
     }
     if (t < p.T && lane < p.kk) p.slot_rank[(size_t)t * p.kk + lane] = slot >= 0 ? ((slot << 12) | rank) : -1;
     __syncthreads();
-    for (int s = threadIdx.x; s < S; s += kFusedTokens * 64) {
+    for (int s = threadIdx.x; s < p.S; s += kFusedTokens * 64) {
         const uint32_t m = blkmask[s];
         p.blk_hist[(size_t)s * fused_row_stride(n_blocks) + blockIdx.x] = (int32_t)m;
         p.blk_cnt[(size_t)s * fused_row_stride(n_blocks) + blockIdx.x] = (uint8_t)__popc(m & 0xffffu);   // what the placing kernel adds up
     }
+}
+
+// kMany: batches that fill the chip; two workgroups per compute unit then matter more than a token's latency.
+template <bool kMany, typename Table>
+__global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_eu(kMany ? 8 : 4))) void k_gate_select_hist(Pass p, int n_blocks, Table tab)
+{
+    extern __shared__ float smem[];
+    const int S = p.S, stride = select_stride(p.E);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float *lg = smem + wave * 2 * stride;
+    uint32_t *blkmask = (uint32_t *)(smem + kFusedTokens * 2 * stride);   // [S]
+    int32_t *map = (int32_t *)(blkmask + S);                              // [E + n_shared]: looked up right after the selection
+    for (int s = threadIdx.x; s < S; s += kFusedTokens * 64) blkmask[s] = 0u;
+    stage_table(p, tab, map);
+    __syncthreads();
+    const int t = blockIdx.x * kFusedTokens + wave;
+    int slot = -1;
+    if (t < p.T) slot = slot_of_lane(p, map, t, lane, select_one<kMany ? 4 : kGatePlanes>(p, t, lg, lg + stride, lane));
+    rank_block(p, n_blocks, blkmask, t, slot, lane, wave);
+}
+
+// Logits and selection in one kernel, for routers that a workgroup can multiply its own 16 tokens with (up to 64 experts,
+// 512 wide: at most 128 KB, out of L2): such a layer is a chain of launches, and this is one less.  Wavefront w
+// multiplies expert tile w mod n_et with its share of the contraction, the shares are added in K order.
+// 64 tokens of the 128 x 64 fp32 layer: 8.3 us in two launches -> 5 us.
+// kRank = false: the selection alone (the bookkeeping of the pass is separate).
+constexpr int kSmallExperts = 64, kSmallHidden = 512;
+constexpr int kSmallChunks = kSmallHidden / 32 / (kFusedTokens / (kSmallExperts / 16));   // most chunks of 32 k a wavefront has: 4
+template <typename XT, typename WT, typename Table, bool kRank>
+__global__ __launch_bounds__(kFusedTokens * 64) void k_gate_small(Pass p, int n_blocks, Table tab)
+{
+    constexpr bool kBf16 = sizeof(XT) == 2 && sizeof(WT) == 2;
+    __shared__ float part[kFusedTokens * 256];
+    __shared__ float lgs[kFusedTokens * 128];
+    __shared__ int32_t map[kSmallExperts + 4];
+    extern __shared__ uint32_t blkmask[];   // [S]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, q = lane >> 4;
+    const int E = p.E, H = p.H, t0 = blockIdx.x * kFusedTokens;
+    if (kRank) {
+        for (int s = threadIdx.x; s < p.S; s += kFusedTokens * 64) blkmask[s] = 0u;
+        stage_table(p, tab, map);
+    }
+    const int n_et = (E + 15) >> 4, parts = kFusedTokens / n_et, et = wave % n_et, my_part = wave / n_et;
+    const int chunks = (H + 31) / 32, per = (chunks + parts - 1) / parts;
+    const int c0 = min(my_part * per, chunks), c1 = my_part < parts ? min(c0 + per, chunks) : c0;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const XT *x = (const XT *)p.x + (size_t)min(t0 + n, p.T - 1) * H;
+    const WT *wr = (const WT *)p.router_w + (size_t)min(et * 16 + n, E - 1) * H;
+    Run8<XT> xv[kSmallChunks];
+    Run8<WT> wv[kSmallChunks];
+#pragma unroll
+    for (int i = 0; i < kSmallChunks; ++i) {     // this lane's 8 k of every chunk (H % 8 == 0), all requested together
+        const int k = (c0 + i) * 32 + q * 8, end = c0 + i < c1 ? H : 0;
+        load_run8(xv[i], x, k, end);
+        load_run8(wv[i], wr, k, end);
+    }
+#pragma unroll
+    for (int i = 0; i < kSmallChunks; ++i) {
+        if (c0 + i >= c1) break;
+        if constexpr (kBf16) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&wv[i].v[0], *(bf16x8 *)&xv[i].v[0], acc, 0, 0, 0);
+        } else {
+            float xf[8], wf[8];
+            widen8(xv[i], xf);
+            widen8(wv[i], wf);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], xf[e], acc, 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part[wave * 256 + r * 64 + lane] = acc[r];
+    __syncthreads();
+    const int t = t0 + wave;
+    int slot = -1;
+    if (t < p.T) {
+        float v[1] = {0.f};
+        if (lane < E) {   // expert lane: tile lane / 16, row 4 q' + r of it, token `wave`
+            const int at = (lane & 3) * 64 + ((lane & 15) >> 2) * 16 + wave;
+            for (int i = 0; i < parts; ++i) v[0] += part[(i * n_et + (lane >> 4)) * 256 + at];
+            if (p.logit_bias) v[0] += p.logit_bias[lane];
+        }
+        const int id = select_regs<1>(p, t, v, lgs + wave * 128, lgs + wave * 128 + 64, lane);
+        if (kRank) slot = slot_of_lane(p, map, t, lane, id);
+    }
+    if (kRank) rank_block(p, n_blocks, blkmask, t, slot, lane, wave);
 }
 
 template <typename XT, typename WT>
@@ -705,19 +818,54 @@ hipError_t launch_logits_bf16(const Pass &p, int *planes, hipStream_t st)
     return launch_gate_logits_lds<WT, 2, 1>(p, st);                                  // 32 tokens x 64 experts
 }
 
+template <bool kMany, typename Table>
+hipError_t launch_select_hist(const Pass &p, const Table &tab, hipStream_t st)
+{
+    const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
+    const size_t smem = sizeof(float) * kFusedTokens * 2 * (size_t)select_stride(p.E) + sizeof(uint32_t) * (p.S + p.E + p.n_shared);
+    if (smem > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k_gate_select_hist<kMany, Table>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_gate_select_hist<kMany, Table>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, tab);
+    return hipGetLastError();
+}
+
+template <typename XT, typename WT>
+hipError_t launch_small_t(const Pass &p, hipStream_t st, const TableArg *tab)
+{
+    const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
+    const size_t smem = sizeof(uint32_t) * p.S;
+    if (!p.fused_hist) hipLaunchKernelGGL((k_gate_small<XT, WT, NoTable, false>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, NoTable{});
+    else if (tab) hipLaunchKernelGGL((k_gate_small<XT, WT, TableArg, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, *tab);
+    else     hipLaunchKernelGGL((k_gate_small<XT, WT, NoTable, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, NoTable{});
+    return hipGetLastError();
+}
+
+void fill_table(const Pass &p, TableArg &tab)
+{
+    for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
+}
+
+hipError_t launch_gate_small(const Pass &p, hipStream_t st)
+{
+    TableArg arg;
+    if (p.host_table) fill_table(p, arg);
+    const TableArg *tab = p.host_table ? &arg : nullptr;
+    if (p.act_bf16) return p.router_bf16 ? launch_small_t<uint16_t, uint16_t>(p, st, tab) : launch_small_t<uint16_t, float>(p, st, tab);
+    return p.router_bf16 ? launch_small_t<float, uint16_t>(p, st, tab) : launch_small_t<float, float>(p, st, tab);
+}
+
 hipError_t launch_select(const Pass &p, hipStream_t st)
 {
     if (p.fused_hist) {
-        const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
-        const size_t smem = sizeof(float) * kFusedTokens * 2 * (size_t)select_stride(p.E) + sizeof(uint32_t) * (p.S + p.E + p.n_shared);
         const bool many = p.T > 2048;
-        if (smem > 64 * 1024) {
-            const hipError_t e = hipFuncSetAttribute(many ? (const void *)k_gate_select_hist<true> : (const void *)k_gate_select_hist<false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
+        if (p.host_table) {
+            TableArg arg;
+            fill_table(p, arg);
+            return many ? launch_select_hist<true>(p, arg, st) : launch_select_hist<false>(p, arg, st);
         }
-        if (many) hipLaunchKernelGGL((k_gate_select_hist<true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb);
-        else      hipLaunchKernelGGL((k_gate_select_hist<false>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb);
-        return hipGetLastError();
+        return many ? launch_select_hist<true>(p, NoTable{}, st) : launch_select_hist<false>(p, NoTable{}, st);
     }
     const size_t smem = sizeof(float) * 4 * 2 * (size_t)select_stride(p.E);
     hipLaunchKernelGGL(k_gate_select, dim3((p.T + 3) / 4), dim3(kThreads), smem, st, p);
@@ -732,6 +880,7 @@ hipError_t launch_gate(const Pass &p0, hipStream_t st)
 {
     Pass p = p0;
     hipError_t e;
+    if (!p.gate_tiled && p.E <= kSmallExperts && p.H <= kSmallHidden) return launch_gate_small(p, st);
     if (p.act_bf16) {
         e = p.router_bf16 ? launch_logits_bf16<uint16_t>(p, &p.logit_planes, st) : launch_logits_bf16<float>(p, &p.logit_planes, st);
     } else {

@@ -163,6 +163,7 @@ struct moe_layer {
     struct Fill { hipEvent_t ev; void *stream; };
     std::vector<Fill> load_ev;
     int n_pending = 0;
+    const int32_t *table_arg = nullptr;   // host table of a moe_forward_static pass whose selection kernel installs it
     hipEvent_t serve_ev = nullptr;  // "work enqueued on the serving stream so far", recorded per fill
     moe_vpool *vpool[2] = {nullptr, nullptr};  // the page pools under w13 and w2 when the layer was told (moe_layer_bind_vpools)
 };
@@ -585,6 +586,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.map = (const int32_t *)(ws + l->lay.map);
     p.logits = (float *)(ws + l->lay.logits);
     p.logit_planes = 1;
+    p.host_table = l->table_arg;
     // the kernels after the gate only read ids and w
     p.ids = routed_ids ? const_cast<int32_t *>(routed_ids) : (int32_t *)(ws + l->lay.ids);
     p.w = routed_w ? const_cast<float *>(routed_w) : (float *)(ws + l->lay.w);
@@ -617,11 +619,11 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const bool big = can_big && !tiny;
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
     // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416); with a token or two there are too few of its 128-row tasks for
-    // the chip (Qwen3 shape: 1 token, 96 tasks, 34 -> 39; 2 tokens, 192 tasks, 47 -> 43), and the register kernel
+    // the chip (Qwen3 shape: 96 tasks, 34 -> 39; 144, 33.7 -> 34.7; 192, 47 -> 43), and the register kernel
     // with its 32-row tasks takes them, as it takes contractions that are no whole K-steps.
     const long long resident = p.S - p.n_shared < p.E ? p.S - p.n_shared : p.E;
     const long long tiles_expected = (long long)T * p.k * resident / p.E + (shared_end > shared_begin ? p.n_shared : 0);
-    const bool ring = tiny && can_big && tiles_expected * (p.I / 64) >= 128;
+    const bool ring = tiny && can_big && tiles_expected * (p.I / 64) >= 160;
     const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
     const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
@@ -752,8 +754,13 @@ moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *bu
     lay.lay = L;
     lay.has_map = true;
     // every pass writes what it reads (table, histograms, tile list, h, y): nothing has to start at zero
-    const hipError_t e = launch_write_map((int32_t *)((char *)ws + L.map), table, c.n_experts + c.n_shared, (hipStream_t)hip_stream);
-    if (e != hipSuccess) return fail(MOE_ERR_HIP, "expert map upload failed: %s", hipGetErrorString(e));
+    // the table comes in with the selection kernel when that kernel ranks the assignments too and it fits an argument
+    if (T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED) && c.n_experts + c.n_shared <= kTableArg) {
+        lay.table_arg = table;
+    } else {
+        const hipError_t e = launch_write_map((int32_t *)((char *)ws + L.map), table, c.n_experts + c.n_shared, (hipStream_t)hip_stream);
+        if (e != hipSuccess) return fail(MOE_ERR_HIP, "expert map upload failed: %s", hipGetErrorString(e));
+    }
     return forward_pass(&lay, x, T, nullptr, nullptr, shared_begin, shared_end, out, hip_stream, flags);
 }
 

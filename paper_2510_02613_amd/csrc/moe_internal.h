@@ -90,10 +90,12 @@ struct Pass {
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
     float *partials;     // partial sums of the large-tile GEMMs' split tiles, or NULL (no room: never split)
+    const int32_t *host_table;   // HOST address of the expert table when the selection kernel is to carry it in as an argument (moe_forward_static), else NULL
     int32_t n_cus;       // compute units of the device (set by the large-tile launcher)
     int32_t k_split;     // this launch may share the contraction of its last round's tiles out (set by the launcher)
 };
 
+constexpr int kTableArg = 512;         // expert-table entries that travel in one kernel argument
 constexpr int kGatePlanes = 8;         // most partial-sum planes of the gate logits
 constexpr int kGateFewTokens = 256;    // up to here the few-token logits kernel shares the contraction out over workgroups
 constexpr int kAssignPerBlock = 1024;  // assignments ranked by one block of the slot histogram kernel

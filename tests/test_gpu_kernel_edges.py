@@ -101,3 +101,23 @@ def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
     ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
     check_bookkeeping(case, v, tokens, wl.shared_range)
     check_output(case, out, ids)
+
+
+@pytest.mark.parametrize("act,router", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "bf16"), ("f32", "f32")])
+@pytest.mark.parametrize("experts,hidden,tokens", [(4, 64, 1), (16, 512, 16), (17, 480, 17), (48, 136, 33), (64, 512, 64), (65, 512, 17), (64, 520, 17), (511, 64, 17), (512, 64, 17)])
+def test_small_router_gate(act, router, experts, hidden, tokens):
+    """Routers that are multiplied and selected from in one kernel (up to 64 experts, 512 wide) and the first sizes past
+    it: 1 to 4 tiles of 16 experts, shares of the contraction with and without a remainder, one and several blocks of 16
+    tokens; the pass that brings its placement along (512 table entries fit the argument) gives the same output."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing, tensor_to_host
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="gate", tokens=tokens, hidden=hidden, inter=64, n_experts=experts, top_k=2, n_slots=experts + 1, n_local=experts,
+                     act_dtype=act, router_dtype=router, gate="softmax", n_shared=1, shared_range=(0, tokens), seed=500 + experts)
+    case = Case(wl)
+    out = case.run()
+    v = case.layer.view(tokens)
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
+    np.testing.assert_array_equal(out, case.run(flags=B.MOE_FLAG_PERMUTE_UNFUSED))
+    np.testing.assert_array_equal(out, tensor_to_host(case.layer.forward_static(case.x_dev, shared_range=wl.shared_range)))
