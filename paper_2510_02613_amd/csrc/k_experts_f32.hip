@@ -10,8 +10,8 @@
 // each walk a quarter of the contraction; the four sums are added in K order through LDS.  Operands go straight from
 // global memory into the layout of v_mfma_f32_16x16x4_f32: lane (n = l % 16, q = l / 16) reads 16 bytes, k = 4q .. 4q+3,
 // of row n per 16 k, and the contraction does not care that MFMA i takes element i of every lane as long as weight
-// and token rows agree.  A tile has up to 64 token rows, which a weight row read once serves; the next 32 k are
-// in flight while 32 are multiplied.
+// and token rows agree.  A tile has up to 64 token rows, which a weight row read once serves; the next 16 k are
+// in flight while 16 are multiplied.
 // Measured against 32 x 64 tiles staged through LDS without overlap: 64 tokens of the 128 x 64 layer, GEMM-1 21 -> 5 us;
 // 1500 tokens of a 264 x 264 layer, GEMM-1 99 -> 18 us, GEMM-2 65 -> 12 us.
 #include "moe_internal.h"
@@ -23,7 +23,8 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSplit = 4;         // wavefronts that share a task's contraction
-constexpr int kKC = 32;           // k per chunk: 128 bytes of every row
+constexpr int kKC = 16;           // k per chunk: with the 128 bytes of 32 k, a 264-wide contraction left a wavefront without work (264 x 264 layer,
+                                  // 1500 tokens, whole pass: 75 -> 70 us)
 constexpr int kWRows = 32;        // weight rows per task
 
 struct Run { f32x4 v[kKC / 16]; };   // a lane's share of one row of a chunk
