@@ -876,6 +876,21 @@ hipError_t launch_select(const Pass &p, hipStream_t st)
 
 int gate_f32_planes(int T, int H) { return few_token_planes(T, H); }
 
+// Logits and selection of the tokens that the logits' memory holds, then of the next ones.
+static hipError_t launch_gate_in_parts(const Pass &p, hipStream_t st)
+{
+    for (int t = 0; t < p.T; t += p.logit_tokens) {
+        Pass q = p;
+        q.T = p.T - t < p.logit_tokens ? p.T - t : p.logit_tokens;
+        q.x = (const char *)p.x + (size_t)t * p.H * (p.act_bf16 ? 2 : 4);
+        q.ids = p.ids + (size_t)t * p.k;
+        q.w = p.w + (size_t)t * p.k;
+        const hipError_t e = launch_gate(q, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_gate(const Pass &p0, hipStream_t st)
 {
     Pass p = p0;
@@ -884,7 +899,9 @@ hipError_t launch_gate(const Pass &p0, hipStream_t st)
     if (p.act_bf16) {
         e = p.router_bf16 ? launch_logits_bf16<uint16_t>(p, &p.logit_planes, st) : launch_logits_bf16<float>(p, &p.logit_planes, st);
     } else {
-        p.logit_planes = gate_f32_planes(p.T, p.H);
+        if (p.T > p.logit_tokens) return launch_gate_in_parts(p, st);
+        const int room = p.logit_tokens / p.T, planes = gate_f32_planes(p.T, p.H);
+        p.logit_planes = planes < room ? planes : room;
         e = p.router_bf16 ? launch_gate_logits<float, uint16_t>(p, p.logit_planes, st) : launch_gate_logits<float, float>(p, p.logit_planes, st);
     }
     return e == hipSuccess ? launch_select(p, st) : e;

@@ -52,7 +52,7 @@ constexpr int kMinTileRows = 16;  // smallest M-tile any expert kernel uses: siz
 // Offsets of every intermediate inside the workspace.
 struct Layout {
     size_t map, logits, ids, w, slot_rank, blk_hist, blk_cnt, counts, offs, perm, inv, tiles, n_tiles, units[2], unit_hdr, h, y, partials, total;
-    size_t unit_cap;
+    size_t unit_cap, logit_tokens;
     bool has_partials;
 };
 
@@ -87,7 +87,10 @@ moe_status_t check_config(const moe_config_t *c)
     return MOE_OK;
 }
 
-Layout make_layout(const moe_config_t &c)
+// tight: where the size is fixed and the pass would not fit otherwise (moe_forward_static) -- the logits of an fp32
+// layer share the memory of what is written after the selection has read them, as many tokens at a time as that
+// holds, and the large-tile GEMMs serve small groups no more (no unit lists)
+Layout make_layout(const moe_config_t &c, bool tight = false)
 {
     Layout L;
     const size_t T = c.max_tokens, k = c.top_k, kk = c.top_k + c.n_shared, S = c.n_slots;
@@ -105,7 +108,9 @@ Layout make_layout(const moe_config_t &c)
         const size_t few = T < (size_t)kGateFewTokens ? T : (size_t)kGateFewTokens;
         planes_of_tokens = few * gate_f32_planes((int)few, c.hidden) > T ? few * gate_f32_planes((int)few, c.hidden) : T;
     }
-    L.logits = take(4 * planes_of_tokens * c.n_experts);
+    const bool shared_logits = tight && c.act_dtype == MOE_F32;
+    L.logits = take(shared_logits ? 0 : 4 * planes_of_tokens * c.n_experts);
+    L.logit_tokens = planes_of_tokens;
     L.ids = take(4 * T * k);
     L.w = take(4 * T * k);
     L.slot_rank = take(4 * A);
@@ -122,7 +127,7 @@ Layout make_layout(const moe_config_t &c)
     L.n_tiles = take(4);
     // unit lists of the large-tile GEMMs (layers they can serve): one entry per (tile, run of N-slices), in rows of 8
     L.unit_cap = 0;
-    if (c.act_dtype == MOE_BF16 && c.hidden % 64 == 0 && c.inter % 64 == 0) {
+    if (c.act_dtype == MOE_BF16 && c.hidden % 64 == 0 && c.inter % 64 == 0 && (!tight || A >= 48 * S)) {
         const size_t big_tiles = (A + mfma8_tile_rows() - 1) / mfma8_tile_rows() + S;
         const int ns0 = mfma8_n_slices(c.hidden, c.inter, 0), ns1 = mfma8_n_slices(c.hidden, c.inter, 1);
         L.unit_cap = 8 * (size_t)mfma8_grid_rows((int)big_tiles, ns0 > ns1 ? ns0 : ns1);
@@ -136,6 +141,10 @@ Layout make_layout(const moe_config_t &c)
     L.has_partials = c.act_dtype == MOE_BF16 && c.hidden % 64 == 0 && c.inter % 64 == 0 && (c.hidden >= 4096 || c.inter >= 4096) &&
                      A >= 48 * S;
     L.partials = take(L.has_partials ? mfma8_partial_bytes() : 0);
+    if (shared_logits) {
+        L.logits = L.perm;
+        L.logit_tokens = (o - L.perm) / (4 * (size_t)c.n_experts);
+    }
     L.total = o;
     return L;
 }
@@ -586,6 +595,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.map = (const int32_t *)(ws + l->lay.map);
     p.logits = (float *)(ws + l->lay.logits);
     p.logit_planes = 1;
+    p.logit_tokens = (int32_t)l->lay.logit_tokens;
     p.host_table = l->table_arg;
     // the kernels after the gate only read ids and w
     p.ids = routed_ids ? const_cast<int32_t *>(routed_ids) : (int32_t *)(ws + l->lay.ids);
@@ -607,7 +617,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
 
     p.gate_tiled = (flags & MOE_FLAG_GATE_TILED) != 0;
     // gated passes up to kFusedMaxTokens tokens: the selection kernel ranks the assignments, one more kernel places them
-    p.fused_hist = !routed_ids && T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
+    p.fused_hist = !routed_ids && T <= kFusedMaxTokens && T <= p.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
     // Small weight-streaming tasks when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
@@ -727,8 +737,9 @@ moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *bu
     // the workspace is laid out for THIS pass's T (max_tokens only bounds T): what must fit is the pass
     moe_config_t c = *cfg;
     c.max_tokens = T > 0 ? T : 1;
-    const Layout L = make_layout(c);
-    if (L.total > (size_t)MOE_STATIC_SCRATCH_BYTES)
+    Layout L = make_layout(c);
+    if (L.total > (size_t)MOE_STATIC_SCRATCH_BYTES) L = make_layout(c, true);
+    if (L.total > (size_t)MOE_STATIC_SCRATCH_BYTES || L.logit_tokens == 0)
         return fail(MOE_ERR_CAPACITY, "a pass of %d tokens of this layer needs %zu bytes of scratch, moe_forward_static has %zu: "
                     "use moe_forward with a workspace", T, L.total, (size_t)MOE_STATIC_SCRATCH_BYTES);
     if (!buf) return fail(MOE_ERR_ARG, "buffers is NULL");
@@ -755,7 +766,7 @@ moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *bu
     lay.has_map = true;
     // every pass writes what it reads (table, histograms, tile list, h, y): nothing has to start at zero
     // the table comes in with the selection kernel when that kernel ranks the assignments too and it fits an argument
-    if (T <= kFusedMaxTokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED) && c.n_experts + c.n_shared <= kTableArg) {
+    if (T <= kFusedMaxTokens && T <= (long long)L.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED) && c.n_experts + c.n_shared <= kTableArg) {
         lay.table_arg = table;
     } else {
         const hipError_t e = launch_write_map((int32_t *)((char *)ws + L.map), table, c.n_experts + c.n_shared, (hipStream_t)hip_stream);

@@ -66,6 +66,7 @@ struct Pass {
     const int32_t *map;  // [E + n_shared] active table, shared slots last
     float *logits;       // [logit_planes][T,E] gate logits: the planes are partial sums over K ranges
     int32_t logit_planes;
+    int32_t logit_tokens;   // tokens the logits' memory holds with one plane; fewer than T (fp32 layers): the gate takes a part of the batch at a time, fused_hist is off
     int32_t *ids;        // [T,k]
     float *w;            // [T,k]
     int32_t *slot_rank;  // [T*kk] (slot << 12 | rank-in-block) or -1

@@ -248,3 +248,21 @@ def test_pool_export_argument_checks():
     assert L.moe_pool_open(None, 0, ctypes.byref(p)) == B.MOE_ERR_ARG
     assert L.moe_pool_open(h, 0, None) == B.MOE_ERR_ARG
     assert L.moe_pool_close(None, 0) == B.MOE_ERR_ARG
+
+
+# The largest passes of three layers that the scratch array holds when the logits of an fp32 layer and the unit
+# lists of the large-tile GEMMs for small groups get no memory of their own.
+STATIC_LIMITS = [
+    (dict(hidden=264, inter=264, n_experts=40, top_k=4, n_slots=34, n_shared=1), 3144),
+    (dict(hidden=64, inter=8, n_experts=1024, top_k=1, n_slots=64), 108033),
+    (dict(hidden=512, inter=512, n_experts=512, top_k=2, n_slots=600, act_dtype=1), 1615),
+]
+
+
+@pytest.mark.parametrize("kw,limit", STATIC_LIMITS)
+def test_static_scratch_capacity(kw, limit):
+    cfg = good_cfg(max_tokens=limit + 1, **kw)
+
+    def status(T):   # buffers are checked after the capacity
+        return B.lib().moe_forward_static(ctypes.byref(cfg), None, None, 0, None, None, T, 0, 0, None, None, 0)
+    assert status(limit) == B.MOE_ERR_ARG and status(limit + 1) == B.MOE_ERR_CAPACITY

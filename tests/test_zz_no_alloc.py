@@ -71,3 +71,27 @@ def test_static_scratch_pass_rejects_what_does_not_fit():
     with pytest.raises(MoEError) as ei:   # a placement that claims a slot twice, on a pass that would fit
         B.moe_forward_static(cfg, buf, [0] * 128, None, d.data_ptr(), 16, d.data_ptr())
     assert ei.value.status == B.MOE_ERR_MAP
+
+
+@pytest.mark.parametrize("kw", [
+    # the logits share the memory of h and y
+    dict(tokens=3144, hidden=264, inter=264, n_experts=40, top_k=4, n_slots=34, n_local=30, n_shared=1,
+         shared_range=(5, 1500), act_dtype="f32"),
+    # ... which holds a fifth of them at a time
+    dict(tokens=20011, hidden=64, inter=8, n_experts=1024, top_k=1, n_slots=64, n_local=64, act_dtype="f32"),
+    # no unit lists: the 128 x 128 kernels take what the large-tile kernels would
+    dict(tokens=1615, hidden=512, inter=512, n_experts=512, top_k=2, n_slots=600, n_local=512, act_dtype="bf16"),
+], ids=["f32", "f32_in_parts", "bf16"])
+def test_static_scratch_pass_at_its_capacity(kw):
+    import torch
+    from gpu_util import Case, tensor_to_host
+    case = Case(MoEWorkload(name="static_limit", router_dtype="f32", gate="softmax", seed=65, **kw))
+    wl = case.wl
+    got = case.layer.forward_static(case.x_dev, shared_range=wl.shared_range)
+    want = case.layer.forward(case.x_dev, shared_range=wl.shared_range)
+    torch.cuda.synchronize()
+    if wl.act_dtype == "f32":
+        np.testing.assert_array_equal(tensor_to_host(got), tensor_to_host(want))
+    else:   # other kernels, sums in another order: one bf16 rounding of h, y and out each (2^-9) apart at most
+        g, w = got.view(torch.bfloat16).double(), want.view(torch.bfloat16).double()
+        assert float((g - w).norm() / w.norm()) <= 3 * 2.0 ** -9
