@@ -167,8 +167,8 @@ struct moe_layer {
     Layout lay;
     bool has_map;
     std::vector<int32_t> slot_owner;  // per slot: entry (expert, or E + shared expert) of the active table that uses it, or -1
-    // slot fills that the next map switch has to wait for: one event per copy stream, recorded again by every fill
-    // on that stream (a stream runs its fills in order), the entries reused after the switch
+    // slot fills that the next map switch has to wait for: one event per copy stream handle, recorded again by every
+    // fill on that stream, the entries reused after the switch
     struct Fill { hipEvent_t ev; void *stream; };
     std::vector<Fill> load_ev;
     int n_pending = 0;
@@ -531,6 +531,9 @@ moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, 
     if (e == hipSuccess)
         e = launch_fill_slot((char *)const_cast<void *>(l->buf.w13) + (size_t)slot * b13, src_w13, b13,
                              (char *)const_cast<void *>(l->buf.w2) + (size_t)slot * b2, src_w2, b2, blocks, (hipStream_t)copy_stream);
+    // the event is about to stand for this fill alone: the one it stood for comes first.  (On one stream it does
+    // anyway; a handle can also name another stream by now, a destroyed one's successor or another thread's own.)
+    if (e == hipSuccess && at < l->n_pending) e = hipStreamWaitEvent((hipStream_t)copy_stream, l->load_ev[at].ev, 0);
     if (e == hipSuccess) e = hipEventRecord(l->load_ev[at].ev, (hipStream_t)copy_stream);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "slot fill failed: %s", hipGetErrorString(e));
     l->load_ev[at].stream = copy_stream;

@@ -110,7 +110,7 @@ class MoELayer:
                  select_bias=None, device="cuda:0", w13_pool: Optional[VirtualPool] = None,
                  w2_pool: Optional[VirtualPool] = None):
         self.device = torch.device(device)
-        if self.device.index is None:
+        if self.device.type == "cuda" and self.device.index is None:
             self.device = torch.device("cuda", torch.cuda.current_device())
         dt = {"f32": B.MOE_F32, "bf16": B.MOE_BF16}
         self.cfg = B.MoEConfig(hidden, inter, n_experts, top_k, n_slots, max_tokens, dt[act_dtype],
@@ -184,8 +184,8 @@ class MoELayer:
                        stream: Optional[torch.cuda.Stream] = None) -> None:
         s = _stream_ptr(stream, self.device)
         # the placement as arrays of the call's type, kept for forward_static
-        m = B.i32_array(expert_map)
-        sh = None if shared_slots is None or len(shared_slots) == 0 else B.i32_array(shared_slots)
+        m = B.i32_array(list(expert_map))
+        sh = None if shared_slots is None or len(shared_slots) == 0 else B.i32_array(list(shared_slots))
         B.moe_set_expert_map(self.handle, m, sh, s)
         self.plain_map = (m, sh)
 
