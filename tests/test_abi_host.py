@@ -266,3 +266,11 @@ def test_static_scratch_capacity(kw, limit):
     def status(T):   # buffers are checked after the capacity
         return B.lib().moe_forward_static(ctypes.byref(cfg), None, None, 0, None, None, T, 0, 0, None, None, 0)
     assert status(limit) == B.MOE_ERR_ARG and status(limit + 1) == B.MOE_ERR_CAPACITY
+
+
+def test_whole_number_sequences_become_int32_arrays():
+    kept = (ctypes.c_int32 * 3)(4, -1, 2)
+    assert B.i32_array(kept) is kept
+    for vals in ([4, -1, 2], (4, -1, 2), [4.0, -1, 2], np.array([4, -1, 2]), (ctypes.c_int64 * 3)(4, -1, 2), [4, 0xffffffff, 2]):
+        assert list(B.i32_array(vals)) == [4, -1, 2]
+    assert list(B.i32_array(bytes([4, 0, 2]))) == [4, 0, 2] and len(B.i32_array([])) == 0
