@@ -6,9 +6,9 @@
 // top-k (group score = sum of the group's two best), both with optional
 // renormalisation over the k selected and a constant scale.
 //
-// Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token: scores
-// live in LDS, every arg-max is a wavefront reduction in which ties go to the lower index exactly as the ordering
-// rule demands.
+// Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token (small
+// routers: one kernel for both): scores live in registers up to 256 experts and in LDS above, every arg-max is a
+// wavefront reduction in which ties go to the lower index exactly as the ordering rule demands.
 #include <type_traits>
 
 #include "moe_internal.h"
