@@ -5,6 +5,7 @@
 // references to tensors kept by the memory daemon, Sec. 3.2 "Decoupled Memory and
 // Execution Layers"); all intermediates live in the caller's workspace, which is
 // carved once at create time, so no later call can allocate.
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -623,20 +624,30 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = !routed_ids && T <= kFusedMaxTokens && T <= p.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // Small weight-streaming tasks when a slot expects only a handful of rows (routed: T*k/E on average); otherwise the
-    // large-tile kernels, which stream the weights through deep LDS rings while groups are small.  The 128 x 128
-    // kernels take what those cannot address (contractions that are no whole K-steps).
+    // Small weight-streaming tasks when a slot expects only a handful of rows (routed: T*k/E on average).  Otherwise the
+    // large-tile kernels once slots average 48 rows, and below that where there are weights to stream: their deep LDS
+    // rings pay from about 400 MB (whole pass, us, 128 x 128 -> large tiles: Qwen3 shape with 64 local experts, 604 MB,
+    // 110 tokens 143 -> 112; 32 of them, 302 MB, 76 -> 62 with an even load but 64 -> 74 with a Zipf(1.2) one, where half
+    // the slots have no rows and a slot's few wide N-slices leave the chip idle), and lose on small layers, whose time is
+    // the bookkeeping (24 experts of 128 x 128, 40 tokens 18 -> 21; of 1024 x 768, 250 tokens 42 -> 50).  The 128 x 128
+    // kernels take the rest, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
-    const bool tiny = mfma && !(can_big && (long long)T * p.kk >= 48ll * p.S) &&
-                      (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
-    const bool big = can_big && !tiny;
+    const bool wide = can_big && (long long)T * p.kk >= 48ll * p.S;
+    const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
+    const long long pool_bytes = 6ll * p.S * p.H * p.I;
+    const bool big = wide || (can_big && !tiny && pool_bytes >= 400000000ll);
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
-    // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416); with a token or two there are too few of its 128-row tasks for
-    // the chip (Qwen3 shape: 96 tasks, 34 -> 39; 144, 33.7 -> 34.7; 192, 47 -> 43), and the register kernel
-    // with its 32-row tasks takes them, as it takes contractions that are no whole K-steps.
-    const long long resident = p.S - p.n_shared < p.E ? p.S - p.n_shared : p.E;
-    const long long tiles_expected = (long long)T * p.k * resident / p.E + (shared_end > shared_begin ? p.n_shared : 0);
-    const bool ring = tiny && can_big && tiles_expected * (p.I / 64) >= 160;
+    // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip, counted
+    // over the slots that an even routing gives rows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207,
+    // 35.1 -> 31.8).  A little more than one task per compute unit is the other exception: a few units then stream two
+    // tasks while the rest stand idle (246 tasks, 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).
+    // Rows of 7168 hide that (262 tasks, 181.6 -> 166.2).  The register kernel with its 32-row tasks takes those passes,
+    // as it takes contractions that are no whole K-steps.
+    const int resident = p.S - p.n_shared < p.E ? p.S - p.n_shared : p.E;
+    const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
+    const double ring_tasks = tiles_expected * (p.I / 64);
+    const bool second_round = p.H <= 4096 && ring_tasks >= 240. && ring_tasks < 330.;
+    const bool ring = tiny && can_big && ring_tasks >= 160. && !second_round;
     const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
     const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled

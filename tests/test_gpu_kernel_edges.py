@@ -86,6 +86,36 @@ def test_decode_ring_kernels_with_a_crowded_expert():
     assert (tiles[tiles[:, 0] == 7][:, 2] == 32).all() and (tiles[:, 0] == 7).sum() == 2
 
 
+@pytest.mark.parametrize("tokens,tile", [(3, 16), (4, 32), (8, 16), (12, 32)])
+def test_few_token_kernels_by_task_count(tokens, tile):
+    """A layer of 64 experts, 768 wide: 135, 175, 310 and 414 expected tasks of the ring kernels, which take the second
+    and the last.  Expert 9 has all assignments (ids may repeat), so the tile list tells the kernels apart."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="tasks", tokens=tokens, hidden=192, inter=768, n_experts=64, top_k=4, n_slots=64, n_local=64,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", seed=80 + tokens)
+    g = np.random.Generator(np.random.PCG64(tokens))
+    case = Case(wl)
+    _check(case, np.full((tokens, 4), 9, np.int32), g.uniform(0.5, 1.5, size=(tokens, 4)).astype(np.float32))
+    rows = case.layer.view(tokens)["tiles"][:, 2]
+    assert rows.sum() == 4 * tokens and len(rows) == -(-4 * tokens // tile)
+
+
+@pytest.mark.parametrize("tokens,tiles", [(200, 2), (255, 2), (256, 1)])
+def test_small_layers_take_the_128_row_kernels(tokens, tiles):
+    """16 slots of a small layer, three assignments per token: 768 assignments are 48 rows a slot, where the large-tile
+    kernels start (320 rows a tile); one expert has 200 rows and more, two tiles of 128 below that line."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="line", tokens=tokens, hidden=128, inter=192, n_experts=16, top_k=3, n_slots=16, n_local=16,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", seed=90 + tokens)
+    g = np.random.Generator(np.random.PCG64(tokens))
+    ids = np.stack([np.concatenate([[5], 6 + g.permutation(10)[:2]]) for _ in range(tokens)]).astype(np.int32)
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    assert (case.layer.view(tokens)["tiles"][:, 0] == 5).sum() == tiles
+
+
 @pytest.mark.parametrize("tokens", [1, 16, 33, 64, 65, 257, 700])
 @pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32")])
 def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
