@@ -189,7 +189,7 @@ __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR],
             float b1[NR], b2[NR];
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
-                b1[i] = v[i];
+                b1[i] = v[i] == v[i] ? v[i] : NEG;   // a NaN does not count (merged, it would make its partner's score count twice)
                 b2[i] = NEG;
                 merge_top2(b1[i], b2[i], dpp_f32<0x128>(b1[i]), dpp_f32<0x128>(b2[i]));   // row_ror 8, 4, 2, 1
                 merge_top2(b1[i], b2[i], dpp_f32<0x124>(b1[i]), dpp_f32<0x124>(b2[i]));

@@ -151,3 +151,39 @@ def test_small_router_gate(act, router, experts, hidden, tokens):
     check_output(case, out, ids)
     np.testing.assert_array_equal(out, case.run(flags=B.MOE_FLAG_PERMUTE_UNFUSED))
     np.testing.assert_array_equal(out, tensor_to_host(case.layer.forward_static(case.x_dev, shared_range=wl.shared_range)))
+
+
+@pytest.mark.parametrize("experts,groups,kept", [(64, 4, 2), (128, 2, 1), (256, 8, 4), (256, 16, 4), (96, 4, 2), (512, 16, 8)])
+def test_group_scores_leave_nan_experts_out(experts, groups, kept):
+    """A NaN among the selection scores of a group (a NaN bias) counts neither as one of its two best nor in the place of
+    one, whichever way the group's lanes are reduced (rows of 16, 32 and 64 lanes, or through LDS); the NaN expert itself
+    sorts before every number when its group is kept."""
+    from gpu_util import Case
+    tokens, k = 200, 6
+    wl = MoEWorkload(name="nan", tokens=tokens, hidden=128, inter=64, n_experts=experts, top_k=k, n_slots=experts, n_local=experts,
+                     act_dtype="bf16", router_dtype="f32", gate="sigmoid_group", n_group=groups, topk_group=kept, seed=600 + experts)
+    per = experts // groups
+    nan_at = np.arange(groups // 2) * 2 * per + np.arange(groups // 2) * 7 % per   # one in every second group
+    bias = np.zeros(experts, np.float32)
+    bias[nan_at] = np.nan
+    case = Case(wl, select_bias=bias)
+    case.run()
+    ids = case.layer.view(tokens)["topk_ids"]
+    case.select_bias = None                                  # the scores without the bias, from the oracle
+    c = case.oracle_route()[3].astype(np.float64)
+    c[:, nan_at] = np.nan
+    checked = 0
+    for t in range(tokens):
+        known = np.where(np.isnan(c[t]), -np.inf, c[t])
+        best = np.sort(known.reshape(groups, per), axis=1)[:, ::-1]
+        score = best[:, 0] + best[:, 1]
+        order = np.sort(score)[::-1]
+        rank = np.argsort(-score, kind="stable")[:kept]
+        # scores are sigmoids: 2 and more stand for NaN (lower expert first, as all NaN are alike), -1 for dropped
+        c_kept = np.where(np.isin(np.arange(experts) // per, rank), np.where(np.isnan(c[t]), 3.0 - np.arange(experts) / 1024, c[t]), -1.0)
+        want = np.argsort(-c_kept, kind="stable")
+        gaps = -np.diff(c_kept[want[:k + 1]])
+        if order[kept - 1] - order[kept] > 2e-5 and (gaps >= 1e-5).all():
+            np.testing.assert_array_equal(ids[t], want[:k], err_msg=f"token {t}")
+            checked += 1
+    assert checked > tokens // 2
