@@ -171,15 +171,16 @@ def moe_layer_create(cfg: MoEConfig, buf: MoEBuffers) -> ctypes.c_void_p:
 
 
 def i32_array(vals: Sequence[int]):
-    """A sequence of whole numbers as the int32 array the calls take (such an array: unchanged)."""
+    """Whole numbers, in anything that can be iterated over, as the int32 array the calls take (such an array: unchanged)."""
     if isinstance(vals, ctypes.Array) and vals._type_ is ctypes.c_int32:
         return vals
     if not isinstance(vals, (list, tuple)):
-        return (ctypes.c_int32 * len(vals))(*[int(v) for v in vals])
+        vals = [int(v) for v in vals]
     try:
         a = array.array("i", vals)
     except (TypeError, OverflowError):
-        return (ctypes.c_int32 * len(vals))(*[int(v) for v in vals])
+        vals = [int(v) for v in vals]
+        return (ctypes.c_int32 * len(vals))(*vals)
     return (ctypes.c_int32 * len(a)).from_buffer(a)
 
 

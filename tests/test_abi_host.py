@@ -273,4 +273,5 @@ def test_whole_number_sequences_become_int32_arrays():
     assert B.i32_array(kept) is kept
     for vals in ([4, -1, 2], (4, -1, 2), [4.0, -1, 2], np.array([4, -1, 2]), (ctypes.c_int64 * 3)(4, -1, 2), [4, 0xffffffff, 2]):
         assert list(B.i32_array(vals)) == [4, -1, 2]
+    assert list(B.i32_array(iter([4, -1, 2]))) == list(B.i32_array(v for v in (4.0, -1, 2))) == [4, -1, 2]   # no length
     assert list(B.i32_array(bytes([4, 0, 2]))) == [4, 0, 2] and len(B.i32_array([])) == 0
