@@ -7,7 +7,7 @@
 // renormalisation over the k selected and a constant scale.
 //
 // Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token (small
-// routers: one kernel for both): scores live in registers up to 256 experts and in LDS above, every arg-max is a
+// routers: one kernel for both): scores live in registers up to 512 experts and in LDS above, every arg-max is a
 // wavefront reduction in which ties go to the lower index exactly as the ordering rule demands.
 #include <type_traits>
 
@@ -145,7 +145,7 @@ __device__ __forceinline__ void merge_top2(float &b1, float &b2, float o1, float
 template <int CTRL>
 __device__ __forceinline__ float dpp_f32(float v) { return __int_as_float(dpp_i32<CTRL, 0xf>(__float_as_int(v), __float_as_int(v))); }
 
-// The same selection for up to 64 NR experts, NR <= 4, with the scores in registers: expert e is entry e / 64 of lane
+// The same selection for up to 64 NR experts, NR <= 8, with the scores in registers: expert e is entry e / 64 of lane
 // e % 64.  With few tokens a selection is one chain of dependent instructions (8 us of the LDS version on a grouped
 // gate with 256 experts, 0.6 of it memory), with many it is bound by their number; both are why nothing here goes
 // through LDS that a lane can keep, and why the candidates of a lane are sorted once, so that a round of the top-k
@@ -154,7 +154,8 @@ __device__ __forceinline__ float dpp_f32(float v) { return __int_as_float(dpp_i3
 template <int NR>
 __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR], float *lg, float *cs, int lane)
 {
-    static_assert(NR <= 4, "a lane's order of experts is kept in 2-bit fields");
+    constexpr int kOrderBits = NR <= 4 ? 2 : 3;
+    static_assert(NR <= 8, "a lane's order of experts is kept in fields of 2 or 3 bits");
     const int E = p.E;
     const float NEG = -__builtin_huge_valf();
     // scores
@@ -232,7 +233,7 @@ __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR],
     }
     wave_sync();
     // Candidates as order-preserving integers (0 = absent), a lane's sorted once, largest first and among equal ones
-    // the lower expert first; `order` has their entries in 2-bit fields.
+    // the lower expert first; `order` has their entries in fields of kOrderBits.
     uint32_t c[NR];
     uint32_t at[NR];
 #pragma unroll
@@ -243,23 +244,20 @@ __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR],
         c[i] = swap ? c[j] : ci; at[i] = swap ? at[j] : ai;
         c[j] = swap ? ci : c[j]; at[j] = swap ? ai : at[j];
     };
-    if constexpr (NR == 2) put_first(0, 1);
-    if constexpr (NR == 4) {                                 // odd-even transposition: four rounds of adjacent exchanges
-        put_first(0, 1); put_first(2, 3);
-        put_first(1, 2);
-        put_first(0, 1); put_first(2, 3);
-        put_first(1, 2);
-    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r)                             // odd-even transposition: NR rounds of adjacent exchanges
+#pragma unroll
+        for (int i = r & 1; i + 1 < NR; i += 2) put_first(i, i + 1);
     uint32_t order = 0;
 #pragma unroll
-    for (int i = 0; i < NR; ++i) order |= at[i] << (2 * i);
+    for (int i = 0; i < NR; ++i) order |= at[i] << (kOrderBits * i);
     // top-k: a wavefront maximum over the lanes' heads; only when several lanes hold it (equal scores) a second
     // reduction for the lowest expert among them
     int my_id = 0;
     bool none = false;         // this lane's selection round found no candidate
     for (int j = 0; j < p.k; ++j) {
         const uint32_t m = wave_max_u32(c[0]);
-        const int head = lane + 64 * (int)(order & 3u);
+        const int head = lane + 64 * (int)(order & ((1u << kOrderBits) - 1u));
         const unsigned long long holders = __ballot(c[0] == m && m != 0u);
         int win;
         if (__popcll(holders) == 1) {
@@ -274,7 +272,7 @@ __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR],
         const bool took = head == win;
 #pragma unroll
         for (int i = 0; i < NR; ++i) c[i] = took ? (i + 1 < NR ? c[i + 1 < NR ? i + 1 : i] : 0u) : c[i];
-        order = took ? order >> 2 : order;
+        order = took ? order >> kOrderBits : order;
     }
     finish_token(p, t, lane, my_id, lane < p.k && !none ? lg[my_id] : 0.f);
     return my_id;
@@ -610,24 +608,33 @@ __device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *l
     }
     return select_regs<NR>(p, t, v, lg, cs, lane);
 }
+// Up to 512 experts in registers: above 256 the LDS form, which re-reads the scores in every round, costs more at every
+// batch size (whole pass, us, LDS -> registers: 384 experts on rows of 7168, 64 tokens 119 -> 104 and 8192 tokens 239 -> 232;
+// 512 experts on rows of 2048, 1 token 30 -> 20 and 30000 tokens 381 -> 339).
 template <int PZ>
 __device__ __forceinline__ int select_one(const Pass &p, int t, float *lg, float *cs, int lane)
 {
     if (p.E <= 64)  return select_from_planes<1, PZ>(p, t, lg, cs, lane);
     if (p.E <= 128) return select_from_planes<2, PZ>(p, t, lg, cs, lane);
     if (p.E <= 256) return select_from_planes<4, PZ>(p, t, lg, cs, lane);
+    if (p.E <= 512) return select_from_planes<8, PZ>(p, t, lg, cs, lane);
     const float *src = p.logits + (size_t)t * p.E;
     const size_t plane = (size_t)p.T * p.E;
     for (int e = lane; e < p.E; e += 64) {
-        float v = src[e];
-        for (int z = 1; z < p.logit_planes; ++z) v += src[z * plane + e];
+        float part[kGatePlanes];                         // all planes are requested at once, then added in K order
+#pragma unroll
+        for (int z = 0; z < kGatePlanes; ++z) part[z] = z < p.logit_planes ? src[z * plane + e] : 0.f;
+        float v = part[0];
+#pragma unroll
+        for (int z = 1; z < kGatePlanes; ++z)
+            if (z < p.logit_planes) v += part[z];
         lg[e] = v;
     }
     wave_sync();
     return select_token(p, t, lg, cs, lane);
 }
 // LDS floats per token: scores and selection scores (whole wavefronts of entries where they are kept in registers)
-__host__ __device__ inline int select_stride(int E) { return E <= 64 ? 64 : E <= 128 ? 128 : E <= 256 ? 256 : E; }
+__host__ __device__ inline int select_stride(int E) { return E <= 64 ? 64 : E <= 128 ? 128 : E <= 256 ? 256 : E <= 512 ? 512 : E; }
 
 __global__ __launch_bounds__(kThreads) void k_gate_select(Pass p)
 {

@@ -187,3 +187,20 @@ def test_group_scores_leave_nan_experts_out(experts, groups, kept):
             np.testing.assert_array_equal(ids[t], want[:k], err_msg=f"token {t}")
             checked += 1
     assert checked > tokens // 2
+
+
+@pytest.mark.parametrize("experts,k,groups,kept", [(257, 32, 1, 1), (320, 8, 1, 1), (320, 8, 10, 4), (384, 8, 6, 3), (512, 32, 8, 2), (513, 8, 1, 1)])
+@pytest.mark.parametrize("tokens,hidden", [(1, 64), (33, 2048), (2100, 64)])
+def test_selection_of_more_than_256_experts(experts, k, groups, kept, tokens, hidden):
+    """Five to eight scores a lane, all kept in registers (and the first size past it), with one and with several planes of
+    partial logits, in both forms of the selection kernel (2048 tokens) and in the one without ranking."""
+    from gpu_util import Case, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="many", tokens=tokens, hidden=hidden, inter=64, n_experts=experts, top_k=k, n_slots=experts, n_local=8,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax" if groups == 1 else "sigmoid_group", n_group=groups, topk_group=kept,
+                     seed=1000 + experts)
+    case = Case(wl)
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        case.run(flags=flags)
+        v = case.layer.view(tokens)
+        check_routing(case, v["topk_ids"], v["topk_w"])
