@@ -168,6 +168,7 @@ struct moe_layer {
     Layout lay;
     bool has_map;
     std::vector<int32_t> slot_owner;  // per slot: entry (expert, or E + shared expert) of the active table that uses it, or -1
+    int slots_used = 0;               // of them, those that are used
     // slot fills that the next map switch has to wait for: one event per copy stream handle, recorded again by every
     // fill on that stream, the entries reused after the switch
     struct Fill { hipEvent_t ev; void *stream; };
@@ -349,6 +350,13 @@ moe_status_t moe_profile_read(moe_layer_t *l, int32_t back, float *ms)
 
 namespace {
 
+int slots_in_use(const int32_t *owner, int n)
+{
+    int used = 0;
+    for (int s = 0; s < n; ++s) used += owner[s] >= 0;
+    return used;
+}
+
 // Validated placement -> the device table.  There is ONE table at a fixed address, rewritten in place by a
 // kernel on hip_stream: passes enqueued on that stream before the switch have read it by then, passes after it
 // (a replay of a captured graph included: the table's address is all a captured pass holds) read the new one.
@@ -366,6 +374,7 @@ moe_status_t install_table(moe_layer_t *l, std::vector<int32_t> &table, std::vec
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "expert map upload failed: %s", hipGetErrorString(e));
     l->has_map = true;
     l->slot_owner.swap(owner);
+    l->slots_used = slots_in_use(l->slot_owner.data(), l->cfg.n_slots);
     return MOE_OK;
 }
 
@@ -624,26 +633,28 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = !routed_ids && T <= kFusedMaxTokens && T <= p.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // Small weight-streaming tasks when a slot expects only a handful of rows (routed: T*k/E on average).  Otherwise the
-    // large-tile kernels once slots average 48 rows, and below that where there are weights to stream: their deep LDS
-    // rings pay from about 400 MB (whole pass, us, 128 x 128 -> large tiles: Qwen3 shape with 64 local experts, 604 MB,
-    // 110 tokens 143 -> 112; 32 of them, 302 MB, 76 -> 62 with an even load but 64 -> 74 with a Zipf(1.2) one, where half
-    // the slots have no rows and a slot's few wide N-slices leave the chip idle), and lose on small layers, whose time is
-    // the bookkeeping (24 experts of 128 x 128, 40 tokens 18 -> 21; of 1024 x 768, 250 tokens 42 -> 50).  The 128 x 128
-    // kernels take the rest, and the contractions that are no whole K-steps.
+    // The large-tile kernels once the whole batch has 48 assignments per slot of the layer (a rank of many holds a part of
+    // them: the DeepSeek-V3 shape with 16 of 256 experts gets there with 3 rows a slot).  Below that small weight-streaming
+    // tasks when a slot expects only a handful of rows (routed: T*k/E on average), and otherwise the large-tile kernels
+    // again where there are weights to stream: their deep LDS rings pay from about 400 MB in the slots that the placement
+    // uses (whole pass, us, 128 x 128 -> large tiles: Qwen3 shape with 64 local experts, 604 MB, 110 tokens 143 -> 112; 32
+    // of them, 302 MB, 76 -> 62 with an even load but 64 -> 74 with a Zipf(1.2) one, where half the slots have no rows and
+    // a slot's few wide N-slices leave the chip idle; those 32 in a layer of 128 slots, 420 tokens, 94 -> 79 and 83 -> 100),
+    // and lose on small layers, whose time is the bookkeeping (24 experts of 128 x 128, 40 tokens 18 -> 21; of 1024 x 768,
+    // 250 tokens 42 -> 50).  The 128 x 128 kernels take the rest, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const bool wide = can_big && (long long)T * p.kk >= 48ll * p.S;
     const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
-    const long long pool_bytes = 6ll * p.S * p.H * p.I;
-    const bool big = wide || (can_big && !tiny && pool_bytes >= 400000000ll);
+    const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
+    const bool big = wide || (can_big && !tiny && used_bytes >= 400000000ll);
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
     // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip, counted
-    // over the slots that an even routing gives rows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207,
+    // over the used slots that an even routing gives rows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207,
     // 35.1 -> 31.8).  A little more than one task per compute unit is the other exception: a few units then stream two
     // tasks while the rest stand idle (246 tasks, 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).
     // Rows of 7168 hide that (262 tasks, 181.6 -> 166.2).  The register kernel with its 32-row tasks takes those passes,
     // as it takes contractions that are no whole K-steps.
-    const int resident = p.S - p.n_shared < p.E ? p.S - p.n_shared : p.E;
+    const int resident = l->slots_used - p.n_shared < p.E ? l->slots_used - p.n_shared : p.E;
     const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
     const double ring_tasks = tiles_expected * (p.I / 64);
     const bool second_round = p.H <= 4096 && ring_tasks >= 240. && ring_tasks < 330.;
@@ -778,6 +789,7 @@ moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *bu
     lay.buf.workspace_bytes = MOE_STATIC_SCRATCH_BYTES;
     lay.lay = L;
     lay.has_map = true;
+    lay.slots_used = slots_in_use(owner, c.n_slots);
     // every pass writes what it reads (table, histograms, tile list, h, y): nothing has to start at zero
     // the table comes in with the selection kernel when that kernel ranks the assignments too and it fits an argument
     if (T <= kFusedMaxTokens && T <= (long long)L.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED) && c.n_experts + c.n_shared <= kTableArg) {

@@ -204,3 +204,21 @@ def test_selection_of_more_than_256_experts(experts, k, groups, kept, tokens, hi
         case.run(flags=flags)
         v = case.layer.view(tokens)
         check_routing(case, v["topk_ids"], v["topk_w"])
+
+
+def test_kernel_choice_counts_the_slots_in_use():
+    """A layer of 80 slots, 503 MB of weights, 7.5 assignments a slot: the large-tile kernels (320-row tiles) while all slots
+    are in use, the 128 x 128 ones with 60 of them (377 MB); free slots hold no weights that a pass reads."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="in_use", tokens=300, hidden=1024, inter=1024, n_experts=80, top_k=2, n_slots=80, n_local=80,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", seed=95)
+    g = np.random.Generator(np.random.PCG64(4))
+    ids = np.stack([np.concatenate([[5 if t < 250 else 6], 7 + g.permutation(73)[:1]]) for t in range(300)]).astype(np.int32)
+    wts = g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32)
+    case = Case(wl)
+    for used, tiles in ((80, 1), (60, 2), (80, 1)):
+        case.expert_map = np.where(np.arange(80) < used, np.arange(80), -1).astype(np.int32)
+        case.layer.set_expert_map(case.expert_map)
+        _check(case, ids, wts)
+        assert (case.layer.view(300)["tiles"][:, 0] == 5).sum() == tiles
