@@ -131,13 +131,12 @@ __global__ void k_write_map(int32_t *dst, MapChunk c, int n)
     if (i < n) dst[i] = c.v[i];
 }
 
-// Fill of one slot: two device-to-device copies (W13, then W2) in one launch.  The grid size is the caller's
-// throttle on how much HBM bandwidth a background fill may take from the forwards, so what a workgroup of it moves
-// matters, and that is bytes in flight over memory latency: a thread holds kCopyUnroll 16-byte pieces and has the
-// next round's requested before it stores them (48 KB per workgroup on their way; a compute unit takes about 64).
-// Read once, written once: neither side is kept in L2.  A 9.4 MB expert with the default 32 workgroups: two
+// Fill of one slot: two device-to-device copies (W13, then W2) in one launch.
+// Without a throttle: what a workgroup moves is bytes in flight over memory latency, so a thread holds kCopyUnroll
+// 16-byte pieces and has the next round's requested before it stores them (48 KB per workgroup on their way; a compute
+// unit takes about 64).  Read once, written once: neither side is kept in L2.  A 9.4 MB expert with 32 workgroups: two
 // launches, one piece per thread and round, 47 us -> 12 us (1.6 TB/s read and written).
-constexpr int kCopyThreads = 1024, kCopyUnroll = 3;
+constexpr int kCopyThreads = 1024, kCopyUnroll = 3, kCopyBlocks = 32;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -172,11 +171,28 @@ __global__ __launch_bounds__(kCopyThreads) void k_fill_slot(void *dst13, const v
     copy_part((u32x4 *)dst2, (const u32x4 *)src2, bytes2 / 16);
 }
 
+// With the caller's number of workgroups, its throttle on the bandwidth that a background fill takes from the forwards: a
+// workgroup is small and has one piece per thread on its way, so that the throttle is a fine one (about 9 GB/s a workgroup;
+// the form above moves 30, and a forward of 137 us beside the fills of 1, 2 or 4 workgroups took 183, 185, 175 us with it
+// against 167, 169, 168).
+constexpr int kThrottleThreads = 256;
+__device__ __forceinline__ void copy_part_throttled(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, size_t n16)
+{
+    const size_t stride = (size_t)gridDim.x * kThrottleThreads;
+    for (size_t i = (size_t)blockIdx.x * kThrottleThreads + threadIdx.x; i < n16; i += stride) dst[i] = src[i];
+}
+__global__ __launch_bounds__(kThrottleThreads) void k_fill_slot_throttled(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2)
+{
+    copy_part_throttled((u32x4 *)dst13, (const u32x4 *)src13, bytes13 / 16);
+    copy_part_throttled((u32x4 *)dst2, (const u32x4 *)src2, bytes2 / 16);
+}
+
 }  // namespace
 
 hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_fill_slot, dim3(blocks), dim3(kCopyThreads), 0, st, dst13, src13, bytes13, dst2, src2, bytes2);
+    if (blocks > 0) hipLaunchKernelGGL(k_fill_slot_throttled, dim3(blocks), dim3(kThrottleThreads), 0, st, dst13, src13, bytes13, dst2, src2, bytes2);
+    else            hipLaunchKernelGGL(k_fill_slot, dim3(kCopyBlocks), dim3(kCopyThreads), 0, st, dst13, src13, bytes13, dst2, src2, bytes2);
     return hipGetLastError();
 }
 

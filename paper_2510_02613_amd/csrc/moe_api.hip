@@ -537,10 +537,9 @@ moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, 
     if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)copy_stream, l->serve_ev, 0);
     const size_t es = esize(c.act_dtype);
     const size_t b13 = 2 * (size_t)c.inter * c.hidden * es, b2 = (size_t)c.hidden * c.inter * es;
-    const int blocks = copy_blocks ? copy_blocks : 32;
     if (e == hipSuccess)
         e = launch_fill_slot((char *)const_cast<void *>(l->buf.w13) + (size_t)slot * b13, src_w13, b13,
-                             (char *)const_cast<void *>(l->buf.w2) + (size_t)slot * b2, src_w2, b2, blocks, (hipStream_t)copy_stream);
+                             (char *)const_cast<void *>(l->buf.w2) + (size_t)slot * b2, src_w2, b2, copy_blocks, (hipStream_t)copy_stream);
     // the event is about to stand for this fill alone: the one it stood for comes first.  (On one stream it does
     // anyway; a handle can also name another stream by now, a destroyed one's successor or another thread's own.)
     if (e == hipSuccess && at < l->n_pending) e = hipStreamWaitEvent((hipStream_t)copy_stream, l->load_ev[at].ev, 0);

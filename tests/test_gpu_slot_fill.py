@@ -66,3 +66,30 @@ def test_fill_of_a_live_slot_and_same_stream_are_rejected():
         case.layer.load_expert_async(16, w13, w2, copy, serve)
     case.layer.load_expert_async(12, w13, w2, copy, serve)               # a free slot is fine
     torch.cuda.synchronize()
+
+
+def test_copy_blocks_throttle_a_fill():
+    """A workgroup of a throttled fill is 256 threads with one 16-byte piece on its way each: 4 KB per memory round trip,
+    9 GB/s where that takes 430 ns.  One of them may not move 16 GB/s (250 ns); without a throttle a fill moves much more.
+    Any number of workgroups copies whole slots, also where they divide unevenly."""
+    import torch
+    from gpu_util import Case
+    wl = MoEWorkload(name="fill_rate", tokens=16, hidden=1024, inter=520, n_experts=8, top_k=2, n_slots=8, n_local=4,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", seed=33)
+    case = Case(wl)
+    copy = torch.cuda.Stream()
+    w13, w2 = (torch.randint(-2**15, 2**15, t.shape, dtype=torch.int16, device=t.device) for t in (case.layer.w13[0], case.layer.w2[0]))
+    nbytes = 2 * (w13.numel() + w2.numel())
+    rate = {}
+    for blocks in (1, 0, 3, 1000):
+        for _ in range(2):                                   # the second one is timed
+            case.layer.w13[6].zero_(), case.layer.w2[6].zero_()
+            torch.cuda.synchronize()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(copy)
+            case.layer.load_expert_async(6, w13, w2, copy, copy_blocks=blocks)
+            b.record(copy)
+            torch.cuda.synchronize()
+            rate[blocks] = nbytes / (a.elapsed_time(b) * 1e6)
+            assert torch.equal(case.layer.w13[6], w13) and torch.equal(case.layer.w2[6], w2)
+    assert rate[1] < 16 < rate[0], rate
