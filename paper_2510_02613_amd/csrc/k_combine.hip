@@ -189,6 +189,7 @@ __global__ __launch_bounds__(kThrottleThreads) void k_fill_slot_throttled(void *
 
 }  // namespace
 
+// blocks 0: not throttled
 hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st)
 {
     if (blocks > 0) hipLaunchKernelGGL(k_fill_slot_throttled, dim3(blocks), dim3(kThrottleThreads), 0, st, dst13, src13, bytes13, dst2, src2, bytes2);

@@ -106,7 +106,7 @@ constexpr int kFusedMaxTokens = 8192;  // largest batch the fused bookkeeping se
 __host__ __device__ constexpr int fused_row_stride(int n_blocks) { return (n_blocks + 63) / 64 * 64; }
 
 hipError_t launch_write_map(int32_t *dst, const int32_t *host_vals, int n, hipStream_t st);
-hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st);  // bytes % 16 == 0; blocks 0: unthrottled
+hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st);  // bytes % 16 == 0
 hipError_t launch_gate(const Pass &p, hipStream_t st);
 int gate_f32_planes(int T, int H);   // partial-sum planes of the gate logits of fp32 layers
 hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st);   // logits only, bf16 activations
