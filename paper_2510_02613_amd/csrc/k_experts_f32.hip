@@ -14,6 +14,8 @@
 // in flight while 16 are multiplied.
 // Measured against 32 x 64 tiles staged through LDS without overlap: 64 tokens of the 128 x 64 layer, GEMM-1 21 -> 5 us;
 // 1500 tokens of a 264 x 264 layer, GEMM-1 99 -> 18 us, GEMM-2 65 -> 12 us.
+#include <type_traits>
+
 #include "moe_internal.h"
 #include "self_tiles.h"
 
@@ -26,6 +28,7 @@ constexpr int kSplit = 4;         // wavefronts that share a task's contraction
 constexpr int kKC = 16;           // k per chunk: with the 128 bytes of 32 k, a 264-wide contraction left a wavefront without work (264 x 264 layer,
                                   // 1500 tokens, whole pass: 75 -> 70 us)
 constexpr int kWRows = 32;        // weight rows per task
+constexpr int kGridRow = 1 << 23; // tasks per row of the grid: a launch takes less than 2^32 threads in one dimension
 
 struct Run { f32x4 v[kKC / 16]; };   // a lane's share of one row of a chunk
 
@@ -109,7 +112,8 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int n0
     }
 }
 
-template <bool kFirst, int TT, bool kSelf>
+// kRows: the grid has several rows of kGridRow tasks.
+template <bool kFirst, int TT, bool kSelf, bool kRows>
 __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
 {
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
@@ -119,12 +123,13 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
     const int N = kFirst ? p.I : p.H;
     const int groups = (N + COLS - 1) / COLS;               // tasks per M-tile
     const int lane = threadIdx.x & 63, n = lane & 15;
-    int task = blockIdx.x;
+    std::conditional_t<kRows, long long, int> task = blockIdx.x;
+    if (kRows) task += (long long)blockIdx.y * kGridRow;
     if (kSelf) {
         if (task == 0) { self_tables(p, TR, part); return; }
         task -= 1;
     }
-    const int tile = task / groups, n0 = task % groups * COLS;
+    const int tile = (int)(task / groups), n0 = (int)(task % groups) * COLS;
     MTile mt;
     int src[TT];                                            // rows past the tile's end re-read its last row; their outputs are dropped
     if (kSelf) {
@@ -151,17 +156,23 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
     task_body<kFirst, 1>(p, mt, n0, src, part);
 }
 
+template <bool kFirst, int TT, bool kSelf>
+void launch_tasks(const Pass &p, long long tasks, hipStream_t st)
+{
+    const dim3 block(64 * kSplit);
+    if (tasks <= kGridRow) hipLaunchKernelGGL((k_expert_f32<kFirst, TT, kSelf, false>), dim3((unsigned)tasks), block, 0, st, p);
+    else hipLaunchKernelGGL((k_expert_f32<kFirst, TT, kSelf, true>), dim3(kGridRow, (unsigned)((tasks + kGridRow - 1) / kGridRow)), block, 0, st, p);
+}
+
 template <int TT>
 void launch_tt(const Pass &p, int which, hipStream_t st)
 {
-    const dim3 block(64 * kSplit);
     if (which == 0) {
-        const int blocks = p.max_tiles * ((p.I + kWRows / 2 - 1) / (kWRows / 2));
-        if (p.self_tiles) hipLaunchKernelGGL((k_expert_f32<true, TT, true>), dim3(blocks + 1), block, 0, st, p);
-        else              hipLaunchKernelGGL((k_expert_f32<true, TT, false>), dim3(blocks), block, 0, st, p);
+        const long long tasks = (long long)p.max_tiles * ((p.I + kWRows / 2 - 1) / (kWRows / 2));
+        if (p.self_tiles) launch_tasks<true, TT, true>(p, tasks + 1, st);
+        else              launch_tasks<true, TT, false>(p, tasks, st);
     } else {
-        const int blocks = p.max_tiles * ((p.H + kWRows - 1) / kWRows);
-        hipLaunchKernelGGL((k_expert_f32<false, TT, false>), dim3(blocks), block, 0, st, p);
+        launch_tasks<false, TT, false>(p, (long long)p.max_tiles * ((p.H + kWRows - 1) / kWRows), st);
     }
 }
 

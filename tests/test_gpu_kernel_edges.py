@@ -222,3 +222,29 @@ def test_kernel_choice_counts_the_slots_in_use():
         case.layer.set_expert_map(case.expert_map)
         _check(case, ids, wts)
         assert (case.layer.view(300)["tiles"][:, 0] == 5).sum() == tiles
+
+
+def test_f32_grid_past_the_launch_limit():
+    """16384 tokens on 1024 experts of 131072 columns: 2048 possible tiles of 8192 tasks of 256 threads are 2^32 threads, one
+    more than a launch takes in one dimension.  W2 has one column per output, spread over the tasks, so that the reference
+    needs only those columns of h."""
+    import torch
+    from paper_2510_02613_amd.layer import MoELayer
+    T, E, H, I = 16384, 1024, 8, 131072
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(3)
+    layer = MoELayer(hidden=H, inter=I, n_experts=E, top_k=1, n_slots=E, max_tokens=T, act_dtype="f32", router_dtype="f32",
+                     gate="softmax", n_group=1, topk_group=1, renormalize=True, routed_scale=1.0, n_shared=0,
+                     router_w=np.zeros((E, H), np.float32), device=dev)
+    layer.w13.normal_(0.0, 0.5, generator=gen)
+    layer.w2.zero_()
+    cols = torch.linspace(0, I - 1, H, device=dev).round().long()
+    layer.w2[:, torch.arange(H, device=dev), cols] = 1.0
+    layer.set_expert_map(list(range(E)))
+    x = torch.randn(T, H, generator=gen, device=dev)
+    ids = torch.randperm(T, generator=gen, device=dev).to(torch.int32)[:, None] % E
+    out = layer.forward_routed(x, ids, torch.ones(T, 1, device=dev))
+    e = ids[:, 0].long()
+    gate, up = ((layer.w13[e[:, None], c[None, :]].double() * x.double()[:, None, :]).sum(2) for c in (cols, cols + I))
+    want = torch.nn.functional.silu(gate) * up
+    assert float((out.double() - want).norm() / want.norm()) < 1e-6      # eight products and a hardware exp, each 2^-23
