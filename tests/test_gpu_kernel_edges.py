@@ -52,9 +52,9 @@ def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
-    """The LDS-ring decode kernels: contractions shorter and longer than the ring, output widths that end inside a task's
-    128 columns, shared rows; tables and output as in
-    the pass with separate bookkeeping kernels, bit for bit."""
+    """The few-token kernels, the LDS-ring or the register ones as the dispatch chooses by the expected tasks: short and long
+    contractions, output widths that end inside a task's 128 columns, shared rows; tables and output as in the pass with
+    separate bookkeeping kernels, bit for bit.  (The ring kernels by themselves: the next test.)"""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     from paper_2510_02613_amd import binding as B
     wl = MoEWorkload(name="ring", tokens=tokens, hidden=hidden, inter=inter, n_experts=96, top_k=4, n_slots=93, n_local=90,
@@ -65,6 +65,49 @@ def test_decode_ring_kernels(tokens, hidden, inter):
         out = case.run(flags=flags)
         runs.append((out, case.layer.view(tokens)))
     ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
+def _ring_cases():
+    """(tokens, experts, k, hidden, inter) that the dispatch sends to the ring kernels: 160 tasks or more, not 240 .. 330."""
+    out = []
+    for hidden, inter, experts, k in [(64, 64, 256, 8), (128, 64, 256, 8), (64, 128, 256, 8), (192, 192, 96, 4), (256, 256, 96, 4),
+                                      (320, 320, 96, 4), (768, 1024, 96, 4)]:
+        for tokens in (17, 32, 47, 64, 90):
+            tasks = ((experts - 2) * (1 - (1 - k / experts) ** tokens) + 1) * (inter // 64)
+            if tokens * k <= 4 * experts and tasks >= 162 and not 238 <= tasks < 332:
+                out.append((tokens, experts, k, hidden, inter))
+    return out
+
+
+@pytest.mark.parametrize("tokens,experts,k,hidden,inter", _ring_cases())
+def test_ring_kernels_at_every_contraction_length(tokens, experts, k, hidden, inter):
+    """Contractions of 1, 2, 3, 4, 5 and more K-steps in both GEMMs of the ring kernels (the ring is 4 deep), with and without
+    self-derived tiles.  A bias sends every token to expert 5: more than 16 rows of it in one tile show that the ring kernels
+    ran.  Tables and output as with separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    from workloads import make_inputs
+    wl = MoEWorkload(name="ring_k", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=k, n_slots=experts, n_local=experts - 2,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, min(tokens, 30)), seed=1200 + tokens)
+    inp = make_inputs(wl)
+    inp["logit_bias"] = np.zeros(experts, np.float32)
+    inp["logit_bias"][5] = 8.0
+    order = np.random.Generator(np.random.PCG64(3)).permutation(experts - 1)[:experts - 2]
+    case = Case(wl, expert_map=block_expert_map(experts, 0, experts - 2, order), inputs=inp)
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    assert (ids == 5).any(1).all()
+    tiles = runs[0][1]["tiles"]
+    rows = tiles[tiles[:, 0] == case.expert_map[5]][:, 2]
+    assert rows.sum() == tokens and len(rows) == -(-tokens // 32)
     check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
     check_output(case, runs[0][0], ids)
     np.testing.assert_array_equal(runs[0][0], runs[1][0])
@@ -101,6 +144,20 @@ def test_few_token_kernels_by_task_count(tokens, tile):
     assert rows.sum() == 4 * tokens and len(rows) == -(-4 * tokens // tile)
 
 
+@pytest.mark.parametrize("hidden,tile", [(4096, 16), (4160, 32)])
+def test_few_token_kernels_by_row_length(hidden, tile):
+    """255 expected tasks, a little more than one per compute unit: the register kernels up to rows of 4096, the ring beyond."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="rows", tokens=8, hidden=hidden, inter=2048, n_experts=8, top_k=4, n_slots=8, n_local=8,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", seed=88)
+    g = np.random.Generator(np.random.PCG64(8))
+    case = Case(wl)
+    _check(case, np.full((8, 4), 3, np.int32), g.uniform(0.5, 1.5, size=(8, 4)).astype(np.float32))
+    rows = case.layer.view(8)["tiles"][:, 2]
+    assert rows.sum() == 32 and len(rows) == 32 // tile
+
+
 @pytest.mark.parametrize("tokens,tiles", [(200, 2), (255, 2), (256, 1)])
 def test_small_layers_take_the_128_row_kernels(tokens, tiles):
     """16 slots of a small layer, three assignments per token: 768 assignments are 48 rows a slot, where the large-tile
@@ -117,10 +174,11 @@ def test_small_layers_take_the_128_row_kernels(tokens, tiles):
 
 
 @pytest.mark.parametrize("tokens", [1, 16, 33, 64, 65, 257, 700])
-@pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32")])
+@pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32"), (1024, 1032, "f32"), (4104, 136, "bf16")])
 def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
     """fp32 layers on both sides of the self-derived tiles (64 tokens) and of every tile height (16, 32, 64 rows), with
-    contractions that leave wavefronts of a task without a chunk, and both router types."""
+    contractions that leave wavefronts of a task without a chunk and long ones (several planes of partial logits), and both
+    router types."""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     wl = MoEWorkload(name="f32_edges", tokens=tokens, hidden=hidden, inter=inter, n_experts=24, top_k=3, n_slots=22, n_local=20,
                      act_dtype="f32", router_dtype=router, gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,

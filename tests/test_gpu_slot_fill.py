@@ -93,3 +93,79 @@ def test_copy_blocks_throttle_a_fill():
             rate[blocks] = nbytes / (a.elapsed_time(b) * 1e6)
             assert torch.equal(case.layer.w13[6], w13) and torch.equal(case.layer.w2[6], w2)
     assert rate[1] < 16 < rate[0], rate
+
+
+@pytest.mark.parametrize("copy_blocks", [0, 1])
+def test_fills_on_two_copy_streams_and_refills(copy_blocks):
+    """Fills alternate between two copy streams (a stream's event stands for its latest fill) while forwards run; the switch
+    waits for all of them.  Then a second round of fills into the slots that this switch freed, the streams in the other order,
+    so that the events of the first round are recorded again for other streams."""
+    import torch
+    from gpu_util import Case, tensor_to_host, check_routing, check_output
+    wl = MoEWorkload(name="fill2", tokens=600, **dict(MID, n_experts=24, n_slots=24, n_local=24))
+    order = np.random.Generator(np.random.PCG64(9)).permutation(24)
+    def placement(experts_in):                               # {expert: slot}
+        m = np.full(24, -1, np.int32)
+        for e, s in experts_in.items():
+            m[e] = s
+        return m
+    first = {e: int(order[e]) for e in range(8)}
+    second = {e: int(order[e]) for e in range(8, 16)}       # into free slots, then the first ones leave
+    third = {e: int(order[e - 16]) for e in range(16, 24)}  # into the slots the first ones left
+    case = Case(wl, expert_map=placement(first))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    src = {e: (case.layer.upload(case.inp["w13_experts"][e]), case.layer.upload(case.inp["w2_experts"][e])) for e in range(8, 24)}
+    torch.cuda.synchronize()
+    for new, turn in ((second, 0), (third, 1)):
+        for i, (e, s) in enumerate(new.items()):
+            case.layer.forward(case.x_dev)
+            case.layer.load_expert_async(s, src[e][0], src[e][1], streams[(i + turn) % 2], copy_blocks=copy_blocks)
+        case.place(placement(new), upload=False)
+        out = case.layer.forward(case.x_dev)
+        torch.cuda.synchronize()
+        for e, s in new.items():
+            np.testing.assert_array_equal(tensor_to_host(case.layer.w13[s]), case.w13_pool[s])
+            np.testing.assert_array_equal(tensor_to_host(case.layer.w2[s]), case.w2_pool[s])
+        v = case.layer.view(wl.tokens)
+        ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+        check_output(case, tensor_to_host(out), ids)
+
+
+def test_fills_from_two_threads_on_their_own_streams_under_one_handle():
+    """The handle of the per-thread stream (2) names another stream in every thread: the event recorded again for the second
+    thread's short fill must still stand for the first thread's long one."""
+    import threading
+    import torch
+    from gpu_util import Case, tensor_to_host
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="fill_threads", tokens=64, **dict(MID, hidden=1024, inter=1024, n_experts=8, n_slots=8, n_local=8))
+    case = Case(wl, expert_map=np.array([0, 1, 2, 3, -1, -1, -1, -1], np.int32))
+    src = {e: (case.layer.upload(case.inp["w13_experts"][e]), case.layer.upload(case.inp["w2_experts"][e])) for e in (4, 5)}
+    serve = torch.cuda.current_stream()
+    case.layer.forward(case.x_dev)
+    torch.cuda.synchronize()
+    done, errors = threading.Event(), []
+
+    def fill(e, blocks, filled):
+        try:
+            torch.cuda.set_device(0)
+            B.moe_load_expert(case.layer.handle, e, src[e][0].data_ptr(), src[e][1].data_ptr(), 2, serve.cuda_stream, blocks)
+        except Exception as ex:   # noqa: BLE001 - reported by the test's thread
+            errors.append(ex)
+        filled.set()
+        done.wait(60)             # the thread, and its stream, live until the fills are done
+    threads = []
+    for e, blocks in ((4, 1), (5, 0)):                       # 6.3 MB by one small workgroup (0.7 ms), then at full speed
+        filled = threading.Event()
+        threads.append(threading.Thread(target=fill, args=(e, blocks, filled)))
+        threads[-1].start()
+        assert filled.wait(60)
+    case.place(np.array([0, 1, 2, 3, 4, 5, -1, -1], np.int32), upload=False)
+    got13, got2 = case.layer.w13[4:6].clone(), case.layer.w2[4:6].clone()   # on the serving stream, behind the switch
+    torch.cuda.synchronize()
+    done.set()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    np.testing.assert_array_equal(tensor_to_host(got13), case.w13_pool[4:6])
+    np.testing.assert_array_equal(tensor_to_host(got2), case.w2_pool[4:6])
