@@ -866,6 +866,8 @@ hipError_t launch_gate_small(const Pass &p, hipStream_t st)
 hipError_t launch_select(const Pass &p, hipStream_t st)
 {
     if (p.fused_hist) {
+        // the two forms are alike up to 4096 tokens (logits and selection of 256 experts 21.7 us both); 5000: 32.9 against 30.7,
+        // 8192: 31.0 against 29.0
         const bool many = p.T > 2048;
         if (p.host_table) {
             TableArg arg;
@@ -882,6 +884,19 @@ hipError_t launch_select(const Pass &p, hipStream_t st)
 }  // namespace
 
 int gate_f32_planes(int T, int H) { return few_token_planes(T, H); }
+
+// Whether logits and selection go in one kernel.  Its workgroups read the whole router per 16 tokens, so where the direct
+// copies of k_gate_logits_dma serve the layer, those are ahead again once tokens x router is large (whole pass, us, one kernel
+// -> separate, 64 experts on rows of 512: bf16 router 8192 tokens 56.2 -> 56.4, 20000: 78.1 -> 72.3, 60000: 179 -> 160; fp32
+// router, where the separate selection ranks the assignments too, 2500: 40.2 -> 43.0, 5000: 47.7 -> 45.0, 8192: 60.6 -> 56.7,
+// and where it does not, 10000: 60.8 -> 62.2, 20000: 87.1 -> 82.2).  The other logits kernels are not, or by 2 percent
+// (rows of 264, 60000 tokens 125 -> 137; of 504, fp32 router, 184 -> 181).
+static bool one_gate_kernel(const Pass &p)
+{
+    if (p.gate_tiled || p.E > kSmallExperts || p.H > kSmallHidden) return false;
+    const long long work = (long long)p.T * p.E * p.H;
+    return !gate_dma_supports(p) || work <= (p.router_bf16 || p.T > kFusedMaxTokens ? 600000000ll : 150000000ll);
+}
 
 // Logits and selection of the tokens that the logits' memory holds, then of the next ones.
 static hipError_t launch_gate_in_parts(const Pass &p, hipStream_t st)
@@ -902,7 +917,7 @@ hipError_t launch_gate(const Pass &p0, hipStream_t st)
 {
     Pass p = p0;
     hipError_t e;
-    if (!p.gate_tiled && p.E <= kSmallExperts && p.H <= kSmallHidden) return launch_gate_small(p, st);
+    if (one_gate_kernel(p)) return launch_gate_small(p, st);
     if (p.act_bf16) {
         e = p.router_bf16 ? launch_logits_bf16<uint16_t>(p, &p.logit_planes, st) : launch_logits_bf16<float>(p, &p.logit_planes, st);
     } else {

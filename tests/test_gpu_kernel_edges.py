@@ -282,6 +282,20 @@ def test_kernel_choice_counts_the_slots_in_use():
         assert (case.layer.view(300)["tiles"][:, 0] == 5).sum() == tiles
 
 
+@pytest.mark.parametrize("router,tokens", [("bf16", 8192), ("bf16", 18310), ("bf16", 18311), ("f32", 4577), ("f32", 4578), ("f32", 8193)])
+def test_small_router_gate_of_many_tokens(router, tokens):
+    """64 experts on rows of 512: both sides of where the separate logits kernel takes over from the one-kernel gate."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    wl = MoEWorkload(name="gate_many", tokens=tokens, hidden=512, inter=8, n_experts=64, top_k=2, n_slots=64, n_local=64,
+                     act_dtype="bf16", router_dtype=router, gate="softmax", seed=78)
+    case = Case(wl)
+    out = case.run()
+    v = case.layer.view(tokens)
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
+
+
 def test_f32_grid_past_the_launch_limit():
     """16384 tokens on 1024 experts of 131072 columns: 2048 possible tiles of 8192 tasks of 256 threads are 2^32 threads, one
     more than a launch takes in one dimension.  W2 has one column per output, spread over the tasks, so that the reference
