@@ -77,7 +77,7 @@ def record_traffic(args):
     name, fetch_kib, write_kib, fs, ws_ = args.record_traffic
     sources = sorted(os.path.join("paper_2510_02613_amd", "csrc", f)
                      for f in os.listdir(os.path.join(ROOT, "paper_2510_02613_amd", "csrc"))
-                     if f.startswith("k_experts") or f in ("moe_internal.h", "k_permute.hip"))
+                     if f.startswith("k_experts") or f in ("moe_internal.h", "self_tiles.h", "k_permute.hip"))
     try:
         with open(TRAFFIC_FILE) as f:
             allrec = json.load(f)

@@ -1,5 +1,6 @@
-// Weight-streaming expert kernels for decode-sized batches (bf16): operands in registers, small tasks; a token or two, and
-// contractions that are no whole K-steps (the LDS-ring kernels take the rest).
+// Weight-streaming expert kernels for decode-sized batches (bf16): operands in registers, small tasks.  They serve what the
+// LDS-ring kernels leave: contractions that are no whole K-steps, passes with too few of the ring's 128-row tasks for the
+// chip, and passes with a little more than one of them per compute unit (the dispatch in moe_api.hip has the counts).
 //
 // With a few tokens per step most resident experts receive 0-4 rows (the
 // memory-bound regime of the layer of Sec. 2.1 of the paper under expert

@@ -647,12 +647,13 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
     const bool big = wide || (can_big && !tiny && used_bytes >= 400000000ll);
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
-    // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip, counted
-    // over the used slots that an even routing gives rows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207,
-    // 35.1 -> 31.8).  A little more than one task per compute unit is the other exception: a few units then stream two
-    // tasks while the rest stand idle (246 tasks, 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).
-    // Rows of 7168 hide that (262 tasks, 181.6 -> 166.2).  The register kernel with its 32-row tasks takes those passes,
-    // as it takes contractions that are no whole K-steps.
+    // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip's 256 compute
+    // units, counted over the used slots that an even routing gives rows and for GEMM-1, which is two thirds of the bytes;
+    // GEMM-2 follows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207, 35.1 -> 31.8).  A little more than one
+    // task per compute unit is the other exception: a few units then stream two tasks while the rest stand idle (246 tasks,
+    // 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).  Rows of 7168 hide that (262 tasks, 181.6 ->
+    // 166.2); nothing was measured between rows of 2048 and of 7168.  The register kernel with its 32-row tasks takes those
+    // passes, as it takes contractions that are no whole K-steps.
     const int resident = l->slots_used - p.n_shared < p.E ? l->slots_used - p.n_shared : p.E;
     const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
     const double ring_tasks = tiles_expected * (p.I / 64);

@@ -86,7 +86,7 @@ struct Pass {
     void *y;             // [A,H]
     int32_t max_tiles;
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
-    int32_t self_tiles;  // weight-streaming GEMM-1 only: its workgroups derive their tile from the selection kernel's per-block counts and
+    int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 only: its workgroups derive their tile from the selection kernel's per-block counts and
                          // masks themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping

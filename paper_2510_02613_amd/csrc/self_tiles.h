@@ -1,5 +1,5 @@
 // Tiles derived by the expert GEMM-1 itself, for passes of at most 64 tokens: shared by the weight-streaming bf16
-// kernel and the fp32 kernel.
+// kernels (registers and LDS ring) and the fp32 kernel.
 #pragma once
 #include "moe_internal.h"
 
