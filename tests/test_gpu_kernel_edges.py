@@ -27,9 +27,9 @@ def test_large_tile_rings_at_every_token_tile_count(hidden, inter):
 
 
 @pytest.mark.parametrize("tokens", [1, 17, 64])
-@pytest.mark.parametrize("local", [64, 65, 127, 130, 255])
+@pytest.mark.parametrize("local", [64, 65, 127, 130, 255, 256])
 def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
-    """1 to 4 slots per lane in the few-token GEMM-1 that derives its tiles itself: output and tables as in the pass
+    """1 to 4 slots per lane in the few-token GEMM-1 that derives its tiles itself, and the first count past it: output and tables as in the pass
     with separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     from paper_2510_02613_amd import binding as B
@@ -320,3 +320,25 @@ def test_f32_grid_past_the_launch_limit():
     gate, up = ((layer.w13[e[:, None], c[None, :]].double() * x.double()[:, None, :]).sum(2) for c in (cols, cols + I))
     want = torch.nn.functional.silu(gate) * up
     assert float((out.double() - want).norm() / want.norm()) < 1e-6      # eight products and a hardware exp, each 2^-23
+
+
+@pytest.mark.parametrize("tokens,k,slots", [(128, 8, 16), (129, 8, 16), (1000, 4, 1500), (8192, 8, 40), (8193, 8, 40)])
+def test_routed_bookkeeping_by_blocks(tokens, k, slots):
+    """1024 assignments (one workgroup does it all), one more, more slots than a workgroup has threads, 65536 assignments (64
+    blocks, the last that are scanned and placed in one launch) and 8 more; ids repeat within a token."""
+    from gpu_util import Case
+    from test_gpu_routed import _check, _routing
+    wl = MoEWorkload(name="blocks", tokens=tokens, hidden=64, inter=8, n_experts=min(slots, 1024), top_k=k, n_slots=slots, n_local=min(slots, 1024),
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", seed=1400)
+    case = Case(wl)
+    ids, wts = _routing(wl, tokens)
+    _check(case, ids, wts)
+    v = case.layer.view(tokens)
+    flat = ids.reshape(-1)
+    rows = np.where((flat >= 0) & (flat < wl.n_experts), 0, -1)
+    slot = np.where(rows == 0, case.expert_map[np.clip(flat, 0, wl.n_experts - 1)], slots)
+    order = np.argsort(slot, kind="stable")[:int((rows == 0).sum())]      # rows: by slot, then token and selection position
+    want = np.full(len(flat), -1)
+    want[order] = np.arange(len(order))
+    np.testing.assert_array_equal(v["inv"].reshape(-1), want)
+    np.testing.assert_array_equal(v["perm"][:len(order)], order // k)
