@@ -5,15 +5,15 @@
 // true fp32 product, fp32 accumulation.
 //
 // What bounds it: a layer of a few megabytes is latency, a chain of memory round trips per launch, so as many of a
-// task's loads as possible go out together; large batches are bound by the fp32 matrix rate.  A task is 16 gate rows
+// task's loads as possible go out together; large batches are bound by the fp32 matrix rate (k_expert_f32_tile, below, serves
+// them).  A task is 16 gate rows
 // and the 16 matching up rows (GEMM-1) or 32 W2 rows (GEMM-2) of one M-tile, one workgroup of four wavefronts that
 // each walk a quarter of the contraction; the four sums are added in K order through LDS.  Operands go straight from
 // global memory into the layout of v_mfma_f32_16x16x4_f32: lane (n = l % 16, q = l / 16) reads 16 bytes, k = 4q .. 4q+3,
 // of row n per 16 k, and the contraction does not care that MFMA i takes element i of every lane as long as weight
-// and token rows agree.  A tile has up to 64 token rows, which a weight row read once serves; the next 16 k are
+// and token rows agree.  A tile has up to 32 token rows, which a weight row read once serves; the next 16 k are
 // in flight while 16 are multiplied.
-// Measured against 32 x 64 tiles staged through LDS without overlap: 64 tokens of the 128 x 64 layer, GEMM-1 21 -> 5 us;
-// 1500 tokens of a 264 x 264 layer, GEMM-1 99 -> 18 us, GEMM-2 65 -> 12 us.
+// Measured against 32 x 64 tiles staged through LDS without overlap: 64 tokens of the 128 x 64 layer, GEMM-1 21 -> 5 us.
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -147,13 +147,141 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
             src[c] = kFirst ? p.perm[r] : r;
         }
     }
-    if constexpr (TT >= 4) {
-        if (mt.rows > 32) { task_body<kFirst, 4>(p, mt, n0, src, part); return; }
-    }
     if constexpr (TT >= 2) {
         if (mt.rows > 16) { task_body<kFirst, 2>(p, mt, n0, src, part); return; }
     }
     task_body<kFirst, 1>(p, mt, n0, src, part);
+}
+
+// Tiles of up to 64 token rows, for slots that expect more than 32: a workgroup multiplies them with 16 gate rows and the 16
+// matching up rows (GEMM-1) or 32 W2 rows (GEMM-2), wavefront g the rows [16 g, 16 g + 16).  The matrix pipes bound this size (an MFMA of
+// 2048 flops takes 32 cycles), if the operands get there: loaded straight into MFMA layout, as in the kernel above, a load
+// touches half a line of 16 rows and every wavefront loads all of the tile's token rows.  Here both operands travel as whole 128-byte
+// lines, once per workgroup, into an LDS tile of 32 k (registers in between: a ragged contraction is zero filled there), the
+// next tile's loads in flight during this one's MFMAs.  Tasks are small, so that a launch has several per compute unit to deal
+// out (64 weight rows: +4 %), and 24 KB of LDS let six run beside each other; two K-steps of loads in flight instead of
+// one changed nothing (+-2 %).  An XCD takes a contiguous run of tasks (GEMM-2 20.5 -> 18.2 us).
+// The contraction is summed in the same four parts as above (a flush every quarter), so both kernels give the same bits.
+// Measured (264 x 264 layer, 30 of 40 experts, top-4, us with two events): 1500 tokens GEMM-1 32.8 -> 28.7, GEMM-2 26.7 -> 18.4, whole
+// pass 71 -> 59.5; 400 tokens 41.8 -> 38.5, 2500: 93 -> 77; 512 x 256, 1500 tokens 92 -> 82.  That is 85 TFLOP/s in GEMM-2
+// at 2500 tokens; the tile's ragged rows and columns cost 20 % more MFMAs than the flops of the layer.
+constexpr int kTileRows = 64, kTileK = 32;
+
+// 16-byte slot of a 128-byte row in LDS: conflict-free operand reads
+__device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row ^ (row >> 3)) & 1) << 2); }
+
+template <bool kFirst, bool kRows>
+__global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
+{
+    constexpr int COLS = kFirst ? kWRows / 2 : kWRows;
+    constexpr int XL = kTileRows * 8 / 256;                   // 16-byte loads of token rows per thread and K-step; one of weight rows
+    static_assert(kWRows * 8 == 256, "one 16-byte load of weight rows per thread");
+    __shared__ f32x4 xs[2][kTileRows * 8], ws[2][kWRows * 8];
+    const int K = kFirst ? p.H : p.I, N = kFirst ? p.I : p.H;
+    const int groups = (N + COLS - 1) / COLS;
+    // workgroups are dealt round-robin to the 8 XCDs: each takes a contiguous run of the tasks, so that a tile's token rows and
+    // a slot's weights are fetched into one L2
+    using Index = std::conditional_t<kRows, long long, int>;
+    Index b = blockIdx.x;
+    if (kRows) b += (long long)blockIdx.y * kGridRow;
+    const Index tasks = (Index)*p.n_tiles * groups, run = (tasks + 7) / 8, task = (b & 7) * run + (b >> 3);
+    if ((b >> 3) >= run || task >= tasks) return;
+    const int tile = (int)(task / groups), n0 = (int)(task % groups) * COLS;
+    const MTile mt = p.tiles[tile];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 15, q = lane >> 4;
+    const float *W = (const float *)(kFirst ? p.w13 : p.w2) + (size_t)mt.slot * (kFirst ? 2 : 1) * (size_t)p.I * p.H;
+    const float *A = (const float *)(kFirst ? p.x : p.h);
+    // ---- staging: thread -> rows tid / 8 + 32 i, 16-byte chunk tid % 8; rows past the end re-read the last one, their outputs are dropped ----
+    const int row = tid >> 3, ch = tid & 7;
+    const float *xsrc[XL];
+    int xat[XL];
+#pragma unroll
+    for (int i = 0; i < XL; ++i) {
+        const int r = row + 32 * i, m = mt.row_begin + min(r, mt.rows - 1);
+        xsrc[i] = A + (size_t)(kFirst ? p.perm[m] : m) * K;
+        xat[i] = r * 8 + (ch ^ swz8(r));
+    }
+    const int wrow = kFirst ? min(n0 + (row & 15), N - 1) + (row < 16 ? 0 : p.I) : min(n0 + row, N - 1);
+    const float *wsrc = W + (size_t)wrow * K;
+    const int wat = row * 8 + (ch ^ swz8(row));
+    f32x4 xr[XL], wr;
+    auto load = [&](int k0) {
+        const int k = k0 + ch * 4;
+        const bool in = k < K;                                        // K % 8 == 0: the 4 elements are all in or all out
+#pragma unroll
+        for (int i = 0; i < XL; ++i) xr[i] = in ? *(const f32x4 *)(xsrc[i] + k) : (f32x4){0.f, 0.f, 0.f, 0.f};
+        wr = in ? *(const f32x4 *)(wsrc + k) : (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int i = 0; i < XL; ++i) xs[b][xat[i]] = xr[i];
+        ws[b][wat] = wr;
+    };
+    // ---- this wavefront's products: a group of 16 rows x both weight blocks ----
+    const bool live = wave * 16 < mt.rows;
+    f32x4 acc[2], sum[2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a) acc[a] = sum[a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const int chunks = (K + kKC - 1) / kKC, per = (chunks + kSplit - 1) / kSplit;
+    int left = per;                                                   // chunks of 16 k until the part's end
+    auto flush = [&]() {
+#pragma unroll
+        for (int a = 0; a < 2; ++a) { sum[a] += acc[a]; acc[a] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+    };
+    auto multiply = [&](int b, int chunk0) {
+        constexpr int J = kTileK / kKC;
+        f32x4 xv[J], wv[J][2];
+        const int r = wave * 16 + n;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            xv[j] = xs[b][r * 8 + ((j * 4 + q) ^ swz8(r))];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) wv[j][a] = ws[b][(a * 16 + n) * 8 + ((j * 4 + q) ^ swz8(a * 16 + n))];
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[j][a][i], xv[j][i], acc[a], 0, 0, 0);
+            if (--left == 0) { flush(); left = per; }                 // past the last chunk: zeros are added
+        }
+    };
+    const int KT = (K + kTileK - 1) / kTileK;
+    load(0);
+    store(0);
+    load(kTileK);
+    __syncthreads();
+    for (int kt = 0; kt < KT; ++kt) {
+        if (live) multiply(kt & 1, kt * (kTileK / kKC));
+        store((kt + 1) & 1);
+        load((kt + 2) * kTileK);
+        __syncthreads();
+    }
+    if (!live) return;
+    if (left != per) flush();
+    // lane holds token n of the group, weight rows 4q .. 4q+3 of both blocks
+    const int m = wave * 16 + n, c0 = n0 + 4 * q, c1 = n0 + 16 + 4 * q;
+    if (m >= mt.rows) return;
+    float *O = (float *)(kFirst ? p.h : p.y) + (size_t)(mt.row_begin + m) * N;
+    if (kFirst) {
+        f32x4 h;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) h[r] = sum[0][r] / (1.f + expf(-sum[0][r])) * sum[1][r];
+        if (c0 < N) *(f32x4 *)(O + c0) = h;
+    } else {
+        if (c0 < N) *(f32x4 *)(O + c0) = sum[0];
+        if (c1 < N) *(f32x4 *)(O + c1) = sum[1];
+    }
+}
+
+template <bool kFirst>
+void launch_tile(const Pass &p, hipStream_t st)
+{
+    long long tasks = (long long)p.max_tiles * (kFirst ? (p.I + kWRows / 2 - 1) / (kWRows / 2) : (p.H + kWRows - 1) / kWRows);
+    tasks = (tasks + 7) / 8 * 8;
+    if (tasks <= kGridRow) hipLaunchKernelGGL((k_expert_f32_tile<kFirst, false>), dim3((unsigned)tasks), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((k_expert_f32_tile<kFirst, true>), dim3(kGridRow, (unsigned)((tasks + kGridRow - 1) / kGridRow)), dim3(256), 0, st, p);
 }
 
 template <bool kFirst, int TT, bool kSelf>
@@ -179,18 +307,20 @@ void launch_tt(const Pass &p, int which, hipStream_t st)
 }  // namespace
 
 // Rows per M-tile: what a slot can expect (its share of the routed assignments), so that a weight row read once
-// serves the slot's rows and small groups are not multiplied with padding.
+// serves the slot's rows and small groups are not multiplied with padding.  64 rows: k_expert_f32_tile, which reads its tiles
+// from the list; up to 64 tokens there may be none (GEMM-1 derives its tiles).
 int f32_tile_rows(const Pass &p)
 {
     const long long r = ((long long)p.T * p.k + p.E - 1) / p.E;
-    return r <= 16 ? 16 : r <= 32 ? 32 : 64;
+    return r <= 16 ? 16 : r <= 32 || p.T <= 64 ? 32 : 64;
 }
 
 hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st)
 {
     if (tile_rows == 16)      launch_tt<1>(p, which, st);
     else if (tile_rows == 32) launch_tt<2>(p, which, st);
-    else                      launch_tt<4>(p, which, st);
+    else if (which == 0)      launch_tile<true>(p, st);
+    else                      launch_tile<false>(p, st);
     return hipGetLastError();
 }
 

@@ -191,6 +191,23 @@ def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
     check_output(case, out, ids)
 
 
+@pytest.mark.parametrize("hidden,inter", [(8, 8), (16, 24), (40, 264), (264, 40), (96, 136)])
+def test_f32_tiles_of_64_rows(hidden, inter):
+    """The fp32 kernel for larger groups: chunks of 64 rows and what is left of every number of 16-row groups, on contractions
+    below, at and past a K-step of 32 and with every remainder of its four parts."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    counts = [1, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 80, 129]
+    tokens = sum(counts)
+    wl = MoEWorkload(name="f32_64", tokens=tokens, hidden=hidden, inter=inter, n_experts=len(counts), top_k=1, n_slots=len(counts),
+                     n_local=len(counts), act_dtype="f32", router_dtype="f32", gate="softmax", seed=500 + hidden)
+    g = np.random.Generator(np.random.PCG64(inter))
+    ids = g.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)[:, None]
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    assert case.layer.view(tokens)["tiles"][:, 2].max() == 64
+
+
 @pytest.mark.parametrize("act,router", [("bf16", "bf16"), ("bf16", "f32"), ("f32", "bf16"), ("f32", "f32")])
 @pytest.mark.parametrize("experts,hidden,tokens", [(4, 64, 1), (16, 512, 16), (17, 480, 17), (48, 136, 33), (64, 512, 64), (65, 512, 17), (64, 520, 17), (511, 64, 17), (512, 64, 17)])
 def test_small_router_gate(act, router, experts, hidden, tokens):
