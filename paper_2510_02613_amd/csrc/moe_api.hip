@@ -632,20 +632,28 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = !routed_ids && T <= kFusedMaxTokens && T <= p.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // The large-tile kernels once the whole batch has 48 assignments per slot of the layer (a rank of many holds a part of
-    // them: the DeepSeek-V3 shape with 16 of 256 experts gets there with 3 rows a slot).  Below that small weight-streaming
-    // tasks when a slot expects only a handful of rows (routed: T*k/E on average), and otherwise the large-tile kernels
-    // again where there are weights to stream: their deep LDS rings pay from about 400 MB in the slots that the placement
-    // uses (whole pass, us, 128 x 128 -> large tiles: Qwen3 shape with 64 local experts, 604 MB, 110 tokens 143 -> 112; 32
-    // of them, 302 MB, 76 -> 62 with an even load but 64 -> 74 with a Zipf(1.2) one, where half the slots have no rows and
-    // a slot's few wide N-slices leave the chip idle; those 32 in a layer of 128 slots, 420 tokens, 94 -> 79 and 83 -> 100),
-    // and lose on small layers, whose time is the bookkeeping (24 experts of 128 x 128, 40 tokens 18 -> 21; of 1024 x 768,
-    // 250 tokens 42 -> 50).  The 128 x 128 kernels take the rest, and the contractions that are no whole K-steps.
+    // bf16 passes.  Small weight-streaming tasks of one token tile when a slot expects only a handful of rows (tiny; routed:
+    // T*k/E on average) and of up to 64 rows for a dozen or two (ring64); the large-tile kernels above that.
+    // Where ring64 ends (`few`; whole pass, us, large tiles or 128 x 128 -> ring64): the finer tasks and the shorter bookkeeping
+    // win, the more so the fewer slots there are to fill the chip (Qwen3 shape with 2 local experts, 50 tokens 55 -> 30; 8, 300
+    // tokens 61 -> 49; 32, 120 tokens 97 -> 75; 64, 200 tokens 134 -> 125; 128, 100 tokens 219 -> 214; 24 experts of 1024 x 768, 250
+    // tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24), until slots with several chunks of 64 rows read their weights several
+    // times: a skewed load on 1.2 GB of slots (Zipf(1.2): 128 experts, 200 tokens 131 -> 132, 333 tokens 138 -> 153; with 302 or
+    // 604 MB of them 500 tokens 84 -> 68 and 109 -> 110) or shared experts with the whole batch (DeepSeek-V2-Lite shape, 16 local
+    // experts, 220 tokens 95 -> 89, 340 tokens 84 -> 96).  Under an even load 350 and 500 tokens of 32 Qwen3 experts are
+    // 80 -> 82 and 82 -> 85.  Rows of 7168 lose at every size (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 ->
+    // 529).  Nothing was measured between rows of 2048 and of 7168, nor with more than 300 MB of shorter ones.
+    // Elsewhere the large tiles serve what has 48 assignments of the whole batch per slot of the layer (a rank of many holds
+    // a part of them), and less when there are weights to stream: 400 MB in the slots that the placement uses (32 Qwen3 experts in
+    // 128 slots, 420 tokens, 128 x 128 -> large tiles: 94 -> 79, Zipf 83 -> 100).  They lose on small layers, whose time is the
+    // bookkeeping; the 128 x 128 kernels take those, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
-    const bool wide = can_big && (long long)T * p.kk >= 48ll * p.S;
-    const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
-    const bool big = wide || (can_big && !tiny && used_bytes >= 400000000ll);
+    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 12ll) * p.E;
+    const bool wide = can_big && !few && (long long)T * p.kk >= 48ll * p.S;
+    const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
+    const bool ring64 = mfma && few && !tiny && mfma8_supports(p);
+    const bool big = wide || (can_big && !few && !tiny && used_bytes >= 400000000ll);
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
     // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip's 256 compute
     // units, counted over the used slots that an even routing gives rows and for GEMM-1, which is two thirds of the bytes;
@@ -658,9 +666,9 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
     const double ring_tasks = tiles_expected * (p.I / 64);
     const bool second_round = p.H <= 4096 && ring_tasks >= 240. && ring_tasks < 330.;
-    const bool ring = tiny && can_big && ring_tasks >= 160. && !second_round;
+    const bool ring = ring64 || (tiny && can_big && ring_tasks >= 160. && !second_round);
     const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows() : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
+    const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows(ring64) : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
     // tile.  With a token or two most slots have none, and thousands of workgroups that only find out that their
     // tile does not exist take longer to dispatch than one token's experts take to stream.
@@ -692,7 +700,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     if (e == hipSuccess) {
         if (identity)  e = launch_identity_experts(p, st);
         else if (big)  e = launch_experts_mfma8(p, 0, st);
-        else if (ring) e = launch_experts_ring(p, 0, st);
+        else if (ring) e = launch_experts_ring(p, tile_rows, 0, st);
         else if (tiny) e = launch_experts_decode(p, 0, st);
         else if (mfma) e = launch_experts_mfma(p, 0, st);
         else if (f32)  e = launch_experts_f32(p, tile_rows, 0, st);
@@ -700,7 +708,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     }
     mark(MOE_PHASE_GEMM2);
     if (e == hipSuccess && !identity)
-        e = big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
+        e = big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, tile_rows, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
             f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
     mark(MOE_PHASE_COMBINE);
     if (e == hipSuccess) e = launch_combine(p, st);

@@ -191,6 +191,25 @@ def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
     check_output(case, out, ids)
 
 
+@pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 192), (192, 320), (256, 64), (704, 128)])
+def test_ring_tiles_of_64_rows(hidden, inter):
+    """Weight-streaming tasks of up to 64 token rows: one token tile and two, full and with one row in the last, 8-row pieces
+    that exist and that do not, several chunks of a slot; contractions of 1 to 11 K-steps, output widths that end inside a task's
+    128 columns.  The tile list (chunks of 64) shows that they ran."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    counts = [1, 8, 9, 31, 32, 33, 40, 41, 56, 57, 64, 65, 128, 129]
+    tokens, S = sum(counts), len(counts) + 40
+    wl = MoEWorkload(name="ring64", tokens=tokens, hidden=hidden, inter=inter, n_experts=64, top_k=1, n_slots=S,
+                     n_local=len(counts), act_dtype="bf16", router_dtype="f32", gate="softmax", seed=1500 + hidden)
+    g = np.random.Generator(np.random.PCG64(hidden + inter))
+    ids = g.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)[:, None]
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    rows = case.layer.view(tokens)["tiles"][:, 2]
+    assert rows.max() == 64 and len(rows) == sum((c + 63) // 64 for c in counts)
+
+
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (16, 24), (40, 264), (264, 40), (96, 136)])
 def test_f32_tiles_of_64_rows(hidden, inter):
     """The fp32 kernel for larger groups: chunks of 64 rows and what is left of every number of 16-row groups, on contractions
