@@ -5,6 +5,8 @@
 // references to tensors kept by the memory daemon, Sec. 3.2 "Decoupled Memory and
 // Execution Layers"); all intermediates live in the caller's workspace, which is
 // carved once at create time, so no later call can allocate.
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -175,7 +177,9 @@ struct moe_layer {
     std::vector<Fill> load_ev;
     int n_pending = 0;
     const int32_t *table_arg = nullptr;   // host table of a moe_forward_static pass whose selection kernel installs it
-    hipEvent_t serve_ev = nullptr;  // "work enqueued on the serving stream so far", recorded per fill
+    hipEvent_t serve_ev = nullptr;  // "work enqueued on the serving stream so far", recorded by a fill that has to wait for it
+    // whether a fill asks first if the serving stream has anything left (serve_pending below); a pass or a switch resets it
+    std::atomic<bool> ask_serve{false};
     moe_vpool *vpool[2] = {nullptr, nullptr};  // the page pools under w13 and w2 when the layer was told (moe_layer_bind_vpools)
 };
 
@@ -373,6 +377,7 @@ moe_status_t install_table(moe_layer_t *l, std::vector<int32_t> &table, std::vec
     e = launch_write_map(dst, table.data(), (int)table.size(), (hipStream_t)hip_stream);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "expert map upload failed: %s", hipGetErrorString(e));
     l->has_map = true;
+    l->ask_serve.store(false, std::memory_order_relaxed);
     l->slot_owner.swap(owner);
     l->slots_used = slots_in_use(l->slot_owner.data(), l->cfg.n_slots);
     return MOE_OK;
@@ -505,6 +510,27 @@ moe_status_t moe_layer_bind_vpools(moe_layer_t *l, moe_vpool_t *w13_pool, moe_vp
     return MOE_OK;
 }
 
+// Whether a fill has to wait for work enqueued on the serving stream.  Making another stream wait for a pending event takes the
+// host 12 us, asking the stream whether it is idle 0.2 (32 fills and two forwards of the Qwen3-shaped rank 950 -> 740 us, 64 tokens 900 -> 425), unless it has
+// work that the runtime has not been asked about, which takes 17: so the first fill behind a pass or a switch of this layer
+// does not ask, and neither does one after an answer that took long (somebody else's work between the fills).  The question is put in
+// the relaxed capture mode: in the others it would end a graph capture under way on some other stream.  Capturing streams are
+// not asked: their fill becomes part of the graph by the event, or is refused.
+static bool serve_pending(moe_layer *l, hipStream_t serve, hipStream_t copy)
+{
+    if (!l->ask_serve.exchange(true, std::memory_order_relaxed)) return true;
+    hipStreamCaptureStatus cs[2] = {hipStreamCaptureStatusActive, hipStreamCaptureStatusActive};
+    if (hipStreamIsCapturing(serve, &cs[0]) != hipSuccess || hipStreamIsCapturing(copy, &cs[1]) != hipSuccess) return true;
+    if (cs[0] != hipStreamCaptureStatusNone || cs[1] != hipStreamCaptureStatusNone) return true;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return true;
+    const auto start = std::chrono::steady_clock::now();
+    const hipError_t q = hipStreamQuery(serve);
+    if (std::chrono::steady_clock::now() - start > std::chrono::microseconds(5)) l->ask_serve.store(false, std::memory_order_relaxed);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return q != hipSuccess;
+}
+
 moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, const void *src_w2,
                              void *copy_stream, void *serve_stream, int32_t copy_blocks)
 {
@@ -533,8 +559,10 @@ moe_status_t moe_load_expert(moe_layer_t *l, int32_t slot, const void *src_w13, 
     }
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "hipEventCreate: %s", hipGetErrorString(e));
     // a forward already enqueued on the serving stream may still read the slot under an older map
-    e = hipEventRecord(l->serve_ev, (hipStream_t)serve_stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)copy_stream, l->serve_ev, 0);
+    if (serve_pending(l, (hipStream_t)serve_stream, (hipStream_t)copy_stream)) {
+        e = hipEventRecord(l->serve_ev, (hipStream_t)serve_stream);
+        if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)copy_stream, l->serve_ev, 0);
+    }
     const size_t es = esize(c.act_dtype);
     const size_t b13 = 2 * (size_t)c.inter * c.hidden * es, b2 = (size_t)c.hidden * c.inter * es;
     if (e == hipSuccess)
@@ -592,6 +620,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     if (!aligned(x, 16) || !aligned(out, 16)) return fail(MOE_ERR_ARG, "x and out must be 16-byte aligned");
 
     hipStream_t st = (hipStream_t)hip_stream;
+    l->ask_serve.store(false, std::memory_order_relaxed);
     char *ws = (char *)l->buf.workspace;
     Pass p;
     memset(&p, 0, sizeof p);

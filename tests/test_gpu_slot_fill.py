@@ -169,3 +169,63 @@ def test_fills_from_two_threads_on_their_own_streams_under_one_handle():
     assert not errors, errors
     np.testing.assert_array_equal(tensor_to_host(got13), case.w13_pool[4:6])
     np.testing.assert_array_equal(tensor_to_host(got2), case.w2_pool[4:6])
+
+
+@pytest.mark.parametrize("serve_default", [True, False])
+def test_a_fill_waits_for_what_the_serving_stream_still_has(serve_default):
+    """Fills in a row with and without work left on the serving stream, which also writes their sources: a fill that asks the stream
+    first must see all of it, whether the layer or somebody else enqueued it."""
+    import torch
+    from gpu_util import Case, tensor_to_host
+    wl = MoEWorkload(name="fill_wait", tokens=64, **dict(MID, hidden=1024, inter=1024, n_experts=8, n_slots=8, n_local=8))
+    case = Case(wl, expert_map=np.array([0, 1, -1, -1, -1, -1, -1, -1], np.int32))
+    src = {e: (case.layer.upload(case.inp["w13_experts"][e]), case.layer.upload(case.inp["w2_experts"][e])) for e in range(2, 8)}
+    serve = torch.cuda.current_stream() if serve_default else torch.cuda.Stream()
+    copy = torch.cuda.Stream()
+    stage = [(torch.zeros_like(a), torch.zeros_like(b)) for a, b in src.values()]
+    work = torch.randn(4096, 4096, device=case.x_dev.device)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(serve):
+        for i, (e, (a, b)) in enumerate(src.items()):
+            if i != 3:                                       # one fill finds the stream as the one before it left it
+                for _ in range(4):
+                    work @ work                              # a while on the serving stream, then the source
+            stage[i][0].copy_(a)
+            stage[i][1].copy_(b)
+            case.layer.load_expert_async(e, stage[i][0], stage[i][1], copy, serve)
+            if i == 1:
+                torch.cuda.synchronize()                     # the next fills ask an idle stream, then a busy one
+            if i == 2:
+                case.layer.forward(case.x_dev)
+        case.place(np.array([0, 1, 2, 3, 4, 5, 6, 7], np.int32), upload=False)
+        got13, got2 = case.layer.w13.clone(), case.layer.w2.clone()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(tensor_to_host(got13), case.w13_pool)
+    np.testing.assert_array_equal(tensor_to_host(got2), case.w2_pool)
+
+
+def test_fills_beside_a_capture_leave_it_alone():
+    """A graph capture of the serving thread's forward goes on while slots are filled on other streams."""
+    import torch
+    from gpu_util import Case, tensor_to_host
+    wl = MoEWorkload(name="fill_cap", tokens=64, **dict(MID, n_experts=8, n_slots=8, n_local=8))
+    case = Case(wl, expert_map=np.array([0, 1, 2, 3, -1, -1, -1, -1], np.int32))
+    src = {e: (case.layer.upload(case.inp["w13_experts"][e]), case.layer.upload(case.inp["w2_experts"][e])) for e in range(4, 8)}
+    before = case.run()
+    copy, other, cap = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Stream()
+    out = torch.empty_like(case.x_dev)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=cap):
+        case.layer.forward(case.x_dev, out=out, shared_range=wl.shared_range)
+        for e in src:                                        # the second and later ones ask `other`, which is idle
+            case.layer.load_expert_async(e, src[e][0], src[e][1], copy, other)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(tensor_to_host(out), before)
+    case.place(np.arange(8, dtype=np.int32), upload=False)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(tensor_to_host(case.layer.w13), case.w13_pool)
+    np.testing.assert_array_equal(tensor_to_host(case.layer.w2), case.w2_pool)
