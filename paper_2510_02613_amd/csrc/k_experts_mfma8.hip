@@ -517,11 +517,18 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     const int KT = w1 - w0;
     // All workgroups of a launch walk K at the same pace, 128 bytes of rows that lie a row length apart: started at the
     // same K-step they ask the same few memory channels at a time (a row length of 4096 bytes is the worst case, and
-    // how bad it gets then changes with where the pool lies).  The N-slices of a tile start spread over K instead.
-    // Only while a tile has few token rows: many of them are shared through L2 by slices at the same K-step.
-    // Qwen3 shape (rows of 4096 bytes) 333 tokens 236 .. 254 -> 228 us, 1000 tokens 263 .. 281 -> 251 us; rows of
-    // 14336 bytes +-0; with the tiles of 8192 tokens of the DeepSeek-V3-shaped rank included 943 -> 998 us.
-    const int first = kPhase == 0 && c.n_tt <= 4 ? n0 / BNO * KT / p.n_slices[kFirst ? 0 : 1] : 0;
+    // how bad it gets then changes with where the pool lies).  So they start spread over K.
+    // Tiles with few token rows: every N-slice at its own step.  Qwen3 shape (rows of 4096 bytes) 333 tokens 236 .. 254 -> 228 us,
+    // 1000 tokens 263 .. 281 -> 251 us; rows of 14336 bytes +-0.
+    // Many token rows are shared through L2 by the slices of a tile at the same step: a unit's slices start together, the units spread
+    // by their place in the list (which does not depend on the slots the experts sit in), where rows are a multiple of 4096 bytes.
+    // Qwen3 shape, GEMM-1 of 2500 tokens 164 .. 176 -> 159 .. 170 us, of 2500 on 64 of its experts 113 -> 89; DeepSeek-V3-shaped
+    // rank, GEMM-2 of 5000 tokens 240 -> 226; rows of 1536 and 2816 bytes +0.5 %.
+    // Not the chunks of one slot, which share its weights the same way, and not beside a shared expert with several of them,
+    // which reads the same token rows as everybody (DeepSeek-V2-Lite shape, GEMM-1 of 1777 tokens 195.6 -> 196.5 us).
+    const int slices = p.n_slices[kFirst ? 0 : 1];
+    const bool spread = mt.single && K % 2048 == 0 && !(kFirst && p.shared_end - p.shared_begin > kBM);
+    const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? n0 / BNO * KT / slices : spread ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
     // token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
     // wavefront's work is specialised on that count so that its K loop is straight-line code.
     const int ntc = (c.n_tt - c.wm + 1) >> 1;
