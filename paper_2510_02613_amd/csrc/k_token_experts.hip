@@ -1,0 +1,193 @@
+// Everything behind the gate of a pass of few tokens through a small layer, in one launch.
+//
+// The expert FFN of Sec. 2.1 of the paper and its weighted combine, token by token: a workgroup reads its token's k + n_shared
+// experts (the slot comes from the selection kernel's table of assignments; Sec. 3.2 / 4.6: placement is data), keeps h
+// and y in LDS and adds them up.
+//
+// What bounds it: nothing but latency.  As GEMM-1, GEMM-2 and combine such a pass is three launches of 3 to 5 us, each a chain of
+// memory round trips; nothing is left of two of them when a token's rows need not meet the other tokens' of the same expert.  The
+// price is that an expert's weights are read once per token instead of once per tile, out of L2, by one compute unit: the host
+// takes this kernel while that is at most 256 KB per token (kTokenBytes) and there is a compute unit per token (kTokens).
+// Whole pass, us, three launches -> this one: 128 x 64 fp32 layer, top-2, 1 token 14.3 -> 11.2, 64 tokens 16.4 -> 12.6, 256
+// tokens 22.0 -> 16.8, in bf16 14.2 -> 11.4, 18.8 -> 16.1, 23.5 -> 18.0; at the limit of the bytes (512 x 16, fp32) 64 tokens 18.9 -> 18.6,
+// 256 tokens 27.5 -> 23.0.
+// Rows of the weights are dotted by quarter wavefronts (16 lanes x 16 bytes), several of them requested together; no matrix
+// instruction, the contractions are too short to fill one.  Sums: a lane's products in order, then the 16 lanes' by halves.
+// Workgroup 0 writes the tables (offsets, permutation, tile list) as in the other kernels that derive their tiles, and h and y go to the
+// workspace too.
+#include "moe_internal.h"
+#include "self_tiles.h"
+#include "wave_ops.h"
+
+namespace emoe {
+namespace {
+
+constexpr int kThreads = 1024, kGroups = kThreads / 16;   // groups of 16 lanes, a weight row each
+constexpr int kMaxKK = 36;                                // top_k <= 32 plus <= 4 shared experts
+constexpr int kTokens = 256;                              // a workgroup per token: one round of the chip
+constexpr long long kTokenBytes = 256 * 1024;
+
+template <typename T> struct Vec;
+template <> struct Vec<float> { static constexpr int n = 4; };
+template <> struct Vec<uint16_t> { static constexpr int n = 8; };
+
+// sum over the 16 lanes of a row of the wavefront, in its lane 15
+__device__ __forceinline__ float row_sum(float v)
+{
+    v += __int_as_float(dpp_i32<0x118, 0xf>(0, __float_as_int(v)));   // row_shr 8, 4, 2, 1
+    v += __int_as_float(dpp_i32<0x114, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_i32<0x112, 0xf>(0, __float_as_int(v)));
+    v += __int_as_float(dpp_i32<0x111, 0xf>(0, __float_as_int(v)));
+    return v;
+}
+
+// acc[u] += rows[u] . v over this lane's share: elements l V + 16 V c .. of K (K % 8 == 0), v in LDS as floats.  (Two c's loads
+// together: no faster, rows of 512 2 % slower.)
+template <typename T, int U>
+__device__ __forceinline__ void dot_rows(float (&acc)[U], const T *const (&rows)[U], const float *const (&v)[U], int K, int l)
+{
+    constexpr int V = Vec<T>::n;
+    for (int k = l * V; k < K; k += 16 * V) {
+        uint4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) raw[u] = *(const uint4 *)(rows[u] + k);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const T *w = (const T *)&raw[u];
+#pragma unroll
+            for (int i = 0; i < V; ++i) acc[u] = fmaf(load_f32<T>(w, i), v[u][k + i], acc[u]);
+        }
+    }
+}
+
+template <typename T> __device__ __forceinline__ float silu_up(float g, float u);
+template <> __device__ __forceinline__ float silu_up<float>(float g, float u) { return g / (1.f + expf(-g)) * u; }
+template <> __device__ __forceinline__ float silu_up<uint16_t>(float g, float u) { return silu_mul(g, u); }
+// v as it is stored in the activation type
+template <typename T> __device__ __forceinline__ float stored(float v);
+template <> __device__ __forceinline__ float stored<float>(float v) { return v; }
+template <> __device__ __forceinline__ float stored<uint16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
+
+template <typename T, bool kSelf>
+__global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_rows)
+{
+    extern __shared__ float sm[];             // x [H], h [n][I], y [n][H]; or workgroup 0's tables
+    __shared__ int32_t slots[kMaxKK], rows[kMaxKK], n_local;
+    __shared__ float wts[kMaxKK];
+    if (kSelf && blockIdx.x == 0) { self_tables(p, tile_rows, sm); return; }
+    const int t = blockIdx.x - (kSelf ? 1 : 0), H = p.H, I = p.I, tid = threadIdx.x, lane = tid & 63, l = tid & 15, g = tid >> 4;
+    float *x = sm, *h = x + H, *y = h + (size_t)p.kk * I;
+    for (int c = tid; c < H; c += kThreads) x[c] = load_f32<T>((const T *)p.x + (size_t)t * H, c);
+    if (tid < 64) {   // first wavefront: the token's local assignments, compacted, in selection order
+        int slot = -1, row = 0;
+        float wv = 0.f;
+        if (lane < p.kk) {
+            const int a = t * p.kk + lane;
+            wv = lane < p.k ? p.w[(size_t)t * p.k + lane] : 1.0f;
+            if (kSelf) {
+                row = p.slot_rank[a];
+                slot = row >> 12;
+            } else {
+                row = p.inv[a];
+                slot = slot_of(p, a);
+            }
+        }
+        if (kSelf) {   // the row among all rows: those of the slots before, of the slot in earlier blocks of tokens, the rank
+            const SelfScan sc = self_scan(p, lane, (p.T + kFusedTokens - 1) / kFusedTokens, tile_rows);
+            const int s = max(slot, 0), owner = s / sc.spl, mine = s - owner * sc.spl;
+            row = (row & 0xfff) + (__shfl(sc.incl - sc.own, owner, 64) >> 16);
+#pragma unroll
+            for (int i = 0; i < kSelfLaneSlots; ++i) {
+                const uint32_t w = (uint32_t)__shfl((int)sc.w[i], owner, 64);
+                if (i < mine) row += rows_of(w);
+                if (i == mine) row += rows_of(w & ((1u << (8 * (t / kFusedTokens))) - 1u));
+            }
+        }
+        const unsigned long long m = __ballot(slot >= 0);
+        if (slot >= 0) {
+            const int at = __popcll(m & ((1ull << lane) - 1ull));
+            slots[at] = slot;
+            rows[at] = row;
+            wts[at] = wv;
+        }
+        if (lane == 0) n_local = __popcll(m);
+    }
+    __syncthreads();
+    const int n = n_local;
+    // ---- h = silu(x . Wg) * (x . Wu): a group of lanes takes columns g, g + 64, ... of all experts, two of them together ----
+    const size_t s13 = 2 * (size_t)I * H, s2 = (size_t)H * I;
+    for (int c0 = g; c0 < n * I; c0 += 2 * kGroups) {
+        const T *w[4];
+        const float *v[4];
+        int task[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            task[u] = min(c0 + u * kGroups, n * I - 1);          // past the end: the last one again, not stored
+            const int j = task[u] / I, col = task[u] - j * I;
+            w[2 * u] = (const T *)p.w13 + (size_t)slots[j] * s13 + (size_t)col * H;
+            w[2 * u + 1] = w[2 * u] + (size_t)I * H;
+            v[2 * u] = v[2 * u + 1] = x;
+        }
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        dot_rows<T, 4>(acc, w, v, H, l);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const float gate = row_sum(acc[2 * u]), up = row_sum(acc[2 * u + 1]);
+            if (l == 15 && c0 + u * kGroups < n * I) h[task[u]] = stored<T>(silu_up<T>(gate, up));
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < n * I; c += kThreads) store_f32<T>((T *)p.h + (size_t)rows[c / I] * I, c % I, h[c]);
+    // ---- y = h . W2 ----
+    for (int c0 = g; c0 < n * H; c0 += 4 * kGroups) {
+        const T *w[4];
+        const float *v[4];
+        int task[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            task[u] = min(c0 + u * kGroups, n * H - 1);
+            const int j = task[u] / H, col = task[u] - j * H;
+            w[u] = (const T *)p.w2 + (size_t)slots[j] * s2 + (size_t)col * I;
+            v[u] = h + j * I;
+        }
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        dot_rows<T, 4>(acc, w, v, I, l);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float s = row_sum(acc[u]);
+            if (l == 15 && c0 + u * kGroups < n * H) y[task[u]] = stored<T>(s);
+        }
+    }
+    __syncthreads();
+    for (int c = tid; c < n * H; c += kThreads) store_f32<T>((T *)p.y + (size_t)rows[c / H] * H, c % H, y[c]);
+    // ---- combine, in selection order ----
+    for (int c = tid; c < H; c += kThreads) {
+        float o = 0.f;
+        for (int j = 0; j < n; ++j) o = fmaf(wts[j], y[(size_t)j * H + c], o);
+        store_f32<T>((T *)p.out + (size_t)t * H, c, o);
+    }
+}
+
+}  // namespace
+
+bool token_experts_supports(const Pass &p)
+{
+    return p.T <= kTokens && 3ll * p.kk * p.H * p.I * (p.act_bf16 ? 2 : 4) <= kTokenBytes;
+}
+
+hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st)
+{
+    const size_t smem = sizeof(float) * ((size_t)p.H + (size_t)p.kk * (p.I + p.H));   // at most 44 KB with kTokenBytes of weights and I >= 8
+    const size_t lds = smem > (size_t)kSelfTableBytes ? smem : (size_t)kSelfTableBytes;
+    const dim3 grid(p.T + (p.self_tiles ? 1 : 0)), block(kThreads);
+    if (p.act_bf16) {
+        if (p.self_tiles) hipLaunchKernelGGL((k_token_experts<uint16_t, true>), grid, block, lds, st, p, tile_rows);
+        else              hipLaunchKernelGGL((k_token_experts<uint16_t, false>), grid, block, lds, st, p, tile_rows);
+    } else {
+        if (p.self_tiles) hipLaunchKernelGGL((k_token_experts<float, true>), grid, block, lds, st, p, tile_rows);
+        else              hipLaunchKernelGGL((k_token_experts<float, false>), grid, block, lds, st, p, tile_rows);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace emoe

@@ -725,9 +725,11 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
     p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
+    const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
     mark(MOE_PHASE_GEMM1);
     if (e == hipSuccess) {
-        if (identity)  e = launch_identity_experts(p, st);
+        if (whole)          e = launch_token_experts(p, tile_rows, st);
+        else if (identity)  e = launch_identity_experts(p, st);
         else if (big)  e = launch_experts_mfma8(p, 0, st);
         else if (ring) e = launch_experts_ring(p, tile_rows, 0, st);
         else if (tiny) e = launch_experts_decode(p, 0, st);
@@ -736,11 +738,11 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
         else           e = launch_experts_generic(p, 0, st);
     }
     mark(MOE_PHASE_GEMM2);
-    if (e == hipSuccess && !identity)
+    if (e == hipSuccess && !identity && !whole)
         e = big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, tile_rows, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
             f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
     mark(MOE_PHASE_COMBINE);
-    if (e == hipSuccess) e = launch_combine(p, st);
+    if (e == hipSuccess && !whole) e = launch_combine(p, st);
     mark(MOE_N_PHASES);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "forward launch failed: %s", hipGetErrorString(e));
     if (ev) l->prof_count++;

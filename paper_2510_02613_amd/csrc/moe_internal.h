@@ -139,6 +139,9 @@ int f32_tile_rows(const Pass &p);
 // GEMM-1 of these can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
 // at most 4 blocks of tokens and 256 slots: no bookkeeping kernel in front of it
 inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 256 && p.T <= 4 * 16; }
+// everything behind the gate and the bookkeeping in one launch, for few tokens of small layers
+bool token_experts_supports(const Pass &p);
+hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st);
 hipError_t launch_identity_experts(const Pass &p, hipStream_t st);
 hipError_t launch_combine(const Pass &p, hipStream_t st);
 
@@ -153,6 +156,27 @@ constexpr int kGenericTileRows = 32;  // M-tile of the plain expert kernels
 
 // ---- small device helpers ---------------------------------------------------
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
+
+// slot of assignment a (token a / kk, column a % kk), or -1 when it is not this rank's
+__device__ __forceinline__ int slot_of(const Pass &p, int a)
+{
+    if (a >= p.T * p.kk) return -1;
+    const int t = a / p.kk, j = a - t * p.kk;
+    if (j < p.k) {
+        // ids come from the gate, or from the caller when the routing is given: an id outside
+        // [0, E) is an assignment that does not exist
+        const int id = p.ids[(size_t)t * p.k + j];
+        if ((unsigned)id >= (unsigned)p.E) return -1;
+        const int m = p.map[id];
+        if (m >= -1) return m;
+        // replicated expert: -2 - m is where its copy list (count R >= 2, then R slots) starts behind
+        // the E + n_shared entries; token t uses copy t mod R
+        const int32_t *copies = p.map + p.E + p.n_shared + (-2 - m);
+        return copies[1 + t % copies[0]];
+    }
+    if (t >= p.shared_begin && t < p.shared_end) return p.map[p.E + (j - p.k)];
+    return -1;
+}
 
 // fp32 -> bf16, round to nearest even (one v_cvt_pk_bf16_f32 per pair on gfx950)
 __device__ __forceinline__ uint16_t f32_to_bf16(float f)

@@ -210,6 +210,32 @@ def test_ring_tiles_of_64_rows(hidden, inter):
     assert rows.max() == 64 and len(rows) == sum((c + 63) // 64 for c in counts)
 
 
+@pytest.mark.parametrize("act", ["f32", "bf16"])
+@pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 256, 257])
+@pytest.mark.parametrize("hidden,inter", [(8, 8), (64, 40), (200, 24), (24, 136), (136, 40), (136, 48), (1024, 8)])
+def test_small_layers_token_by_token(act, tokens, hidden, inter):
+    """Small layers whose experts run in one launch behind the bookkeeping (up to 256 tokens and 256 KB of weights per token; the
+    first sizes past either go the common way): rows shorter and longer than 16 lanes' loads, one and several rounds of weight rows,
+    shared rows, tokens without local experts.  Output, h, y and tables as with separate bookkeeping, bit for bit, and within the
+    oracle's bar."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="token", tokens=tokens, hidden=hidden, inter=inter, n_experts=24, top_k=3, n_slots=22, n_local=12,
+                     act_dtype=act, router_dtype="f32", gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,
+                     n_shared=1, shared_range=(tokens // 3, tokens // 3 + min(30, tokens - tokens // 3)), seed=1600 + tokens)
+    case = Case(wl)
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (16, 24), (40, 264), (264, 40), (96, 136)])
 def test_f32_tiles_of_64_rows(hidden, inter):
     """The fp32 kernel for larger groups: chunks of 64 rows and what is left of every number of 16-row groups, on contractions
