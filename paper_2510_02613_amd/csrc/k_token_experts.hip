@@ -1,4 +1,5 @@
-// Everything behind the gate of a pass of few tokens through a small layer, in one launch.
+// Launches saved where a pass is a chain of them: everything behind the gate of a pass of few tokens through a small layer in one
+// launch (k_token_experts), GEMM-2 and combine of a token or two in one (k_gemm2_combine, at the end).
 //
 // The expert FFN of Sec. 2.1 of the paper and its weighted combine, token by token: a workgroup reads its token's k + n_shared
 // experts (the slot comes from the selection kernel's table of assignments; Sec. 3.2 / 4.6: placement is data), keeps h
@@ -168,7 +169,80 @@ __global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_row
     }
 }
 
+// GEMM-2 and combine of a token or two (bf16): a token's experts share no rows with another token's worth speaking of, so
+// a workgroup takes 8 columns of out for one token, wavefront j its j-th local expert (and the j + 8-th): 8 rows of W2, all
+// of a row's loads a lane has in flight together, dotted without matrix instructions, y rounded as it is stored, added up in
+// selection order.  What bounds it: the weights' way from HBM and the launch; the combine by itself was 4 us of latency behind it.
+// One token of the Qwen3 shape (8 experts, 25 MB of W2): GEMM-2 7.1 us and combine 4.3 us -> 8.4 us.  (When it pays: moe_api.hip.)
+constexpr int kCols = 8, kColWaves = 8;
+__global__ __launch_bounds__(64 * kColWaves) void k_gemm2_combine(Pass p)
+{
+    __shared__ float y[kMaxKK][kCols];
+    const int t = blockIdx.y, n0 = blockIdx.x * kCols, H = p.H, I = p.I, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int slot = -1, row = 0;
+    if (lane < p.kk) {
+        slot = slot_of(p, t * p.kk + lane);
+        row = p.inv[(size_t)t * p.kk + lane];
+    }
+    unsigned long long left = __ballot(slot >= 0);           // local assignments, in selection order
+    const int n = __popcll(left);
+    for (int i = 0; i < n; ++i, left &= left - 1) {
+        if (i % kColWaves != wave) continue;                 // uniform
+        const int j = __ffsll((long long)left) - 1, s = __builtin_amdgcn_readlane(slot, j), r = __builtin_amdgcn_readlane(row, j);
+        const uint16_t *w = (const uint16_t *)p.w2 + (size_t)s * H * I + (size_t)n0 * I, *h = (const uint16_t *)p.h + (size_t)r * I;
+        float acc[kCols] = {};
+        for (int k0 = 0; k0 < I; k0 += 1024) {               // two pieces of 512: one 16-byte load per row, lane and piece
+            uint4 raw[2][kCols], hv[2];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int k = k0 + c * 512 + lane * 8;
+                const bool in = k < I;                       // I % 8 == 0
+                hv[c] = in ? *(const uint4 *)(h + k) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < kCols; ++q) raw[c][q] = in ? *(const uint4 *)(w + (size_t)q * I + k) : make_uint4(0, 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);               // all loads go out before the first product
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int q = 0; q < kCols; ++q)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        acc[q] = fmaf(load_f32<uint16_t>((const uint16_t *)&raw[c][q], e), load_f32<uint16_t>((const uint16_t *)&hv[c], e), acc[q]);
+        }
+        float mine = 0.f;
+#pragma unroll
+        for (int q = 0; q < kCols; ++q) {
+            const float sum = wave_sum_f32(acc[q]);
+            mine = lane == q ? sum : mine;
+        }
+        if (lane < kCols) {
+            const uint16_t b = f32_to_bf16(mine);
+            ((uint16_t *)p.y)[(size_t)r * H + n0 + lane] = b;
+            y[i][lane] = bf16_to_f32(b);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    unsigned long long m = __ballot(slot >= 0);
+    const float wv = lane < p.k ? p.w[(size_t)t * p.k + lane] : 1.0f;
+    float o = 0.f;
+    for (int i = 0; i < n; ++i, m &= m - 1) {
+        const float wj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wv), __ffsll((long long)m) - 1));
+        if (lane < kCols) o = fmaf(wj, y[i][lane], o);
+    }
+    if (lane < kCols) ((uint16_t *)p.out)[(size_t)t * H + n0 + lane] = f32_to_bf16(o);
+}
+
 }  // namespace
+
+// H % 8 == 0 as everywhere
+hipError_t launch_gemm2_combine(const Pass &p, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_gemm2_combine, dim3(p.H / kCols, p.T), dim3(64 * kColWaves), 0, st, p);
+    return hipGetLastError();
+}
 
 bool token_experts_supports(const Pass &p)
 {

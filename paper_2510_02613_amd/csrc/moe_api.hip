@@ -726,6 +726,10 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
     const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
+    // GEMM-2 and combine in one launch (recorded as GEMM-2): one token, or two where rows are short (whole pass, us, two launches ->
+    // one: Qwen3 shape 1 token 36.5 -> 33.9, 2 tokens 44.3 -> 40.9, 3 tokens 64.5 -> 62.5, 4 tokens 69.0 -> 68.8; DeepSeek-V2-Lite
+    // shape 38.7 -> 33.3, 62.6 -> 57.2, 4 tokens 77.8 -> 80.5; DeepSeek-V3-shaped rank 41.7 -> 40.2, 78.9 -> 79.5, 4 tokens 89.0 -> 91.0)
+    const bool fused2 = !whole && !identity && tiny && T <= (p.H <= 4096 ? 2 : 1);
     mark(MOE_PHASE_GEMM1);
     if (e == hipSuccess) {
         if (whole)          e = launch_token_experts(p, tile_rows, st);
@@ -739,10 +743,10 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     }
     mark(MOE_PHASE_GEMM2);
     if (e == hipSuccess && !identity && !whole)
-        e = big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, tile_rows, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
+        e = fused2 ? launch_gemm2_combine(p, st) : big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, tile_rows, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
             f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
     mark(MOE_PHASE_COMBINE);
-    if (e == hipSuccess && !whole) e = launch_combine(p, st);
+    if (e == hipSuccess && !whole && !fused2) e = launch_combine(p, st);
     mark(MOE_N_PHASES);
     if (e != hipSuccess) return fail(MOE_ERR_HIP, "forward launch failed: %s", hipGetErrorString(e));
     if (ev) l->prof_count++;

@@ -142,6 +142,7 @@ inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 2
 // everything behind the gate and the bookkeeping in one launch, for few tokens of small layers
 bool token_experts_supports(const Pass &p);
 hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st);
+hipError_t launch_gemm2_combine(const Pass &p, hipStream_t st);   // GEMM-2 and combine of a token or two (bf16)
 hipError_t launch_identity_experts(const Pass &p, hipStream_t st);
 hipError_t launch_combine(const Pass &p, hipStream_t st);
 

@@ -236,6 +236,29 @@ def test_small_layers_token_by_token(act, tokens, hidden, inter):
         np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
 
 
+@pytest.mark.parametrize("tokens", [1, 2, 3])
+@pytest.mark.parametrize("hidden,inter", [(136, 512), (72, 520), (64, 1024), (104, 1544), (4096, 72), (4104, 72)])
+def test_second_gemm_and_combine_of_a_token_or_two(tokens, hidden, inter):
+    """One launch for GEMM-2 and combine (one token; two on rows of up to 4096): contractions of one to four pieces of 512 with and
+    without a remainder, more local experts than the workgroup has wavefronts, experts on other ranks, a shared one.  Output, h, y and
+    tables as with separate bookkeeping, bit for bit, and within the oracle's bar."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="two", tokens=tokens, hidden=hidden, inter=inter, n_experts=40, top_k=13, n_slots=40, n_local=36,
+                     act_dtype="bf16", router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, 1), seed=1700 + hidden)
+    case = Case(wl)
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (16, 24), (40, 264), (264, 40), (96, 136)])
 def test_f32_tiles_of_64_rows(hidden, inter):
     """The fp32 kernel for larger groups: chunks of 64 rows and what is left of every number of 16-row groups, on contractions
