@@ -6,9 +6,8 @@
 //
 // What bounds it: a layer of a few megabytes is latency, a chain of memory round trips per launch, so as many of a
 // task's loads as possible go out together; large batches are bound by the fp32 matrix rate (k_expert_f32_tile, below, serves
-// them).  A task is 16 gate rows
-// and the 16 matching up rows (GEMM-1) or 32 W2 rows (GEMM-2) of one M-tile, one workgroup of four wavefronts that
-// each walk a quarter of the contraction; the four sums are added in K order through LDS.  Operands go straight from
+// them).  A task is 16 gate rows and the 16 matching up rows (GEMM-1) or 32 W2 rows (GEMM-2) of one M-tile, one workgroup of
+// four wavefronts that each walk a quarter of the contraction; the four sums are added in K order through LDS.  Operands go straight from
 // global memory into the layout of v_mfma_f32_16x16x4_f32: lane (n = l % 16, q = l / 16) reads 16 bytes, k = 4q .. 4q+3,
 // of row n per 16 k, and the contraction does not care that MFMA i takes element i of every lane as long as weight
 // and token rows agree.  A tile has up to 32 token rows, which a weight row read once serves; the next 16 k are
