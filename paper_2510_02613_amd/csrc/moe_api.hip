@@ -667,10 +667,11 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // win, the more so the fewer slots there are to fill the chip (Qwen3 shape with 2 local experts, 50 tokens 55 -> 30; 8, 300
     // tokens 61 -> 49; 32, 120 tokens 97 -> 75; 64, 200 tokens 134 -> 125; 128, 100 tokens 219 -> 214; 24 experts of 1024 x 768, 250
     // tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24), until slots with several chunks of 64 rows read their weights several
-    // times: a skewed load on 1.2 GB of slots (Zipf(1.2): 128 experts, 200 tokens 131 -> 132, 333 tokens 138 -> 153; with 302 or
-    // 604 MB of them 500 tokens 84 -> 68 and 109 -> 110) or shared experts with the whole batch (DeepSeek-V2-Lite shape, 16 local
-    // experts, 220 tokens 95 -> 89, 340 tokens 84 -> 96).  Under an even load 350 and 500 tokens of 32 Qwen3 experts are
-    // 80 -> 82 and 82 -> 85.  Rows of 7168 lose at every size (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 ->
+    // times: a skewed load on 1.2 GB of slots (Zipf(1.2): 128 experts, 140 tokens 122 -> 119, 165 tokens 122.5 -> 126, 333 tokens
+    // 138 -> 153; an even one gains 2 % up to 190; with 302 or 604 MB of slots 310 tokens 98 -> 68 and 109 -> 86, 500 tokens 84 -> 68
+    // and 109 -> 110) or shared experts with the whole batch (DeepSeek-V2-Lite shape, 16 local
+    // experts, 220 tokens 95 -> 89, 340 tokens 84 -> 96).  Under an even load 210, 300 and 500 tokens
+    // of 32 Qwen3 experts are 74.7 -> 75.2, 76.4 -> 78.0 and 82 -> 85, 240 and 310 of 64 of them 128 -> 123 and 129 -> 130.  Rows of 7168 lose at every size (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 ->
     // 529).  Nothing was measured between rows of 2048 and of 7168, nor with more than 300 MB of shorter ones.
     // Elsewhere the large tiles serve what has 48 assignments of the whole batch per slot of the layer (a rank of many holds
     // a part of them), and less when there are weights to stream: 400 MB in the slots that the placement uses (32 Qwen3 experts in
@@ -678,7 +679,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // bookkeeping; the 128 x 128 kernels take those, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
-    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 12ll) * p.E;
+    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E;
     const bool wide = can_big && !few && (long long)T * p.kk >= 48ll * p.S;
     const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool ring64 = mfma && few && !tiny && mfma8_supports(p);
