@@ -403,7 +403,8 @@ __device__ __forceinline__ void sum_body(const Pass &p, const WaveCtx &c, const 
     emit_token_tile<kFirst>(p, c, mt, n0, N, ring, t, s);
 }
 
-template <bool kFirst, int kPhase>
+// kSpread: units of more than four token tiles start spread over K (the launcher's choice, see `first`).
+template <bool kFirst, int kPhase, bool kSpread = false>
 __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
 {
     const int K = kFirst ? p.H : p.I;
@@ -520,15 +521,10 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     // how bad it gets then changes with where the pool lies).  So they start spread over K.
     // Tiles with few token rows: every N-slice at its own step.  Qwen3 shape (rows of 4096 bytes) 333 tokens 236 .. 254 -> 228 us,
     // 1000 tokens 263 .. 281 -> 251 us; rows of 14336 bytes +-0.
-    // Many token rows are shared through L2 by the slices of a tile at the same step: a unit's slices start together, the units spread
-    // by their place in the list (which does not depend on the slots the experts sit in), where rows are a multiple of 4096 bytes.
-    // Qwen3 shape, GEMM-1 of 2500 tokens 164 .. 176 -> 159 .. 170 us, of 2500 on 64 of its experts 113 -> 89; DeepSeek-V3-shaped
-    // rank, GEMM-2 of 5000 tokens 240 -> 226; rows of 1536 and 2816 bytes +0.5 %.
-    // Not the chunks of one slot, which share its weights the same way, and not beside a shared expert with several of them,
-    // which reads the same token rows as everybody (DeepSeek-V2-Lite shape, GEMM-1 of 1777 tokens 195.6 -> 196.5 us).
-    const int slices = p.n_slices[kFirst ? 0 : 1];
-    const bool spread = mt.single && K % 2048 == 0 && !(kFirst && p.shared_end - p.shared_begin > kBM);
-    const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? n0 / BNO * KT / slices : spread ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
+    // Tiles with many: their rows are shared through L2 by slices at the same step, so a unit's slices start together and the units are
+    // spread by their place in the list (kSpread: launch_experts_mfma8), 5 steps from one to the next (1 and 3: the same within 1 %).
+    // Not the chunks of one slot, which share its weights the same way.
+    const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? n0 / BNO * KT / p.n_slices[kFirst ? 0 : 1] : kSpread && mt.single ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
     // token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
     // wavefront's work is specialised on that count so that its K loop is straight-line code.
     const int ntc = (c.n_tt - c.wm + 1) >> 1;
@@ -598,14 +594,25 @@ hipError_t launch_experts_mfma8(const Pass &p0, int which, hipStream_t st)
     const int nt = p.n_slices[which];
     const int grid = mfma8_grid_rows(p.max_tiles, nt) * kXcds;
     const int round_blocks = (cus < kMaxPartialSets ? cus : kMaxPartialSets) / kXcds * kXcds;
+    // K starts of many-row units spread over K (see the kernel): where rows are a multiple of 4096 bytes, and the order of the tile
+    // list does not follow from the slots the experts sit in -- a row's sum would.
+    // us, together -> spread: GEMM-1, rows of 4096 bytes, Qwen3 shape 1700 tokens 141 -> 142, 2500 tokens 165 -> 158, 4096 tokens
+    // 198 -> 198, 2500 tokens on 64 of its experts 112 -> 90, Zipf(1.2) 180 -> 180; DeepSeek-V2-Lite shape without shared rows 1777 tokens
+    // 185 -> 160; rows of 8192 and 12288 bytes, 32 experts, 1500 tokens 130 -> 107 and 338 -> 324, of 6144 153 -> 154; GEMM-2, rows of
+    // 4096 bytes, DeepSeek-V3-shaped rank 5000 tokens 262 -> 224, 8192 tokens 292 -> 280; of 8192 237 -> 235.
+    // A shared expert with several chunks reads the same token rows as everybody: DeepSeek-V2-Lite shape with the whole batch,
+    // GEMM-1 of 1000 tokens 166 -> 168, 1777 tokens 194.5 -> 198.6, 3000 tokens 270 -> 259.  There the starts stay together.
+    const bool spread = K % 2048 == 0 && tile_list_sorted(p) && !(which == 0 && p.shared_end - p.shared_begin > kBM);
     if (which == 0) {
-        hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 0>), dim3(grid), dim3(kThreads), 0, st, p);
+        if (spread) hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 0, true>), dim3(grid), dim3(kThreads), 0, st, p);
+        else        hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 0, false>), dim3(grid), dim3(kThreads), 0, st, p);
         if (p.k_split) {
             hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 1>), dim3(round_blocks), dim3(kThreads), 0, st, p);
             hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 2>), dim3(round_blocks / 2, kTC), dim3(kThreads), 0, st, p);
         }
     } else {
-        hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 0>), dim3(grid), dim3(kThreads), 0, st, p);
+        if (spread) hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 0, true>), dim3(grid), dim3(kThreads), 0, st, p);
+        else        hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 0, false>), dim3(grid), dim3(kThreads), 0, st, p);
         if (p.k_split) {
             hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 1>), dim3(round_blocks), dim3(kThreads), 0, st, p);
             hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 2>), dim3(round_blocks / 2, kTC), dim3(kThreads), 0, st, p);

@@ -155,7 +155,6 @@ __device__ __forceinline__ void emit_tiles(const Pass &p, int s, int c, int nt, 
     }
 }
 
-constexpr int kSortMax = 2048;   // tile lists up to this long can be ordered by size (staged in LDS)
 constexpr int kSizeBins = 12;    // size classes: 32-row token tiles of a chunk, capped
 
 constexpr int kMaxSlots = 2048;  // n_slots <= 2047
@@ -589,7 +588,7 @@ __global__ __launch_bounds__(kThreads) void k_slot_scan(Pass p, int n_blocks, in
         fkey[s] = key;
     }
     __syncthreads();
-    offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && p.max_tiles <= kSortMax, cnt, fkey);
+    offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && tile_list_sorted(p), cnt, fkey);
 }
 
 // Second and last kernel of the fused bookkeeping (after k_gate_select_hist).  Workgroup 0 writes counts,
@@ -687,7 +686,7 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
         // four wavefronts carry on (the barriers below count the wavefronts still running): the steps are short and
         // many, sixteen wavefronts meet at each of them too slowly (measured: 1 to 4 us more)
         if (tid >= kThreads) return;
-        offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && p.max_tiles <= kSortMax, total, base);
+        offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && tile_list_sorted(p), total, base);
         return;
     }
     // exclusive scan of the totals: total[s] becomes the first grouped row of slot s
@@ -752,7 +751,7 @@ __global__ __launch_bounds__(kHistThreads) __attribute__((amdgpu_waves_per_eu(4)
     __syncthreads();
     if (tiles_wg) {
         if (tid >= kThreads) return;
-        offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && p.max_tiles <= kSortMax, total, base);
+        offsets_and_tiles<kThreads>(p, tile_rows, sort_tiles && tile_list_sorted(p), total, base);
         return;
     }
     int carry = 0;

@@ -96,6 +96,8 @@ struct Pass {
     int32_t k_split;     // this launch may share the contraction of its last round's tiles out (set by the launcher)
 };
 
+constexpr int kSortMax = 2048;         // tile lists of the large-tile kernels that may get this long are ordered by size and first assignment, longer ones by slot
+inline __host__ __device__ bool tile_list_sorted(const Pass &p) { return p.max_tiles <= kSortMax; }
 constexpr int kTableArg = 512;         // expert-table entries that travel in one kernel argument
 constexpr int kGatePlanes = 8;         // most partial-sum planes of the gate logits
 constexpr int kGateFewTokens = 256;    // up to here the few-token logits kernel shares the contraction out over workgroups

@@ -427,3 +427,39 @@ def test_routed_bookkeeping_by_blocks(tokens, k, slots):
     want[order] = np.arange(len(order))
     np.testing.assert_array_equal(v["inv"].reshape(-1), want)
     np.testing.assert_array_equal(v["perm"][:len(order)], order // k)
+
+
+@pytest.mark.parametrize("slots", [40, 1800])
+@pytest.mark.parametrize("hidden,inter", [(2048, 64), (64, 2048)])
+def test_large_tiles_on_long_rows_do_not_follow_the_slots(hidden, inter, slots):
+    """Contractions of 2048, whose units of 129 to 320 rows may start anywhere in K: the same bits whichever slots the experts sit in,
+    with a tile list that is ordered by size (40 slots) and with one that can get too long for that and stays in slot order (1800)."""
+    import torch
+    from paper_2510_02613_amd.layer import MoELayer
+    E, k = 24, 8
+    tokens = 48 * slots // k
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(hidden + slots)
+    g = np.random.Generator(np.random.PCG64(slots))
+    layer = MoELayer(hidden=hidden, inter=inter, n_experts=E, top_k=k, n_slots=slots, max_tokens=tokens, act_dtype="bf16", router_dtype="f32",
+                     gate="softmax", router_w=np.zeros((E, hidden), np.float32), device=dev)
+    counts = np.array([129, 160, 161, 192, 200, 224, 225, 256, 257, 288, 289, 320, 400, 1] + [140 + 16 * i for i in range(10)])
+    if counts.sum() > tokens * k:                            # the small list: as many experts as the batch has assignments for
+        counts[np.cumsum(counts) > tokens * k] = 0
+    ids = np.full(tokens * k, -1, np.int32)
+    ids[g.permutation(tokens * k)[:counts.sum()]] = g.permutation(np.repeat(np.arange(E), counts))
+    ids = torch.from_numpy(ids.reshape(tokens, k)).to(dev)
+    wts = torch.rand(tokens, k, generator=gen, device=dev) + 0.5
+    x = torch.randn(tokens, hidden, generator=gen, device=dev).bfloat16().view(torch.int16)
+    w13 = (torch.randn(E, 2 * inter, hidden, generator=gen, device=dev) * 0.05).bfloat16().view(torch.int16)
+    w2 = (torch.randn(E, hidden, inter, generator=gen, device=dev) * 0.05).bfloat16().view(torch.int16)
+    outs = []
+    for order in (np.arange(E), slots - 1 - np.arange(E), g.permutation(slots)[:E]):
+        at = torch.from_numpy(order.copy()).to(dev)
+        layer.w13[at], layer.w2[at] = w13, w2
+        layer.set_expert_map(order.tolist())
+        outs.append(layer.forward_routed(x, ids, wts))
+        tiles = layer.view(tokens)["tiles"]
+        assert sorted(tiles[tiles[:, 3] == 1][:, 2]) == sorted(c for c in counts if 0 < c <= 320)   # the large-tile kernels ran
+    assert outs[0].view(torch.bfloat16).float().abs().max() > 0
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
