@@ -2,6 +2,8 @@
 run it through the C ABI, and grade it against the CPU oracle."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 
 import oracle
@@ -88,6 +90,45 @@ class Case:
                               forced_ids=forced_ids, identity_experts=identity)
 
 
+class _KernelNode(ctypes.Structure):   # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint * 3),
+                ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+
+def kernels_of(call):
+    """The kernels that call(stream) launches, in order, as "k_name<template arguments>": the call is captured into a graph that is
+    read and thrown away, nothing runs."""
+    import torch
+    hip, cxx = ctypes.CDLL("libamdhip64.so"), ctypes.CDLL("libstdc++.so.6")
+    vp = ctypes.c_void_p
+
+    def ok(rc):
+        assert rc == 0, f"hip error {rc}"
+    hip.hipKernelNameRefByPtr.restype, hip.hipKernelNameRefByPtr.argtypes = ctypes.c_char_p, [vp, vp]
+    cxx.__cxa_demangle.restype, cxx.__cxa_demangle.argtypes = vp, [ctypes.c_char_p, vp, vp, vp]
+    stream, graph, n = torch.cuda.Stream(), vp(), ctypes.c_size_t(0)
+    ok(hip.hipStreamBeginCapture(vp(stream.cuda_stream), 2))              # relaxed
+    try:
+        call(stream)
+    finally:
+        ok(hip.hipStreamEndCapture(vp(stream.cuda_stream), ctypes.byref(graph)))
+    names = []
+    ok(hip.hipGraphGetNodes(graph, None, ctypes.byref(n)))
+    nodes = (vp * n.value)()
+    ok(hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)))
+    for node in nodes:
+        node_type, k = ctypes.c_int(-1), _KernelNode()
+        ok(hip.hipGraphNodeGetType(vp(node), ctypes.byref(node_type)))
+        if node_type.value != 0:
+            continue
+        ok(hip.hipGraphKernelNodeGetParams(vp(node), ctypes.byref(k)))
+        text = cxx.__cxa_demangle(hip.hipKernelNameRefByPtr(k.func, None), None, None, None)
+        name = ctypes.string_at(text).decode().replace("(anonymous namespace)::", "").replace("emoe::", "")
+        names.append(name.split("(")[0].removeprefix("void "))
+    ok(hip.hipGraphDestroy(graph))
+    return names
+
+
 def legal_selection(c_t: np.ndarray, ids: np.ndarray, k: int, n_group: int, topk_group: int):
     """Is `ids` a selection the ordering rule allows for selection scores c_t once fp32 scores
     closer than TIE count as equal?  Returns None when it is, else a sentence saying why not.
@@ -170,10 +211,11 @@ def check_routing(case: Case, gpu_ids: np.ndarray, gpu_w: np.ndarray):
     return gpu_ids, int((flags != 0).sum()), flips
 
 
-def ran_large_tiles(wl, T, flags=0):
-    """Did a pass of T tokens run the large-tile expert kernels (the host's rule, from shapes alone)?"""
-    return (wl.act_dtype == "bf16" and wl.hidden % 64 == 0 and wl.inter % 64 == 0 and not (flags & 3)
-            and T * (wl.top_k + wl.n_shared) >= 48 * wl.n_slots)
+def ran_large_tiles(case: Case, T: int, shared_range, flags=0):
+    """Does such a pass run the large-tile expert kernels?"""
+    import torch
+    x, out = case.x_dev[:T], torch.empty_like(case.x_dev[:T])
+    return any("mfma8" in k for k in kernels_of(lambda s: case.layer.forward(x, out=out, shared_range=shared_range, flags=flags, stream=s)))
 
 
 def check_bookkeeping(case: Case, v: dict, T: int, shared_range, flags=0):
@@ -217,7 +259,7 @@ def check_bookkeeping(case: Case, v: dict, T: int, shared_range, flags=0):
         assert (covered == 1).all(), "tiles do not partition the grouped rows"
     else:
         assert len(tiles) == 0
-    if A and ran_large_tiles(wl, T, flags):
+    if A and ran_large_tiles(case, T, shared_range, flags):
         check_units(case, v)
 
 

@@ -210,6 +210,39 @@ def test_ring_tiles_of_64_rows(hidden, inter):
     assert rows.max() == 64 and len(rows) == sum((c + 63) // 64 for c in counts)
 
 
+@pytest.mark.parametrize("tokens,hidden,inter", [(40, 320, 192), (300, 192, 320), (320, 64, 64)])
+def test_ring_tiles_of_64_rows_behind_the_gate(tokens, hidden, inter):
+    """The same kernels behind both bookkeeping paths of a gated pass, with shared rows, through the entry without a workspace and
+    under replicas: tables and output within the oracle's bar and the same bits every way; more assignments per slot than the large-tile kernels
+    take elsewhere."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing, kernels_of, tensor_to_host
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="ring64g", tokens=tokens, hidden=hidden, inter=inter, n_experts=64, top_k=4 if tokens > 40 else 8, n_slots=14 if tokens > 40 else 6,
+                     n_local=9 if tokens > 40 else 4, act_dtype="bf16", router_dtype="bf16", gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,
+                     n_shared=1, shared_range=(tokens // 8, tokens), seed=1550 + tokens)
+    case = Case(wl)
+    sr = wl.shared_range
+    buf = case.layer.forward(case.x_dev, shared_range=sr)
+    names = kernels_of(lambda s: case.layer.forward(case.x_dev, out=buf, shared_range=sr, stream=s))
+    assert names[-3:] == ["k_expert_ring<true, false, 2>", "k_expert_ring<false, false, 2>", "k_combine<unsigned short, 0>"], names
+    assert tokens * (wl.top_k + 1) >= 48 * wl.n_slots
+    out = case.run()
+    v = case.layer.view(tokens)
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, sr)
+    check_output(case, out, ids)
+    np.testing.assert_array_equal(out, case.run(flags=B.MOE_FLAG_PERMUTE_UNFUSED))
+    np.testing.assert_array_equal(out, tensor_to_host(case.layer.forward_static(case.x_dev, shared_range=sr)))
+    spare = sorted(set(range(wl.n_slots)) - set(case.expert_map.tolist()) - set(case.shared_slots.tolist()))
+    copies = [[int(s)] if s >= 0 else [] for s in case.expert_map]
+    for s, e in zip(spare, np.flatnonzero(case.expert_map >= 0)):
+        case.layer.w13[s], case.layer.w2[s] = case.layer.w13[copies[e][0]], case.layer.w2[copies[e][0]]
+        copies[e].append(int(s))
+    case.layer.set_expert_replicas(copies, case.shared_slots.tolist())
+    assert max(len(c) for c in copies) == 2
+    np.testing.assert_array_equal(out, case.run())
+
+
 @pytest.mark.parametrize("act", ["f32", "bf16"])
 @pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 256, 257])
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (64, 40), (200, 24), (24, 136), (136, 40), (136, 48), (1024, 8)])
