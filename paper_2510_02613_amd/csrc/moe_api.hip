@@ -669,8 +669,9 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24), until slots with several chunks of 64 rows read their weights several
     // times: a skewed load on 1.2 GB of slots (Zipf(1.2): 128 experts, 140 tokens 122 -> 119, 165 tokens 122.5 -> 126, 333 tokens
     // 138 -> 153; an even one gains 2 % up to 190; with 302 or 604 MB of slots 310 tokens 98 -> 68 and 109 -> 86, 500 tokens 84 -> 68
-    // and 109 -> 110) or shared experts with the whole batch (DeepSeek-V2-Lite shape, 16 local
-    // experts, 220 tokens 95 -> 89, 340 tokens 84 -> 96).  Under an even load 210, 300 and 500 tokens
+    // and 109 -> 110) or a shared expert has many rows: up to 320 of them, one tile of the large kernels (DeepSeek-V2-Lite shape, top-1
+    // to top-6, 16 local experts: 220 shared rows 100 -> 93, 320 of 1280 tokens 122 -> 103, 340 90 -> 98, 640 114.5 -> 117, 1280 125 -> 154; 64 local
+    // experts: 150 199 -> 193, 220 209 -> 214, 340 222 -> 219, 640 234 -> 243, 1280 247 -> 293).  Under an even load 210, 300 and 500 tokens
     // of 32 Qwen3 experts are 74.7 -> 75.2, 76.4 -> 78.0 and 82 -> 85, 240 and 310 of 64 of them 128 -> 123 and 129 -> 130.  Rows of 7168 lose at every size (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 ->
     // 529).  Nothing was measured between rows of 2048 and of 7168, nor with more than 300 MB of shorter ones.
     // Elsewhere the large tiles serve what has 48 assignments of the whole batch per slot of the layer (a rank of many holds
@@ -679,7 +680,8 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // bookkeeping; the 128 x 128 kernels take those, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
-    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E;
+    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E &&
+                     shared_end - shared_begin <= mfma8_tile_rows();
     const bool wide = can_big && !few && (long long)T * p.kk >= 48ll * p.S;
     const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool ring64 = mfma && few && !tiny && mfma8_supports(p);

@@ -243,6 +243,35 @@ def test_ring_tiles_of_64_rows_behind_the_gate(tokens, hidden, inter):
     np.testing.assert_array_equal(out, case.run())
 
 
+def _expert_kernels(case, tokens, shared_range=(0, 0), routed=False):
+    """The kernel of GEMM-1 in a pass over the case's first tokens: its name without template arguments."""
+    import torch
+    from gpu_util import kernels_of
+    x, out, k = case.x_dev[:tokens], torch.empty_like(case.x_dev[:tokens]), case.wl.top_k
+    if routed:
+        ids, w = (torch.zeros((tokens, k), dtype=t, device=x.device) for t in (torch.int32, torch.float32))
+        names = kernels_of(lambda s: case.layer.forward_routed(x, ids, w, out=out, shared_range=shared_range, stream=s))
+    else:
+        names = kernels_of(lambda s: case.layer.forward(x, out=out, shared_range=shared_range, stream=s))
+    return next(n.split("<")[0] for n in names if "expert" in n)
+
+
+@pytest.mark.parametrize("tokens,shared,kernel", [(320, 320, "k_expert_ring"), (321, 321, "k_expert_gemm_mfma8"), (1280, 320, "k_expert_ring"),
+                                                  (1280, 321, "k_expert_gemm_mfma8"), (1281, 320, "k_expert_gemm_mfma8")])
+def test_ring_tiles_of_64_rows_up_to_320_shared_rows(tokens, shared, kernel):
+    """Top-1 of 64 experts: 20 assignments a slot are 1280 tokens, but a shared expert's weights are read once per 64 of its rows."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    wl = MoEWorkload(name="few_shared", tokens=tokens, hidden=128, inter=192, n_experts=64, top_k=1, n_slots=9, n_local=8, act_dtype="bf16",
+                     router_dtype="f32", gate="softmax", n_shared=1, shared_range=(tokens - shared, tokens), seed=1580)
+    case = Case(wl)
+    assert _expert_kernels(case, tokens, wl.shared_range) == kernel
+    out = case.run()
+    v = case.layer.view(tokens)
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
+
+
 @pytest.mark.parametrize("act", ["f32", "bf16"])
 @pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 256, 257])
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (64, 40), (200, 24), (24, 136), (136, 40), (136, 48), (1024, 8)])
