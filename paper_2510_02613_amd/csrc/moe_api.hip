@@ -680,7 +680,16 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // bookkeeping; the 128 x 128 kernels take those, and the contractions that are no whole K-steps.
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
-    const bool few = p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E &&
+    // A gated pass has T k / E rows for a slot.  Tokens that arrive routed were sent because one of their experts is here: with few of the
+    // experts that is many times as much, and several chunks read a slot's weights again.  That pays while all tasks of GEMM-1 run at the
+    // same time, two per compute unit, and share them in L2 (us, large tiles -> ring64, ids all local: DeepSeek-V2-Lite shape without
+    // shared experts, top-1, 1280 tokens on 2 experts 99 -> 65, 440 tasks; 4 105 -> 77, 440; 8 76.5 -> 98, 528; 16 78 -> 115, 704; 8, 640
+    // tokens 67 -> 63, 352; Qwen3 shape, 320 tokens on 8 experts 92 -> 60, 480; 16 73 -> 83, 576; 32 77 -> 114, 768).
+    const int resident = l->slots_used - p.n_shared < p.E ? l->slots_used - p.n_shared : p.E;
+    const double here = routed_ids ? 1.0 - std::pow(1.0 - (double)resident / p.E, p.k) : 1.0;   // share of all tokens that are sent here
+    const double chunks = resident > 0 ? std::ceil((double)T * p.k / p.E / here / ring_tile_rows(true)) : 0.0;
+    const bool at_once = chunks <= 1.0 || chunks * resident * (p.I / 64) <= 512.0;
+    const bool few = at_once && p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E &&
                      shared_end - shared_begin <= mfma8_tile_rows();
     const bool wide = can_big && !few && (long long)T * p.kk >= 48ll * p.S;
     const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
@@ -694,7 +703,6 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).  Rows of 7168 hide that (262 tasks, 181.6 ->
     // 166.2); nothing was measured between rows of 2048 and of 7168.  The register kernel with its 32-row tasks takes those
     // passes, as it takes contractions that are no whole K-steps.
-    const int resident = l->slots_used - p.n_shared < p.E ? l->slots_used - p.n_shared : p.E;
     const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
     const double ring_tasks = tiles_expected * (p.I / 64);
     const bool second_round = p.H <= 4096 && ring_tasks >= 240. && ring_tasks < 330.;

@@ -272,6 +272,24 @@ def test_ring_tiles_of_64_rows_up_to_320_shared_rows(tokens, shared, kernel):
     check_output(case, out, ids)
 
 
+@pytest.mark.parametrize("tokens,local,routed,kernel", [(512, 8, True, "k_expert_ring"), (513, 8, True, "k_expert_ring"), (1024, 8, True, "k_expert_ring"),
+                                                        (1025, 8, True, "k_expert_gemm_mfma8"), (1280, 8, False, "k_expert_ring"),
+                                                        (1280, 4, True, "k_expert_ring"), (1280, 64, True, "k_expert_ring")])
+def test_ring_tiles_of_64_rows_while_all_tasks_run_at_once(tokens, local, routed, kernel):
+    """Top-1 of 64 experts, 1408 wide (22 tasks a tile): every token that arrives routed has its expert here, so 8 local ones expect
+    tokens / 8 rows each -- one tile of 64, two (352 tasks) and three (528, more than two per compute unit).  A gated pass has 20 a slot."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    wl = MoEWorkload(name="at_once", tokens=tokens, hidden=64, inter=1408, n_experts=64, top_k=1, n_slots=local, n_local=local, act_dtype="bf16",
+                     router_dtype="f32", gate="softmax", seed=1590)
+    case = Case(wl)
+    assert _expert_kernels(case, tokens, routed=routed) == kernel
+    g = np.random.Generator(np.random.PCG64(tokens))
+    ids = g.integers(0, local, size=(tokens, 1)).astype(np.int32)
+    if routed:
+        _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+
+
 @pytest.mark.parametrize("act", ["f32", "bf16"])
 @pytest.mark.parametrize("tokens", [1, 16, 17, 64, 65, 256, 257])
 @pytest.mark.parametrize("hidden,inter", [(8, 8), (64, 40), (200, 24), (24, 136), (136, 40), (136, 48), (1024, 8)])
