@@ -17,6 +17,12 @@ SHAPES = {
                              routed_scale=2.5, n_shared=1, shared_range=(2, 22), seed=52),
     "f32": dict(tokens=200, hidden=136, inter=72, n_experts=8, top_k=2, n_slots=8, n_local=8,
                 act_dtype="f32", router_dtype="f32", gate="softmax", seed=53),
+    "f32_gemms": dict(tokens=300, hidden=136, inter=72, n_experts=8, top_k=2, n_slots=8, n_local=8,
+                      act_dtype="f32", router_dtype="f32", gate="softmax", seed=54),
+    "ring_64_rows": dict(tokens=100, hidden=192, inter=128, n_experts=32, top_k=4, n_slots=17, n_local=16,
+                         act_dtype="bf16", router_dtype="bf16", gate="softmax", n_shared=1, shared_range=(2, 90), seed=55),
+    "one_token": dict(tokens=1, hidden=192, inter=512, n_experts=32, top_k=4, n_slots=17, n_local=16,
+                      act_dtype="bf16", router_dtype="bf16", gate="softmax", n_shared=1, shared_range=(0, 1), seed=56),
 }
 
 

@@ -8,6 +8,24 @@ from workloads import MoEWorkload, block_expert_map
 pytestmark = pytest.mark.gpu
 
 
+def _kernels(case, tokens, shared_range=(0, 0), routed=False):
+    """The kernels of a pass over the case's first tokens, names without template arguments."""
+    import torch
+    from gpu_util import kernels_of
+    x, out, k = case.x_dev[:tokens], torch.empty_like(case.x_dev[:tokens]), case.layer.cfg.top_k
+    if routed:
+        ids, w = (torch.zeros((tokens, k), dtype=t, device=x.device) for t in (torch.int32, torch.float32))
+        names = kernels_of(lambda s: case.layer.forward_routed(x, ids, w, out=out, shared_range=shared_range, stream=s))
+    else:
+        names = kernels_of(lambda s: case.layer.forward(x, out=out, shared_range=shared_range, stream=s))
+    return [n.split("<")[0] for n in names]
+
+
+def _expert_kernels(case, tokens, shared_range=(0, 0), routed=False):
+    """The kernel of GEMM-1 in such a pass."""
+    return next(n for n in _kernels(case, tokens, shared_range, routed) if "expert" in n)
+
+
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 192), (192, 128), (320, 256), (512, 320)])
 def test_large_tile_rings_at_every_token_tile_count(hidden, inter):
     """Slots with 1, 2, 3 ... 10 token tiles of 32 rows, full and with one row in the last, on contractions of 1 to 8
@@ -57,9 +75,13 @@ def test_decode_ring_kernels(tokens, hidden, inter):
     separate bookkeeping kernels, bit for bit.  (The ring kernels by themselves: the next test.)"""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     from paper_2510_02613_amd import binding as B
-    wl = MoEWorkload(name="ring", tokens=tokens, hidden=hidden, inter=inter, n_experts=96, top_k=4, n_slots=93, n_local=90,
+    # eleven assignments a token keep the smallest layer above what k_token_experts takes
+    experts, k = (256, 10) if hidden * inter < 8192 else (96, 4)
+    local = experts - 6
+    wl = MoEWorkload(name="ring", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=k, n_slots=local + 3, n_local=local,
                      act_dtype="bf16", router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, min(tokens, 30)), seed=700 + tokens)
-    case = Case(wl, expert_map=block_expert_map(96, 0, 90, np.random.Generator(np.random.PCG64(3)).permutation(92)[:90]))
+    case = Case(wl, expert_map=block_expert_map(experts, 0, local, np.random.Generator(np.random.PCG64(3)).permutation(local + 2)[:local]))
+    assert _expert_kernels(case, tokens, wl.shared_range) in ("k_expert_decode", "k_expert_ring")
     runs = []
     for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
         out = case.run(flags=flags)
@@ -75,7 +97,7 @@ def test_decode_ring_kernels(tokens, hidden, inter):
 def _ring_cases():
     """(tokens, experts, k, hidden, inter) that the dispatch sends to the ring kernels: 160 tasks or more, not 240 .. 330."""
     out = []
-    for hidden, inter, experts, k in [(64, 64, 256, 8), (128, 64, 256, 8), (64, 128, 256, 8), (192, 192, 96, 4), (256, 256, 96, 4),
+    for hidden, inter, experts, k in [(64, 64, 256, 10), (128, 64, 256, 8), (64, 128, 256, 8), (192, 192, 96, 4), (256, 256, 96, 4),
                                       (320, 320, 96, 4), (768, 1024, 96, 4)]:
         for tokens in (17, 32, 47, 64, 90):
             tasks = ((experts - 2) * (1 - (1 - k / experts) ** tokens) + 1) * (inter // 64)
@@ -87,8 +109,7 @@ def _ring_cases():
 @pytest.mark.parametrize("tokens,experts,k,hidden,inter", _ring_cases())
 def test_ring_kernels_at_every_contraction_length(tokens, experts, k, hidden, inter):
     """Contractions of 1, 2, 3, 4, 5 and more K-steps in both GEMMs of the ring kernels (the ring is 4 deep), with and without
-    self-derived tiles.  A bias sends every token to expert 5: more than 16 rows of it in one tile show that the ring kernels
-    ran.  Tables and output as with separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
+    self-derived tiles.  A bias sends every token to expert 5, whose rows are full tiles of 32.  Tables and output as with separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     from paper_2510_02613_amd import binding as B
     from workloads import make_inputs
@@ -99,6 +120,7 @@ def test_ring_kernels_at_every_contraction_length(tokens, experts, k, hidden, in
     inp["logit_bias"][5] = 8.0
     order = np.random.Generator(np.random.PCG64(3)).permutation(experts - 1)[:experts - 2]
     case = Case(wl, expert_map=block_expert_map(experts, 0, experts - 2, order), inputs=inp)
+    assert _expert_kernels(case, tokens, wl.shared_range) == "k_expert_ring"
     runs = []
     for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
         out = case.run(flags=flags)
@@ -174,21 +196,42 @@ def test_small_layers_take_the_128_row_kernels(tokens, tiles):
 
 
 @pytest.mark.parametrize("tokens", [1, 16, 33, 64, 65, 257, 700])
-@pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (136, 72, "bf16"), (264, 136, "f32"), (1024, 1032, "f32"), (4104, 136, "bf16")])
+@pytest.mark.parametrize("hidden,inter,router", [(64, 8, "f32"), (1368, 8, "f32"), (8, 1368, "bf16"), (136, 72, "bf16"), (264, 136, "f32"), (1024, 1032, "f32"),
+                                                 (4104, 136, "bf16")])
 def test_f32_layer_tiles_and_contractions(tokens, hidden, inter, router):
-    """fp32 layers on both sides of the self-derived tiles (64 tokens) and of every tile height (16, 32, 64 rows), with
-    contractions that leave wavefronts of a task without a chunk and long ones (several planes of partial logits), and both
+    """fp32 layers on both sides of the self-derived tiles (64 tokens) and of every tile height (16, 32, 64 rows), outputs narrower than a
+    task's columns (the 64 x 8 layer goes token by token up to 256 tokens), with contractions that leave wavefronts of a task without a chunk and long ones (several planes of partial logits), and both
     router types."""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     wl = MoEWorkload(name="f32_edges", tokens=tokens, hidden=hidden, inter=inter, n_experts=24, top_k=3, n_slots=22, n_local=20,
                      act_dtype="f32", router_dtype=router, gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,
                      n_shared=1, shared_range=(tokens // 3, tokens), seed=400 + tokens)
     case = Case(wl)
+    small = hidden * inter < 1000 and tokens <= 256
+    assert _expert_kernels(case, tokens, wl.shared_range) == ("k_token_experts" if small else "k_expert_f32" if tokens * 3 <= 32 * 24 else "k_expert_f32_tile")
     out = case.run()
     v = case.layer.view(tokens)
     ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
     check_bookkeeping(case, v, tokens, wl.shared_range)
     check_output(case, out, ids)
+
+
+@pytest.mark.parametrize("tokens", [33, 64])
+def test_f32_self_derived_tiles_of_32_rows(tokens):
+    """Up to 64 tokens with 17 to 32 rows a slot: GEMM-1 derives tiles of 32 rows; the same bits as with separate bookkeeping."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="f32_32", tokens=tokens, hidden=136, inter=72, n_experts=8, top_k=5, n_slots=8, n_local=6, act_dtype="f32",
+                     router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, tokens), seed=470)
+    case = Case(wl)
+    assert _expert_kernels(case, tokens, wl.shared_range) == "k_expert_f32"
+    out = case.run()
+    v = case.layer.view(tokens)
+    assert 16 < v["tiles"][:, 2].max() <= 32
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
+    np.testing.assert_array_equal(out, case.run(flags=B.MOE_FLAG_PERMUTE_UNFUSED))
 
 
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 192), (192, 320), (256, 64), (704, 128)])
@@ -243,17 +286,23 @@ def test_ring_tiles_of_64_rows_behind_the_gate(tokens, hidden, inter):
     np.testing.assert_array_equal(out, case.run())
 
 
-def _expert_kernels(case, tokens, shared_range=(0, 0), routed=False):
-    """The kernel of GEMM-1 in a pass over the case's first tokens: its name without template arguments."""
+@pytest.mark.parametrize("hidden,inter,experts,k,local,tokens,kernel", [
+    (2048, 768, 64, 4, 16, 320, "k_expert_ring"), (2048, 768, 64, 4, 16, 321, "k_expert_gemm_mfma8"),            # 20 rows a slot
+    (2048, 768, 128, 8, 84, 145, "k_expert_ring"),                                                               # 793 MB in use
+    (2048, 768, 128, 8, 85, 144, "k_expert_ring"), (2048, 768, 128, 8, 85, 145, "k_expert_gemm_mfma8"),          # 802 MB: 9 rows a slot
+    (1984, 768, 128, 8, 32, 100, "k_expert_ring"), (1984, 768, 128, 8, 33, 100, "k_expert_gemm_mfma"),           # shorter rows: 293 and 302 MB
+    (2048, 768, 128, 8, 33, 100, "k_expert_ring"),
+    (4096, 128, 128, 8, 33, 100, "k_expert_ring"), (4160, 128, 128, 8, 33, 100, "k_expert_gemm_mfma")])
+def test_ring_tiles_of_64_rows_at_the_limits(hidden, inter, experts, k, local, tokens, kernel):
+    """Both sides of every limit of the rule that sends a pass to them.  (Nothing runs: the weights are whatever the memory holds.)"""
+    import types
     import torch
-    from gpu_util import kernels_of
-    x, out, k = case.x_dev[:tokens], torch.empty_like(case.x_dev[:tokens]), case.wl.top_k
-    if routed:
-        ids, w = (torch.zeros((tokens, k), dtype=t, device=x.device) for t in (torch.int32, torch.float32))
-        names = kernels_of(lambda s: case.layer.forward_routed(x, ids, w, out=out, shared_range=shared_range, stream=s))
-    else:
-        names = kernels_of(lambda s: case.layer.forward(x, out=out, shared_range=shared_range, stream=s))
-    return next(n.split("<")[0] for n in names if "expert" in n)
+    from paper_2510_02613_amd.layer import MoELayer
+    layer = MoELayer(hidden=hidden, inter=inter, n_experts=experts, top_k=k, n_slots=local, max_tokens=tokens, act_dtype="bf16", router_dtype="f32",
+                     gate="softmax", router_w=np.zeros((experts, hidden), np.float32))
+    layer.set_expert_map(list(range(local)) + [-1] * (experts - local))
+    x = torch.empty(tokens, hidden, dtype=torch.int16, device="cuda:0")
+    assert _expert_kernels(types.SimpleNamespace(layer=layer, x_dev=x), tokens) == kernel
 
 
 @pytest.mark.parametrize("tokens,shared,kernel", [(320, 320, "k_expert_ring"), (321, 321, "k_expert_gemm_mfma8"), (1280, 320, "k_expert_ring"),
@@ -304,6 +353,8 @@ def test_small_layers_token_by_token(act, tokens, hidden, inter):
                      act_dtype=act, router_dtype="f32", gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5,
                      n_shared=1, shared_range=(tokens // 3, tokens // 3 + min(30, tokens - tokens // 3)), seed=1600 + tokens)
     case = Case(wl)
+    small = tokens <= 256 and 3 * 4 * hidden * inter * (4 if act == "f32" else 2) <= 256 * 1024
+    assert (_expert_kernels(case, tokens, wl.shared_range) == "k_token_experts") == small
     runs = []
     for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
         out = case.run(flags=flags)
@@ -327,6 +378,7 @@ def test_second_gemm_and_combine_of_a_token_or_two(tokens, hidden, inter):
     wl = MoEWorkload(name="two", tokens=tokens, hidden=hidden, inter=inter, n_experts=40, top_k=13, n_slots=40, n_local=36,
                      act_dtype="bf16", router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, 1), seed=1700 + hidden)
     case = Case(wl)
+    assert ("k_gemm2_combine" in _kernels(case, tokens, wl.shared_range)) == (tokens == 1 or (tokens == 2 and hidden <= 4096))
     runs = []
     for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
         out = case.run(flags=flags)
@@ -485,6 +537,34 @@ def test_f32_grid_past_the_launch_limit():
     gate, up = ((layer.w13[e[:, None], c[None, :]].double() * x.double()[:, None, :]).sum(2) for c in (cols, cols + I))
     want = torch.nn.functional.silu(gate) * up
     assert float((out.double() - want).norm() / want.norm()) < 1e-6      # eight products and a hardware exp, each 2^-23
+
+
+def test_f32_tiles_of_64_rows_past_one_row_of_the_grid():
+    """33 rows a slot on 490 experts of 278528 columns: 8.5 million tasks of k_expert_f32_tile, more than the 2^23 of one row of the
+    grid; every XCD's run of tasks ends in the second.  W2 as in the test above."""
+    import torch
+    from gpu_util import kernels_of
+    from paper_2510_02613_amd.layer import MoELayer
+    T, E, H, I = 16384, 490, 8, 278528
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(4)
+    layer = MoELayer(hidden=H, inter=I, n_experts=E, top_k=1, n_slots=E, max_tokens=T, act_dtype="f32", router_dtype="f32",
+                     gate="softmax", router_w=np.zeros((E, H), np.float32), device=dev)
+    layer.w13.normal_(0.0, 0.5, generator=gen)
+    layer.w2.zero_()
+    cols = torch.linspace(0, I - 1, H, device=dev).round().long()
+    layer.w2[:, torch.arange(H, device=dev), cols] = 1.0
+    layer.set_expert_map(list(range(E)))
+    x = torch.randn(T, H, generator=gen, device=dev)
+    ids = torch.randperm(T, generator=gen, device=dev).to(torch.int32)[:, None] % E
+    w = torch.ones(T, 1, device=dev)
+    out = torch.empty_like(x)
+    assert "k_expert_f32_tile<true, true>" in kernels_of(lambda s: layer.forward_routed(x, ids, w, out=out, stream=s))
+    layer.forward_routed(x, ids, w, out=out)
+    e = ids[:, 0].long()
+    gate, up = ((layer.w13[e[:, None], c[None, :]].double() * x.double()[:, None, :]).sum(2) for c in (cols, cols + I))
+    want = torch.nn.functional.silu(gate) * up
+    assert float((out.double() - want).norm() / want.norm()) < 1e-6      # as above
 
 
 @pytest.mark.parametrize("tokens,k,slots", [(128, 8, 16), (129, 8, 16), (1000, 4, 1500), (8192, 8, 40), (8193, 8, 40)])

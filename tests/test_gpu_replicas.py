@@ -55,6 +55,9 @@ def _slot_of(replicas, ids, T):
 CASES = [
     # name, act, T, H, I, E, k, S, shared, remote, max copies, gate
     ("generic_f32", "f32", 150, 64, 40, 8, 2, 16, 1, 1, 3, "softmax"),
+    ("f32_gemms", "f32", 300, 64, 40, 8, 2, 16, 1, 1, 3, "softmax"),
+    ("ring_64_rows", "bf16", 150, 192, 128, 32, 4, 60, 1, 4, 3, "sigmoid_group"),
+    ("one_token", "bf16", 1, 192, 512, 32, 4, 60, 1, 4, 3, "softmax"),
     ("one_block_bf16", "bf16", 33, 128, 64, 16, 4, 30, 0, 3, 4, "softmax"),
     ("mfma_bf16", "bf16", 700, 256, 136, 24, 4, 40, 2, 4, 3, "sigmoid_group"),
     ("large_tiles_bf16", "bf16", 2600, 256, 128, 16, 6, 30, 1, 2, 5, "softmax"),

@@ -21,6 +21,8 @@ SHAPES = {
                 act_dtype="bf16", router_dtype="f32", gate="softmax", seed=63),
     "f32": dict(tokens=200, hidden=136, inter=72, n_experts=8, top_k=2, n_slots=8, n_local=8,
                 act_dtype="f32", router_dtype="f32", gate="softmax", seed=64),
+    "f32_gemms": dict(tokens=300, hidden=136, inter=72, n_experts=8, top_k=2, n_slots=8, n_local=8,
+                      act_dtype="f32", router_dtype="f32", gate="softmax", seed=66),
 }
 
 
