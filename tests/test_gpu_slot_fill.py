@@ -194,9 +194,38 @@ def test_a_fill_waits_for_what_the_serving_stream_still_has(serve_default):
             stage[i][1].copy_(b)
             case.layer.load_expert_async(e, stage[i][0], stage[i][1], copy, serve)
             if i == 1:
-                torch.cuda.synchronize()                     # the next fills ask an idle stream, then a busy one
+                torch.cuda.synchronize()                     # everything done once in between; the next sources are behind it again
             if i == 2:
                 case.layer.forward(case.x_dev)
+        case.place(np.array([0, 1, 2, 3, 4, 5, 6, 7], np.int32), upload=False)
+        got13, got2 = case.layer.w13.clone(), case.layer.w2.clone()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(tensor_to_host(got13), case.w13_pool)
+    np.testing.assert_array_equal(tensor_to_host(got2), case.w2_pool)
+
+
+@pytest.mark.parametrize("serve_default", [True, False])
+def test_fills_behind_work_that_the_serving_stream_has_done(serve_default):
+    """Sources written by the serving stream, which is idle again when the fills are issued: all but the first find it so and go without
+    an event.  They copy what was written, round after round into the same source buffers."""
+    import torch
+    from gpu_util import Case, tensor_to_host
+    wl = MoEWorkload(name="fill_idle", tokens=64, **dict(MID, hidden=1024, inter=1024, n_experts=8, n_slots=8, n_local=8))
+    case = Case(wl, expert_map=np.array([0, 1, -1, -1, -1, -1, -1, -1], np.int32))
+    src = {e: (case.layer.upload(case.inp["w13_experts"][e]), case.layer.upload(case.inp["w2_experts"][e])) for e in range(2, 8)}
+    serve = torch.cuda.current_stream() if serve_default else torch.cuda.Stream()
+    copy = torch.cuda.Stream()
+    stage = [(torch.zeros_like(src[2][0]), torch.zeros_like(src[2][1])) for _ in range(3)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(serve):
+        for first in (2, 5):
+            for i, (s13, s2) in enumerate(stage):
+                s13.copy_(src[first + i][0])
+                s2.copy_(src[first + i][1])
+            serve.synchronize()
+            for i, (s13, s2) in enumerate(stage):            # nothing else on the serving stream from here on
+                case.layer.load_expert_async(first + i, s13, s2, copy, serve)
+            copy.synchronize()
         case.place(np.array([0, 1, 2, 3, 4, 5, 6, 7], np.int32), upload=False)
         got13, got2 = case.layer.w13.clone(), case.layer.w2.clone()
     torch.cuda.synchronize()
