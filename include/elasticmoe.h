@@ -209,9 +209,10 @@ moe_status_t moe_set_expert_replicas(moe_layer_t *layer, const int32_t *host_rep
  *   copy_blocks the throttle on how much HBM bandwidth the fill may take from the
  *               forwards: workgroups of the copy kernel, 256 threads each, about 9 GB/s
  *               read and written per workgroup; 0 = no throttle (9.4 MB in 6.5 us)
- * Ordering, all by events, no host synchronisation and no allocation: the copy starts
+ * Ordering, without host synchronisation and without allocation: the copy starts
  * after the work ALREADY enqueued on serve_stream (a forward that still reads the slot
- * under an older map); the next moe_set_expert_map makes its stream wait for every
+ * under an older map, or what writes the sources) -- by an event, unless the host finds
+ * that work already done when it asks the stream; the next moe_set_expert_map makes its stream wait for every
  * fill issued since the previous switch, so forwards after that switch see the
  * weights.  The weight pools given at moe_layer_create must be writable.  Forwards
  * that run on other streams than serve_stream are the caller's to order.
@@ -275,7 +276,10 @@ moe_status_t moe_forward_routed(moe_layer_t *layer, const void *x, int32_t T,
  * All calls on one GPU share that GPU's array, which keeps the previous call's contents (a pass
  * writes everything it reads, so nothing needs clearing): calls that overlap on one GPU -- on
  * different streams, or from different host threads -- race; calls on one stream are ordered.
- * The result is bit-identical to moe_forward on a layer of the same configuration and placement.
+ * The result is that of moe_forward on a layer of the same configuration and placement, bit for
+ * bit where both run the same kernels.  A layer's workspace, sized for its max_tokens, may have room
+ * for the large-tile kernels' work lists and partial sums where the array has not: such passes (a
+ * hundred tokens and more) add their fp32 sums in another order.
  */
 #define MOE_STATIC_SCRATCH_BYTES (32u << 20)
 moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *buf,
@@ -294,6 +298,9 @@ moe_status_t moe_workspace_view(const moe_layer_t *layer, moe_workspace_view_t *
  * most passes) records HIP events around its phases; the last 64 recorded forwards are
  * kept.  moe_profile_read waits for the recorded forward `back` recordings ago
  * (0 = most recent) and writes the milliseconds of each phase to ms[MOE_N_PHASES].
+ * Launches that do several phases' work count as the first of them: GEMM1 is all of the
+ * experts and the combine where a small layer goes token by token, GEMM2 has the combine
+ * in passes of a token or two; the phases behind then read the events' own cost.
  * Enabling creates the events (host objects), disabling or destroying the layer
  * destroys them.  moe_profile_select(phase) restricts the recording to the two events
  * around ONE phase (moe_profile_read then writes 0 for the others), -1 (the default)

@@ -135,8 +135,9 @@ __global__ void k_write_map(int32_t *dst, MapChunk c, int n)
 // Without a throttle: what a workgroup moves is bytes in flight over memory latency, so a thread holds kCopyUnroll
 // 16-byte pieces and has the next round's requested before it stores them (48 KB per workgroup on their way; a compute
 // unit takes about 64).  Read once, written once: neither side is kept in L2.  A 9.4 MB expert with 32 workgroups: two
-// launches, one piece per thread and round, 47 us -> 12 us; with 128 of them 6.5 us (1.5 TB/s read and as much written; 196
-// workgroups, one round, are no faster).  A forward of 138 us beside fills takes 146 us with 32, 145 with 128: more
+// launches, one piece per thread and round, 47 us -> 12 us; with 128 of them 6.5 us (1.5 TB/s read and as much written).
+// 128 are one round of that expert's W13; 256 workgroups, us from fill to fill (8.5 of them the host's): 4.7 MB 8.5 -> 8.5, 9.4 MB 9.3 -> 9.2,
+// 17.3 MB 12.0 -> 10.6, 37.7 MB 20.1 -> 17.2, 88 MB 41.4 -> 35.3 (32 of them 105), for all of the chip instead of half.  A forward of 138 us beside fills takes 146 us with 32, 145 with 128: more
 // compute units, for half as long.  Scaling the Qwen3-shaped rank up (32 fills, switch, two forwards) 1015 -> 950 us.
 constexpr int kCopyThreads = 1024, kCopyUnroll = 3, kCopyBlocks = 128;
 

@@ -166,9 +166,6 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
 // at 2500 tokens; the tile's ragged rows and columns cost 20 % more MFMAs than the flops of the layer.
 constexpr int kTileRows = 64, kTileK = 32;
 
-// 16-byte slot of a 128-byte row in LDS: conflict-free operand reads
-__device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row ^ (row >> 3)) & 1) << 2); }
-
 template <bool kFirst, bool kRows>
 __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
 {
@@ -227,7 +224,7 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
 #pragma unroll
         for (int a = 0; a < 2; ++a) { sum[a] += acc[a]; acc[a] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
     };
-    auto multiply = [&](int b, int chunk0) {
+    auto multiply = [&](int b) {
         constexpr int J = kTileK / kKC;
         f32x4 xv[J], wv[J][2];
         const int r = wave * 16 + n;
@@ -252,7 +249,7 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
     load(kTileK);
     __syncthreads();
     for (int kt = 0; kt < KT; ++kt) {
-        if (live) multiply(kt & 1, kt * (kTileK / kKC));
+        if (live) multiply(kt & 1);
         store((kt + 1) & 1);
         load((kt + 2) * kTileK);
         __syncthreads();

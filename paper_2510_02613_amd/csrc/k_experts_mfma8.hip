@@ -85,12 +85,6 @@ struct WaveCtx {
     int xlive;                            // token-loader wavefronts: how many of their pieces hold rows that exist
 };
 
-// 16-byte slot swizzle of a 128-byte tile row: slot = chunk ^ swz8(row).  An LDS read of 16 bytes
-// per lane is served 16 lanes at a time over 64 four-byte banks (256 bytes, i.e. 2 rows): the
-// 16 consecutive rows a half-wavefront reads for one MFMA operand must therefore hit 16 distinct
-// 16-byte bank groups.  Row bits (1, 2, 0^3) do that.
-__device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row ^ (row >> 3)) & 1) << 2); }
-
 // LDS byte address of a __shared__ object (LDS pointers are 32-bit offsets in address space 3).
 __device__ __forceinline__ uint32_t lds_addr(const void *p)
 {

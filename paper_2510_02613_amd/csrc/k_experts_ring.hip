@@ -36,9 +36,6 @@ template <int TT> struct Ring {
     static_assert(kDepth == 3 || kDepth == 4, "the waits of the K loop");
 };
 
-// 16-byte slot of a 128-byte row in LDS: conflict-free operand reads (the large-tile kernels' swizzle)
-__device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row ^ (row >> 3)) & 1) << 2); }
-
 __device__ __forceinline__ uint32_t lds_addr(const void *p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;

@@ -661,23 +661,29 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.fused_hist = !routed_ids && T <= kFusedMaxTokens && T <= p.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED);
     const bool identity = flags & MOE_FLAG_IDENTITY_EXPERTS;
     const bool mfma = p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    // bf16 passes.  Small weight-streaming tasks of one token tile when a slot expects only a handful of rows (tiny; routed:
-    // T*k/E on average) and of up to 64 rows for a dozen or two (ring64); the large-tile kernels above that.
-    // Where ring64 ends (`few`; whole pass, us, large tiles or 128 x 128 -> ring64): the finer tasks and the shorter bookkeeping
-    // win, the more so the fewer slots there are to fill the chip (Qwen3 shape with 2 local experts, 50 tokens 55 -> 30; 8, 300
-    // tokens 61 -> 49; 32, 120 tokens 97 -> 75; 64, 200 tokens 134 -> 125; 128, 100 tokens 219 -> 214; 24 experts of 1024 x 768, 250
-    // tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24), until slots with several chunks of 64 rows read their weights several
-    // times: a skewed load on 1.2 GB of slots (Zipf(1.2): 128 experts, 140 tokens 122 -> 119, 165 tokens 122.5 -> 126, 333 tokens
-    // 138 -> 153; an even one gains 2 % up to 190; with 302 or 604 MB of slots 310 tokens 98 -> 68 and 109 -> 86, 500 tokens 84 -> 68
-    // and 109 -> 110) or a shared expert has many rows: up to 320 of them, one tile of the large kernels (DeepSeek-V2-Lite shape, top-1
-    // to top-6, 16 local experts: 220 shared rows 100 -> 93, 320 of 1280 tokens 122 -> 103, 340 90 -> 98, 640 114.5 -> 117, 1280 125 -> 154; 64 local
-    // experts: 150 199 -> 193, 220 209 -> 214, 340 222 -> 219, 640 234 -> 243, 1280 247 -> 293).  Under an even load 210, 300 and 500 tokens
-    // of 32 Qwen3 experts are 74.7 -> 75.2, 76.4 -> 78.0 and 82 -> 85, 240 and 310 of 64 of them 128 -> 123 and 129 -> 130.  Rows of 7168 lose at every size (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 ->
-    // 529).  Nothing was measured between rows of 2048 and of 7168, nor with more than 300 MB of shorter ones.
+    // bf16 passes: small weight-streaming tasks of one token tile when a slot expects only a handful of rows (tiny; routed: T*k/E on
+    // average) and of up to 64 rows for a dozen or two (ring64), the large-tile kernels above that (wide, big), the 128 x 128 kernels for
+    // small layers, whose time is the bookkeeping, and for contractions that are no whole K-steps.
+    // Where ring64 ends (`few`).  Whole pass, us, large tiles or 128 x 128 -> ring64:
+    //  * finer tasks and shorter bookkeeping win, the more so the fewer slots there are to fill the chip: Qwen3 shape with 2 local experts,
+    //    50 tokens 55 -> 30; 8, 300 tokens 59 -> 46; 32, 140 tokens 96 -> 74; 64, 200 tokens 127 -> 120; 128, 100 tokens 219 -> 214;
+    //    24 experts of 1024 x 768, 250 tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24;
+    //  * what it costs: an even load of 200 or 300 tokens on 32 Qwen3 experts 74.5 -> 75, 75.5 -> 77, of 160 on 24 of them 54 -> 58 (a
+    //    Zipf(1.2) one, 310 tokens on 32, 98 -> 68);
+    //  * rows of 2560, 3072 and 4096 gain as much: 768 wide, 80 to 300 tokens, 8 local experts -27 to -32 %, 16 -17 to -40 %, 32 0 to
+    //    -28 %, 64 -6 to -11 %; 4096 x 1536 -2 to -30 %, an even load on 16 experts +0 to +6 % (Zipf -5 to -17 %).  Rows of 7168 lose at every size
+    //    (DeepSeek-V3-shaped rank 140 tokens 489 -> 499, 512 tokens 512 -> 529).  Nothing was measured between, nor with more than 300 MB of
+    //    rows shorter than 2048;
+    //  * 20 rows a slot, 9 above 800 MB of slots in use: then a skewed load has slots with several chunks of 64 rows, which read their
+    //    weights several times (Zipf(1.2): 128 Qwen3 experts, 140 tokens 122 -> 119, 165 tokens 122.5 -> 126, 333 tokens 138 -> 153; an even
+    //    load gains 2 % up to 190; with 302 or 604 MB of slots 310 tokens 98 -> 68 and 109 -> 86, 500 tokens 84 -> 68 and 109 -> 110);
+    //  * so does a shared expert with many rows: up to 320 of them, one tile of the large kernels (DeepSeek-V2-Lite shape, top-1 to top-6, 16
+    //    local experts: 220 shared rows 100 -> 93, 320 of 1280 tokens 122 -> 103, 340 90 -> 98, 640 114.5 -> 117, 1280 125 -> 154; 64
+    //    local experts: 150 199 -> 193, 220 209 -> 214, 340 222 -> 219, 640 234 -> 243, 1280 247 -> 293);
+    //  * and a routed pass (at_once).
     // Elsewhere the large tiles serve what has 48 assignments of the whole batch per slot of the layer (a rank of many holds
     // a part of them), and less when there are weights to stream: 400 MB in the slots that the placement uses (32 Qwen3 experts in
-    // 128 slots, 420 tokens, 128 x 128 -> large tiles: 94 -> 79, Zipf 83 -> 100).  They lose on small layers, whose time is the
-    // bookkeeping; the 128 x 128 kernels take those, and the contractions that are no whole K-steps.
+    // 128 slots, 420 tokens, 128 x 128 -> large tiles: 94 -> 79, Zipf 83 -> 100).
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
     // A gated pass has T k / E rows for a slot.  Tokens that arrive routed were sent because one of their experts is here: with few of the
@@ -701,14 +707,34 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // GEMM-2 follows (Qwen3 shape: 139 tasks, 27.7 -> 28.6; 175, 35.6 -> 32.5; 207, 35.1 -> 31.8).  A little more than one
     // task per compute unit is the other exception: a few units then stream two tasks while the rest stand idle (246 tasks,
     // 47.0 -> 51.5; 270, 49.5 -> 52.5; 318, 48.8 -> 52.2; 350, 59.8 -> 56.1).  Rows of 7168 hide that (262 tasks, 181.6 ->
-    // 166.2); nothing was measured between rows of 2048 and of 7168.  The register kernel with its 32-row tasks takes those
+    // 166.2); this exception was not measured between rows of 2048 and of 7168.  The register kernel with its 32-row tasks takes those
     // passes, as it takes contractions that are no whole K-steps.
     const double tiles_expected = resident * (1.0 - std::pow(1.0 - (double)p.k / p.E, T)) + (shared_end > shared_begin ? p.n_shared : 0);
     const double ring_tasks = tiles_expected * (p.I / 64);
     const bool second_round = p.H <= 4096 && ring_tasks >= 240. && ring_tasks < 330.;
     const bool ring = ring64 || (tiny && can_big && ring_tasks >= 160. && !second_round);
     const bool f32 = !p.act_bf16 && !(flags & MOE_FLAG_FORCE_GENERIC);
-    const int tile_rows = big ? mfma8_tile_rows() : ring ? ring_tile_rows(ring64) : tiny ? decode_tile_rows() : mfma ? mfma_tile_rows() : f32 ? f32_tile_rows(p) : kGenericTileRows;
+    enum class Kernels { big, ring, decode, mfma, f32, generic };
+    const Kernels kernels = big ? Kernels::big : ring ? Kernels::ring : tiny ? Kernels::decode : mfma ? Kernels::mfma : f32 ? Kernels::f32 : Kernels::generic;
+    int tile_rows = 0;
+    switch (kernels) {
+    case Kernels::big:     tile_rows = mfma8_tile_rows(); break;
+    case Kernels::ring:    tile_rows = ring_tile_rows(ring64); break;
+    case Kernels::decode:  tile_rows = decode_tile_rows(); break;
+    case Kernels::mfma:    tile_rows = mfma_tile_rows(); break;
+    case Kernels::f32:     tile_rows = f32_tile_rows(p); break;
+    case Kernels::generic: tile_rows = kGenericTileRows; break;
+    }
+    auto launch_gemm = [&](int which) {
+        switch (kernels) {
+        case Kernels::big:    return launch_experts_mfma8(p, which, st);
+        case Kernels::ring:   return launch_experts_ring(p, tile_rows, which, st);
+        case Kernels::decode: return launch_experts_decode(p, which, st);
+        case Kernels::mfma:   return launch_experts_mfma(p, which, st);
+        case Kernels::f32:    return launch_experts_f32(p, tile_rows, which, st);
+        default:              return launch_experts_generic(p, which, st);
+        }
+    };
     // Upper bound of the tile count, which sizes the grids: every slot with rows adds at most one partly filled
     // tile.  With a token or two most slots have none, and thousands of workgroups that only find out that their
     // tile does not exist take longer to dispatch than one token's experts take to stream.
@@ -742,20 +768,9 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // shape 38.7 -> 33.3, 62.6 -> 57.2, 4 tokens 77.8 -> 80.5; DeepSeek-V3-shaped rank 41.7 -> 40.2, 78.9 -> 79.5, 4 tokens 89.0 -> 91.0)
     const bool fused2 = !whole && !identity && tiny && T <= (p.H <= 4096 ? 2 : 1);
     mark(MOE_PHASE_GEMM1);
-    if (e == hipSuccess) {
-        if (whole)          e = launch_token_experts(p, tile_rows, st);
-        else if (identity)  e = launch_identity_experts(p, st);
-        else if (big)  e = launch_experts_mfma8(p, 0, st);
-        else if (ring) e = launch_experts_ring(p, tile_rows, 0, st);
-        else if (tiny) e = launch_experts_decode(p, 0, st);
-        else if (mfma) e = launch_experts_mfma(p, 0, st);
-        else if (f32)  e = launch_experts_f32(p, tile_rows, 0, st);
-        else           e = launch_experts_generic(p, 0, st);
-    }
+    if (e == hipSuccess) e = whole ? launch_token_experts(p, tile_rows, st) : identity ? launch_identity_experts(p, st) : launch_gemm(0);
     mark(MOE_PHASE_GEMM2);
-    if (e == hipSuccess && !identity && !whole)
-        e = fused2 ? launch_gemm2_combine(p, st) : big ? launch_experts_mfma8(p, 1, st) : ring ? launch_experts_ring(p, tile_rows, 1, st) : tiny ? launch_experts_decode(p, 1, st) : mfma ? launch_experts_mfma(p, 1, st) :
-            f32 ? launch_experts_f32(p, tile_rows, 1, st) : launch_experts_generic(p, 1, st);
+    if (e == hipSuccess && !identity && !whole) e = fused2 ? launch_gemm2_combine(p, st) : launch_gemm(1);
     mark(MOE_PHASE_COMBINE);
     if (e == hipSuccess && !whole && !fused2) e = launch_combine(p, st);
     mark(MOE_N_PHASES);

@@ -86,7 +86,7 @@ struct Pass {
     void *y;             // [A,H]
     int32_t max_tiles;
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
-    int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 only: its workgroups derive their tile from the selection kernel's per-block counts and
+    int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 and k_token_experts only: their workgroups derive their tile from the selection kernel's per-block counts and
                          // masks themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
@@ -134,7 +134,7 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st);
 int decode_tile_rows();
 // the same for contractions that are whole K-steps (H and I multiples of 64)
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st);
-int ring_tile_rows(bool large);   // large: 64 rows, where a slot expects more than 32
+int ring_tile_rows(bool large);   // large: 64 rows, for a dozen or two a slot
 // fp32 layers, M-tiles of 16, 32 or 64 rows
 hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st);
 int f32_tile_rows(const Pass &p);
@@ -180,6 +180,12 @@ __device__ __forceinline__ int slot_of(const Pass &p, int a)
     if (t >= p.shared_begin && t < p.shared_end) return p.map[p.E + (j - p.k)];
     return -1;
 }
+
+// 16-byte slot swizzle of a 128-byte tile row: slot = chunk ^ swz8(row).  An LDS read of 16 bytes
+// per lane is served 16 lanes at a time over 64 four-byte banks (256 bytes, i.e. 2 rows): the
+// 16 consecutive rows a half-wavefront reads for one MFMA operand must therefore hit 16 distinct
+// 16-byte bank groups.  Row bits (1, 2, 0^3) do that.
+__device__ __forceinline__ int swz8(int row) { return ((row >> 1) & 3) | (((row ^ (row >> 3)) & 1) << 2); }
 
 // fp32 -> bf16, round to nearest even (one v_cvt_pk_bf16_f32 per pair on gfx950)
 __device__ __forceinline__ uint16_t f32_to_bf16(float f)

@@ -1,5 +1,5 @@
 // Tiles derived by the expert GEMM-1 itself, for passes of at most 64 tokens: shared by the weight-streaming bf16
-// kernels (registers and LDS ring) and the fp32 kernel.
+// kernels (registers and LDS ring), the fp32 kernel and the token-by-token one.
 #pragma once
 #include "moe_internal.h"
 
@@ -65,7 +65,7 @@ __device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, i
 }
 
 // Workgroup 0: counts, offsets, tile list (slot order, chunks of tile_rows), permutation and its inverse --
-// the tables of the bookkeeping kernels, for the few-token case.  256 threads; lds: kSelfTableBytes of LDS.
+// the tables of the bookkeeping kernels, for the few-token case.  All threads of the workgroup (256 or 1024); lds: kSelfTableBytes of LDS.
 constexpr int kSelfTableBytes = kSelfMaxSlots * 8;
 __device__ inline void self_tables(const Pass &p, int tile_rows, void *lds)
 {
