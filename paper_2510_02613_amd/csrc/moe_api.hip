@@ -680,27 +680,40 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     //  * so does a shared expert with many rows: up to 320 of them, one tile of the large kernels (DeepSeek-V2-Lite shape, top-1 to top-6, 16
     //    local experts: 220 shared rows 100 -> 93, 320 of 1280 tokens 122 -> 103, 340 90 -> 98, 640 114.5 -> 117, 1280 125 -> 154; 64
     //    local experts: 150 199 -> 193, 220 209 -> 214, 340 222 -> 219, 640 234 -> 243, 1280 247 -> 293);
-    //  * and a routed pass (at_once).
+    //  * and so does a routed pass (at_once, below).
     // Elsewhere the large tiles serve what has 48 assignments of the whole batch per slot of the layer (a rank of many holds
     // a part of them), and less when there are weights to stream: 400 MB in the slots that the placement uses (32 Qwen3 experts in
     // 128 slots, 420 tokens, 128 x 128 -> large tiles: 94 -> 79, Zipf 83 -> 100).
     const bool can_big = mfma && mfma8_supports(p) && l->lay.unit_cap > 0;
     const long long used_bytes = 6ll * l->slots_used * p.H * p.I;
+    const bool large = can_big && ((long long)T * p.kk >= 48ll * p.S || used_bytes >= 400000000ll);   // what the large tiles take unless `few` or `tiny` does
     // A gated pass has T k / E rows for a slot.  Tokens that arrive routed were sent because one of their experts is here: with few of the
-    // experts that is many times as much, and several chunks read a slot's weights again.  That pays while all tasks of GEMM-1 run at the
-    // same time, two per compute unit, and share them in L2 (us, large tiles -> ring64, ids all local: DeepSeek-V2-Lite shape without
-    // shared experts, top-1, 1280 tokens on 2 experts 99 -> 65, 440 tasks; 4 105 -> 77, 440; 8 76.5 -> 98, 528; 16 78 -> 115, 704; 8, 640
-    // tokens 67 -> 63, 352; Qwen3 shape, 320 tokens on 8 experts 92 -> 60, 480; 16 73 -> 83, 576; 32 77 -> 114, 768).
+    // experts that is many times as much, and several chunks read a slot's weights again.  us, the tokens' experts drawn from all of them, one
+    // at least of the local ones:
+    //  * ring64 against the large tiles (at_once): up to 24 rows a slot as in a gated pass (Qwen3 shape, 269 tokens on 12 of 64 experts, top-1
+    //    53 -> 37; 48 of 256 3072 x 768 experts, top-8, 522 tokens 154 -> 136; 16 of 4096 x 1536 112 -> 112 at 16 rows, 113 -> 128 at 38); above, while
+    //    all tasks of GEMM-1 have a place and few large tiles would (an N-slice of 128 columns per slot on less than a third of the chip:
+    //    DeepSeek-V2-Lite shape, 1280 tokens on 2 and 4 of 64 experts, top-1, 99 -> 65 and 105 -> 77; 6 of 256 4096 x 1536 experts, top-6, 705
+    //    tokens 118 -> 95.5; 4, top-1, 1024 tokens 150 -> 101; on 8 of them 512 tokens 100 -> 113, 1024 120 -> 128; 8 of DeepSeek-V2-Lite, 1280 tokens 76.5 ->
+    //    95) or the tasks are fewer still (640 tokens on those 8: 67 -> 63; 372 tokens on 16 Qwen3 experts 52 -> 38).  What that leaves: rows of 1024
+    //    would gain further up (24 experts of 1024 x 512, 2525 tokens, 384 tasks 49 -> 43);
+    //  * where the large tiles do not take the pass ring64 has no such limit (DeepSeek-V2-Lite shape, 923 tokens on 20 experts, 128 x 128 -> ring64
+    //    103 -> 85);
+    //  * ring64 against the kernels of one token tile (several), whose register form has tiles of 16 rows: once more of those tasks
+    //    are expected than run at a time (2 of 256 4096 x 1536 experts, top-1, 256 tokens 109 -> 58.5, 1024 tokens 404 -> 79, the large tiles 136; 512 tokens on
+    //    8 of 128 Qwen3 experts 69 -> 39, on 2 69 -> 37.5; below, 128 tokens on 2 of them, 384 tasks, 30 -> 36).
     const int resident = l->slots_used - p.n_shared < p.E ? l->slots_used - p.n_shared : p.E;
     const double here = routed_ids ? 1.0 - std::pow(1.0 - (double)resident / p.E, p.k) : 1.0;   // share of all tokens that are sent here
-    const double chunks = resident > 0 ? std::ceil((double)T * p.k / p.E / here / ring_tile_rows(true)) : 0.0;
-    const bool at_once = chunks <= 1.0 || chunks * resident * (p.I / 64) <= 512.0;
-    const bool few = at_once && p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) && (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E &&
-                     shared_end - shared_begin <= mfma8_tile_rows();
+    const double rows = resident > 0 ? (double)T * p.k / p.E / here : 0.0;
+    const double tasks = std::ceil((rows + 2.0 * std::sqrt(rows)) / ring_tile_rows(true)) * resident * (p.I / 64);
+    const bool at_once = rows <= 24.0 || tasks <= 360.0 || (tasks <= 560.0 && resident * (p.I / 128) <= 80);
+    const bool few = (at_once || !large) && p.H <= 4096 && (p.H >= 2048 || used_bytes <= 300000000ll) &&
+                     (long long)T * p.k <= (used_bytes <= 800000000ll ? 20ll : 9ll) * p.E && shared_end - shared_begin <= mfma8_tile_rows();
     const bool wide = can_big && !few && (long long)T * p.kk >= 48ll * p.S;
-    const bool tiny = mfma && !wide && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
+    const bool several = few && mfma8_supports(p) && rows > decode_tile_rows() && std::ceil(rows / decode_tile_rows()) * resident * (p.I / 16) > 576.0;
+    const bool tiny = mfma && !wide && !several && (long long)T * p.k <= 4ll * p.E && shared_end - shared_begin <= 2 * decode_tile_rows();
     const bool ring64 = mfma && few && !tiny && mfma8_supports(p);
-    const bool big = wide || (can_big && !few && !tiny && used_bytes >= 400000000ll);
+    const bool big = wide || (large && !few && !tiny);
     // Of the small-task kernels the LDS ring streams faster (whole pass, us, registers -> ring: Qwen3 shape 48 tokens 218 ->
     // 197, DeepSeek-V3-shaped rank 64 tokens 464 -> 416) once there are enough of its 128-row tasks for the chip's 256 compute
     // units, counted over the used slots that an even routing gives rows and for GEMM-1, which is two thirds of the bytes;

@@ -321,22 +321,31 @@ def test_ring_tiles_of_64_rows_up_to_320_shared_rows(tokens, shared, kernel):
     check_output(case, out, ids)
 
 
-@pytest.mark.parametrize("tokens,local,routed,kernel", [(512, 8, True, "k_expert_ring"), (513, 8, True, "k_expert_ring"), (1024, 8, True, "k_expert_ring"),
-                                                        (1025, 8, True, "k_expert_gemm_mfma8"), (1280, 8, False, "k_expert_ring"),
-                                                        (1280, 4, True, "k_expert_ring"), (1280, 64, True, "k_expert_ring")])
-def test_ring_tiles_of_64_rows_while_all_tasks_run_at_once(tokens, local, routed, kernel):
-    """Top-1 of 64 experts, 1408 wide (22 tasks a tile): every token that arrives routed has its expert here, so 8 local ones expect
-    tokens / 8 rows each -- one tile of 64, two (352 tasks) and three (528, more than two per compute unit).  A gated pass has 20 a slot."""
+@pytest.mark.parametrize("tokens,experts,k,local,routed,kernel", [
+    (858, 64, 1, 8, True, "k_expert_ring"), (859, 64, 1, 8, True, "k_expert_gemm_mfma8"),       # 352 tasks of up to 64 rows, 528 on 8 slots
+    (1163, 64, 1, 7, True, "k_expert_ring"), (1164, 64, 1, 7, True, "k_expert_gemm_mfma8"),     # 462 on 7 slots, 616
+    (959, 64, 1, 20, True, "k_expert_ring"), (960, 64, 1, 20, True, "k_expert_gemm_mfma8"),     # not large: 440; large
+    (622, 256, 8, 48, True, "k_expert_ring"), (623, 256, 8, 48, True, "k_expert_gemm_mfma8"),   # 24 rows a slot
+    (96, 64, 1, 3, True, "k_expert_decode"), (97, 64, 1, 3, True, "k_expert_ring"),             # 528 tasks of 16 rows, 792
+    (112, 64, 1, 7, True, "k_expert_decode"), (113, 64, 1, 7, True, "k_expert_ring"),           # 16 rows a slot
+    (256, 64, 1, 2, True, "k_expert_ring"), (1024, 256, 1, 2, True, "k_expert_ring"),
+    (1280, 64, 1, 8, False, "k_expert_ring"), (1280, 64, 1, 4, True, "k_expert_ring"), (1280, 64, 1, 64, True, "k_expert_ring")])
+def test_routed_passes_count_the_rows_that_arrive(tokens, experts, k, local, routed, kernel):
+    """Experts 1408 wide (22 tasks of the ring kernels a tile, 88 of the register ones): tokens that arrive routed have an expert here, so that
+    few local ones expect many rows each, where a gated pass of as many tokens has T k / E.  Both sides of every limit."""
     from gpu_util import Case
     from test_gpu_routed import _check
-    wl = MoEWorkload(name="at_once", tokens=tokens, hidden=64, inter=1408, n_experts=64, top_k=1, n_slots=local, n_local=local, act_dtype="bf16",
+    wl = MoEWorkload(name="arrive", tokens=tokens, hidden=64, inter=1408, n_experts=experts, top_k=k, n_slots=local, n_local=local, act_dtype="bf16",
                      router_dtype="f32", gate="softmax", seed=1590)
     case = Case(wl)
     assert _expert_kernels(case, tokens, routed=routed) == kernel
+    if not routed:
+        return
     g = np.random.Generator(np.random.PCG64(tokens))
-    ids = g.integers(0, local, size=(tokens, 1)).astype(np.int32)
-    if routed:
-        _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    ids = np.concatenate([g.integers(0, local, size=(tokens, 1)), g.integers(0, experts, size=(tokens, k - 1))], 1).astype(np.int32)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    most = case.layer.view(tokens)["tiles"][:, 2].max()
+    assert most <= {"k_expert_ring": 64, "k_expert_decode": 16}.get(kernel, 320) and (tokens < 32 * local or most > 32 or kernel == "k_expert_decode")
 
 
 @pytest.mark.parametrize("act", ["f32", "bf16"])
