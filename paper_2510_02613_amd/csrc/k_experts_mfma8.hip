@@ -419,7 +419,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     // chip costs a whole round.  When the launch allows it (p.k_split), the workgroups of that last
     // round are run separately: each tile's contraction is shared out over n_parts workgroups
     // (phase 1, partial sums to p.partials), which a third launch adds up in K order (phase 2).  The
-    // split is a function of the unit list alone, so all three launches agree on it.
+    // split is a function of the unit list alone, so all three launches agree on it, and of an ordered one only
+    // (the launcher's choice), so that it does not follow from the slots that the experts sit in.
     const int rows_total = hdr.n_rows;                 // rows of 8 workgroups, holes at the ends of the columns included
     const int rows_round = min(p.n_cus, kMaxPartialSets) / kXcds;
     int tail_rows = 0, n_parts = 1;
@@ -583,7 +584,9 @@ hipError_t launch_experts_mfma8(const Pass &p0, int which, hipStream_t st)
     p.n_cus = cus;
     // sharing out the contraction of the last round's tiles pays when a tile is long: 64 weight steps or more
     const int K = which == 0 ? p.H : p.I;
-    p.k_split = p.partials != nullptr && K / kBKW >= 64;
+    // a list in slot order would let the slots decide which tiles fall into the last round, and with that how their rows are summed
+    // (300 tiles in 1800 slots, rows of 4096, split -> not: 64 wide, 300 workgroups, 552 -> 555 us the whole pass; 192 wide 764 -> 757)
+    p.k_split = p.partials != nullptr && K / kBKW >= 64 && tile_list_sorted(p);
     if (!p.units[0] || !p.unit_hdr) return hipErrorInvalidValue;   // the bookkeeping kernel must have been asked for unit lists
     const int nt = p.n_slices[which];
     const int grid = mfma8_grid_rows(p.max_tiles, nt) * kXcds;

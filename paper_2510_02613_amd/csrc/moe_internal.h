@@ -134,7 +134,7 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st);
 int decode_tile_rows();
 // the same for contractions that are whole K-steps (H and I multiples of 64)
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st);
-int ring_tile_rows(bool large);   // large: 64 rows, for a dozen or two a slot
+int ring_tile_rows(bool large);   // large: 64 rows, for a dozen or two a slot and for more on few slots
 // fp32 layers, M-tiles of 16, 32 or 64 rows
 hipError_t launch_experts_f32(const Pass &p, int tile_rows, int which, hipStream_t st);
 int f32_tile_rows(const Pass &p);

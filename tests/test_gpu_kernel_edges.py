@@ -632,3 +632,33 @@ def test_large_tiles_on_long_rows_do_not_follow_the_slots(hidden, inter, slots):
         assert sorted(tiles[tiles[:, 3] == 1][:, 2]) == sorted(c for c in counts if 0 < c <= 320)   # the large-tile kernels ran
     assert outs[0].view(torch.bfloat16).float().abs().max() > 0
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+def test_split_last_round_does_not_follow_the_slots_of_a_long_list():
+    """A contraction of 4096 on 300 tiles, a full round and 44 of another, under a list that can get too long to be ordered and stays in slot
+    order: which tiles are the last ones follows from the slots, so none is shared out over K -- the same bits whichever slots the experts sit in."""
+    import torch
+    from paper_2510_02613_amd.layer import MoELayer
+    E, k, slots, hidden, inter = 300, 8, 1800, 4096, 64
+    tokens = 48 * slots // k
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev).manual_seed(21)
+    g = np.random.Generator(np.random.PCG64(21))
+    layer = MoELayer(hidden=hidden, inter=inter, n_experts=E, top_k=k, n_slots=slots, max_tokens=tokens, act_dtype="bf16", router_dtype="f32",
+                     gate="softmax", router_w=np.zeros((E, hidden), np.float32), device=dev)
+    counts = g.integers(129, 321, size=E)
+    ids = np.full(tokens * k, -1, np.int32)
+    ids[g.permutation(tokens * k)[:counts.sum()]] = g.permutation(np.repeat(np.arange(E), counts))
+    ids = torch.from_numpy(ids.reshape(tokens, k)).to(dev)
+    wts = torch.rand(tokens, k, generator=gen, device=dev) + 0.5
+    x = torch.randn(tokens, hidden, generator=gen, device=dev).bfloat16().view(torch.int16)
+    w13 = (torch.randn(E, 2 * inter, hidden, generator=gen, device=dev) * 0.05).bfloat16().view(torch.int16)
+    w2 = (torch.randn(E, hidden, inter, generator=gen, device=dev) * 0.05).bfloat16().view(torch.int16)
+    outs = []
+    for order in (np.arange(E), slots - 1 - np.arange(E)):
+        at = torch.from_numpy(order.copy()).to(dev)
+        layer.w13[at], layer.w2[at] = w13, w2
+        layer.set_expert_map(order.tolist())
+        outs.append(layer.forward_routed(x, ids, wts))
+        assert len(layer.view(tokens)["tiles"]) == E                                     # the large-tile kernels ran
+    assert torch.equal(outs[0], outs[1])
