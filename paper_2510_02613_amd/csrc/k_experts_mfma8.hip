@@ -25,8 +25,16 @@
 //
 // Workgroup: 8 wavefronts as 2 (token) x 4 (weight).  Wavefront (wm, wn) owns weight
 // rows [wn*64, wn*64+64) and token tiles wm, wm+2, ... (interleaved so that a ragged
-// tile count splits evenly): up to 2 x 5 accumulators of 32x32 = 160 registers, two
+// tile count splits evenly): up to 4 x 10 accumulators of 16x16 = 160 registers, two
 // wavefronts per SIMD so that one's LDS waits hide under the other's MFMAs.
+//
+// v_mfma_f32_16x16x32_bf16, not 32x32x16.  With hundreds of token rows a slot this chip runs at its power limit
+// (1400 W; the whole pass of the Qwen3 shape draws 1370 and more), so that a kernel's time follows from the energy it spends.
+// Per product the 16x16x32 form reads and writes half as many accumulators: a register-only stream of it on
+// the layer's operands sustains 2.14 PFLOP/s at 1326 W, one of the 32x32x16 form 1.88 at 1300 W.  LDS operand
+// reads per product are the same.  Whole pass of routed tokens, the same rows in every slot, us, 32x32x16 -> 16x16x32: Qwen3
+// shape 64 rows 235 -> 235, 128 269.5 -> 265, 192 326 -> 304, 256 358 -> 342.5, 288 383 -> 367; DeepSeek-V2-Lite shape 162
+// rows 276 -> 265; DeepSeek-V3-shaped, 32 experts, 256 rows 735 -> 680, 288 rows 800 -> 752.  The sums come out the same to the bit.
 //
 // Staging: global_load_lds_dwordx4 -- global memory straight into LDS, 16 bytes per
 // lane, no VGPR round trip, no ds_write.  One instruction fills 1 KB: 8 rows of
@@ -34,9 +42,9 @@
 // piece, so it FETCHES the chunk that belongs there: the XOR swizzle that keeps the
 // 16-byte operand reads conflict free is applied on the global side.
 //
-// GEMM-1 packs every 32-row MFMA weight tile as 16 gate rows followed by the 16
-// matching up rows; in the 32x32 accumulator layout a lane then holds gate value r
-// and up value r+8 of the same (token, column), so silu(g)*u needs no shuffles.
+// GEMM-1 stages 16 gate rows and then the 16 matching up rows, and so on: a lane holds
+// the gate value and the up value of the same (token, column) in the same element of two
+// neighbouring accumulators, so silu(g)*u needs no shuffles.
 //
 // Epilogue: every wavefront transposes its accumulators through a private LDS
 // region (row stride = row bytes + 16: rows stay 16-byte aligned for the copy out, the
@@ -51,7 +59,7 @@ namespace emoe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 64;                    // K-step: 128 bytes per tile row, one whole cache line, for both operands
 constexpr int kThreads = 512;
@@ -68,9 +76,9 @@ constexpr int kLdsBytes = 160 * 1024;      // all of a compute unit's LDS: the r
 constexpr int kXcds = 8;
 constexpr int kMaxPartialSets = 256;        // partial-sum sets the workspace has room for: one round of a 256-unit chip
 constexpr int kTC = kMaxTT / 2;            // token tiles per wavefront
-constexpr int kWT = 2;                     // weight tiles per wavefront
-constexpr int kEpiStride1 = 2 * kWT * 16 + 16;  // GEMM-1: 32 h columns per wavefront, bytes per staged row (rows stay 16-byte aligned)
-constexpr int kEpiStride2 = 2 * kWT * 32 + 16;  // GEMM-2: 64 y columns per wavefront
+constexpr int kWT = 4;                     // 16-row weight tiles per wavefront
+constexpr int kEpiStride1 = 2 * kWT * 8 + 16;  // GEMM-1: 32 h columns per wavefront, bytes per staged row (rows stay 16-byte aligned)
+constexpr int kEpiStride2 = 2 * kWT * 16 + 16;  // GEMM-2: 64 y columns per wavefront
 constexpr int kEpiBytes = 32 * kEpiStride2;     // one token tile of one wavefront
 static_assert(kWaves * kEpiBytes <= kLdsBytes, "epilogue staging reuses the ring");
 static_assert(kMaxTT == 10, "the dispatch on token tiles below lists 1..10");
@@ -79,7 +87,7 @@ static_assert(kMaxTT == 10, "the dispatch on token tiles below lists 1..10");
 struct WaveCtx {
     const uint16_t *wbase, *abase;        // slot's weight matrix, activation matrix
     uint32_t off[kXPieces > kWPieces ? kXPieces : kWPieces];               // this lane's byte offset (from the matrix base) of each piece it stages, k = 0
-    uint32_t woff[kBKW / 16], xoff[kBK / 16]; // LDS byte offsets (inside a stage) of this lane's operand rows per sub-step
+    uint32_t woff[kBKW / 32], xoff[kBK / 32]; // LDS byte offsets (inside a stage) of this lane's operand rows per sub-step
     int wave, lane, wm, wn, n_tt;
     bool stream_w;                        // this tile's weight rows are read by no other tile: copy them non-temporally
     int xlive;                            // token-loader wavefronts: how many of their pieces hold rows that exist
@@ -152,26 +160,27 @@ __device__ __forceinline__ void wait_loads()
     __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// One K-step (64 k) of this wavefront: NTC token tiles x 2 weight tiles x 4 sub-steps of 16 k.  The
+// One K-step (64 k) of this wavefront: 2 NTC token tiles of 16 rows x 4 weight tiles x 2 sub-steps of 32 k.  The
 // (sub-step, token tile) pairs run as one software pipeline: the token operand of pair s+2 and the
-// weight operands of the next sub-step are requested from LDS before the MFMAs of pair s.  `mid` is
-// called once, half way through.
+// weight operands of the next sub-step are requested from LDS before the MFMAs of pair s.  Every other token tile takes
+// its weight tiles backwards, so that an MFMA always has one operand of the one before it (0.6 to 1 % of the whole pass).
+// `mid` is called once, half way through.
 template <int NTC, typename Mid>
-__device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x16 (&acc)[kWT][kTC], Mid mid)
+__device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x4 (&acc)[kWT][2 * kTC], Mid mid)
 {
     if constexpr (NTC > 0) {
-        constexpr int KS = kBK / 16, STEPS = KS * NTC, D = 2;
+        constexpr int KS = kBK / 32, NT = 2 * NTC, STEPS = KS * NT, D = 2;
         bf16x8 wf[2][kWT], xf[D + 1];
         auto fetch_w = [&](int ks) {
 #pragma unroll
             for (int a = 0; a < kWT; ++a) {
-                const uint4 v = *(const uint4 *)(Ws + c.woff[ks] + a * 32 * 128);
+                const uint4 v = *(const uint4 *)(Ws + c.woff[ks] + a * 16 * 128);
                 wf[ks & 1][a] = *(const bf16x8 *)&v;
             }
         };
         auto fetch_x = [&](int step) {
-            const int ks = step / NTC, t = step % NTC;
-            const uint4 v = *(const uint4 *)(Xs + c.xoff[ks] + t * 64 * 128);
+            const int ks = step / NT, t = step % NT;
+            const uint4 v = *(const uint4 *)(Xs + c.xoff[ks] + (t >> 1) * 64 * 128 + (t & 1) * 16 * 128);
             xf[step % (D + 1)] = *(const bf16x8 *)&v;
         };
         fetch_w(0);
@@ -179,13 +188,15 @@ __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws,
         for (int s0 = 0; s0 < D && s0 < STEPS; ++s0) fetch_x(s0);
 #pragma unroll
         for (int step = 0; step < STEPS; ++step) {
-            const int ks = step / NTC, t = step % NTC;
+            const int ks = step / NT, t = step % NT;
             if (step == STEPS / 2) mid();
             if (t == 0 && ks + 1 < KS) fetch_w(ks + 1);
             if (step + D < STEPS) fetch_x(step + D);
 #pragma unroll
-            for (int a = 0; a < kWT; ++a)
-                acc[a][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[ks & 1][a], xf[step % (D + 1)], acc[a][t], 0, 0, 0);
+            for (int i = 0; i < kWT; ++i) {
+                const int a = t & 1 ? kWT - 1 - i : i;
+                acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ks & 1][a], xf[step % (D + 1)], acc[a][t], 0, 0, 0);
+            }
             __builtin_amdgcn_sched_barrier(0);  // keep the written order: the prefetch depth is the register budget
         }
     } else {
@@ -242,7 +253,7 @@ __device__ __forceinline__ int step_at(int i, int first, int KT) { return i + fi
 
 // KT K-steps of 64 of this wavefront.  The caller issued the first depth - 1 steps of the ring this wavefront loads.
 template <int NTC, typename R>
-__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x16 (&acc)[kWT][kTC])
+__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x4 (&acc)[kWT][2 * kTC])
 {
     const bool wloader = c.wave < 4;
     const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
@@ -265,45 +276,41 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
 
 // Partial sums of a tile whose contraction is shared out over several workgroups (the tail of a
 // launch, see the kernel): floats per set, and where a wavefront's accumulator registers go.
-constexpr int kPartialFloats = kWaves * kWT * kTC * 16 * 64;   // 81920 = 320 KB
-__device__ __forceinline__ float *partial_at(float *set, int wave, int a, int t, int r4, int lane)
+constexpr int kPartialFloats = kWaves * kWT * 2 * kTC * 4 * 64;   // 81920 = 320 KB
+__device__ __forceinline__ float *partial_at(float *set, int wave, int a, int t, int lane)
 {
-    return set + ((((wave * kWT + a) * kTC + t) * 4 + r4) * 64 + lane) * 4;   // 16 bytes per lane, 1 KB per instruction
+    return set + (((wave * kWT + a) * 2 * kTC + t) * 64 + lane) * 4;   // 16 bytes per lane, 1 KB per instruction
 }
 
-// Epilogue of one token tile of a wavefront: accumulators (token tile t of the wavefront, its kWT weight
+// Epilogue of one 32-row token tile of a wavefront: accumulators (both halves of token tile t of the wavefront, its kWT weight
 // tiles) -> the wavefront's private LDS region [token row][column] -> coalesced rows of h (with SwiGLU) or y.
 template <bool kFirst>
 __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, char *ring, int t,
-                                                const f32x16 (&v)[kWT])
+                                                const f32x4 (&v)[2][kWT])
 {
-    constexpr int COLS = kFirst ? kWT * 16 : kWT * 32;      // output columns of this wavefront
+    constexpr int COLS = kFirst ? kWT * 8 : kWT * 16;      // output columns of this wavefront
     constexpr int STRIDE = kFirst ? kEpiStride1 : kEpiStride2;
     char *mine = ring + c.wave * kEpiBytes;
-    const int l31 = c.lane & 31, khalf = c.lane >> 5;
+    const int l15 = c.lane & 15, quad = c.lane >> 4;
     constexpr int LPR = COLS / 8;                           // copy out: 16 bytes per lane, LPR lanes per row,
     constexpr int RPI = 64 / LPR;                           // 64/LPR rows per instruction
     static_assert(STRIDE % 16 == 0 && kEpiBytes % 16 == 0 && 32 % RPI == 0, "16-byte reads of the staged rows");
     uint16_t *O = (uint16_t *)(kFirst ? p.h : p.y);
     const int ncol0 = n0 + c.wn * COLS;
     const int lr = c.lane / LPR, lc = (c.lane % LPR) * 8;
-    char *row = mine + l31 * STRIDE;
 #pragma unroll
-    for (int a = 0; a < kWT; ++a) {
-        constexpr int Q = kFirst ? 2 : 4;
+    for (int half = 0; half < 2; ++half) {
+        char *row = mine + (half * 16 + l15) * STRIDE;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
+        for (int a = 0; a < kWT; a += kFirst ? 2 : 1) {
             uint16_t o[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                float g = v[a][q * 4 + e];
-                if (kFirst) {
-                    const float u = v[a][(q + 2) * 4 + e];
-                    g = silu_mul(g, u);
-                }
+                float g = v[half][a][e];
+                if (kFirst) g = silu_mul(g, v[half][a + (kFirst ? 1 : 0)][e]);
                 o[e] = f32_to_bf16(g);
             }
-            const int col = a * (kFirst ? 16 : 32) + q * 8 + khalf * 4;
+            const int col = (kFirst ? a / 2 : a) * 16 + quad * 4;
             *(uint2 *)(row + col * 2) = make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
         }
     }
@@ -327,13 +334,13 @@ template <bool kFirst, int NTC, int kPhase, typename R>
 __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, int first, char *ring,
                                           float *tile_sets, int part)
 {
-    f32x16 acc[kWT][kTC];
+    f32x4 acc[kWT][2 * kTC];
 #pragma unroll
     for (int a = 0; a < kWT; ++a)
 #pragma unroll
-        for (int t = 0; t < kTC; ++t)
+        for (int t = 0; t < 2 * kTC; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
+            for (int r = 0; r < 4; ++r) acc[a][t][r] = 0.f;
     k_loop<NTC, R>(c, ring, KT, first, acc);
     __syncthreads();  // all operand reads are done: the ring becomes the epilogue staging area
     if (kPhase == 1) {
@@ -341,19 +348,14 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
 #pragma unroll
         for (int a = 0; a < kWT; ++a)
 #pragma unroll
-            for (int t = 0; t < NTC; ++t)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    float4 v = make_float4(acc[a][t][r4 * 4], acc[a][t][r4 * 4 + 1], acc[a][t][r4 * 4 + 2], acc[a][t][r4 * 4 + 3]);
-                    *(float4 *)partial_at(mine, c.wave, a, t, r4, c.lane) = v;
-                }
+            for (int t = 0; t < 2 * NTC; ++t) *(f32x4 *)partial_at(mine, c.wave, a, t, c.lane) = acc[a][t];
         return;
     }
 #pragma unroll
     for (int t = 0; t < NTC; ++t) {
-        f32x16 v[kWT];
+        f32x4 v[2][kWT];
 #pragma unroll
-        for (int a = 0; a < kWT; ++a) v[a] = acc[a][t];
+        for (int a = 0; a < kWT; ++a) { v[0][a] = acc[a][2 * t]; v[1][a] = acc[a][2 * t + 1]; }
         emit_token_tile<kFirst>(p, c, mt, n0, N, ring, t, v);
     }
 }
@@ -366,32 +368,29 @@ template <bool kFirst>
 __device__ __forceinline__ void sum_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, char *ring,
                                          float *tile_sets, int n_parts, int t)
 {
-    f32x16 s[kWT];
+    f32x4 s[2][kWT];
 #pragma unroll
-    for (int a = 0; a < kWT; ++a)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[a][r] = 0.f;
+        for (int a = 0; a < kWT; ++a) s[h][a] = (f32x4){0.f, 0.f, 0.f, 0.f};
     for (int q0 = 0; q0 < n_parts; q0 += 4) {
-        float4 v[4][kWT][4];
+        f32x4 v[4][2][kWT];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (q0 + u >= n_parts) continue;               // uniform
             float *set = tile_sets + (size_t)(q0 + u) * kPartialFloats;
 #pragma unroll
-            for (int a = 0; a < kWT; ++a)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) v[u][a][r4] = *(const float4 *)partial_at(set, c.wave, a, t, r4, c.lane);
+                for (int a = 0; a < kWT; ++a) v[u][h][a] = *(const f32x4 *)partial_at(set, c.wave, a, 2 * t + h, c.lane);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (q0 + u >= n_parts) continue;
 #pragma unroll
-            for (int a = 0; a < kWT; ++a)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    s[a][r4 * 4] += v[u][a][r4].x; s[a][r4 * 4 + 1] += v[u][a][r4].y;
-                    s[a][r4 * 4 + 2] += v[u][a][r4].z; s[a][r4 * 4 + 3] += v[u][a][r4].w;
-                }
+                for (int a = 0; a < kWT; ++a) s[h][a] += v[u][h][a];
         }
     }
     emit_token_tile<kFirst>(p, c, mt, n0, N, ring, t, s);
@@ -501,13 +500,13 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
             c.off[i] = ((uint32_t)sr * K + chunk * 8) * 2;
         }
     }
-    {   // operand rows of this lane: weight row wn*64 + l31 (+32a), token row wm*32 + l31 (+64t)
-        const int l31 = c.lane & 31, khalf = c.lane >> 5;
-        const int wr = c.wn * kWT * 32 + l31, xr = c.wm * 32 + l31;
+    {   // operand rows of this lane: weight row wn*64 + l15 (+16a), token row wm*32 + l15 (+64 per 32-row token tile, +16 for its second half)
+        const int l15 = c.lane & 15, quad = c.lane >> 4;
+        const int wr = c.wn * kWT * 16 + l15, xr = c.wm * 32 + l15;
 #pragma unroll
-        for (int ks = 0; ks < kBKW / 16; ++ks) c.woff[ks] = wr * 128 + (((ks * 2 + khalf) ^ swz8(wr)) << 4);
+        for (int ks = 0; ks < kBKW / 32; ++ks) c.woff[ks] = wr * 128 + (((ks * 4 + quad) ^ swz8(wr)) << 4);
 #pragma unroll
-        for (int ks = 0; ks < kBK / 16; ++ks) c.xoff[ks] = xr * 128 + (((ks * 2 + khalf) ^ swz8(xr)) << 4);
+        for (int ks = 0; ks < kBK / 32; ++ks) c.xoff[ks] = xr * 128 + (((ks * 4 + quad) ^ swz8(xr)) << 4);
     }
 
     const int KT = w1 - w0;
