@@ -21,7 +21,11 @@
 //    should be staged once, and token rows that do not exist not at all.
 //  * Groups are ragged (tokens per expert are binomial): the tile list carries
 //    chunks of <= 320 rows balanced in units of 32 (one chunk for all but the
-//    largest groups), token rows that do not exist are neither staged nor multiplied.
+//    largest groups), token rows that do not exist are neither staged nor multiplied:
+//    above 128 rows they are staged by 8 and multiplied by 16 (all by 32 -> so, whole pass, us: Qwen3 shape 200
+//    rows a slot 314.7 -> 308, 266 rows 361.7 -> 351.5; DeepSeek-V2-Lite shape 166 rows 264.7 -> 260.7; DeepSeek-V3-shaped, 32 experts,
+//    264 rows 748 -> 730).  Tiles of up to 128 rows, which wait for weights, go by 32: twice as many loop bodies
+//    there made 20 rows a slot 0.6 % slower.
 //
 // Workgroup: 8 wavefronts as 2 (token) x 4 (weight).  Wavefront (wm, wn) owns weight
 // rows [wn*64, wn*64+64) and token tiles wm, wm+2, ... (interleaved so that a ragged
@@ -90,7 +94,7 @@ struct WaveCtx {
     uint32_t woff[kBKW / 32], xoff[kBK / 32]; // LDS byte offsets (inside a stage) of this lane's operand rows per sub-step
     int wave, lane, wm, wn, n_tt;
     bool stream_w;                        // this tile's weight rows are read by no other tile: copy them non-temporally
-    int xlive;                            // token-loader wavefronts: how many of their pieces hold rows that exist
+    int xlive;                            // token-loader wavefronts: how many of their pieces (8 rows each) are staged
 };
 
 // LDS byte address of a __shared__ object (LDS pointers are 32-bit offsets in address space 3).
@@ -160,16 +164,16 @@ __device__ __forceinline__ void wait_loads()
     __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// One K-step (64 k) of this wavefront: 2 NTC token tiles of 16 rows x 4 weight tiles x 2 sub-steps of 32 k.  The
+// One K-step (64 k) of this wavefront: NT token tiles of 16 rows x 4 weight tiles x 2 sub-steps of 32 k.  The
 // (sub-step, token tile) pairs run as one software pipeline: the token operand of pair s+2 and the
 // weight operands of the next sub-step are requested from LDS before the MFMAs of pair s.  Every other token tile takes
 // its weight tiles backwards, so that an MFMA always has one operand of the one before it (0.6 to 1 % of the whole pass).
 // `mid` is called once, half way through.
-template <int NTC, typename Mid>
+template <int NT, typename Mid>
 __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x4 (&acc)[kWT][2 * kTC], Mid mid)
 {
-    if constexpr (NTC > 0) {
-        constexpr int KS = kBK / 32, NT = 2 * NTC, STEPS = KS * NT, D = 2;
+    if constexpr (NT > 0) {
+        constexpr int KS = kBK / 32, STEPS = KS * NT, D = 2;
         bf16x8 wf[2][kWT], xf[D + 1];
         auto fetch_w = [&](int ks) {
 #pragma unroll
@@ -252,7 +256,7 @@ __device__ __forceinline__ void wait_copies(int n)
 __device__ __forceinline__ int step_at(int i, int first, int KT) { return i + first < KT ? i + first : i + first - KT; }
 
 // KT K-steps of 64 of this wavefront.  The caller issued the first depth - 1 steps of the ring this wavefront loads.
-template <int NTC, typename R>
+template <int NT, typename R>
 __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x4 (&acc)[kWT][2 * kTC])
 {
     const bool wloader = c.wave < 4;
@@ -268,7 +272,7 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
             fill = fill + 1 == depth ? 0 : fill + 1;
         };
         if (!wloader || !R::kMid) issue();
-        multiply_stage<NTC>(c, ring + ws * kWStage, ring + R::XBase + xs * R::XStage, acc, [&]() { if (wloader && R::kMid) issue(); });
+        multiply_stage<NT>(c, ring + ws * kWStage, ring + R::XBase + xs * R::XStage, acc, [&]() { if (wloader && R::kMid) issue(); });
         ws = ws + 1 == R::NW ? 0 : ws + 1;
         xs = xs + 1 == R::NX ? 0 : xs + 1;
     }
@@ -330,7 +334,7 @@ __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c,
 // p.partials (phase 2, sum_body below, adds them up).
 // (Letting the last of a tile's workgroups to finish do the adding, in the same launch, was
 // measured and is slower: the device-wide fence it needs costs more than the third launch.)
-template <bool kFirst, int NTC, int kPhase, typename R>
+template <bool kFirst, int NT, int kPhase, typename R>
 __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, int first, char *ring,
                                           float *tile_sets, int part)
 {
@@ -341,18 +345,18 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
         for (int t = 0; t < 2 * kTC; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[a][t][r] = 0.f;
-    k_loop<NTC, R>(c, ring, KT, first, acc);
+    k_loop<NT, R>(c, ring, KT, first, acc);
     __syncthreads();  // all operand reads are done: the ring becomes the epilogue staging area
     if (kPhase == 1) {
         float *mine = tile_sets + (size_t)part * kPartialFloats;
 #pragma unroll
         for (int a = 0; a < kWT; ++a)
 #pragma unroll
-            for (int t = 0; t < 2 * NTC; ++t) *(f32x4 *)partial_at(mine, c.wave, a, t, c.lane) = acc[a][t];
+            for (int t = 0; t < NT; ++t) *(f32x4 *)partial_at(mine, c.wave, a, t, c.lane) = acc[a][t];
         return;
     }
 #pragma unroll
-    for (int t = 0; t < NTC; ++t) {
+    for (int t = 0; t < (NT + 1) / 2; ++t) {
         f32x4 v[2][kWT];
 #pragma unroll
         for (int a = 0; a < kWT; ++a) { v[0][a] = acc[a][2 * t]; v[1][a] = acc[a][2 * t + 1]; }
@@ -363,7 +367,7 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
 // Phase 2: the sum of a tile's partial sums, in K order, for token tile t of this wavefront, then the
 // same epilogue as a whole tile.  The sets of four parts are requested together (32 loads of 16 bytes
 // per lane in flight: the launch is one round of the chip, its length is that of one workgroup) and
-// added one after the other.
+// added one after the other.  A 16-row half that holds no rows was not written by phase 1: what is read in its place is summed and not emitted.
 template <bool kFirst>
 __device__ __forceinline__ void sum_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, char *ring,
                                          float *tile_sets, int n_parts, int t)
@@ -460,7 +464,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     c.wm = c.wave >> 2;
     c.n_tt = (mt.rows + 31) >> 5;                      // token tiles that exist
     c.stream_w = mt.single != 0;                       // the slot's rows are one chunk: nobody else reads these weights (known from the tile itself: no further lookup before the first weight copies)
-    c.xlive = c.wave < 4 ? 0 : min(kXPieces, c.n_tt);  // pieces w, w+4, ... < 4*n_tt (8 rows each)
+    // pieces w, w + 4, ... that hold rows; up to 128 rows all of a 32-row tile's
+    c.xlive = c.wave < 4 ? 0 : c.n_tt <= 4 ? c.n_tt : (((mt.rows + 7) >> 3) - (c.wave & 3) + 3) >> 2;
 
     // ---- staging plan ----
     // this workgroup's K range: everything, or (phase 1) weight steps [w0, w1) of the tile
@@ -519,14 +524,14 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     // spread by their place in the list (kSpread: launch_experts_mfma8), 5 steps from one to the next (1 and 3: the same within 1 %).
     // Not the chunks of one slot, which share its weights the same way.
     const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? n0 / BNO * KT / p.n_slices[kFirst ? 0 : 1] : kSpread && mt.single ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
-    // token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
-    // wavefront's work is specialised on that count so that its K loop is straight-line code.
+    // 32-row token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
+    // wavefront's work is specialised on their number, above 128 rows on that of their 16-row halves, so that its K loop is straight-line code.
     const int ntc = (c.n_tt - c.wm + 1) >> 1;
     if constexpr (kPhase == 2) {
         // phase 2 is spread over the token tiles too: a workgroup adds up one per wavefront
         if ((int)blockIdx.y < ntc) sum_body<kFirst>(p, c, mt, n0, N, ring, tile_sets, n_parts, (int)blockIdx.y);
     } else {
-        auto run = [&](auto geometry, auto tiles) {
+        auto run = [&](auto geometry, auto tiles) __attribute__((always_inline)) {
             using R = decltype(geometry);
             const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
             const int depth = c.wave < 4 ? R::NW : R::NX;
@@ -534,10 +539,19 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
             wave_body<kFirst, decltype(tiles)::value, kPhase, R>(p, c, mt, n0, N, KT, first, ring, tile_sets, part);
         };
         using std::integral_constant;
-        if (c.n_tt <= 2)      { if (ntc == 1) run(Ring2{}, integral_constant<int, 1>{}); else run(Ring2{}, integral_constant<int, 0>{}); }
-        else if (c.n_tt <= 4) { if (ntc == 2) run(Ring4{}, integral_constant<int, 2>{}); else run(Ring4{}, integral_constant<int, 1>{}); }
-        else if (c.n_tt <= 8) { if (ntc == 4) run(Ring8{}, integral_constant<int, 4>{}); else if (ntc == 3) run(Ring8{}, integral_constant<int, 3>{}); else run(Ring8{}, integral_constant<int, 2>{}); }
-        else                  { if (ntc == 5) run(Ring10{}, integral_constant<int, 5>{}); else run(Ring10{}, integral_constant<int, 4>{}); }
+        // the body for nt, n .. most: the numbers of 16-row token tiles that a wavefront of this geometry can have
+        auto pick = [&](auto self, auto geometry, auto n, auto most, int nt) __attribute__((always_inline)) {
+            constexpr int v = decltype(n)::value;
+            if constexpr (v == decltype(most)::value) run(geometry, n);
+            else if (nt == v) run(geometry, n);
+            else self(self, geometry, integral_constant<int, v + 1>{}, most, nt);
+        };
+        if (c.n_tt <= 2)      { if (ntc == 1) run(Ring2{}, integral_constant<int, 2>{}); else run(Ring2{}, integral_constant<int, 0>{}); return; }
+        if (c.n_tt <= 4)      { if (ntc == 2) run(Ring4{}, integral_constant<int, 4>{}); else run(Ring4{}, integral_constant<int, 2>{}); return; }
+        // the last 32-row tile's owner leaves its second half out when it has no rows
+        const int nt = __builtin_amdgcn_readfirstlane(2 * ntc - (((mt.rows + 15) >> 4) & ((c.n_tt - 1) == 2 * (ntc - 1) + c.wm)));
+        if (c.n_tt <= 8)      pick(pick, Ring8{}, integral_constant<int, 4>{}, integral_constant<int, 8>{}, nt);
+        else                  pick(pick, Ring10{}, integral_constant<int, 8>{}, integral_constant<int, 10>{}, nt);
     }
 }
 

@@ -44,6 +44,23 @@ def test_large_tile_rings_at_every_token_tile_count(hidden, inter):
     np.testing.assert_array_equal(rows, np.sort(counts))      # the large-tile kernels ran: a tile per slot
 
 
+@pytest.mark.parametrize("hidden,inter", [(64, 192), (320, 128)])
+def test_large_tiles_stage_by_8_rows_and_multiply_by_16(hidden, inter):
+    """Slots of more than 128 rows that end just before, at and behind multiples of 8 and 16, in each half of a 32-row tile and
+    with the last tile at either wavefront row."""
+    from gpu_util import Case
+    from test_gpu_routed import _check
+    counts = [130, 136, 137, 143, 144, 145, 152, 153, 168, 176, 177, 184, 185, 208, 209, 239, 240, 241, 271, 272, 273, 280, 281, 303, 304, 305, 312, 313]
+    tokens = sum(counts)
+    wl = MoEWorkload(name="halves", tokens=tokens, hidden=hidden, inter=inter, n_experts=len(counts), top_k=1, n_slots=len(counts),
+                     n_local=len(counts), act_dtype="bf16", router_dtype="f32", gate="softmax", seed=340 + hidden)
+    g = np.random.Generator(np.random.PCG64(hidden))
+    ids = g.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)[:, None]
+    case = Case(wl)
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+    np.testing.assert_array_equal(np.sort(case.layer.view(tokens)["tiles"][:, 2]), np.sort(counts))
+
+
 @pytest.mark.parametrize("tokens", [1, 17, 64])
 @pytest.mark.parametrize("local", [64, 65, 127, 130, 255, 256])
 def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
