@@ -54,7 +54,12 @@ constexpr int kBlocks2 = 2;   // 16-row weight blocks per task in GEMM-2
 constexpr int kSplit1 = 4;
 constexpr int kSplit2 = 4;
 
-template <bool kFirst, bool kSelf = false>
+// kAhead: K-chunks requested ahead of the one multiplied; the K loop is unrolled by one more, so that a chunk's registers are where the
+// MFMAs read them (copied from the prefetched chunk's after every step before: whole pass, us, copied -> unrolled, one ahead: one token of the
+// Qwen3 shape 30.7 -> 30.1, of the DeepSeek-V3-shaped rank 48.7 -> 46.3, two 50.9 -> 47.5, five on 16 of its experts 68.0 -> 65.3).
+// Three ahead where a wavefront's quarter of the contraction is more than eight chunks (rows of 7168: 46.3 -> 45.1, 47.5 -> 46.4, 65.3 -> 64.6;
+// rows of 2048, four chunks: one token 30.1 -> 30.4, three 55.1 -> 56.8; nothing was measured between).
+template <bool kFirst, bool kSelf, int kAhead>
 __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) void k_expert_decode(Pass p)
 {
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
@@ -100,23 +105,29 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     const int chunks = (K + 127) >> 7, per = (chunks + NS - 1) / NS;
     const int kbeg = min(ks * per, chunks) * 128, kend = min(min((ks + 1) * per, chunks) * 128, K), kstep = 128;
     f32x4 acc_a = {0.f, 0.f, 0.f, 0.f}, acc_b = {0.f, 0.f, 0.f, 0.f};
-    Run ca, cb, cx, na, nb, nx;
-    load_run(ca, wa, kbeg, q, K);
-    if (kTwo) load_run(cb, wb, kbeg, q, K);
-    load_run(cx, xr, kbeg, q, K);
-    for (int k0 = kbeg; k0 < kend; k0 += kstep) {
-        if (k0 + kstep < kend) {
-            load_run(na, wa, k0 + kstep, q, K);
-            if (kTwo) load_run(nb, wb, k0 + kstep, q, K);
-            load_run(nx, xr, k0 + kstep, q, K);
-        }
-        __builtin_amdgcn_sched_barrier(0);  // the prefetch must be issued before this chunk's MFMAs, not after
+    constexpr int D = kAhead + 1;
+    Run ca[D], cb[D], cx[D];
+    auto load_chunk = [&](int u, int k) {
+        load_run(ca[u], wa, k, q, K);
+        if (kTwo) load_run(cb[u], wb, k, q, K);
+        load_run(cx[u], xr, k, q, K);
+    };
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            acc_a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&ca.v[jj], *(bf16x8 *)&cx.v[jj], acc_a, 0, 0, 0);
-            if (kTwo) acc_b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&cb.v[jj], *(bf16x8 *)&cx.v[jj], acc_b, 0, 0, 0);
+    for (int u = 0; u < kAhead; ++u)
+        if (u == 0 || kbeg + u * kstep < kend) load_chunk(u, kbeg + u * kstep);
+    for (int k0 = kbeg; k0 < kend; k0 += D * kstep) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            const int k = k0 + u * kstep;
+            if (k >= kend) break;
+            if (k + kAhead * kstep < kend) load_chunk((u + kAhead) % D, k + kAhead * kstep);
+            __builtin_amdgcn_sched_barrier(0);  // the prefetch must be issued before this chunk's MFMAs, not after
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                acc_a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&ca[u].v[jj], *(bf16x8 *)&cx[u].v[jj], acc_a, 0, 0, 0);
+                if (kTwo) acc_b = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&cb[u].v[jj], *(bf16x8 *)&cx[u].v[jj], acc_b, 0, 0, 0);
+            }
         }
-        ca = na; cb = nb; cx = nx;
     }
 
     if constexpr (NS > 1) {   // the parts' sums, added in K order by the first wavefront
@@ -162,12 +173,16 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
     if (which == 0) {
         const int groups = (p.I + kWRows / 2 - 1) / (kWRows / 2);
         const int blocks = p.max_tiles * groups;
-        if (p.self_tiles) hipLaunchKernelGGL((k_expert_decode<true, true>), dim3(blocks + 1), dim3(kThreads * kSplit1), 0, st, p);
-        else              hipLaunchKernelGGL((k_expert_decode<true>), dim3(blocks), dim3(kThreads * kSplit1), 0, st, p);
+        const dim3 grid(blocks + (p.self_tiles ? 1 : 0)), block(kThreads * kSplit1);
+        const bool deep = p.H > 4096;   // see kAhead
+        if (p.self_tiles && deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3>), grid, block, 0, st, p);
+        else if (p.self_tiles)    hipLaunchKernelGGL((k_expert_decode<true, true, 1>), grid, block, 0, st, p);
+        else if (deep)            hipLaunchKernelGGL((k_expert_decode<true, false, 3>), grid, block, 0, st, p);
+        else                      hipLaunchKernelGGL((k_expert_decode<true, false, 1>), grid, block, 0, st, p);
     } else {
         const int groups = (p.H + 16 * kBlocks2 - 1) / (16 * kBlocks2);
         const int blocks = p.max_tiles * groups;
-        hipLaunchKernelGGL((k_expert_decode<false>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
+        hipLaunchKernelGGL((k_expert_decode<false, false, 1>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
     }
     return hipGetLastError();
 }
