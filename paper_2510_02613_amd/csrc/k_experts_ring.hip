@@ -11,7 +11,9 @@
 // 32 or 64 token rows on four wavefronts in 80 KB of LDS, so that a compute unit runs two (120 KB in flight), one's first and
 // last steps run beside the other's, and the end of a launch is dealt out in small pieces.  A wavefront stages and
 // multiplies its own 32 weight rows; the token rows (4 KB per step and 32 rows) are shared.  Tiles of 33 to 64 rows have a ring of
-// three stages instead of four.
+// three stages instead of four.  Products are v_mfma_f32_16x16x32_bf16 over the 16-row token tiles that have rows: next to the
+// 32x32x16 form on 32-row tiles, whole pass, us: Qwen3 shape 48 tokens 188.8 -> 187.6, DeepSeek-V3-shaped rank 8 tokens 184.8 -> 180 .. 184,
+// 30 tokens 381 -> 380, 64 tokens 471 -> 470.
 // Against weights and token rows loaded into registers in MFMA layout (k_expert_decode, which serves contractions that are
 // no whole K-steps): see the dispatch in moe_api.hip.
 #include "moe_internal.h"
@@ -21,7 +23,7 @@ namespace emoe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 constexpr int kBN = 128;                     // weight rows per task, 32 per wavefront
@@ -65,11 +67,12 @@ __device__ __forceinline__ void wait_younger(int xlive)
     else                       wait_loads<kSteps * kWPieces>();
 }
 
-// The part of a task behind the tile lookup, for a tile of up to 32 TT rows; tokens, tok0: the tile's rows where GEMM-1 derived
+// The part of a task behind the tile lookup, for a tile of up to 16 HT rows; tokens, tok0: the tile's rows where GEMM-1 derived
 // them (kSelf).
-template <bool kFirst, bool kSelf, int TT>
+template <bool kFirst, bool kSelf, int HT>
 __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int slice, int slices, unsigned long long tokens, int tok0, char *ring)
 {
+    constexpr int TT = (HT + 1) / 2;
     using R = Ring<TT>;
     constexpr int BNO = kFirst ? kBN / 2 : kBN;             // output columns per task
     constexpr int kDepth = R::kDepth;
@@ -120,19 +123,19 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
         for (int j = 0; j < TT; ++j)
             if (j < xlive) copy_piece<false>(A + k0, xoff[j], st + kWStage + (wave + kWaves * j) * 1024);
     };
-    // ---- operand rows of this lane ----
-    const int l31 = lane & 31, khalf = lane >> 5, wr = wave * 32 + l31;
-    uint32_t wo[4], xo[4];
+    // ---- operand rows of this lane: 16-row tiles, two of weights, HT of tokens ----
+    const int l15 = lane & 15, quad = lane >> 4, wr = wave * 32 + l15;
+    uint32_t wo[2], xo[2];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-        wo[ks] = wr * 128 + (((ks * 2 + khalf) ^ swz8(wr)) << 4);
-        xo[ks] = kWStage + l31 * 128 + (((ks * 2 + khalf) ^ swz8(l31)) << 4);
+    for (int ks = 0; ks < 2; ++ks) {
+        wo[ks] = wr * 128 + (((ks * 4 + quad) ^ swz8(wr)) << 4);
+        xo[ks] = kWStage + l15 * 128 + (((ks * 4 + quad) ^ swz8(l15)) << 4);
     }
-    f32x16 acc[TT];
+    f32x4 acc[2][HT];
 #pragma unroll
-    for (int t = 0; t < TT; ++t)
+    for (int a = 0; a < 2; ++a)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        for (int t = 0; t < HT; ++t) acc[a][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     for (int s = 0; s < kDepth - 1 && s < KT; ++s) issue(s);
     for (int kt = 0; kt < KT; ++kt) {
         // step kt has landed when at most the copies of the younger steps (kDepth - 2 at most) are still on their way
@@ -143,33 +146,36 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
         __syncthreads();   // everyone's pieces of step kt are in LDS; everyone is done reading step kt-1
         if (kt + kDepth - 1 < KT) issue(kt + kDepth - 1);
         const char *st = ring + (kt % kDepth) * R::kStage;
-        uint4 w[4], x[4][TT];
+        uint4 w[2][2], x[2][HT];
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            w[ks] = *(const uint4 *)(st + wo[ks]);
+        for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-            for (int t = 0; t < TT; ++t) x[ks][t] = *(const uint4 *)(st + xo[ks] + t * 4096);
+            for (int a = 0; a < 2; ++a) w[ks][a] = *(const uint4 *)(st + wo[ks] + a * 2048);
+#pragma unroll
+            for (int t = 0; t < HT; ++t) x[ks][t] = *(const uint4 *)(st + xo[ks] + t * 2048);
         }
         __builtin_amdgcn_sched_barrier(0);   // all reads go out before the first product waits for its own
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-            for (int t = 0; t < TT; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*(const bf16x8 *)&w[ks], *(const bf16x8 *)&x[ks][t], acc[t], 0, 0, 0);
+            for (int t = 0; t < HT; ++t)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+                    acc[a][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8 *)&w[ks][a], *(const bf16x8 *)&x[ks][t], acc[a][t], 0, 0, 0);
     }
-    // lane holds token rows 32 t + l31, weight rows 8 q + 4 khalf + 0..3 of this wavefront's 32
+    // lane holds token rows 16 t + l15, weight rows 16 a + 4 quad + 0..3 of this wavefront's 32
 #pragma unroll
-    for (int t = 0; t < TT; ++t) {
-        const int m = 32 * t + l31;
+    for (int t = 0; t < HT; ++t) {
+        const int m = 16 * t + l15;
         if (m >= mt.rows) continue;
         uint16_t *O = (uint16_t *)(kFirst ? p.h : p.y) + (size_t)(mt.row_begin + m) * N;
 #pragma unroll
-        for (int q = 0; q < (kFirst ? 2 : 4); ++q) {
-            const int col = n0 + wave * (kFirst ? 16 : 32) + q * 8 + khalf * 4;
+        for (int a = 0; a < (kFirst ? 1 : 2); ++a) {
+            const int col = n0 + wave * (kFirst ? 16 : 32) + a * 16 + quad * 4;
             if (col >= N) continue;
             uint16_t o[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(kFirst ? silu_mul(acc[t][q * 4 + e], acc[t][(q + 2) * 4 + e]) : acc[t][q * 4 + e]);
+            for (int e = 0; e < 4; ++e) o[e] = f32_to_bf16(kFirst ? silu_mul(acc[0][t][e], acc[1][t][e]) : acc[a][t][e]);
             *(uint2 *)(O + col) = make_uint2((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16));
         }
     }
@@ -200,9 +206,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p)
         mt = p.tiles[tile];
     }
     if constexpr (kTiles == 2) {
-        if (mt.rows > 32) { task_body<kFirst, kSelf, 2>(p, mt, slice, slices, tokens, tok0, ring); return; }
+        if (mt.rows > 48) { task_body<kFirst, kSelf, 4>(p, mt, slice, slices, tokens, tok0, ring); return; }
+        if (mt.rows > 32) { task_body<kFirst, kSelf, 3>(p, mt, slice, slices, tokens, tok0, ring); return; }
     }
-    task_body<kFirst, kSelf, 1>(p, mt, slice, slices, tokens, tok0, ring);
+    if (mt.rows > 16) task_body<kFirst, kSelf, 2>(p, mt, slice, slices, tokens, tok0, ring);
+    else              task_body<kFirst, kSelf, 1>(p, mt, slice, slices, tokens, tok0, ring);
 }
 
 }  // namespace
