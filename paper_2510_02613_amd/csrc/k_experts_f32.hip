@@ -158,8 +158,11 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
 // touches half a line of 16 rows and every wavefront loads all of the tile's token rows.  Here both operands travel as whole 128-byte
 // lines, once per workgroup, into an LDS tile of 32 k (registers in between: a ragged contraction is zero filled there), the
 // next tile's loads in flight during this one's MFMAs.  Tasks are small, so that a launch has several per compute unit to deal
-// out (64 weight rows: +4 %), and 24 KB of LDS let six run beside each other; two K-steps of loads in flight instead of
-// one changed nothing (+-2 %).  An XCD takes a contiguous run of tasks (GEMM-2 20.5 -> 18.2 us).
+// out (64 weight rows: +4 %); two K-steps of loads in flight instead of one changed nothing (+-2 %).  One LDS tile of 12 KB and a second
+// barrier a step, not two tiles: eight tasks run beside each other instead of six, and whoever waits at a barrier has seven others to wait
+// beside (whole pass, us, two tiles -> one: 1500 tokens 57.9 -> 56.2, 400 38.3 -> 37.4, 2500 76.1 -> 75.2, 512 x 256, 1500 tokens 82.4 -> 80.2).
+// Not multiplying the half of the last K-step that a ragged contraction leaves empty changed nothing: it is the loads that bound it.
+// An XCD takes a contiguous run of tasks (GEMM-2 20.5 -> 18.2 us).
 // The contraction is summed in the same four parts as above (a flush every quarter), so both kernels give the same bits.
 // Measured (264 x 264 layer, 30 of 40 experts, top-4, us with two events): 1500 tokens GEMM-1 32.8 -> 28.7, GEMM-2 26.7 -> 18.4, whole
 // pass 71 -> 59.5; 400 tokens 41.8 -> 38.5, 2500: 93 -> 77; 512 x 256, 1500 tokens 92 -> 82.  That is 85 TFLOP/s in GEMM-2
@@ -172,7 +175,7 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
     constexpr int COLS = kFirst ? kWRows / 2 : kWRows;
     constexpr int XL = kTileRows * 8 / 256;                   // 16-byte loads of token rows per thread and K-step; one of weight rows
     static_assert(kWRows * 8 == 256, "one 16-byte load of weight rows per thread");
-    __shared__ f32x4 xs[2][kTileRows * 8], ws[2][kWRows * 8];
+    __shared__ f32x4 xs[kTileRows * 8], ws[kWRows * 8];
     const int K = kFirst ? p.H : p.I, N = kFirst ? p.I : p.H;
     const int groups = (N + COLS - 1) / COLS;
     // workgroups are dealt round-robin to the 8 XCDs: each takes a contiguous run of the tasks, so that a tile's token rows and
@@ -208,10 +211,10 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
         for (int i = 0; i < XL; ++i) xr[i] = in ? *(const f32x4 *)(xsrc[i] + k) : (f32x4){0.f, 0.f, 0.f, 0.f};
         wr = in ? *(const f32x4 *)(wsrc + k) : (f32x4){0.f, 0.f, 0.f, 0.f};
     };
-    auto store = [&](int b) {
+    auto store = [&]() {
 #pragma unroll
-        for (int i = 0; i < XL; ++i) xs[b][xat[i]] = xr[i];
-        ws[b][wat] = wr;
+        for (int i = 0; i < XL; ++i) xs[xat[i]] = xr[i];
+        ws[wat] = wr;
     };
     // ---- this wavefront's products: a group of 16 rows x both weight blocks ----
     const bool live = wave * 16 < mt.rows;
@@ -224,15 +227,15 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
 #pragma unroll
         for (int a = 0; a < 2; ++a) { sum[a] += acc[a]; acc[a] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
     };
-    auto multiply = [&](int b) {
+    auto multiply = [&]() {
         constexpr int J = kTileK / kKC;
         f32x4 xv[J], wv[J][2];
         const int r = wave * 16 + n;
 #pragma unroll
         for (int j = 0; j < J; ++j) {
-            xv[j] = xs[b][r * 8 + ((j * 4 + q) ^ swz8(r))];
+            xv[j] = xs[r * 8 + ((j * 4 + q) ^ swz8(r))];
 #pragma unroll
-            for (int a = 0; a < 2; ++a) wv[j][a] = ws[b][(a * 16 + n) * 8 + ((j * 4 + q) ^ swz8(a * 16 + n))];
+            for (int a = 0; a < 2; ++a) wv[j][a] = ws[(a * 16 + n) * 8 + ((j * 4 + q) ^ swz8(a * 16 + n))];
         }
 #pragma unroll
         for (int j = 0; j < J; ++j) {
@@ -245,13 +248,11 @@ __global__ __launch_bounds__(256) void k_expert_f32_tile(Pass p)
     };
     const int KT = (K + kTileK - 1) / kTileK;
     load(0);
-    store(0);
-    load(kTileK);
-    __syncthreads();
     for (int kt = 0; kt < KT; ++kt) {
-        if (live) multiply(kt & 1);
-        store((kt + 1) & 1);
-        load((kt + 2) * kTileK);
+        store();
+        if (kt + 1 < KT) load((kt + 1) * kTileK);
+        __syncthreads();
+        if (live) multiply();
         __syncthreads();
     }
     if (!live) return;
