@@ -11,6 +11,7 @@
 // wavefront reduction in which ties go to the lower index exactly as the ordering rule demands.
 #include <type_traits>
 
+#include "gate_select.h"
 #include "moe_internal.h"
 #include "wave_ops.h"
 
@@ -19,264 +20,6 @@ namespace emoe {
 namespace {
 
 constexpr int kThreads = 256;  // 4 wavefronts
-
-// Monotone map float -> uint32 (larger float <-> larger integer).
-__device__ __forceinline__ uint32_t orderable(float f)
-{
-    uint32_t b = __float_as_uint(f);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-
-// key: larger = better score, and among equal scores the LOWER index
-__device__ __forceinline__ unsigned long long make_key(float score, int idx)
-{
-    return ((unsigned long long)orderable(score) << 32) | (unsigned long long)(0xffffffffu - (uint32_t)idx);
-}
-__device__ __forceinline__ int key_index(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull)); }
-
-// Lane j < k holds the j-th selected expert and its score: ids and combine weights of the token.
-__device__ __forceinline__ void finish_token(const Pass &p, int t, int lane, int my_id, float my_s)
-{
-    const float sum = wave_sum_f32(lane < p.k ? my_s : 0.f);
-    if (lane < p.k) {
-        const float wv = p.renormalize ? my_s / sum : my_s;
-        p.ids[(size_t)t * p.k + lane] = my_id;
-        p.w[(size_t)t * p.k + lane] = wv * p.routed_scale;
-    }
-}
-
-// Group scores and group limiting by way of LDS, any group size: cs [E] selection scores, those of dropped groups
-// become -inf.
-__device__ void limit_groups_lds(const Pass &p, float *cs, int lane)
-{
-    const int E = p.E;
-    const float NEG = -__builtin_huge_valf();
-    const int G = p.n_group, per = E / G;
-    // L lanes share a group's experts (L a power of two, G * L <= 64): each finds the two largest
-    // of its share, then the pairs are merged across the L lanes -- a group's score is the sum of
-    // its two largest selection scores, which does not depend on the order they are found in
-    int Lsh = 0;
-    while ((2 * G) << Lsh <= 64) ++Lsh;
-    const int L = 1 << Lsh;
-    const int g = lane >> Lsh, sub = lane & (L - 1);
-    float b1 = NEG, b2 = NEG;
-    if (g < G) {
-        for (int e = g * per + sub; e < (g + 1) * per; e += L) {
-            const float v = cs[e];
-            if (v > b1) { b2 = b1; b1 = v; } else if (v > b2) { b2 = v; }
-        }
-    }
-    for (int d = 1; d < L; d <<= 1) {
-        const float o1 = __shfl_xor(b1, d, 64), o2 = __shfl_xor(b2, d, 64);
-        b2 = fmaxf(fminf(b1, o1), fmaxf(b2, o2));
-        b1 = fmaxf(b1, o1);
-    }
-    // every lane of a group now holds the group's score.  The topk_group best groups are kept, the lower
-    // index first among equal scores: a group's rank is the number of groups that come before it in that
-    // order (the scores of all groups are read lane by lane), and it is kept when its rank is below topk_group
-    const uint32_t mine = orderable((per > 1) ? b1 + b2 : b1);
-    int rank = 0;
-    for (int h = 0; h < G; ++h) {
-        const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, h << Lsh);
-        rank += (other > mine || (other == mine && h < g)) ? 1 : 0;
-    }
-    const unsigned long long keptmask = __ballot(g < G && rank < p.topk_group);   // bit g L: group g is kept
-    const bool pow2 = (per & (per - 1)) == 0;
-    const int psh = 31 - __clz(per);
-    for (int e = lane; e < E; e += 64) {
-        const int ge = pow2 ? e >> psh : e / per;
-        if (!((keptmask >> (ge << Lsh)) & 1ull)) cs[e] = NEG;
-    }
-    wave_sync();
-}
-
-// Selection for one token, run by one wavefront, any number of experts.
-//   lg   : LDS [E] logits in, scores out
-//   cs   : LDS [E] selection scores (biased), destroyed (taken entries -> -inf)
-// Returns the expert this lane holds (lane j < k: the j-th selected), which is also written to p.ids.
-__device__ int select_token(const Pass &p, int t, float *lg, float *cs, int lane)
-{
-    const int E = p.E;
-    const float NEG = -__builtin_huge_valf();
-    // scores
-    if (p.gate == MOE_GATE_SOFTMAX_TOPK) {
-        float m = NEG;
-        for (int e = lane; e < E; e += 64) m = fmaxf(m, lg[e]);
-        m = wave_max_f32(m);
-        float z = 0.f;
-        for (int e = lane; e < E; e += 64) { float v = __expf(lg[e] - m); lg[e] = v; z += v; }   // hardware exp2: ~1e-7 relative, far inside the 1e-5 tie bar
-        z = wave_sum_f32(z);
-        for (int e = lane; e < E; e += 64) lg[e] = lg[e] / z;
-    } else {
-        for (int e = lane; e < E; e += 64) lg[e] = __builtin_amdgcn_rcpf(1.f + __expf(-lg[e]));   // hardware exp2 and reciprocal, ~1 ulp each
-    }
-    for (int e = lane; e < E; e += 64) cs[e] = lg[e] + (p.select_bias ? p.select_bias[e] : 0.f);
-    wave_sync();
-    // group limiting
-    if (p.gate == MOE_GATE_SIGMOID_GROUP_TOPK && p.n_group > 1) {
-        limit_groups_lds(p, cs, lane);
-    }
-    // top-k by repeated wavefront arg-max
-    int my_id = 0;
-    float my_s = 0.f;
-    for (int j = 0; j < p.k; ++j) {
-        unsigned long long key = 0ull;
-        for (int e = lane; e < E; e += 64) {
-            float v = cs[e];
-            if (v != NEG) { unsigned long long kk = make_key(v, e); key = kk > key ? kk : key; }
-        }
-        key = wave_max_u64(key);
-        if (key == 0ull) continue;                     // no candidate left: id 0, weight 0 (wave-uniform)
-        int win = key_index(key);
-        if (lane == j) { my_id = win; my_s = lg[win]; }
-        if (lane == (win & 63)) cs[win] = NEG;
-        wave_sync();
-    }
-    finish_token(p, t, lane, my_id, my_s);
-    return my_id;
-}
-
-// largest and second largest of two pairs
-__device__ __forceinline__ void merge_top2(float &b1, float &b2, float o1, float o2)
-{
-    b2 = fmaxf(fminf(b1, o1), fmaxf(b2, o2));
-    b1 = fmaxf(b1, o1);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v) { return __int_as_float(dpp_i32<CTRL, 0xf>(__float_as_int(v), __float_as_int(v))); }
-
-// The same selection for up to 64 NR experts, NR <= 8, with the scores in registers: expert e is entry e / 64 of lane
-// e % 64.  With few tokens a selection is one chain of dependent instructions (8 us of the LDS version on a grouped
-// gate with 256 experts, 0.6 of it memory), with many it is bound by their number; both are why nothing here goes
-// through LDS that a lane can keep, and why the candidates of a lane are sorted once, so that a round of the top-k
-// is a wavefront maximum over the lanes' heads.
-//   v    : logits of this lane's experts      lg : LDS [64 NR] scratch, scores out      cs : LDS [64 NR] scratch
-template <int NR>
-__device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR], float *lg, float *cs, int lane)
-{
-    constexpr int kOrderBits = NR <= 4 ? 2 : 3;
-    static_assert(NR <= 8, "a lane's order of experts is kept in fields of 2 or 3 bits");
-    const int E = p.E;
-    const float NEG = -__builtin_huge_valf();
-    // scores
-    if (p.gate == MOE_GATE_SOFTMAX_TOPK) {
-        float m = NEG;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) m = fmaxf(m, lane + 64 * i < E ? v[i] : NEG);
-        m = wave_max_f32(m);
-        float z = 0.f;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            v[i] = __expf(v[i] - m);   // hardware exp2: ~1e-7 relative, far inside the 1e-5 tie bar
-            z += lane + 64 * i < E ? v[i] : 0.f;
-        }
-        z = wave_sum_f32(z);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) v[i] = v[i] / z;
-    } else {
-#pragma unroll
-        for (int i = 0; i < NR; ++i) v[i] = __builtin_amdgcn_rcpf(1.f + __expf(-v[i]));   // hardware exp2 and reciprocal, ~1 ulp each
-    }
-#pragma unroll
-    for (int i = 0; i < NR; ++i) lg[64 * i + lane] = v[i];   // the winners' scores are fetched from here after the last round
-#pragma unroll
-    for (int i = 0; i < NR; ++i) v[i] = lane + 64 * i < E ? v[i] + (p.select_bias ? p.select_bias[lane + 64 * i] : 0.f) : NEG;
-    // group limiting
-    if (p.gate == MOE_GATE_SIGMOID_GROUP_TOPK && p.n_group > 1) {
-        const int G = p.n_group, per = E / G;
-        if ((per & (per - 1)) == 0 && per >= 16 && per <= 64) {
-            // a group is one row of 16 lanes, two or four of one entry: the two largest of a row by rotations
-            // (each doubles the set a lane has seen, all sets disjoint), of several rows by shuffles
-            float b1[NR], b2[NR];
-#pragma unroll
-            for (int i = 0; i < NR; ++i) {
-                b1[i] = v[i] == v[i] ? v[i] : NEG;   // a NaN does not count (merged, it would make its partner's score count twice)
-                b2[i] = NEG;
-                merge_top2(b1[i], b2[i], dpp_f32<0x128>(b1[i]), dpp_f32<0x128>(b2[i]));   // row_ror 8, 4, 2, 1
-                merge_top2(b1[i], b2[i], dpp_f32<0x124>(b1[i]), dpp_f32<0x124>(b2[i]));
-                merge_top2(b1[i], b2[i], dpp_f32<0x122>(b1[i]), dpp_f32<0x122>(b2[i]));
-                merge_top2(b1[i], b2[i], dpp_f32<0x121>(b1[i]), dpp_f32<0x121>(b2[i]));
-            }
-            if (per >= 32) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) merge_top2(b1[i], b2[i], __shfl_xor(b1[i], 16, 64), __shfl_xor(b2[i], 16, 64));
-            }
-            if (per == 64) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) merge_top2(b1[i], b2[i], __shfl_xor(b1[i], 32, 64), __shfl_xor(b2[i], 32, 64));
-            }
-            // lane g < G takes group g's score; a group's rank is the number of groups before it in (score, lower
-            // index first) order, and it is kept when its rank is below topk_group
-            const int psh = 31 - __clz(per);
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-                if ((lane & (per - 1)) == 0 && 64 * i + lane < E) cs[(64 * i + lane) >> psh] = b1[i] + b2[i];
-            wave_sync();
-            const uint32_t mine = lane < G ? orderable(cs[lane]) : 0u;
-            int rank = 0;
-            for (int h = 0; h < G; ++h) {
-                const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, h);
-                rank += (other > mine || (other == mine && h < lane)) ? 1 : 0;
-            }
-            const unsigned long long kept = __ballot(lane < G && rank < p.topk_group);
-#pragma unroll
-            for (int i = 0; i < NR; ++i)
-                if (!((kept >> ((64 * i + lane) >> psh)) & 1ull)) v[i] = NEG;
-        } else {
-#pragma unroll
-            for (int i = 0; i < NR; ++i) cs[64 * i + lane] = v[i];
-            wave_sync();
-            limit_groups_lds(p, cs, lane);
-#pragma unroll
-            for (int i = 0; i < NR; ++i) v[i] = cs[64 * i + lane];
-        }
-    }
-    wave_sync();
-    // Candidates as order-preserving integers (0 = absent), a lane's sorted once, largest first and among equal ones
-    // the lower expert first; `order` has their entries in fields of kOrderBits.
-    uint32_t c[NR];
-    uint32_t at[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) { c[i] = v[i] != NEG ? orderable(v[i]) : 0u; at[i] = i; }
-    auto put_first = [&](int i, int j) {                     // i < j: the larger one to i, equal ones stay (adjacent steps only: stable)
-        const bool swap = c[j] > c[i];
-        const uint32_t ci = c[i], ai = at[i];
-        c[i] = swap ? c[j] : ci; at[i] = swap ? at[j] : ai;
-        c[j] = swap ? ci : c[j]; at[j] = swap ? ai : at[j];
-    };
-#pragma unroll
-    for (int r = 0; r < NR; ++r)                             // odd-even transposition: NR rounds of adjacent exchanges
-#pragma unroll
-        for (int i = r & 1; i + 1 < NR; i += 2) put_first(i, i + 1);
-    uint32_t order = 0;
-#pragma unroll
-    for (int i = 0; i < NR; ++i) order |= at[i] << (kOrderBits * i);
-    // top-k: a wavefront maximum over the lanes' heads; only when several lanes hold it (equal scores) a second
-    // reduction for the lowest expert among them
-    int my_id = 0;
-    bool none = false;         // this lane's selection round found no candidate
-    for (int j = 0; j < p.k; ++j) {
-        const uint32_t m = wave_max_u32(c[0]);
-        const int head = lane + 64 * (int)(order & ((1u << kOrderBits) - 1u));
-        const unsigned long long holders = __ballot(c[0] == m && m != 0u);
-        int win;
-        if (__popcll(holders) == 1) {
-            win = __builtin_amdgcn_readlane(head, __ffsll((long long)holders) - 1);
-        } else {
-            win = wave_min_i32(c[0] == m && m != 0u ? head : 0x7fffffff);
-            if (win == 0x7fffffff) win = -1;             // no candidate left
-        }
-        // fewer than k candidates (non-finite biases or activations): the slot keeps id 0 with weight 0
-        // (my_s is only fetched for a real winner), so that nothing is indexed by -1
-        if (lane == j) { my_id = win < 0 ? 0 : win; none = win < 0; }
-        const bool took = head == win;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) c[i] = took ? (i + 1 < NR ? c[i + 1 < NR ? i + 1 : i] : 0u) : c[i];
-        order = took ? order >> kOrderBits : order;
-    }
-    finish_token(p, t, lane, my_id, lane < p.k && !none ? lg[my_id] : 0.f);
-    return my_id;
-}
 
 // ---------------------------------------------------------------------------------
 // k_gate_logits.  A workgroup owns 16 tokens x 16 experts (its logits go to the workspace in fp32).  Both MFMA
@@ -581,61 +324,6 @@ hipError_t launch_gate_logits_lds(const Pass &p, hipStream_t st)
     return hipGetLastError();
 }
 
-// One token's selection from its logits: the planes (partial sums of the K ranges) are added in K order.  They come
-// from other XCDs' L2s, so PZ planes of all of a lane's experts are requested before anything is added.
-template <int NR, int PZ>
-__device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *lg, float *cs, int lane)
-{
-    const float *src = p.logits + (size_t)t * p.E;
-    const size_t plane = (size_t)p.T * p.E;
-    float v[NR];
-#pragma unroll
-    for (int z0 = 0; z0 < kGatePlanes; z0 += PZ) {
-        if (z0 >= p.logit_planes) break;
-        float part[PZ][NR];
-#pragma unroll
-        for (int z = 0; z < PZ; ++z)
-            if (z0 + z < p.logit_planes) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) part[z][i] = src[(z0 + z) * plane + min(64 * i + lane, p.E - 1)];
-            }
-#pragma unroll
-        for (int z = 0; z < PZ; ++z)
-            if (z0 + z < p.logit_planes) {
-#pragma unroll
-                for (int i = 0; i < NR; ++i) v[i] = z0 + z == 0 ? part[z][i] : v[i] + part[z][i];
-            }
-    }
-    return select_regs<NR>(p, t, v, lg, cs, lane);
-}
-// Up to 512 experts in registers: above 256 the LDS form, which re-reads the scores in every round, costs more at every
-// batch size (whole pass, us, LDS -> registers: 384 experts on rows of 7168, 64 tokens 119 -> 104 and 8192 tokens 239 -> 232;
-// 512 experts on rows of 2048, 1 token 30 -> 20 and 30000 tokens 381 -> 339).
-template <int PZ>
-__device__ __forceinline__ int select_one(const Pass &p, int t, float *lg, float *cs, int lane)
-{
-    if (p.E <= 64)  return select_from_planes<1, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 128) return select_from_planes<2, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 256) return select_from_planes<4, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 512) return select_from_planes<8, PZ>(p, t, lg, cs, lane);
-    const float *src = p.logits + (size_t)t * p.E;
-    const size_t plane = (size_t)p.T * p.E;
-    for (int e = lane; e < p.E; e += 64) {
-        float part[kGatePlanes];                         // all planes are requested at once, then added in K order
-#pragma unroll
-        for (int z = 0; z < kGatePlanes; ++z) part[z] = z < p.logit_planes ? src[z * plane + e] : 0.f;
-        float v = part[0];
-#pragma unroll
-        for (int z = 1; z < kGatePlanes; ++z)
-            if (z < p.logit_planes) v += part[z];
-        lg[e] = v;
-    }
-    wave_sync();
-    return select_token(p, t, lg, cs, lane);
-}
-// LDS floats per token: scores and selection scores (whole wavefronts of entries where they are kept in registers)
-__host__ __device__ inline int select_stride(int E) { return E <= 64 ? 64 : E <= 128 ? 128 : E <= 256 ? 256 : E <= 512 ? 512 : E; }
-
 __global__ __launch_bounds__(kThreads) void k_gate_select(Pass p)
 {
     extern __shared__ float smem[];
@@ -656,37 +344,6 @@ __global__ __launch_bounds__(kThreads) void k_gate_select(Pass p)
 // Word [slot][block] of blk_hist: the mask, and above it (bits 16..21) the selection position of the
 // block's first row in the slot (with the token it makes the group's first-assignment key); byte
 // [slot][block] of blk_cnt: the number of rows, i.e. of mask bits.
-// The expert table's entries [0, E + n_shared) -> LDS: from the workspace, or from the kernel's argument (a pass that
-// brings its placement along: the first workgroup then leaves it in the workspace too).
-struct NoTable {};
-struct TableArg { int32_t v[kTableArg]; };
-__device__ __forceinline__ void stage_table(const Pass &p, const NoTable &, int32_t *map)
-{
-    for (int e = threadIdx.x; e < p.E + p.n_shared; e += kFusedTokens * 64) map[e] = p.map[e];
-}
-__device__ __forceinline__ void stage_table(const Pass &p, const TableArg &tab, int32_t *map)
-{
-    for (int e = threadIdx.x; e < p.E + p.n_shared; e += kFusedTokens * 64) {
-        const int32_t v = tab.v[e];
-        map[e] = v;
-        if (blockIdx.x == 0) const_cast<int32_t *>(p.map)[e] = v;
-    }
-}
-
-// Slot of this lane's assignment of token t (lane j < k: the j-th selected expert `id`, then the shared experts), or -1.
-__device__ __forceinline__ int slot_of_lane(const Pass &p, const int32_t *map, int t, int lane, int id)
-{
-    if (lane < p.k) {
-        const int m = map[id];
-        if (m >= -1) return m;
-        // an expert with several copies: token t uses copy t mod R of the list behind the table's entries
-        const int32_t *copies = p.map + p.E + p.n_shared + (-2 - m);
-        return copies[1 + t % copies[0]];
-    }
-    if (lane < p.kk && t >= p.shared_begin && t < p.shared_end) return map[p.E + (lane - p.k)];
-    return -1;
-}
-
 // The block's token masks from its assignments' slots, and every assignment's rank.  All threads call it.
 __device__ __forceinline__ void rank_block(const Pass &p, int n_blocks, uint32_t *blkmask, int t, int slot, int lane, int wave)
 {
@@ -717,7 +374,7 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
     uint32_t *blkmask = (uint32_t *)(smem + kFusedTokens * 2 * stride);   // [S]
     int32_t *map = (int32_t *)(blkmask + S);                              // [E + n_shared]: looked up right after the selection
     for (int s = threadIdx.x; s < S; s += kFusedTokens * 64) blkmask[s] = 0u;
-    stage_table(p, tab, map);
+    stage_table(p, tab, map, kFusedTokens * 64);
     __syncthreads();
     const int t = blockIdx.x * kFusedTokens + wave;
     int slot = -1;
@@ -744,7 +401,7 @@ __global__ __launch_bounds__(kFusedTokens * 64) void k_gate_small(Pass p, int n_
     const int E = p.E, H = p.H, t0 = blockIdx.x * kFusedTokens;
     if (kRank) {
         for (int s = threadIdx.x; s < p.S; s += kFusedTokens * 64) blkmask[s] = 0u;
-        stage_table(p, tab, map);
+        stage_table(p, tab, map, kFusedTokens * 64);
     }
     const int n_et = (E + 15) >> 4, parts = kFusedTokens / n_et, et = wave % n_et, my_part = wave / n_et;
     const int chunks = (H + 31) / 32, per = (chunks + parts - 1) / parts;
@@ -891,7 +548,7 @@ int gate_f32_planes(int T, int H) { return few_token_planes(T, H); }
 // router, where the separate selection ranks the assignments too, 2500: 40.2 -> 43.0, 5000: 47.7 -> 45.0, 8192: 60.6 -> 56.7,
 // and where it does not, 10000: 60.8 -> 62.2, 20000: 87.1 -> 82.2).  The other logits kernels are not, or by 2 percent
 // (rows of 264, 60000 tokens 125 -> 137; of 504, fp32 router, 184 -> 181).
-static bool one_gate_kernel(const Pass &p)
+bool one_gate_kernel(const Pass &p)
 {
     if (p.gate_tiled || p.E > kSmallExperts || p.H > kSmallHidden) return false;
     const long long work = (long long)p.T * p.E * p.H;
@@ -913,9 +570,8 @@ static hipError_t launch_gate_in_parts(const Pass &p, hipStream_t st)
     return hipSuccess;
 }
 
-hipError_t launch_gate(const Pass &p0, hipStream_t st)
+hipError_t launch_gate(Pass &p, hipStream_t st)
 {
-    Pass p = p0;
     hipError_t e;
     if (one_gate_kernel(p)) return launch_gate_small(p, st);
     if (p.act_bf16) {
@@ -926,7 +582,7 @@ hipError_t launch_gate(const Pass &p0, hipStream_t st)
         p.logit_planes = planes < room ? planes : room;
         e = p.router_bf16 ? launch_gate_logits<float, uint16_t>(p, p.logit_planes, st) : launch_gate_logits<float, float>(p, p.logit_planes, st);
     }
-    return e == hipSuccess ? launch_select(p, st) : e;
+    return e == hipSuccess && !p.self_select ? launch_select(p, st) : e;
 }
 
 }  // namespace emoe

@@ -764,6 +764,12 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
         p.n_slices[1] = mfma8_n_slices(p.H, p.I, 1);
     }
 
+    const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
+    // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
+    p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
+    // a token to four: that of the register kernels selects the experts too
+    p.self_select = kernels == Kernels::decode && !whole && !routed_ids && decode_selects(p) && !one_gate_kernel(p);
+
     // optional phase events (benchmarks): event j is recorded before phase j, the last one after the pass
     hipEvent_t *ev = l->prof_on && l->prof_seen++ % l->prof_every == 0 ? l->ev[l->prof_count % kProfRing] : nullptr;
     hipError_t e = hipSuccess;
@@ -772,10 +778,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     mark(MOE_PHASE_GATE);
     if (e == hipSuccess && !routed_ids) e = launch_gate(p, st);
     mark(MOE_PHASE_PERMUTE);
-    // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
-    p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
-    const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
     // GEMM-2 and combine in one launch (recorded as GEMM-2): one token, or two where rows are short (whole pass, us, two launches ->
     // one: Qwen3 shape 1 token 36.5 -> 33.9, 2 tokens 44.3 -> 40.9, 3 tokens 64.5 -> 62.5, 4 tokens 69.0 -> 68.8; DeepSeek-V2-Lite
     // shape 38.7 -> 33.3, 62.6 -> 57.2, 4 tokens 77.8 -> 80.5; DeepSeek-V3-shaped rank 41.7 -> 40.2, 78.9 -> 79.5, 4 tokens 89.0 -> 91.0)

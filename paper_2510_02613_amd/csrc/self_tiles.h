@@ -26,12 +26,25 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long m, int r)
     return pos;
 }
 
-// the count bytes of slot s that exist (blocks past nb hold nothing defined)
-__device__ __forceinline__ uint32_t self_counts(const Pass &p, int s, int nb)
-{
-    const uint32_t w = *(const uint32_t *)(p.blk_cnt + (size_t)s * fused_row_stride(nb));
-    return nb >= 4 ? w : w & ((1u << (8 * nb)) - 1u);
-}
+// Where the masks come from.  The selection kernel's tables:
+struct SelfTables {
+    // the count bytes of slot s that exist (blocks past nb hold nothing defined)
+    __device__ __forceinline__ uint32_t counts(const Pass &p, int s, int nb) const
+    {
+        const uint32_t w = *(const uint32_t *)(p.blk_cnt + (size_t)s * fused_row_stride(nb));
+        return nb >= 4 ? w : w & ((1u << (8 * nb)) - 1u);
+    }
+    __device__ __forceinline__ uint32_t mask(const Pass &p, int s, int b, int nb) const { return (uint32_t)p.blk_hist[(size_t)s * fused_row_stride(nb) + b]; }
+    __device__ __forceinline__ int slot_rank(const Pass &p, int a) const { return p.slot_rank[a]; }
+};
+// or LDS, where the workgroup has selected the (at most 16) tokens' experts itself:
+struct SelfLds {
+    const uint32_t *masks;     // per slot
+    const int32_t *ranks;      // per assignment: slot << 12 | rank, or -1 (the workgroup that writes the tables)
+    __device__ __forceinline__ uint32_t counts(const Pass &, int s, int) const { return (uint32_t)__popc(masks[s]); }
+    __device__ __forceinline__ uint32_t mask(const Pass &, int s, int, int) const { return masks[s]; }
+    __device__ __forceinline__ int slot_rank(const Pass &, int a) const { return ranks[a]; }
+};
 
 // Lane l of a wavefront: the count bytes of its slots l * spl + i, i < spl = ceil(S / 64), and the sums over all
 // slots up to and including its own (rows in the high half, tiles of tile_rows in the low one).
@@ -40,7 +53,8 @@ struct SelfScan {
     int own, incl, spl;
 };
 __device__ __forceinline__ int rows_of(uint32_t count_bytes) { return (int)__builtin_amdgcn_sad_u8(count_bytes, 0u, 0u); }
-__device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, int tile_rows)
+template <typename Src = SelfTables>
+__device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, int tile_rows, const Src &src = Src())
 {
     SelfScan r;
     r.spl = (p.S + 63) >> 6;
@@ -48,7 +62,7 @@ __device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, i
 #pragma unroll
     for (int i = 0; i < kSelfLaneSlots; ++i) {
         const int s = lane * r.spl + i;
-        r.w[i] = i < r.spl && s < p.S ? self_counts(p, s, nb) : 0u;
+        r.w[i] = i < r.spl && s < p.S ? src.counts(p, s, nb) : 0u;
     }
 #pragma unroll
     for (int i = 0; i < kSelfLaneSlots; ++i) {
@@ -67,13 +81,14 @@ __device__ __forceinline__ SelfScan self_scan(const Pass &p, int lane, int nb, i
 // Workgroup 0: counts, offsets, tile list (slot order, chunks of tile_rows), permutation and its inverse --
 // the tables of the bookkeeping kernels, for the few-token case.  All threads of the workgroup (256 or 1024); lds: kSelfTableBytes of LDS.
 constexpr int kSelfTableBytes = kSelfMaxSlots * 8;
-__device__ inline void self_tables(const Pass &p, int tile_rows, void *lds)
+template <typename Src = SelfTables>
+__device__ inline void self_tables(const Pass &p, int tile_rows, void *lds, const Src &src = Src())
 {
     uint32_t *s_cb = (uint32_t *)lds;                        // count bytes of slot s
     int32_t *s_off = (int32_t *)(s_cb + kSelfMaxSlots);
     const int tid = threadIdx.x, nb = (p.T + kFusedTokens - 1) / kFusedTokens;
     if (tid < 64) {
-        const SelfScan sc = self_scan(p, tid, nb, tile_rows);
+        const SelfScan sc = self_scan(p, tid, nb, tile_rows, src);
         int row = (sc.incl - sc.own) >> 16, tl = (sc.incl - sc.own) & 0xffff;
 #pragma unroll
         for (int i = 0; i < kSelfLaneSlots; ++i) {
@@ -99,7 +114,7 @@ __device__ inline void self_tables(const Pass &p, int tile_rows, void *lds)
     }
     __syncthreads();
     for (int a = tid; a < p.T * p.kk; a += blockDim.x) {
-        const int sr = p.slot_rank[a];
+        const int sr = src.slot_rank(p, a);
         int row = -1;
         if (sr >= 0) {
             const int slot = sr >> 12, rank = sr & 0xfff, t = a / p.kk, b = t / kFusedTokens;
@@ -113,10 +128,11 @@ __device__ inline void self_tables(const Pass &p, int tile_rows, void *lds)
 
 // The tile of a task of a GEMM-1 that derives its tiles, the same in every wavefront; false past the last tile.
 // *tokens: the slot's tokens, ascending, as a bit mask; *first: the tile's first row among them.
-__device__ __forceinline__ bool self_tile(const Pass &p, int lane, int tile, int tile_rows, MTile *mt, unsigned long long *tokens, int *first)
+template <typename Src = SelfTables>
+__device__ __forceinline__ bool self_tile(const Pass &p, int lane, int tile, int tile_rows, MTile *mt, unsigned long long *tokens, int *first, const Src &src = Src())
 {
-    const int nb = (p.T + kFusedTokens - 1) / kFusedTokens, stride = fused_row_stride(nb);
-    const SelfScan sc = self_scan(p, lane, nb, tile_rows);
+    const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
+    const SelfScan sc = self_scan(p, lane, nb, tile_rows, src);
     const unsigned long long owners = __ballot((sc.incl & 0xffff) > tile);
     if (owners == 0) return false;
     const int l = __ffsll((long long)owners) - 1;
@@ -136,7 +152,7 @@ __device__ __forceinline__ bool self_tile(const Pass &p, int lane, int tile, int
     mt->single = cs <= tile_rows;
     // bit t of the block masks side by side
     unsigned long long m = 0;
-    for (int b = 0; b < nb; ++b) m |= (unsigned long long)((uint32_t)p.blk_hist[(size_t)s * stride + b] & 0xffffu) << (16 * b);
+    for (int b = 0; b < nb; ++b) m |= (unsigned long long)(src.mask(p, s, b, nb) & 0xffffu) << (16 * b);
     *tokens = m;
     *first = chunk * tile_rows;
     return true;

@@ -84,6 +84,38 @@ def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
         np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
 
 
+@pytest.mark.parametrize("tokens", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("experts,gate,hidden,inter,shared,most", [(65, "softmax", 136, 72, 0, 4), (128, "softmax", 520, 64, 2, 4), (96, "softmax", 64, 1200, 0, 3),
+                                                                   (100, "softmax", 4160, 24, 4, 4), (129, "softmax", 136, 72, 0, 0), (96, "sigmoid_group", 64, 200, 1, 0)])
+def test_a_token_to_four_are_selected_in_gemm1(tokens, experts, gate, hidden, inter, shared, most):
+    """The register GEMM-1 that selects the experts itself (up to 4 tokens, 128 experts and 1760 workgroups, no groups) and the sizes past it: routing, tables and output as in
+    the pass with separate selection and bookkeeping kernels, bit for bit, and through the entry that brings its placement along."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    local = experts - 8
+    grouped = dict(gate="sigmoid_group", n_group=4, topk_group=2, routed_scale=2.5) if gate == "sigmoid_group" else dict(gate="softmax")
+    wl = MoEWorkload(name="select", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=7, n_slots=local + shared, n_local=local,
+                     act_dtype="bf16", router_dtype="f32", n_shared=shared, shared_range=(0, min(tokens, 2) if shared else 0), seed=77 + experts, **grouped)
+    g = np.random.Generator(np.random.PCG64(experts + tokens))
+    case = Case(wl, expert_map=block_expert_map(experts, 0, local, g.permutation(local)))
+    assert ("k_gate_select_hist" not in _kernels(case, tokens, wl.shared_range)) == (tokens <= most)
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED, 0):
+        case.layer.workspace[int(B.moe_workspace_view(case.layer.handle).topk_ids - case.layer.workspace.data_ptr()):].fill_(0xee)
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, wl.shared_range)
+    check_output(case, runs[0][0], ids)
+    for other in runs[1:]:
+        np.testing.assert_array_equal(runs[0][0], other[0])
+        for key in ("topk_ids", "topk_w", "counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+            np.testing.assert_array_equal(runs[0][1][key], other[1][key])
+    x = case.x_dev[:tokens]
+    out = case.layer.forward_static(x, shared_range=wl.shared_range)
+    np.testing.assert_array_equal(out.cpu().numpy().view(np.uint16).ravel(), np.asarray(runs[0][0]).view(np.uint16).ravel())
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
