@@ -76,13 +76,14 @@ __device__ __forceinline__ void split3(const uint4 &lo4, const uint4 &hi4, bf16x
     ph = pack(h); pm = pack(m); pl = pack(l);
 }
 
-// NSW = 0: one ring of NS stages, a stage = the step's token rows + router rows, every wavefront
-// copies its share of both.  NSW > 0: two rings -- NS stages of token rows, NSW of router rows;
-// the first half of the wavefronts copies token rows, the second half router rows.  A
-// wavefront's copies complete in order, so only with separate loaders can the token rows (each
-// read once, from HBM, ~4 us away) be many steps ahead while the router rows (re-read by every
-// workgroup, from L2) are one or two: LDS then holds mostly token rows in flight, which is what
-// the HBM stream of x needs at large T * H.
+// NSW = 0: one ring of NS stages, a stage = the step's token rows + router rows.  NSW > 0: two rings -- NS stages of
+// token rows (each read once, from HBM), NSW <= NS of router rows (re-read by every workgroup, from L2): LDS then holds mostly
+// token rows in flight, which is what the HBM stream of x needs at large T * H.  Every wavefront copies its share of
+// both in every step, token rows first; its copies complete in order, so a step's router rows stand for its token rows, which were
+// issued a step or more earlier, and the count that the K loop waits for is one immediate.  (Half of the wavefronts copying token
+// rows and half router rows, each with a count of its own out of a switch: whole pass, us, that -> this: DeepSeek-V3-shaped, 16 experts,
+// 2500 tokens 398 -> 393, the logits 42 -> 37; rank, 512 tokens 502.7 -> 501; Qwen3 shape, 32 experts, 6000 tokens 195 -> 192.6, 64 experts, 1500 tokens
+// 162 -> 160.4; 4096 tokens 360 -> 360, DeepSeek-V3-shaped rank 8192 tokens 892 -> 893.)
 template <typename WT, int TBT, int EBT, int NS, int NW, int WM, int NSW>
 __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
 {
@@ -92,10 +93,10 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     constexpr int TB = 16 * TBT * WM, EB = 16 * EBT * WE;
     constexpr int XBYTES = TB * 128, WROW = F32 ? 256 : 128, WBYTES = EB * WROW, STAGE = XBYTES + WBYTES;
     constexpr int XP = XBYTES / 1024, WP = WBYTES / 1024;   // 1 KB pieces: 8 rows of 128 B, or 4 rows of 256 B
-    constexpr int XPW = TWO ? XP / (NW / 2) : 0, WPW = TWO ? WP / (NW / 2) : 0;   // two rings: pieces per loader per K-step
-    constexpr int PW = TWO ? (XPW > WPW ? XPW : WPW) : (XP + WP) / kWaves;        // pieces per wavefront per K-step
+    constexpr int XPW = TWO ? XP / NW : 0, WPW = TWO ? WP / NW : 0;   // two rings: pieces of each per wavefront per K-step
+    constexpr int PW = (XP + WP) / kWaves;                  // pieces per wavefront per K-step
     static_assert(TWO || (XP + WP) % kWaves == 0, "pieces are dealt evenly to the wavefronts");
-    static_assert(!TWO || (XP % (NW / 2) == 0 && WP % (NW / 2) == 0 && NSW >= 2), "pieces are dealt evenly to the loaders of a ring");
+    static_assert(!TWO || (XP % NW == 0 && WP % NW == 0 && NSW >= 2 && NS >= NSW), "pieces of both rings are dealt evenly to the wavefronts, token rows go first");
     static_assert(NS >= 2 && (NS - 2) * PW < 64, "load counter");
     constexpr int LDS = TWO ? NS * XBYTES + NSW * WBYTES : NS * STAGE;
     static_assert(LDS <= 160 * 1024, "rings fit LDS");
@@ -114,18 +115,15 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     const char *wbase = (const char *)p.router_w;
 
     // ---- this lane's share of every K-step: its pieces, their global byte offsets at k = 0 ----
-    const bool xloader = TWO && wave < NW / 2;
     uint32_t src[PW];
     uint32_t dst[PW];   // wave-uniform LDS offset of the piece inside its stage
     bool isx[PW];
 #pragma unroll
     for (int i = 0; i < PW; ++i) {
-        // single ring: piece wave + NW i of the XP + WP pieces of a stage.  Two rings: token piece
-        // wave + (NW/2) i for the first half of the wavefronts, router piece likewise for the second.
-        int pc = TWO ? (wave % (NW / 2)) + (NW / 2) * i : wave + kWaves * i;
-        isx[i] = TWO ? xloader : pc < XP;
-        if (!TWO && !isx[i]) pc -= XP;
-        if (TWO && pc >= (xloader ? XP : WP)) pc = 0;       // never issued (i >= this ring's pieces per loader)
+        // piece wave + NW i of a step's XP pieces of token rows and WP of router rows
+        int pc = wave + kWaves * i;
+        isx[i] = pc < XP;
+        if (!isx[i]) pc -= XP;
         if (isx[i]) {
             const int row = pc * 8 + (lane >> 3);
             const int chunk = (lane & 7) ^ ((row >> 1) & 7);
@@ -142,13 +140,13 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
         dst[i] = pc * 1024;
     }
     const uint32_t ring_a = lds_addr(ring);
-    // copies of this wavefront for K-step kt into stage `slot` of the ring(s) it loads
-    auto issue = [&](int kt, int slot) {
+    // this wavefront's copies of token (x) or router rows for K-step kt into stage `slot` of their ring
+    auto issue = [&](int kt, int slot, bool x) {
 #pragma unroll
         for (int i = 0; i < PW; ++i) {
-            if (TWO && i >= (xloader ? XPW : WPW)) continue;
-            const char *b = isx[i] ? xbase + (size_t)kt * (kBK * 2) : wbase + (size_t)kt * (kBK * (F32 ? 4 : 2));
-            const uint32_t stage = isx[i] ? slot * XSTRIDE : WRING0 + slot * WSTRIDE;
+            if (isx[i] != x) continue;
+            const char *b = x ? xbase + (size_t)kt * (kBK * 2) : wbase + (size_t)kt * (kBK * (F32 ? 4 : 2));
+            const uint32_t stage = x ? slot * XSTRIDE : WRING0 + slot * WSTRIDE;
             dma_piece(b, src[i], ring_a + stage + __builtin_amdgcn_readfirstlane(dst[i]));
         }
     };
@@ -210,27 +208,25 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     };
 
     // ---- K loop: steps kt+1 .. kt+depth-1 of a ring are in flight while step kt is multiplied ----
-    const int depth = TWO && !xloader ? NSW : NS;              // of the ring this wavefront loads
-    const int mine = TWO ? (xloader ? XPW : WPW) : PW;         // copies it issues per K-step
-    for (int s = 0; s < depth - 1 && kt0 + s < kt1; ++s) issue(kt0 + s, s);
-    int xs = 0, ws = 0, fill = depth - 1;
+    constexpr int DX = NS, DW = TWO ? NSW : NS;
+    for (int s = 1 - DX; s < 0; ++s) {
+        if (kt0 + s + DX - 1 < kt1) issue(kt0 + s + DX - 1, s + DX - 1, true);
+        if (s + DW - 1 >= 0 && kt0 + s + DW - 1 < kt1) issue(kt0 + s + DW - 1, s + DW - 1, false);
+    }
+    int xs = 0, ws = 0, xfill = DX - 1, wfill = DW - 1;
     for (int kt = kt0; kt < kt1; ++kt) {
-        // younger steps that may stay in flight: those issued after step kt, at most depth-2 of them
-        const int allowed = min(depth - 2, kt1 - 1 - kt) * mine;
-        switch (allowed) {   // the count is an immediate of the wait instruction
-#define EMOE_WAIT_CASE(N) case N: wait_loads<N>(); break;
-        EMOE_WAIT_CASE(1) EMOE_WAIT_CASE(2) EMOE_WAIT_CASE(3) EMOE_WAIT_CASE(4) EMOE_WAIT_CASE(5) EMOE_WAIT_CASE(6)
-        EMOE_WAIT_CASE(8) EMOE_WAIT_CASE(9) EMOE_WAIT_CASE(10) EMOE_WAIT_CASE(12) EMOE_WAIT_CASE(15) EMOE_WAIT_CASE(16)
-        EMOE_WAIT_CASE(18) EMOE_WAIT_CASE(20) EMOE_WAIT_CASE(24) EMOE_WAIT_CASE(32)
-#undef EMOE_WAIT_CASE
-        default: wait_loads<0>(); break;   // a count not listed waits for everything: always safe
-        }
+        // Behind step kt's router rows DW - 2 steps' copies were issued and may stay on their way; the last steps wait for all.  (Counted down
+        // exactly, by a switch over the immediates of the instruction, it was slower.)
+        if (kt + DX - 2 < kt1) wait_loads<(DW - 2) * PW>();
+        else                   wait_loads<0>();
         __syncthreads();   // everyone's pieces of step kt have landed; everyone is done reading step kt-1
-        if (kt + depth - 1 < kt1) issue(kt + depth - 1, fill);
+        if (kt + DX - 1 < kt1) issue(kt + DX - 1, xfill, true);
+        if (kt + DW - 1 < kt1) issue(kt + DW - 1, wfill, false);
         multiply(xs, ws);
         xs = xs + 1 == NS ? 0 : xs + 1;
         ws = ws + 1 == (TWO ? NSW : NS) ? 0 : ws + 1;
-        fill = fill + 1 == depth ? 0 : fill + 1;
+        xfill = xfill + 1 == DX ? 0 : xfill + 1;
+        wfill = wfill + 1 == DW ? 0 : wfill + 1;
     }
 
     // ---- epilogue: accumulators -> this wavefront's LDS region [token][expert] -> whole row segments ----
