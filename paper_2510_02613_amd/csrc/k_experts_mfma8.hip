@@ -226,31 +226,15 @@ __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws,
 // 674 -> 597, 6500 tokens 885 -> 839; 1777 routed tokens of the DeepSeek-V2-Lite shape 367 -> 340.
 template <int NW_, int NX_, int TT_, bool kMid_>
 struct Ring {
-    static constexpr int NW = NW_, NX = NX_, XStage = TT_ * kXTile, XBase = NW_ * kWStage;
+    static constexpr int NW = NW_, NX = NX_, TT = TT_, XStage = TT_ * kXTile, XBase = NW_ * kWStage;
     static constexpr bool kMid = kMid_;
-    static_assert(NW_ >= 2 && NX_ >= 2 && XBase + NX_ * XStage <= kLdsBytes, "LDS budget");
+    static_assert((NX_ == 2 || (NX_ == 4 && TT_ <= 4)) && NW_ >= 2 && NW_ <= 4, "the waits of the K loop");
+    static_assert(XBase + NX_ * XStage <= kLdsBytes, "LDS budget");
 };
 using Ring2 = Ring<4, 4, 2, false>;
 using Ring4 = Ring<3, 4, 4, false>;
 using Ring8 = Ring<3, 2, 8, true>;
 using Ring10 = Ring<2, 2, kMaxTT, true>;
-
-// Wait until at most n of this wavefront's copies are in flight.  n: steps that may stay in flight times copies
-// per step (8 for a weight loader, the token tiles that exist for a token loader); the count is an immediate of
-// the instruction, and a count not listed waits for everything.
-__device__ __forceinline__ void wait_copies(int n)
-{
-    switch (n) {
-    case 1: wait_loads<1>(); break;
-    case 2: wait_loads<2>(); break;
-    case 3: wait_loads<3>(); break;
-    case 4: wait_loads<4>(); break;
-    case 6: wait_loads<6>(); break;
-    case 8: wait_loads<8>(); break;
-    case 16: wait_loads<16>(); break;
-    default: wait_loads<0>(); break;
-    }
-}
 
 // K-step number i in the order this workgroup walks its KT steps: it starts at step `first` and wraps around.
 __device__ __forceinline__ int step_at(int i, int first, int KT) { return i + first < KT ? i + first : i + first - KT; }
@@ -261,10 +245,24 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
 {
     const bool wloader = c.wave < 4;
     const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
-    const int depth = wloader ? R::NW : R::NX, per_step = wloader ? kWPieces : c.xlive;
+    const int depth = wloader ? R::NW : R::NX;
     int ws = 0, xs = 0, fill = depth - 1;
     for (int kt = 0; kt < KT; ++kt) {
-        wait_copies(min(depth - 2, KT - 1 - kt) * per_step);   // this wavefront's share of step kt has landed
+        // This wavefront's share of step kt has landed when only the copies of the younger steps (depth - 2 at most) are on their way: 8 a step
+        // for a weight loader; for a token loader the 32-row tiles that exist, which with a ring of four are as many as the ring is for or
+        // one fewer.  The count is an immediate of the instruction; a switch over it was slower (whole pass, us, switch -> here:
+        // DeepSeek-V3-shaped, 32 experts, 264 rows 716.5 -> 710, Qwen3 shape 266 rows 348 -> 345, 128 rows 266 -> 265.4, 64 rows 235.6 -> 234.6).
+        if (wloader) {
+            if (kt + R::NW - 2 < KT)                  wait_loads<(R::NW - 2) * kWPieces>();
+            else if (R::NW == 4 && kt + 1 < KT)       wait_loads<kWPieces>();
+            else                                      wait_loads<0>();
+        } else if (R::NX == 2 || kt + 1 >= KT) {
+            wait_loads<0>();
+        } else if (kt + 2 < KT) {
+            if (c.xlive == R::TT) wait_loads<2 * R::TT>(); else wait_loads<2 * (R::TT - 1)>();
+        } else {
+            if (c.xlive == R::TT) wait_loads<R::TT>(); else wait_loads<R::TT - 1>();
+        }
         __syncthreads();   // everyone's share of step kt is in LDS; everyone is done reading step kt-1
         auto issue = [&]() {
             if (kt + depth - 1 >= KT) return;
