@@ -22,7 +22,6 @@
 // wavefronts per SIMD that keeps more than 128 KB per compute unit on its way from HBM.
 #include <type_traits>
 
-#include "gate_select.h"
 #include "moe_internal.h"
 #include "self_tiles.h"
 
@@ -63,18 +62,19 @@ constexpr int kSplit2 = 4;
 // Three ahead where a wavefront's quarter of the contraction is more than eight chunks (rows of 7168: 46.3 -> 45.1, 47.5 -> 46.4, 65.3 -> 64.6;
 // rows of 2048, four chunks: one token 30.1 -> 30.4, three 55.1 -> 56.8; nothing was measured between).
 //
-// kSelect: GEMM-1 of a token to four, behind the logits kernel alone.  The selection kernel is nothing but latency then (one
+// Table (NoTable or TableArg, or none): GEMM-1 of a token to four selects its experts, behind the logits kernel alone.  The selection kernel is nothing but latency then (one
 // workgroup between two launches).  Every workgroup selects all tokens itself instead, a wavefront each, and workgroup 0 leaves the ids,
 // the weights and (tab) the placement in the workspace.  Whole pass, us, selection kernel -> here: one token of the Qwen3 shape 30.5 ->
 // 27.4, three 55.3 -> 53.6, four on 32 of its experts 32.4 -> 29.1 (1536 workgroups); DeepSeek-V2-Lite shape two tokens 52.3 -> 50.3, on
 // 16 of its experts one 27.4 -> 25.1, four 38.4 -> 36.7 (1760 workgroups).  A workgroup pays 1 to 2 us for it, one that finds no tile too, so
 // there is a limit on their number; nothing was measured above it.  Group-limited gates take several times as long to select (DeepSeek-V3-shaped
-// rank one token 45.0 -> 45.0, two 46.2 -> 55.4): they keep their kernel, and so do more than 128 experts, which were not measured.
-constexpr int kSelectTokens = 4, kSelectExperts = 128, kMaxKK = 36;   // a wavefront per token; top_k <= 32 plus <= 4 shared experts
+// rank one token 45.0 -> 45.0, two 46.2 -> 55.4): they keep their kernel, and so do more than 128 experts, which were not measured, and
+// more tokens: two a wavefront made five tokens of the DeepSeek-V2-Lite shape 90.5 -> 95.3, eight on 32 Qwen3 experts 34.9 -> 43.0.
 constexpr long long kSelectBlocks = 1760;
-template <bool kFirst, bool kSelf, int kAhead, bool kSelect, typename Table>
-__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) void k_expert_decode(Pass p, Table tab)
+template <bool kFirst, bool kSelf, int kAhead, typename... Table>
+__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) void k_expert_decode(Pass p, Table... tab)
 {
+    constexpr bool kSelect = sizeof...(Table) == 1;
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
     static_assert(!kSelect || kSelf, "a GEMM-1 that selects derives its tiles too");
     constexpr int NS = kFirst ? kSplit1 : kSplit2;                // wavefronts of this workgroup (one task)
@@ -88,26 +88,9 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     int task = blockIdx.x;
     std::conditional_t<kSelect, SelfLds, SelfTables> src;
     if constexpr (kSelect) {
-        __shared__ float scores[kSelectTokens][2 * kSelectExperts];
-        __shared__ uint32_t masks[kSelfMaxSlots];
-        __shared__ int32_t ranks[kSelectTokens * kMaxKK], map[kSelectExperts + 4];
         static_assert(kSelectTokens == NS, "a wavefront selects a token");
-        for (int s = threadIdx.x; s < kSelfMaxSlots; s += NS * 64) masks[s] = 0u;
-        stage_table(p, tab, map, NS * 64);
-        __syncthreads();
-        int slot = -1;
-        if (ks < p.T) {
-            float *lg = scores[ks], *cs = lg + kSelectExperts;
-            const bool store = task == 0;
-            const int id = p.E <= 64 ? select_from_planes<1, kGatePlanes>(p, ks, lg, cs, lane, store)
-                                     : select_from_planes<2, kGatePlanes>(p, ks, lg, cs, lane, store);
-            slot = slot_of_lane(p, map, ks, lane, id);
-            if (slot >= 0) atomicOr(&masks[slot], 1u << ks);
-        }
-        __syncthreads();
-        if (task == 0 && ks < p.T && lane < p.kk) ranks[ks * p.kk + lane] = slot >= 0 ? (slot << 12) | __popc(masks[slot] & ((1u << ks) - 1u)) : -1;
-        src.masks = masks;
-        src.ranks = ranks;
+        __shared__ SelectLds sel;
+        src = select_few(p, sel, tab...);
     }
     if (kSelf) {
         __shared__ int32_t lds[kSelfTableBytes / 4];
@@ -204,19 +187,19 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
 template <typename Table>
 void launch_select(const Pass &p, bool deep, dim3 grid, dim3 block, hipStream_t st, const Table &tab)
 {
-    if (deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3, true, Table>), grid, block, 0, st, p, tab);
-    else      hipLaunchKernelGGL((k_expert_decode<true, true, 1, true, Table>), grid, block, 0, st, p, tab);
+    if (deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3, Table>), grid, block, 0, st, p, tab);
+    else      hipLaunchKernelGGL((k_expert_decode<true, true, 1, Table>), grid, block, 0, st, p, tab);
 }
 
 }  // namespace
 
 int decode_tile_rows() { return kTileRows; }
 
-bool decode_selects(const Pass &p)
+bool gemm1_selects(const Pass &p, int blocks)
 {
-    const long long blocks = (long long)p.max_tiles * ((p.I + kWRows / 2 - 1) / (kWRows / 2));
     return p.self_tiles && p.gate == MOE_GATE_SOFTMAX_TOPK && p.T <= kSelectTokens && p.E <= kSelectExperts && blocks <= kSelectBlocks;
 }
+int decode_blocks(const Pass &p) { return p.max_tiles * ((p.I + kWRows / 2 - 1) / (kWRows / 2)); }
 
 hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
 {
@@ -233,14 +216,14 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
             } else {
                 launch_select<NoTable>(p, deep, grid, block, st, NoTable{});
             }
-        } else if (p.self_tiles && deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3, false, NoTable>), grid, block, 0, st, p, NoTable{});
-        else if (p.self_tiles)           hipLaunchKernelGGL((k_expert_decode<true, true, 1, false, NoTable>), grid, block, 0, st, p, NoTable{});
-        else if (deep)                   hipLaunchKernelGGL((k_expert_decode<true, false, 3, false, NoTable>), grid, block, 0, st, p, NoTable{});
-        else                             hipLaunchKernelGGL((k_expert_decode<true, false, 1, false, NoTable>), grid, block, 0, st, p, NoTable{});
+        } else if (p.self_tiles && deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3>), grid, block, 0, st, p);
+        else if (p.self_tiles)           hipLaunchKernelGGL((k_expert_decode<true, true, 1>), grid, block, 0, st, p);
+        else if (deep)                   hipLaunchKernelGGL((k_expert_decode<true, false, 3>), grid, block, 0, st, p);
+        else                             hipLaunchKernelGGL((k_expert_decode<true, false, 1>), grid, block, 0, st, p);
     } else {
         const int groups = (p.H + 16 * kBlocks2 - 1) / (16 * kBlocks2);
         const int blocks = p.max_tiles * groups;
-        hipLaunchKernelGGL((k_expert_decode<false, false, 1, false, NoTable>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p, NoTable{});
+        hipLaunchKernelGGL((k_expert_decode<false, false, 1>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
     }
     return hipGetLastError();
 }

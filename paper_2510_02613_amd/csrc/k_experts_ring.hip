@@ -16,6 +16,8 @@
 // 30 tokens 381 -> 380, 64 tokens 471 -> 470.
 // Against weights and token rows loaded into registers in MFMA layout (k_expert_decode, which serves contractions that are
 // no whole K-steps): see the dispatch in moe_api.hip.
+#include <type_traits>
+
 #include "moe_internal.h"
 #include "self_tiles.h"
 
@@ -182,17 +184,25 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
 }
 
 // kTiles: the most token tiles of 32 rows an M-tile has.
-template <bool kFirst, bool kSelf, int kTiles>
-__global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p)
+// Table (NoTable or TableArg, or none): GEMM-1 of a token to four selects the experts too (see k_experts_decode.hip).  Whole pass, us, selection kernel -> here: Qwen3
+// shape two tokens 39.7 -> 36.9, four 63.7 -> 61.0, four on half of its experts 36.0 -> 33.3; DeepSeek-V2-Lite shape three tokens 68.7 -> 66.2, four
+// 75.2 -> 72.5.
+template <bool kFirst, bool kSelf, int kTiles, typename... Table>
+__global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... tab)
 {
+    constexpr bool kSelect = sizeof...(Table) == 1;
+    static_assert(!kSelect || (kSelf && kSelectTokens == kWaves), "a GEMM-1 that selects derives its tiles too, a wavefront selects a token");
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
     constexpr int BNO = kFirst ? kBN / 2 : kBN;             // output columns per task
     __shared__ __attribute__((aligned(1024))) char ring[kLds];
     const int N = kFirst ? p.I : p.H;
     const int slices = (N + BNO - 1) / BNO;
     int task = blockIdx.x;
+    std::conditional_t<kSelect, SelfLds, SelfTables> src;
+    static_assert(sizeof(SelectLds) <= kLds - 16384 && kSelfTableBytes <= 16384, "the selection borrows the ring, the tables are put together in front of it");
+    if constexpr (kSelect) src = select_few(p, *(SelectLds *)(ring + 16384), tab...);
     if (kSelf) {
-        if (task == 0) { self_tables(p, kRows, ring); return; }
+        if (task == 0) { self_tables(p, kRows, ring, src); return; }
         task -= 1;
     }
     const int tile = task / slices, slice = task - tile * slices;
@@ -200,7 +210,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p)
     unsigned long long tokens = 0;
     int tok0 = 0;
     if (kSelf) {
-        if (!self_tile(p, threadIdx.x & 63, tile, kRows, &mt, &tokens, &tok0)) return;
+        if (!self_tile(p, threadIdx.x & 63, tile, kRows, &mt, &tokens, &tok0, src)) return;
+        if (kSelect) __syncthreads();   // everyone has read the masks: the ring is free
     } else {
         if (tile >= *p.n_tiles) return;
         mt = p.tiles[tile];
@@ -217,17 +228,28 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p)
 
 int ring_tile_rows(bool large) { return large ? 2 * kRows : kRows; }
 
+int ring_blocks(const Pass &p) { return p.max_tiles * ((p.I + kBN / 2 - 1) / (kBN / 2)); }
+
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st)
 {
-    const int blocks = p.max_tiles * (which == 0 ? (p.I + kBN / 2 - 1) / (kBN / 2) : (p.H + kBN - 1) / kBN);
+    const dim3 block(kThreads), grid(which == 0 ? ring_blocks(p) + (p.self_tiles && tile_rows <= kRows ? 1 : 0) : p.max_tiles * ((p.H + kBN - 1) / kBN));
     if (tile_rows > kRows) {
-        if (which == 0) hipLaunchKernelGGL((k_expert_ring<true, false, 2>), dim3(blocks), dim3(kThreads), 0, st, p);
-        else            hipLaunchKernelGGL((k_expert_ring<false, false, 2>), dim3(blocks), dim3(kThreads), 0, st, p);
+        if (which == 0) hipLaunchKernelGGL((k_expert_ring<true, false, 2>), grid, block, 0, st, p);
+        else            hipLaunchKernelGGL((k_expert_ring<false, false, 2>), grid, block, 0, st, p);
     } else if (which == 0) {
-        if (p.self_tiles) hipLaunchKernelGGL((k_expert_ring<true, true, 1>), dim3(blocks + 1), dim3(kThreads), 0, st, p);
-        else              hipLaunchKernelGGL((k_expert_ring<true, false, 1>), dim3(blocks), dim3(kThreads), 0, st, p);
+        if (p.self_select && p.host_table) {
+            TableArg tab;
+            for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
+            hipLaunchKernelGGL((k_expert_ring<true, true, 1, TableArg>), grid, block, 0, st, p, tab);
+        } else if (p.self_select) {
+            hipLaunchKernelGGL((k_expert_ring<true, true, 1, NoTable>), grid, block, 0, st, p, NoTable{});
+        } else if (p.self_tiles) {
+            hipLaunchKernelGGL((k_expert_ring<true, true, 1>), grid, block, 0, st, p);
+        } else {
+            hipLaunchKernelGGL((k_expert_ring<true, false, 1>), grid, block, 0, st, p);
+        }
     } else {
-        hipLaunchKernelGGL((k_expert_ring<false, false, 1>), dim3(blocks), dim3(kThreads), 0, st, p);
+        hipLaunchKernelGGL((k_expert_ring<false, false, 1>), grid, block, 0, st, p);
     }
     return hipGetLastError();
 }

@@ -767,8 +767,9 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
     // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
     p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
-    // a token to four: that of the register kernels selects the experts too
-    p.self_select = kernels == Kernels::decode && !whole && !routed_ids && decode_selects(p) && !one_gate_kernel(p);
+    // a token to four: it selects the experts too
+    p.self_select = (kernels == Kernels::decode || (kernels == Kernels::ring && !ring64)) && !whole && !routed_ids &&
+                    gemm1_selects(p, kernels == Kernels::decode ? decode_blocks(p) : ring_blocks(p)) && !one_gate_kernel(p);
 
     // optional phase events (benchmarks): event j is recorded before phase j, the last one after the pass
     hipEvent_t *ev = l->prof_on && l->prof_seen++ % l->prof_every == 0 ? l->ev[l->prof_count % kProfRing] : nullptr;

@@ -88,7 +88,7 @@ struct Pass {
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
     int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 and k_token_experts only: their workgroups derive their tile from the selection kernel's per-block counts and
                          // masks themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
-    int32_t self_select; // GEMM-1 selects the experts itself from the logits (few tokens, k_expert_decode): no selection kernel
+    int32_t self_select; // GEMM-1 selects the experts itself from the logits (a token to four): no selection kernel
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
     float *partials;     // partial sums of the large-tile GEMMs' split tiles, or NULL (no room: never split)
@@ -112,7 +112,9 @@ hipError_t launch_write_map(int32_t *dst, const int32_t *host_vals, int n, hipSt
 hipError_t launch_fill_slot(void *dst13, const void *src13, size_t bytes13, void *dst2, const void *src2, size_t bytes2, int blocks, hipStream_t st);  // bytes % 16 == 0
 hipError_t launch_gate(Pass &p, hipStream_t st);   // sets logit_planes
 bool one_gate_kernel(const Pass &p);                 // logits and selection are one kernel
-bool decode_selects(const Pass &p);                  // k_expert_decode's GEMM-1 can do the selection
+bool gemm1_selects(const Pass &p, int blocks);       // a GEMM-1 of that many workgroups that derives its tiles does the selection too
+int decode_blocks(const Pass &p);                    // workgroups of the GEMM-1 of k_expert_decode, of k_expert_ring (one that writes the tables aside)
+int ring_blocks(const Pass &p);
 int gate_f32_planes(int T, int H);   // partial-sum planes of the gate logits of fp32 layers
 hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st);   // logits only, bf16 activations
 bool gate_dma_supports(const Pass &p);

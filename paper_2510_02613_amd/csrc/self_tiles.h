@@ -1,6 +1,7 @@
 // Tiles derived by the expert GEMM-1 itself, for passes of at most 64 tokens: shared by the weight-streaming bf16
 // kernels (registers and LDS ring), the fp32 kernel and the token-by-token one.
 #pragma once
+#include "gate_select.h"
 #include "moe_internal.h"
 
 namespace emoe {
@@ -156,6 +157,38 @@ __device__ __forceinline__ bool self_tile(const Pass &p, int lane, int tile, int
     *tokens = m;
     *first = chunk * tile_rows;
     return true;
+}
+
+// A token to four behind the logits kernel alone, selected by a GEMM-1's workgroup of four wavefronts, one a token: their masks and (workgroup 0, which
+// also leaves the ids, the weights and what `tab` brings in the workspace) ranks in LDS.
+constexpr int kSelectTokens = 4, kSelectExperts = 128, kSelectKK = 36;   // top_k <= 32 plus <= 4 shared experts
+struct SelectLds {
+    float scores[kSelectTokens][2 * kSelectExperts];
+    uint32_t masks[kSelfMaxSlots];
+    int32_t ranks[kSelectTokens * kSelectKK], map[kSelectExperts + 4];
+};
+template <typename Table>
+__device__ __forceinline__ SelfLds select_few(const Pass &p, SelectLds &s, const Table &tab)
+{
+    const int lane = threadIdx.x & 63, t = (int)(threadIdx.x >> 6);
+    const bool first = blockIdx.x == 0;
+    for (int i = threadIdx.x; i < kSelfMaxSlots; i += kSelectTokens * 64) s.masks[i] = 0u;
+    stage_table(p, tab, s.map, kSelectTokens * 64);
+    __syncthreads();
+    int slot = -1;
+    if (t < p.T) {
+        float *lg = s.scores[t], *cs = lg + kSelectExperts;
+        const int id = p.E <= 64 ? select_from_planes<1, kGatePlanes>(p, t, lg, cs, lane, first)
+                                 : select_from_planes<2, kGatePlanes>(p, t, lg, cs, lane, first);
+        slot = slot_of_lane(p, s.map, t, lane, id);
+        if (slot >= 0) atomicOr(&s.masks[slot], 1u << t);
+    }
+    __syncthreads();
+    if (first && t < p.T && lane < p.kk) s.ranks[t * p.kk + lane] = slot >= 0 ? (slot << 12) | __popc(s.masks[slot] & ((1u << t) - 1u)) : -1;
+    SelfLds src;
+    src.masks = s.masks;
+    src.ranks = s.ranks;
+    return src;
 }
 
 }  // namespace emoe

@@ -86,9 +86,10 @@ def test_few_tokens_many_slots_derive_their_tiles(tokens, local):
 
 @pytest.mark.parametrize("tokens", [1, 2, 3, 4, 5])
 @pytest.mark.parametrize("experts,gate,hidden,inter,shared,most", [(65, "softmax", 136, 72, 0, 4), (128, "softmax", 520, 64, 2, 4), (96, "softmax", 64, 1200, 0, 3),
-                                                                   (100, "softmax", 4160, 24, 4, 4), (129, "softmax", 136, 72, 0, 0), (96, "sigmoid_group", 64, 200, 1, 0)])
+                                                                   (100, "softmax", 4160, 24, 4, 4), (129, "softmax", 136, 72, 0, 0), (96, "sigmoid_group", 64, 200, 1, 0),
+                                                                   (100, "softmax", 128, 512, 2, 4)])
 def test_a_token_to_four_are_selected_in_gemm1(tokens, experts, gate, hidden, inter, shared, most):
-    """The register GEMM-1 that selects the experts itself (up to 4 tokens, 128 experts and 1760 workgroups, no groups) and the sizes past it: routing, tables and output as in
+    """The register and ring GEMM-1 that select the experts themselves (up to 4 tokens, 128 experts and 1760 workgroups, no groups) and the sizes past it: routing, tables and output as in
     the pass with separate selection and bookkeeping kernels, bit for bit, and through the entry that brings its placement along."""
     from gpu_util import Case, check_bookkeeping, check_output, check_routing
     from paper_2510_02613_amd import binding as B
@@ -99,6 +100,7 @@ def test_a_token_to_four_are_selected_in_gemm1(tokens, experts, gate, hidden, in
     g = np.random.Generator(np.random.PCG64(experts + tokens))
     case = Case(wl, expert_map=block_expert_map(experts, 0, local, g.permutation(local)))
     assert ("k_gate_select_hist" not in _kernels(case, tokens, wl.shared_range)) == (tokens <= most)
+    assert _expert_kernels(case, tokens, wl.shared_range) == ("k_expert_ring" if inter == 512 and tokens >= 4 else "k_expert_decode")
     runs = []
     for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED, 0):
         case.layer.workspace[int(B.moe_workspace_view(case.layer.handle).topk_ids - case.layer.workspace.data_ptr()):].fill_(0xee)
