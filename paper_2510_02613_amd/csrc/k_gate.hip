@@ -6,9 +6,9 @@
 // top-k (group score = sum of the group's two best), both with optional
 // renormalisation over the k selected and a constant scale.
 //
-// Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token (small
-// routers: one kernel for both): scores live in registers up to 512 experts and in LDS above, every arg-max is a
-// wavefront reduction in which ties go to the lower index exactly as the ordering rule demands.
+// Two kernels: logits (matrix cores, fp32 accumulation), then selection, one 64-lane wavefront per token (gate_select.h; small
+// routers: one kernel for both; a token to four: GEMM-1 selects): scores live in registers up to 512 experts and in LDS above,
+// every arg-max is a wavefront reduction in which ties go to the lower index exactly as the ordering rule demands.
 #include <type_traits>
 
 #include "gate_select.h"
@@ -37,7 +37,7 @@ constexpr int kThreads = 256;  // 4 wavefronts
 // through LDS -> 4 us; 1500 tokens of a 264-wide layer with 40 experts: 32 -> 7 us).
 //
 // k_gate_select.  One wavefront per token: scores, group limiting, top-k, weights
-// (select_token above).  Its reductions are latency chains, so it runs as many small
+// (select_token in gate_select.h).  Its reductions are latency chains, so it runs as many small
 // workgroups as possible and lets occupancy hide them.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
