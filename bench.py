@@ -25,6 +25,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -57,6 +58,23 @@ def source_hash(paths):
     return h.hexdigest()
 
 
+def kernel_sources():
+    """The sources of the expert kernels and of the tile list that they walk, with every header of this tree that they include,
+    directly or by way of another."""
+    csrc = os.path.join("paper_2510_02613_amd", "csrc")
+    todo = [os.path.join(csrc, f) for f in os.listdir(os.path.join(ROOT, csrc)) if f.startswith("k_experts") or f == "k_permute.hip"]
+    found = set()
+    while todo:
+        rel = todo.pop()
+        if rel in found:
+            continue
+        found.add(rel)
+        with open(os.path.join(ROOT, rel)) as f:
+            names = re.findall(r'^\s*#\s*include\s+"([^"]+)"', f.read(), re.M)
+        todo += [os.path.join(d, n) for n in names for d in (csrc, "include") if os.path.exists(os.path.join(ROOT, d, n))]
+    return sorted(found)
+
+
 def measured_traffic(workload):
     """Bytes per launch of the dominant kernel from profiles/traffic.json, or None when there is no record
     for this workload or the kernel's sources have changed since it was taken."""
@@ -75,9 +93,7 @@ def record_traffic(args):
     rocprofv3 --pmc run (KiB per launch of the dominant kernel, summed over its launches of one pass) with
     the hash of the kernel sources as they are now."""
     name, fetch_kib, write_kib, fs, ws_ = args.record_traffic
-    sources = sorted(os.path.join("paper_2510_02613_amd", "csrc", f)
-                     for f in os.listdir(os.path.join(ROOT, "paper_2510_02613_amd", "csrc"))
-                     if f.startswith("k_experts") or f in ("moe_internal.h", "self_tiles.h", "k_permute.hip"))
+    sources = kernel_sources()
     try:
         with open(TRAFFIC_FILE) as f:
             allrec = json.load(f)

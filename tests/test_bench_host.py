@@ -50,6 +50,23 @@ def test_committed_traffic_records_match_the_sources():
     assert bench.measured_traffic("tiny_f32") is None    # no record: null, not a guess
 
 
+def test_traffic_records_hash_every_file_that_the_expert_kernels_are_compiled_from():
+    """What the compiler itself reads of this tree for the GEMM kernels is what their records are hashed over: a change in a header
+    that only another header includes makes them stale too."""
+    from paper_2510_02613_amd import build
+    with open(bench.TRAFFIC_FILE) as f:
+        rec = json.load(f)
+    names = [s for s in build.sources() if os.path.basename(s).startswith("k_experts")]
+    assert names
+    for src in names:
+        r = subprocess.run([build.HIPCC, *build.FLAGS, "-H", "-fsyntax-only", "--cuda-device-only", src], capture_output=True, text=True, check=True)
+        read = [line.split(" ", 1)[1] for line in r.stderr.splitlines() if line.startswith(".")]       # "... path" of every file included
+        used = {os.path.relpath(p, ROOT) for p in [src, *read] if os.path.abspath(p).startswith(ROOT + os.sep)}
+        assert any(p.endswith("moe_internal.h") for p in used)
+        for name, one in rec.items():
+            assert used <= set(one["sources"]), (name, used - set(one["sources"]))
+
+
 def test_traffic_record_round_trip_and_staleness(tmp_path, monkeypatch):
     path = tmp_path / "traffic.json"
     monkeypatch.setattr(bench, "TRAFFIC_FILE", str(path))
