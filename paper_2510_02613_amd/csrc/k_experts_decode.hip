@@ -18,8 +18,8 @@
 // loads issued back to back, so every row contributes a contiguous 256-byte run per
 // chunk.  v_mfma_f32_16x16x32_bf16 with the weights as first operand gives lane
 // (j = l%16, q) the outputs of token j for weight rows 4q..4q+3: one 8-byte store.
-// The next chunk's loads are in flight during the current chunk's MFMAs; with 4
-// wavefronts per SIMD that keeps more than 128 KB per compute unit on its way from HBM.
+// The next chunk's loads are in flight during the current chunk's MFMAs: 8 KB of weights (and 4 KB of token rows, which mostly
+// come from L2) per wavefront, 96 to 128 KB of weights per compute unit with 12 to 16 wavefronts, 192 KB with 8 that are three chunks ahead (the forms below).
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -48,7 +48,7 @@ __device__ __forceinline__ void load_run(Run &r, const uint16_t *row, int k0, in
 
 constexpr int kBlocks2 = 2;   // 16-row weight blocks per task in GEMM-2
 // Wavefronts that share a task's contraction: each takes a contiguous quarter of the K-chunks, the first adds
-// the four sums in K order (through LDS) and stores.  A wavefront's stream is latency bound (one chunk in
+// the four sums in K order (through LDS) and stores.  A wavefront's stream is latency bound (one chunk or three in
 // flight), so a launch ends with a tail as long as one task in which ever fewer wavefronts stream; with four
 // wavefronts per task that tail is a quarter as long, and the tasks of a launch (several rounds of the chip's
 // wavefront slots in GEMM-2) are dealt to the compute units in finer pieces.  Measured on the DeepSeek-V3-shaped
@@ -56,12 +56,25 @@ constexpr int kBlocks2 = 2;   // 16-row weight blocks per task in GEMM-2
 constexpr int kSplit1 = 4;
 constexpr int kSplit2 = 4;
 
-// kAhead: K-chunks requested ahead of the one multiplied; the K loop is unrolled by one more, so that a chunk's registers are where the
-// MFMAs read them (copied from the prefetched chunk's after every step before: whole pass, us, copied -> unrolled, one ahead: one token of the
+// The K loop is unrolled over the chunk multiplied and those requested ahead of it, so that a chunk's registers are where the MFMAs read
+// them (copied from the prefetched chunk's after every step before: whole pass, us, copied -> unrolled, one ahead: one token of the
 // Qwen3 shape 30.7 -> 30.1, of the DeepSeek-V3-shaped rank 48.7 -> 46.3, two 50.9 -> 47.5, five on 16 of its experts 68.0 -> 65.3).
-// Three ahead where a wavefront's quarter of the contraction is more than eight chunks (rows of 7168: 46.3 -> 45.1, 47.5 -> 46.4, 65.3 -> 64.6;
-// rows of 2048, four chunks: one token 30.1 -> 30.4, three 55.1 -> 56.8; nothing was measured between).
-//
+// Three forms, by the length of the contraction:
+//  * kShort: one chunk ahead on four wavefronts per SIMD.  kMiddle: the same on three (held there: its registers would allow a fourth).  With one to three chunks a wavefront
+//    there is little to request ahead, and what hides a task's first loads is another task; with more the fourth wavefront only makes
+//    more rows be walked at a time.  128 experts, T tokens, us, one ahead on three -> on four wavefronts.  GEMM-2, rows of I: 264 wide, T = 16, H = 2056 20.4 ->
+//    19.1, T = 48 30.7 -> 27.6; 520, T = 16, H = 1032 21.6 -> 20.5, H = 2056 35.4 -> 35.2, T = 48 50.5 -> 51.5; 760 and more 48.2 -> 50.0, 70.9 -> 75.2
+//    (nothing between 520 and 760).  GEMM-1, rows of H: 264, T = 48 14.8 -> 14.2; 776 22.9 -> 22.2; 1032, I = 264 28.9 -> 28.2, I = 1032, T = 16 80.2 -> 79.3;
+//    1544, I = 264, T = 48 42.4 -> 43.5; 2056, I = 760 153 -> 158 (nothing between 1032 and 1544).  Whole pass, copied -> three everywhere -> the forms: 520 x 264, T = 48 40.7 -> 41.7
+//    -> 40.2; 2056 x 264 100.1 -> 101.3 -> 98.0; 2056 x 760 247.4 -> 237.4 -> 237.6.  What is left: 1032 x 520, T = 6 44.4 -> 43.2 -> 43.9.
+//  * kLong: three chunks ahead on two wavefronts per SIMD, GEMM-1 only.  Rows of 7168: one token 46.3 -> 44.6, five on 16 experts 66.7 -> 65.3, 64 tokens, I = 2040, 513 -> 508;
+//    6152, 24 tokens 550 -> 530; 5128 460 -> 445; 4104 339 -> 326; 3080 283 -> 274, but rows of 4096 and three tokens 78.1 -> 79.9, of 3072
+//    71.6 -> 75.2, of 2048 54.0 -> 58.5: what few tokens lose there is more than what many gain.
+enum Form { kShort, kMiddle, kLong };
+constexpr int kShort1 = 1280, kLong1 = 4096;   // GEMM-1: the last H of kShort and of kMiddle
+constexpr int kShort2 = 640;                   // GEMM-2: the last I of kShort
+constexpr int waves_of(int form) { return form == kShort ? 4 : form == kMiddle ? 3 : 2; }
+
 // Table (NoTable or TableArg, or none): GEMM-1 of a token to four selects its experts, behind the logits kernel alone.  The selection kernel is nothing but latency then (one
 // workgroup between two launches).  Every workgroup selects all tokens itself instead, a wavefront each, and workgroup 0 leaves the ids,
 // the weights and (tab) the placement in the workspace.  Whole pass, us, selection kernel -> here: one token of the Qwen3 shape 30.5 ->
@@ -71,8 +84,8 @@ constexpr int kSplit2 = 4;
 // rank one token 45.0 -> 45.0, two 46.2 -> 55.4): they keep their kernel, and so do more than 128 experts, which were not measured, and
 // more tokens: two a wavefront made five tokens of the DeepSeek-V2-Lite shape 90.5 -> 95.3, eight on 32 Qwen3 experts 34.9 -> 43.0.
 constexpr long long kSelectBlocks = 1760;
-template <bool kFirst, bool kSelf, int kAhead, typename... Table>
-__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) void k_expert_decode(Pass p, Table... tab)
+template <bool kFirst, bool kSelf, int kForm, typename... Table>
+__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) __attribute__((amdgpu_waves_per_eu(waves_of(kForm), waves_of(kForm)))) void k_expert_decode(Pass p, Table... tab)
 {
     constexpr bool kSelect = sizeof...(Table) == 1;
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
@@ -125,7 +138,7 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     const int chunks = (K + 127) >> 7, per = (chunks + NS - 1) / NS;
     const int kbeg = min(ks * per, chunks) * 128, kend = min(min((ks + 1) * per, chunks) * 128, K), kstep = 128;
     f32x4 acc_a = {0.f, 0.f, 0.f, 0.f}, acc_b = {0.f, 0.f, 0.f, 0.f};
-    constexpr int D = kAhead + 1;
+    constexpr int kAhead = kForm == kLong ? 3 : 1, D = kAhead + 1;
     Run ca[D], cb[D], cx[D];
     auto load_chunk = [&](int u, int k) {
         load_run(ca[u], wa, k, q, K);
@@ -184,11 +197,13 @@ __global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) v
     }
 }
 
-template <typename Table>
-void launch_select(const Pass &p, bool deep, dim3 grid, dim3 block, hipStream_t st, const Table &tab)
+// GEMM-1 with its table, if it selects
+template <bool kSelf, typename... Table>
+void launch_first(const Pass &p, dim3 grid, dim3 block, hipStream_t st, const Table &...tab)
 {
-    if (deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3, Table>), grid, block, 0, st, p, tab);
-    else      hipLaunchKernelGGL((k_expert_decode<true, true, 1, Table>), grid, block, 0, st, p, tab);
+    if (p.H <= kShort1)     hipLaunchKernelGGL((k_expert_decode<true, kSelf, kShort, Table...>), grid, block, 0, st, p, tab...);
+    else if (p.H <= kLong1) hipLaunchKernelGGL((k_expert_decode<true, kSelf, kMiddle, Table...>), grid, block, 0, st, p, tab...);
+    else                    hipLaunchKernelGGL((k_expert_decode<true, kSelf, kLong, Table...>), grid, block, 0, st, p, tab...);
 }
 
 }  // namespace
@@ -207,23 +222,18 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
         const int groups = (p.I + kWRows / 2 - 1) / (kWRows / 2);
         const int blocks = p.max_tiles * groups;
         const dim3 grid(blocks + (p.self_tiles ? 1 : 0)), block(kThreads * kSplit1);
-        const bool deep = p.H > 4096;   // see kAhead
-        if (p.self_select) {
-            if (p.host_table) {
-                TableArg tab;
-                for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
-                launch_select<TableArg>(p, deep, grid, block, st, tab);
-            } else {
-                launch_select<NoTable>(p, deep, grid, block, st, NoTable{});
-            }
-        } else if (p.self_tiles && deep) hipLaunchKernelGGL((k_expert_decode<true, true, 3>), grid, block, 0, st, p);
-        else if (p.self_tiles)           hipLaunchKernelGGL((k_expert_decode<true, true, 1>), grid, block, 0, st, p);
-        else if (deep)                   hipLaunchKernelGGL((k_expert_decode<true, false, 3>), grid, block, 0, st, p);
-        else                             hipLaunchKernelGGL((k_expert_decode<true, false, 1>), grid, block, 0, st, p);
+        if (p.self_select && p.host_table) {
+            TableArg tab;
+            for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
+            launch_first<true>(p, grid, block, st, tab);
+        } else if (p.self_select) launch_first<true>(p, grid, block, st, NoTable{});
+        else if (p.self_tiles)    launch_first<true>(p, grid, block, st);
+        else                      launch_first<false>(p, grid, block, st);
     } else {
         const int groups = (p.H + 16 * kBlocks2 - 1) / (16 * kBlocks2);
         const int blocks = p.max_tiles * groups;
-        hipLaunchKernelGGL((k_expert_decode<false, false, 1>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
+        if (p.I <= kShort2) hipLaunchKernelGGL((k_expert_decode<false, false, kShort>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
+        else                hipLaunchKernelGGL((k_expert_decode<false, false, kMiddle>), dim3(blocks), dim3(kThreads * kSplit2), 0, st, p);
     }
     return hipGetLastError();
 }

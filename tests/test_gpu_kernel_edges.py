@@ -118,6 +118,32 @@ def test_a_token_to_four_are_selected_in_gemm1(tokens, experts, gate, hidden, in
     np.testing.assert_array_equal(out.cpu().numpy().view(np.uint16).ravel(), np.asarray(runs[0][0]).view(np.uint16).ravel())
 
 
+@pytest.mark.parametrize("tokens", [3, 17, 40])
+@pytest.mark.parametrize("hidden,inter,first,second", [(1280, 640, 0, 0), (1288, 640, 1, 0), (1272, 648, 0, 1), (4096, 648, 1, 1), (4104, 72, 2, 0), (264, 264, 0, 0)])
+def test_register_kernels_at_the_ends_of_their_forms(tokens, hidden, inter, first, second):
+    """Contractions on both sides of the lines between the forms (wavefronts per SIMD, chunks ahead) of the register kernels: the form, tables and output as with
+    separate bookkeeping kernels, bit for bit, and within the oracle's bar."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing, kernels_of
+    from paper_2510_02613_amd import binding as B
+    # rows of 8 more than a multiple of 64 stay off the ring kernels; the others are too few tasks for them
+    wl = MoEWorkload(name="forms", tokens=tokens, hidden=hidden, inter=inter, n_experts=80, top_k=4, n_slots=14, n_local=14,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", seed=500 + hidden)
+    case = Case(wl, expert_map=block_expert_map(80, 0, 14, np.random.Generator(np.random.PCG64(hidden)).permutation(14)))
+    x, spare, runs = case.x_dev[:tokens], case.x_dev[:tokens].clone(), []
+    names = kernels_of(lambda s: case.layer.forward(x, out=spare, stream=s))
+    forms = [n.split("<")[1].rstrip(">").split(", ")[2] for n in names if n.startswith("k_expert_decode")]
+    assert forms == [str(first), str(second)]
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = case.run(flags=flags)
+        runs.append((out, case.layer.view(tokens)))
+    ids, _, _ = check_routing(case, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    check_bookkeeping(case, runs[0][1], tokens, (0, 0))
+    check_output(case, runs[0][0], ids)
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
