@@ -76,33 +76,26 @@ __device__ __forceinline__ void split3(const uint4 &lo4, const uint4 &hi4, bf16x
     ph = pack(h); pm = pack(m); pl = pack(l);
 }
 
-// NSW = 0: one ring of NS stages, a stage = the step's token rows + router rows.  NSW > 0: two rings -- NS stages of
-// token rows (each read once, from HBM), NSW <= NS of router rows (re-read by every workgroup, from L2): LDS then holds mostly
-// token rows in flight, which is what the HBM stream of x needs at large T * H.  Every wavefront copies its share of
-// both in every step, token rows first; its copies complete in order, so a step's router rows stand for its token rows, which were
-// issued a step or more earlier, and the count that the K loop waits for is one immediate.  (Half of the wavefronts copying token
-// rows and half router rows, each with a count of its own out of a switch: whole pass, us, that -> this: DeepSeek-V3-shaped, 16 experts,
-// 2500 tokens 398 -> 393, the logits 42 -> 37; rank, 512 tokens 502.7 -> 501; Qwen3 shape, 32 experts, 6000 tokens 195 -> 192.6, 64 experts, 1500 tokens
-// 162 -> 160.4; 4096 tokens 360 -> 360, DeepSeek-V3-shaped rank 8192 tokens 892 -> 893.)
-template <typename WT, int TBT, int EBT, int NS, int NW, int WM, int NSW>
+// One ring of NS stages, a stage = the step's token rows + router rows.  Every wavefront copies its share of both, so one count, an immediate of
+// the instruction, says that a step has landed.  Copies complete in order: a deeper ring for the token rows alone (each read once, from HBM; the router rows
+// come from L2) keeps no more of them on their way, unless half of the wavefronts copy token rows and half router rows.  In the largest tilings (three
+// stages of 48 KB) neither pays: gate phase, us, this -> four token stages, all wavefronts copying both -> four token stages, separate loaders:
+// DeepSeek-V3-shaped rank 8192 tokens 69.5 -> 70.0 -> 70.0, with 16 experts 67.0 -> 68.7 -> 69.0, 2500 tokens 37.2 -> 37.2 -> 37.4; Qwen3 shape 4096 tokens
+// 25.4 -> 25.6 -> 25.5; an fp32 router of 256 experts on rows of 7168, 4096 tokens 62.3 -> 63.9 -> 63.1.
+template <typename WT, int TBT, int EBT, int NS, int NW, int WM>
 __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
 {
     constexpr bool F32 = sizeof(WT) == 4;
-    constexpr bool TWO = NSW > 0;
     constexpr int kWaves = NW, WE = NW / WM;
     constexpr int TB = 16 * TBT * WM, EB = 16 * EBT * WE;
     constexpr int XBYTES = TB * 128, WROW = F32 ? 256 : 128, WBYTES = EB * WROW, STAGE = XBYTES + WBYTES;
     constexpr int XP = XBYTES / 1024, WP = WBYTES / 1024;   // 1 KB pieces: 8 rows of 128 B, or 4 rows of 256 B
-    constexpr int XPW = TWO ? XP / NW : 0, WPW = TWO ? WP / NW : 0;   // two rings: pieces of each per wavefront per K-step
     constexpr int PW = (XP + WP) / kWaves;                  // pieces per wavefront per K-step
-    static_assert(TWO || (XP + WP) % kWaves == 0, "pieces are dealt evenly to the wavefronts");
-    static_assert(!TWO || (XP % NW == 0 && WP % NW == 0 && NSW >= 2 && NS >= NSW), "pieces of both rings are dealt evenly to the wavefronts, token rows go first");
+    static_assert((XP + WP) % kWaves == 0, "pieces are dealt evenly to the wavefronts");
     static_assert(NS >= 2 && (NS - 2) * PW < 64, "load counter");
-    constexpr int LDS = TWO ? NS * XBYTES + NSW * WBYTES : NS * STAGE;
-    static_assert(LDS <= 160 * 1024, "rings fit LDS");
-    __shared__ __attribute__((aligned(1024))) char ring[LDS];
-    // single ring: stage s at s * STAGE, token rows first.  Two rings: token stages, then router stages.
-    constexpr int XSTRIDE = TWO ? XBYTES : STAGE, WSTRIDE = TWO ? WBYTES : STAGE, WRING0 = TWO ? NS * XBYTES : XBYTES;
+    constexpr int LDS = NS * STAGE;
+    static_assert(LDS <= 160 * 1024, "the ring fits LDS");
+    __shared__ __attribute__((aligned(1024))) char ring[LDS];   // a stage: token rows, then router rows
 
     const int E = p.E, H = p.H;
     const int lane = threadIdx.x & 63;
@@ -140,14 +133,12 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
         dst[i] = pc * 1024;
     }
     const uint32_t ring_a = lds_addr(ring);
-    // this wavefront's copies of token (x) or router rows for K-step kt into stage `slot` of their ring
-    auto issue = [&](int kt, int slot, bool x) {
+    // this wavefront's copies for K-step kt into stage `slot`
+    auto issue = [&](int kt, int slot) {
 #pragma unroll
         for (int i = 0; i < PW; ++i) {
-            if (isx[i] != x) continue;
-            const char *b = x ? xbase + (size_t)kt * (kBK * 2) : wbase + (size_t)kt * (kBK * (F32 ? 4 : 2));
-            const uint32_t stage = x ? slot * XSTRIDE : WRING0 + slot * WSTRIDE;
-            dma_piece(b, src[i], ring_a + stage + __builtin_amdgcn_readfirstlane(dst[i]));
+            const char *b = isx[i] ? xbase + (size_t)kt * (kBK * 2) : wbase + (size_t)kt * (kBK * (F32 ? 4 : 2));
+            dma_piece(b, src[i], ring_a + slot * STAGE + (isx[i] ? 0 : XBYTES) + __builtin_amdgcn_readfirstlane(dst[i]));
         }
     };
 
@@ -172,9 +163,9 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
 #pragma unroll
         for (int tb = 0; tb < TBT; ++tb) acc[a][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    auto multiply = [&](int xslot, int wslot) {
-        const char *W = ring + WRING0 + wslot * WSTRIDE + we * EBT * 16 * WROW;
-        const char *X = ring + xslot * XSTRIDE + wt * TBT * 16 * 128;
+    auto multiply = [&](int slot) {
+        const char *X = ring + slot * STAGE + wt * TBT * 16 * 128;
+        const char *W = ring + slot * STAGE + XBYTES + we * EBT * 16 * WROW;
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             bf16x8 xf[TBT];
@@ -207,26 +198,19 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
         }
     };
 
-    // ---- K loop: steps kt+1 .. kt+depth-1 of a ring are in flight while step kt is multiplied ----
-    constexpr int DX = NS, DW = TWO ? NSW : NS;
-    for (int s = 1 - DX; s < 0; ++s) {
-        if (kt0 + s + DX - 1 < kt1) issue(kt0 + s + DX - 1, s + DX - 1, true);
-        if (s + DW - 1 >= 0 && kt0 + s + DW - 1 < kt1) issue(kt0 + s + DW - 1, s + DW - 1, false);
-    }
-    int xs = 0, ws = 0, xfill = DX - 1, wfill = DW - 1;
+    // ---- K loop: steps kt+1 .. kt+NS-1 are in flight while step kt is multiplied ----
+    for (int s = 0; s < NS - 1 && kt0 + s < kt1; ++s) issue(kt0 + s, s);
+    int slot = 0, fill = NS - 1;
     for (int kt = kt0; kt < kt1; ++kt) {
-        // Behind step kt's router rows DW - 2 steps' copies were issued and may stay on their way; the last steps wait for all.  (Counted down
+        // Behind step kt's copies those of NS - 2 steps were issued and may stay on their way; the last steps wait for all.  (Counted down
         // exactly, by a switch over the immediates of the instruction, it was slower.)
-        if (kt + DX - 2 < kt1) wait_loads<(DW - 2) * PW>();
+        if (kt + NS - 2 < kt1) wait_loads<(NS - 2) * PW>();
         else                   wait_loads<0>();
         __syncthreads();   // everyone's pieces of step kt have landed; everyone is done reading step kt-1
-        if (kt + DX - 1 < kt1) issue(kt + DX - 1, xfill, true);
-        if (kt + DW - 1 < kt1) issue(kt + DW - 1, wfill, false);
-        multiply(xs, ws);
-        xs = xs + 1 == NS ? 0 : xs + 1;
-        ws = ws + 1 == (TWO ? NSW : NS) ? 0 : ws + 1;
-        xfill = xfill + 1 == DX ? 0 : xfill + 1;
-        wfill = wfill + 1 == DW ? 0 : wfill + 1;
+        if (kt + NS - 1 < kt1) issue(kt + NS - 1, fill);
+        multiply(slot);
+        slot = slot + 1 == NS ? 0 : slot + 1;
+        fill = fill + 1 == NS ? 0 : fill + 1;
     }
 
     // ---- epilogue: accumulators -> this wavefront's LDS region [token][expert] -> whole row segments ----
@@ -273,12 +257,12 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     }
 }
 
-template <typename WT, int TBT, int EBT, int NS, int NW, int WM, int NSW = 0>
+template <typename WT, int TBT, int EBT, int NS, int NW, int WM>
 hipError_t launch_t(const Pass &p, int planes, hipStream_t st)
 {
     constexpr int TB = 16 * TBT * WM, EB = 16 * EBT * (NW / WM);
     dim3 grid((p.T + TB - 1) / TB, (p.E + EB - 1) / EB, planes);
-    hipLaunchKernelGGL((k_gate_logits_dma<WT, TBT, EBT, NS, NW, WM, NSW>), grid, dim3(NW * 64), 0, st, p);
+    hipLaunchKernelGGL((k_gate_logits_dma<WT, TBT, EBT, NS, NW, WM>), grid, dim3(NW * 64), 0, st, p);
     return hipGetLastError();
 }
 
@@ -313,10 +297,9 @@ hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st)
     else if (p.E > 64 && tiles(64, 128) * splits_for(tiles(64, 128), KT) >= 192) cfg = 1;
     const int z = cfg == 2 ? splits_for(tiles(128, ebL), KT) : cfg == 1 ? splits_for(tiles(64, 128), KT) : splits_for(tiles(32, 64), KT);
     *planes = z;
-    // 128 x 256 (bf16 router) or 128 x 128 (fp32 router) on 8 wavefronts (2 x 4) with two rings: 4 stages of
-    // token rows (16 KB each), 3 of router rows (32 KB each); 64 x 128 on 8 wavefronts and 32 x 64 on 4, one ring
-    if (p.router_bf16) return cfg == 2 ? launch_t<uint16_t, 4, 4, 4, 8, 2, 3>(p, z, st) : cfg == 1 ? launch_t<uint16_t, 2, 2, 6, 8, 2>(p, z, st) : launch_t<uint16_t, 2, 1, 6, 4, 1>(p, z, st);
-    return cfg == 2 ? launch_t<float, 4, 2, 4, 8, 2, 3>(p, z, st) : cfg == 1 ? launch_t<float, 4, 1, 4, 8, 1>(p, z, st) : launch_t<float, 2, 1, 6, 4, 1>(p, z, st);
+    // 128 x 256 (bf16 router) or 128 x 128 (fp32 router) on 8 wavefronts (2 x 4), 64 x 128 on 8, 32 x 64 on 4
+    if (p.router_bf16) return cfg == 2 ? launch_t<uint16_t, 4, 4, 3, 8, 2>(p, z, st) : cfg == 1 ? launch_t<uint16_t, 2, 2, 6, 8, 2>(p, z, st) : launch_t<uint16_t, 2, 1, 6, 4, 1>(p, z, st);
+    return cfg == 2 ? launch_t<float, 4, 2, 3, 8, 2>(p, z, st) : cfg == 1 ? launch_t<float, 4, 1, 4, 8, 1>(p, z, st) : launch_t<float, 2, 1, 6, 4, 1>(p, z, st);
 }
 
 }  // namespace emoe

@@ -144,6 +144,23 @@ def test_register_kernels_at_the_ends_of_their_forms(tokens, hidden, inter, firs
         np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
 
 
+@pytest.mark.parametrize("router,experts", [("bf16", 200), ("f32", 100)])
+@pytest.mark.parametrize("hidden,tokens", [(64, 24460), (128, 24460), (192, 24460), (256, 24460), (320, 24460), (1024, 12300)])
+def test_largest_gate_tilings_at_few_steps(hidden, tokens, router, experts):
+    """The largest tilings of the direct-to-LDS gate logits kernel (128 tokens x 256 experts, 128 with an fp32 router; a ring of three stages) on contractions of 1 to 5
+    K-steps, shorter and longer than the ring, and of 8 in each of two K ranges; the last token and expert tiles are ragged.  Routing of every token against the oracle."""
+    from gpu_util import Case, check_routing, kernels_of
+    wl = MoEWorkload(name="gate_ring", tokens=tokens, hidden=hidden, inter=8, n_experts=experts, top_k=3, n_slots=2, n_local=2,
+                     act_dtype="bf16", router_dtype=router, gate="softmax", seed=40 + hidden)
+    case = Case(wl)
+    spare = case.x_dev.clone()
+    names = kernels_of(lambda s: case.layer.forward(case.x_dev, out=spare, stream=s))
+    assert any(n.startswith("k_gate_logits_dma") and n.rstrip(">").endswith(", 3, 8, 2") for n in names), names
+    case.run()
+    v = case.layer.view(tokens)
+    check_routing(case, v["topk_ids"], v["topk_w"])
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
