@@ -9,13 +9,13 @@ from workloads import MoEWorkload, make_inputs
 pytestmark = pytest.mark.gpu
 
 
-def _layer(wl, inp):
+def _layer(wl, inp, select_bias=None):
     from paper_2510_02613_amd.layer import MoELayer
     return MoELayer(hidden=wl.hidden, inter=wl.inter, n_experts=wl.n_experts, top_k=wl.top_k, n_slots=wl.n_slots,
                     max_tokens=wl.tokens, act_dtype=wl.act_dtype, router_dtype=wl.router_dtype, gate=wl.gate,
                     n_group=wl.n_group, topk_group=wl.topk_group, renormalize=wl.renormalize,
                     routed_scale=wl.routed_scale, n_shared=wl.n_shared, router_w=inp["router_w"],
-                    logit_bias=inp["logit_bias"])
+                    logit_bias=inp["logit_bias"], select_bias=select_bias)
 
 
 def _random_pool(g, shape, act):
@@ -114,6 +114,56 @@ def test_distinct_copies_follow_the_choice_rule(case):
     got = to_f64(out)
     assert np.isfinite(got).all()
     assert rel_err(got, want) <= TOL[act]
+    layer.close()
+
+
+@pytest.mark.parametrize("tokens", [1, 2, 3, 4])
+@pytest.mark.parametrize("experts,hidden,inter,shared,kernel", [(96, 136, 72, 2, "k_expert_decode"), (128, 1288, 24, 0, "k_expert_decode"), (66, 4160, 16, 1, "k_expert_decode"),
+                                                                (96, 64, 1600, 1, "k_expert_ring"), (128, 128, 1600, 0, "k_expert_ring")])
+def test_gemm1_that_selects_with_copies_and_a_selection_bias(tokens, experts, hidden, inter, shared, kernel):
+    """A token to four behind a softmax gate: GEMM-1 selects the experts itself.  Experts in up to three slots, each slot with weights of its own, and a bias that
+    changes the selection but not the weights: routing, tables and output as with separate selection and bookkeeping kernels, bit for bit, and within the oracle's bar."""
+    import torch
+    import oracle
+    from oracle import LayerSpec
+    from gpu_util import Case, check_routing, kernels_of, tensor_to_host, to_f64, rel_err, TOL
+    from paper_2510_02613_amd import binding as B
+    S = experts + 20
+    wl = MoEWorkload(name="select_copies", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=7, n_slots=S, n_local=1, act_dtype="bf16",
+                     router_dtype="f32", gate="softmax", n_shared=shared, shared_range=(0, min(tokens, 2) if shared else 0), seed=60 + experts)
+    g = np.random.Generator(np.random.PCG64(experts + hidden + tokens))
+    inp = make_inputs(wl)
+    bias = (g.standard_normal(experts) * 0.05).astype(np.float32)
+    replicas = _placement(g, experts, S, shared, 5, 3)
+    shared_slots = np.arange(S - shared, S, dtype=np.int32)
+    w13, w2 = _random_pool(g, (S, 2 * inter, hidden), "bf16"), _random_pool(g, (S, hidden, inter), "bf16")
+    layer = _layer(wl, inp, bias)
+    layer.load_pool(w13, w2)
+    layer.set_expert_replicas(replicas, shared_slots if shared else None)
+    x = layer.upload(inp["x"])
+    spare = x.clone()
+    names = [n.split("<")[0] for n in kernels_of(lambda s: layer.forward(x, out=spare, shared_range=wl.shared_range, stream=s))]
+    assert "k_gate_select_hist" not in names and next(n for n in names if "expert" in n) == kernel
+    runs = []
+    for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+        out = layer.forward(x, shared_range=wl.shared_range, flags=flags)
+        torch.cuda.synchronize()
+        runs.append((tensor_to_host(out), layer.view(tokens)))
+    np.testing.assert_array_equal(runs[0][0], runs[1][0])
+    for key in ("topk_ids", "topk_w", "counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+    c = Case.__new__(Case)
+    c.wl, c.inp, c.spec, c.select_bias = wl, inp, LayerSpec.from_workload(wl), bias
+    ids, _, _ = check_routing(c, runs[0][1]["topk_ids"], runs[0][1]["topk_w"])
+    slot = _slot_of(replicas, ids, tokens)
+    counts = np.bincount(slot[slot >= 0], minlength=S)
+    counts[S - shared:] += wl.shared_range[1]
+    np.testing.assert_array_equal(runs[0][1]["counts"], counts)
+    want = oracle.forward_replicated(c.spec, inp["x"], inp["router_w"], w13, w2, replicas, logit_bias=inp["logit_bias"], select_bias=bias,
+                                     shared_slots=shared_slots, shared_range=wl.shared_range, forced_ids=ids)
+    assert rel_err(to_f64(runs[0][0]), want) <= TOL["bf16"]
+    plain = oracle.route(c.spec, inp["x"], inp["router_w"], inp["logit_bias"], None)[0]
+    assert (np.sort(ids, 1) != np.sort(plain, 1)).any()          # the bias was used
     layer.close()
 
 
