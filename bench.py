@@ -597,7 +597,7 @@ def measure_ceilings(torch, B, layer, stream):
     out = {"mfma_bf16_tflops_constant_operands": flops / t_c / 1e12,
            "mfma_bf16_tflops_random_operands": flops / t_r / 1e12,
            "stream_read_gbs": reps * w_bytes / t_s / 1e9, "stream_bytes": w_bytes, "stream_reps": reps,
-           "note": "sustained rates of this chip: register-only v_mfma_f32_32x32x16_bf16 (8 wavefronts per workgroup) "
+           "note": "sustained rates of this chip: register-only v_mfma_f32_16x16x32_bf16 (8 wavefronts per workgroup) "
                    "on constant and on changing pseudo-random operands, a plain read of the W13 pool, and the same pool "
                    "read as the large-tile kernels' weight loaders read it (256-row tiles, 128 bytes per row per step, "
                    "global -> LDS, default and non-temporal)"}

@@ -319,7 +319,8 @@ moe_status_t moe_profile_read(moe_layer_t *layer, int32_t back, float *ms);
  * `hip_stream`; the caller times it.  `sink` is a device float the kernels may
  * write (they practically never do); nothing is allocated.
  *   moe_ceiling_mfma:   `blocks` workgroups of 8 wavefronts each run `iters` rounds of
- *                       8 independent register-only v_mfma_f32_32x32x16_bf16;
+ *                       16 independent register-only v_mfma_f32_16x16x32_bf16, each with one
+ *                       operand of the one before it;
  *                       *flops receives the flops of the launch.  random_operands != 0
  *                       multiplies pseudo-random values in (-1, 1) that change from one
  *                       MFMA to the next (the sustained rate under realistic switching

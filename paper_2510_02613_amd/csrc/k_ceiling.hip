@@ -8,21 +8,22 @@ namespace emoe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 512;        // 8 wavefronts, two per SIMD, as in the large-tile expert kernels
-constexpr int kChains = 8;           // independent accumulators per wavefront
+constexpr int kSide = 4;             // a wavefront's accumulators: kSide x kSide tiles of 16 x 16
 
-// Register-only v_mfma_f32_32x32x16_bf16 stream: `iters` rounds of kChains independent MFMAs.
+// Register-only v_mfma_f32_16x16x32_bf16 stream, the instruction of the expert kernels: `iters` rounds of kSide^2 independent MFMAs in the
+// kernels' order, each with one operand of the one before it.
 // `random_operands` != 0 feeds the multipliers pseudo-random values in (-1, 1) that change from
 // one MFMA to the next (the power such data draws is what sets the sustained clock of real
 // kernels); 0 feeds small constants (the issue-rate ceiling).
 __global__ __launch_bounds__(kThreads) void k_ceiling_mfma(int iters, int random_operands, float *sink)
 {
-    bf16x8 a[4], b[4];
+    bf16x8 a[kSide], b[kSide];
     uint32_t h = (threadIdx.x + 1u) * 0x9e3779b9u + blockIdx.x * 0x85ebca6bu;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < kSide; ++j)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             h = h * 1664525u + 1013904223u;
@@ -32,20 +33,28 @@ __global__ __launch_bounds__(kThreads) void k_ceiling_mfma(int iters, int random
             a[j][i] = (__bf16)ra;
             b[j][i] = (__bf16)rb;
         }
-    f32x16 acc[kChains];
+    f32x4 acc[kSide][kSide];
 #pragma unroll
-    for (int c = 0; c < kChains; ++c)
+    for (int t = 0; t < kSide; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[c][r] = 0.f;
+        for (int c = 0; c < kSide; ++c) acc[t][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int c = 0; c < kChains; ++c) acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c & 3], b[(c + (c >> 2)) & 3], acc[c], 0, 0, 0);
+        for (int t = 0; t < kSide; ++t)
+#pragma unroll
+            for (int i = 0; i < kSide; ++i) {
+                const int c = t & 1 ? kSide - 1 - i : i;
+                acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b[t], acc[t][c], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);   // in this order
+            }
     }
     float s = 0.f;
 #pragma unroll
-    for (int c = 0; c < kChains; ++c)
+    for (int t = 0; t < kSide; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s += acc[c][r];
+        for (int c = 0; c < kSide; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s += acc[t][c][r];
     if (s == 123456.789f) sink[0] = s;   // keeps the chains alive; practically never true
 }
 
@@ -99,7 +108,7 @@ __global__ __launch_bounds__(256) void k_ceiling_tile_stream(const char *buf, si
 
 }  // namespace
 
-double ceiling_mfma_flops(int blocks, int iters) { return (double)blocks * (kThreads / 64) * (double)iters * kChains * 2.0 * 32 * 32 * 16; }
+double ceiling_mfma_flops(int blocks, int iters) { return (double)blocks * (kThreads / 64) * (double)iters * kSide * kSide * 2.0 * 16 * 16 * 32; }
 
 hipError_t launch_ceiling_mfma(int blocks, int iters, int random_operands, float *sink, hipStream_t st)
 {
