@@ -325,6 +325,12 @@ __host__ __device__ inline int select_stride(int E) { return E <= 64 ? 64 : E <=
 // brings its placement along: the first workgroup then leaves it in the workspace too).
 struct NoTable {};
 struct TableArg { int32_t v[kTableArg]; };
+inline TableArg fill_table(const Pass &p)
+{
+    TableArg tab;
+    for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
+    return tab;
+}
 __device__ __forceinline__ void stage_table(const Pass &p, const NoTable &, int32_t *map, int threads)
 {
     for (int e = threadIdx.x; e < p.E + p.n_shared; e += threads) map[e] = p.map[e];

@@ -222,13 +222,10 @@ hipError_t launch_experts_decode(const Pass &p, int which, hipStream_t st)
         const int groups = (p.I + kWRows / 2 - 1) / (kWRows / 2);
         const int blocks = p.max_tiles * groups;
         const dim3 grid(blocks + (p.self_tiles ? 1 : 0)), block(kThreads * kSplit1);
-        if (p.self_select && p.host_table) {
-            TableArg tab;
-            for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
-            launch_first<true>(p, grid, block, st, tab);
-        } else if (p.self_select) launch_first<true>(p, grid, block, st, NoTable{});
-        else if (p.self_tiles)    launch_first<true>(p, grid, block, st);
-        else                      launch_first<false>(p, grid, block, st);
+        if (p.self_select && p.host_table) launch_first<true>(p, grid, block, st, fill_table(p));
+        else if (p.self_select)            launch_first<true>(p, grid, block, st, NoTable{});
+        else if (p.self_tiles)             launch_first<true>(p, grid, block, st);
+        else                               launch_first<false>(p, grid, block, st);
     } else {
         const int groups = (p.H + 16 * kBlocks2 - 1) / (16 * kBlocks2);
         const int blocks = p.max_tiles * groups;

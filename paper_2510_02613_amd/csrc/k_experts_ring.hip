@@ -238,9 +238,7 @@ hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStrea
         else            hipLaunchKernelGGL((k_expert_ring<false, false, 2>), grid, block, 0, st, p);
     } else if (which == 0) {
         if (p.self_select && p.host_table) {
-            TableArg tab;
-            for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
-            hipLaunchKernelGGL((k_expert_ring<true, true, 1, TableArg>), grid, block, 0, st, p, tab);
+            hipLaunchKernelGGL((k_expert_ring<true, true, 1, TableArg>), grid, block, 0, st, p, fill_table(p));
         } else if (p.self_select) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1, NoTable>), grid, block, 0, st, p, NoTable{});
         } else if (p.self_tiles) {

@@ -496,28 +496,20 @@ hipError_t launch_select_hist(const Pass &p, const Table &tab, hipStream_t st)
 }
 
 template <typename XT, typename WT>
-hipError_t launch_small_t(const Pass &p, hipStream_t st, const TableArg *tab)
+hipError_t launch_small_t(const Pass &p, hipStream_t st)
 {
     const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
     const size_t smem = sizeof(uint32_t) * p.S;
     if (!p.fused_hist) hipLaunchKernelGGL((k_gate_small<XT, WT, NoTable, false>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, NoTable{});
-    else if (tab) hipLaunchKernelGGL((k_gate_small<XT, WT, TableArg, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, *tab);
-    else     hipLaunchKernelGGL((k_gate_small<XT, WT, NoTable, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, NoTable{});
+    else if (p.host_table) hipLaunchKernelGGL((k_gate_small<XT, WT, TableArg, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, fill_table(p));
+    else hipLaunchKernelGGL((k_gate_small<XT, WT, NoTable, true>), dim3(nb), dim3(kFusedTokens * 64), smem, st, p, nb, NoTable{});
     return hipGetLastError();
-}
-
-void fill_table(const Pass &p, TableArg &tab)
-{
-    for (int i = 0; i < kTableArg; ++i) tab.v[i] = i < p.E + p.n_shared ? p.host_table[i] : -1;
 }
 
 hipError_t launch_gate_small(const Pass &p, hipStream_t st)
 {
-    TableArg arg;
-    if (p.host_table) fill_table(p, arg);
-    const TableArg *tab = p.host_table ? &arg : nullptr;
-    if (p.act_bf16) return p.router_bf16 ? launch_small_t<uint16_t, uint16_t>(p, st, tab) : launch_small_t<uint16_t, float>(p, st, tab);
-    return p.router_bf16 ? launch_small_t<float, uint16_t>(p, st, tab) : launch_small_t<float, float>(p, st, tab);
+    if (p.act_bf16) return p.router_bf16 ? launch_small_t<uint16_t, uint16_t>(p, st) : launch_small_t<uint16_t, float>(p, st);
+    return p.router_bf16 ? launch_small_t<float, uint16_t>(p, st) : launch_small_t<float, float>(p, st);
 }
 
 hipError_t launch_select(const Pass &p, hipStream_t st)
@@ -526,11 +518,7 @@ hipError_t launch_select(const Pass &p, hipStream_t st)
         // the two forms are alike up to 4096 tokens (logits and selection of 256 experts 21.7 us both); 5000: 32.9 against 30.7,
         // 8192: 31.0 against 29.0
         const bool many = p.T > 2048;
-        if (p.host_table) {
-            TableArg arg;
-            fill_table(p, arg);
-            return many ? launch_select_hist<true>(p, arg, st) : launch_select_hist<false>(p, arg, st);
-        }
+        if (p.host_table) return many ? launch_select_hist<true>(p, fill_table(p), st) : launch_select_hist<false>(p, fill_table(p), st);
         return many ? launch_select_hist<true>(p, NoTable{}, st) : launch_select_hist<false>(p, NoTable{}, st);
     }
     const size_t smem = sizeof(float) * 4 * 2 * (size_t)select_stride(p.E);
