@@ -1,5 +1,5 @@
 // Selection of a token's experts by one wavefront, and the look-up of their slots: shared by the selection kernels (k_gate.hip)
-// and by the few-token GEMM-1 that selects itself (k_experts_decode.hip).  Sec. 2.1 of the paper (gating) and 3.2 / 4.6 (placement is
+// and by the few-token GEMM-1 that selects itself (k_experts_decode.hip, k_experts_ring.hip).  Sec. 2.1 of the paper (gating) and 3.2 / 4.6 (placement is
 // data); the rules are described in k_gate.hip.
 #pragma once
 #include "moe_internal.h"

@@ -80,8 +80,11 @@ constexpr int waves_of(int form) { return form == kShort ? 4 : form == kMiddle ?
 // the weights and (tab) the placement in the workspace.  Whole pass, us, selection kernel -> here: one token of the Qwen3 shape 30.5 ->
 // 27.4, three 55.3 -> 53.6, four on 32 of its experts 32.4 -> 29.1 (1536 workgroups); DeepSeek-V2-Lite shape two tokens 52.3 -> 50.3, on
 // 16 of its experts one 27.4 -> 25.1, four 38.4 -> 36.7 (1760 workgroups).  A workgroup pays 1 to 2 us for it, one that finds no tile too, so
-// there is a limit on their number; nothing was measured above it.  Group-limited gates take several times as long to select (DeepSeek-V3-shaped
-// rank one token 45.0 -> 45.0, two 46.2 -> 55.4): they keep their kernel, and so do more than 128 experts, which were not measured, and
+// there is a limit on their number.  Rows of 2048, 16 experts of 128 here, so that most workgroups find no tile: 1728 workgroups 32.5 -> 31.8, 2048 29.2 -> 29.2, 2304 33.0 ->
+// 36.7, 2560 31.3 -> 35.0, 3456 42.7 -> 49.6; all 128 here, whose weight stream hides it: 2112 94.2 -> 92.1, 3072 125.4 -> 123.6, 4096 151.0 -> 150.1.  The ring
+// kernels, the same line: 1536 workgroups, all experts here 187 -> 182, 1088, 16 experts here 58.9 -> 56.7; 2048, all here 273.6 -> 270.6, half of them 103.2 -> 105.0, 4096 185 -> 200.  Group-limited gates take several times as long to select (DeepSeek-V3-shaped
+// rank one token 45.0 -> 45.0, two 46.2 -> 55.4): they keep their kernel, and so do
+// more than 128 experts (256 in GEMM-1, four scores a lane, not taken up: rows of 2048, one token 30.7 -> 27.6, four 64.9 -> 61.9, on 32 of them one 21.0 -> 18.8, four 25.0 -> 25.5) and
 // more tokens: two a wavefront made five tokens of the DeepSeek-V2-Lite shape 90.5 -> 95.3, eight on 32 Qwen3 experts 34.9 -> 43.0.
 constexpr long long kSelectBlocks = 1760;
 template <bool kFirst, bool kSelf, int kForm, typename... Table>

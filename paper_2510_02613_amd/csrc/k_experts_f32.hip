@@ -159,8 +159,8 @@ __global__ __launch_bounds__(64 * kSplit) void k_expert_f32(Pass p)
 // lines, once per workgroup, into an LDS tile of 32 k (registers in between: a ragged contraction is zero filled there), the
 // next tile's loads in flight during this one's MFMAs.  Tasks are small, so that a launch has several per compute unit to deal
 // out (64 weight rows: +4 %); two K-steps of loads in flight instead of one changed nothing (+-2 %).  One LDS tile of 12 KB and a second
-// barrier a step, not two tiles: eight tasks run beside each other instead of six, and whoever waits at a barrier has seven others to wait
-// beside (whole pass, us, two tiles -> one: 1500 tokens 57.9 -> 56.2, 400 38.3 -> 37.4, 2500 76.1 -> 75.2, 512 x 256, 1500 tokens 82.4 -> 80.2).
+// barrier a step, not two tiles: seven tasks run beside each other instead of six (72 registers a lane are the limit now; a launch bound of eight spills), and whoever
+// waits at a barrier has six others to wait beside (whole pass, us, two tiles -> one: 1500 tokens 57.9 -> 56.2, 400 38.3 -> 37.4, 2500 76.1 -> 75.2, 512 x 256, 1500 tokens 82.4 -> 80.2).
 // Not multiplying the half of the last K-step that a ragged contraction leaves empty changed nothing: it is the loads that bound it.
 // An XCD takes a contiguous run of tasks (GEMM-2 20.5 -> 18.2 us).
 // The contraction is summed in the same four parts as above (a flush every quarter), so both kernels give the same bits.

@@ -33,7 +33,8 @@
 // wavefronts per SIMD so that one's LDS waits hide under the other's MFMAs.
 //
 // v_mfma_f32_16x16x32_bf16, not 32x32x16.  With hundreds of token rows a slot this chip runs at its power limit
-// (1400 W; the whole pass of the Qwen3 shape draws 1370 and more), so that a kernel's time follows from the energy it spends.
+// (whole passes draw 1350 to 1397 W of 1400), so that part of a kernel's time follows from the energy it spends: on zero operands, at 960 to 1120 W, GEMM-1 of the
+// Qwen3 shape, 256 rows, takes 170 us instead of 206, of the DeepSeek-V3-shaped rank 478 instead of 518, of the DeepSeek-V2-Lite shape, 167 rows, 187 instead of 203.
 // Per product the 16x16x32 form reads and writes half as many accumulators: a register-only stream of it on
 // the layer's operands sustains 2.14 PFLOP/s at 1326 W, one of the 32x32x16 form 1.88 at 1300 W.  LDS operand
 // reads per product are the same.  Whole pass of routed tokens, the same rows in every slot, us, 32x32x16 -> 16x16x32: Qwen3

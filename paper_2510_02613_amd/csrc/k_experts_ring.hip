@@ -186,7 +186,7 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
 // kTiles: the most token tiles of 32 rows an M-tile has.
 // Table (NoTable or TableArg, or none): GEMM-1 of a token to four selects the experts too (see k_experts_decode.hip).  Whole pass, us, selection kernel -> here: Qwen3
 // shape two tokens 39.7 -> 36.9, four 63.7 -> 61.0, four on half of its experts 36.0 -> 33.3; DeepSeek-V2-Lite shape three tokens 68.7 -> 66.2, four
-// 75.2 -> 72.5.
+// 75.2 -> 72.5.  The limit on the workgroups is the register kernels', measured for both there.
 template <bool kFirst, bool kSelf, int kTiles, typename... Table>
 __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... tab)
 {

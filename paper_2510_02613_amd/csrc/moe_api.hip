@@ -176,7 +176,7 @@ struct moe_layer {
     struct Fill { hipEvent_t ev; void *stream; };
     std::vector<Fill> load_ev;
     int n_pending = 0;
-    const int32_t *table_arg = nullptr;   // host table of a moe_forward_static pass whose selection kernel installs it
+    const int32_t *table_arg = nullptr;   // host table of a moe_forward_static pass whose selecting kernel installs it
     hipEvent_t serve_ev = nullptr;  // "work enqueued on the serving stream so far", recorded by a fill that has to wait for it
     // whether a fill asks first if the serving stream has anything left (serve_pending below); a pass or a switch resets it
     std::atomic<bool> ask_serve{false};
@@ -877,7 +877,7 @@ moe_status_t moe_forward_static(const moe_config_t *cfg, const moe_buffers_t *bu
     lay.has_map = true;
     lay.slots_used = slots_in_use(owner, c.n_slots);
     // every pass writes what it reads (table, histograms, tile list, h, y): nothing has to start at zero
-    // the table comes in with the selection kernel when that kernel ranks the assignments too and it fits an argument
+    // the table comes in with the kernel that selects when that kernel ranks the assignments too, or derives the tiles, and it fits an argument
     if (T <= kFusedMaxTokens && T <= (long long)L.logit_tokens && !(flags & MOE_FLAG_PERMUTE_UNFUSED) && c.n_experts + c.n_shared <= kTableArg) {
         lay.table_arg = table;
     } else {

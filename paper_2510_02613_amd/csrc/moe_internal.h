@@ -87,12 +87,12 @@ struct Pass {
     int32_t max_tiles;
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
     int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 and k_token_experts only: their workgroups derive their tile from the selection kernel's per-block counts and
-                         // masks themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
+                         // masks (self_select: from their own selection) themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
     int32_t self_select; // GEMM-1 selects the experts itself from the logits (a token to four): no selection kernel
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
     float *partials;     // partial sums of the large-tile GEMMs' split tiles, or NULL (no room: never split)
-    const int32_t *host_table;   // HOST address of the expert table when the selection kernel is to carry it in as an argument (moe_forward_static), else NULL
+    const int32_t *host_table;   // HOST address of the expert table when the kernel that selects (selection kernel, k_gate_small, GEMM-1 of a token to four) is to carry it in as an argument (moe_forward_static), else NULL
     int32_t n_cus;       // compute units of the device (set by the large-tile launcher)
     int32_t k_split;     // this launch may share the contraction of its last round's tiles out (set by the launcher)
 };

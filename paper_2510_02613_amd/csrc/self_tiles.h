@@ -38,7 +38,7 @@ struct SelfTables {
     __device__ __forceinline__ uint32_t mask(const Pass &p, int s, int b, int nb) const { return (uint32_t)p.blk_hist[(size_t)s * fused_row_stride(nb) + b]; }
     __device__ __forceinline__ int slot_rank(const Pass &p, int a) const { return p.slot_rank[a]; }
 };
-// or LDS, where the workgroup has selected the (at most 16) tokens' experts itself:
+// or LDS, where the workgroup has selected the (at most kSelectTokens) tokens' experts itself:
 struct SelfLds {
     const uint32_t *masks;     // per slot
     const int32_t *ranks;      // per assignment: slot << 12 | rank, or -1 (the workgroup that writes the tables)
