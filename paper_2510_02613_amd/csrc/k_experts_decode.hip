@@ -60,16 +60,18 @@ constexpr int kSplit2 = 4;
 // them (copied from the prefetched chunk's after every step before: whole pass, us, copied -> unrolled, one ahead: one token of the
 // Qwen3 shape 30.7 -> 30.1, of the DeepSeek-V3-shaped rank 48.7 -> 46.3, two 50.9 -> 47.5, five on 16 of its experts 68.0 -> 65.3).
 // Three forms, by the length of the contraction:
-//  * kShort: one chunk ahead on four wavefronts per SIMD.  kMiddle: the same on three (held there: its registers would allow a fourth).  With one to three chunks a wavefront
+//  * kShort: one chunk ahead on four wavefronts per SIMD.  kMiddle: the same on three (134 to 138 registers; never more, should a compiler find fewer).  With one to three chunks a wavefront
 //    there is little to request ahead, and what hides a task's first loads is another task; with more the fourth wavefront only makes
 //    more rows be walked at a time.  128 experts, T tokens, us, one ahead on three -> on four wavefronts.  GEMM-2, rows of I: 264 wide, T = 16, H = 2056 20.4 ->
 //    19.1, T = 48 30.7 -> 27.6; 520, T = 16, H = 1032 21.6 -> 20.5, H = 2056 35.4 -> 35.2, T = 48 50.5 -> 51.5; 760 and more 48.2 -> 50.0, 70.9 -> 75.2
 //    (nothing between 520 and 760).  GEMM-1, rows of H: 264, T = 48 14.8 -> 14.2; 776 22.9 -> 22.2; 1032, I = 264 28.9 -> 28.2, I = 1032, T = 16 80.2 -> 79.3;
 //    1544, I = 264, T = 48 42.4 -> 43.5; 2056, I = 760 153 -> 158 (nothing between 1032 and 1544).  Whole pass, copied -> three everywhere -> the forms: 520 x 264, T = 48 40.7 -> 41.7
-//    -> 40.2; 2056 x 264 100.1 -> 101.3 -> 98.0; 2056 x 760 247.4 -> 237.4 -> 237.6.  What is left: 1032 x 520, T = 6 44.4 -> 43.2 -> 43.9.
+//    -> 40.2; 2056 x 264 100.1 -> 101.3 -> 98.0; 2056 x 760 247.4 -> 237.4 -> 237.6.  What is left: 1032 x 520, T = 6 44.4 -> 43.2 -> 43.9; a little over one round of
+//    four (the Qwen3 shape, 32 of its experts, T = 16 to 28) 48.9 -> 49.3 -> 49.3, where GEMM-2 on four would be 48.4, but three tokens 54.2 -> 54.4 and five 78.1 -> 78.7.
 //  * kLong: three chunks ahead on two wavefronts per SIMD, GEMM-1 only.  Rows of 7168: one token 46.3 -> 44.6, five on 16 experts 66.7 -> 65.3, 64 tokens, I = 2040, 513 -> 508;
 //    6152, 24 tokens 550 -> 530; 5128 460 -> 445; 4104 339 -> 326; 3080 283 -> 274, but rows of 4096 and three tokens 78.1 -> 79.9, of 3072
-//    71.6 -> 75.2, of 2048 54.0 -> 58.5: what few tokens lose there is more than what many gain.
+//    71.6 -> 75.2, of 2048 54.0 -> 58.5: what few tokens lose there is more than what many gain.  Workgroups that
+//    find no tile take their turn two to a compute unit: where none of a token's or two's experts are here, 15.6 -> 16.4, 18.2 -> 19.8 (on three wavefronts 15.9, 18.8).
 enum Form { kShort, kMiddle, kLong };
 constexpr int kShort1 = 1280, kLong1 = 4096;   // GEMM-1: the last H of kShort and of kMiddle
 constexpr int kShort2 = 640;                   // GEMM-2: the last I of kShort
@@ -88,7 +90,7 @@ constexpr int waves_of(int form) { return form == kShort ? 4 : form == kMiddle ?
 // more tokens: two a wavefront made five tokens of the DeepSeek-V2-Lite shape 90.5 -> 95.3, eight on 32 Qwen3 experts 34.9 -> 43.0.
 constexpr long long kSelectBlocks = 1760;
 template <bool kFirst, bool kSelf, int kForm, typename... Table>
-__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) __attribute__((amdgpu_waves_per_eu(waves_of(kForm), waves_of(kForm)))) void k_expert_decode(Pass p, Table... tab)
+__global__ __launch_bounds__(kFirst ? kThreads * kSplit1 : kThreads * kSplit2) __attribute__((amdgpu_waves_per_eu(kForm == kShort ? waves_of(kForm) : 1, waves_of(kForm)))) void k_expert_decode(Pass p, Table... tab)
 {
     constexpr bool kSelect = sizeof...(Table) == 1;
     static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
