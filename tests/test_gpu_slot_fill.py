@@ -71,7 +71,9 @@ def test_fill_of_a_live_slot_and_same_stream_are_rejected():
 def test_copy_blocks_throttle_a_fill():
     """A workgroup of a throttled fill is 256 threads with one 16-byte piece on its way each: 4 KB per memory round trip,
     9 GB/s where that takes 430 ns.  One of them may not move 16 GB/s (250 ns); without a throttle a fill moves much more.
-    Any number of workgroups copies whole slots, also where they divide unevenly."""
+    (The source has to come from memory: out of an XCD's L2, where a fill before it has left it, a round trip takes 250 to 265 ns,
+    15.2 to 16.2 GB/s, on the limit; a write of 512 MB, twice what the caches hold, puts it out of them: 8.8 to 9.3.)  Any number
+    of workgroups copies whole slots, also where they divide unevenly."""
     import torch
     from gpu_util import Case
     wl = MoEWorkload(name="fill_rate", tokens=16, hidden=1024, inter=520, n_experts=8, top_k=2, n_slots=8, n_local=4,
@@ -80,10 +82,10 @@ def test_copy_blocks_throttle_a_fill():
     copy = torch.cuda.Stream()
     w13, w2 = (torch.randint(-2**15, 2**15, t.shape, dtype=torch.int16, device=t.device) for t in (case.layer.w13[0], case.layer.w2[0]))
     nbytes = 2 * (w13.numel() + w2.numel())
-    rate = {}
+    rate, elsewhere = {}, torch.empty(1 << 27, dtype=torch.int32, device=w13.device)
     for blocks in (1, 0, 3, 1000):
         for _ in range(2):                                   # the second one is timed
-            case.layer.w13[6].zero_(), case.layer.w2[6].zero_()
+            case.layer.w13[6].zero_(), case.layer.w2[6].zero_(), elsewhere.fill_(blocks)
             torch.cuda.synchronize()
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record(copy)
