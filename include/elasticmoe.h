@@ -300,9 +300,10 @@ moe_status_t moe_workspace_view(const moe_layer_t *layer, moe_workspace_view_t *
  * (0 = most recent) and writes the milliseconds of each phase to ms[MOE_N_PHASES].
  * Launches that do several phases' work count as the first of them: GEMM1 is all of the
  * experts and the combine where a small layer goes token by token, GEMM2 has the combine
- * in passes of a token or two; the phases behind then read the events' own cost.  One
- * launch counts as the later of its phases: a GEMM-1 that selects the experts itself (a
- * token to four) is GEMM1 selection included, GATE is then the logits alone.
+ * in passes of a token or two; the phases behind then read the events' own cost.  Two
+ * launches count as the later of their phases: a GEMM-1 that selects the experts itself (a
+ * token to four) is GEMM1 selection included, GATE is then the logits alone; a small layer's
+ * whole pass in one launch is GEMM1, GATE then reads the events' own cost.
  * Enabling creates the events (host objects), disabling or destroying the layer
  * destroys them.  moe_profile_select(phase) restricts the recording to the two events
  * around ONE phase (moe_profile_read then writes 0 for the others), -1 (the default)

@@ -21,15 +21,19 @@ __device__ __forceinline__ unsigned long long make_key(float score, int idx)
 }
 __device__ __forceinline__ int key_index(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)(key & 0xffffffffull)); }
 
-// Lane j < k holds the j-th selected expert and its score: ids and combine weights of the token (store: they go to the workspace).
-__device__ __forceinline__ void finish_token(const Pass &p, int t, int lane, int my_id, float my_s, bool store)
+// Lane j < k holds the j-th selected expert and its score: ids and combine weights of the token (store: they go to the workspace;
+// keep: where the weights go as well, or NULL).
+__device__ __forceinline__ void finish_token(const Pass &p, int t, int lane, int my_id, float my_s, bool store, float *keep = nullptr)
 {
-    if (!store) return;   // uniform
+    if (!store && !keep) return;   // uniform
     const float sum = wave_sum_f32(lane < p.k ? my_s : 0.f);
     if (lane < p.k) {
-        const float wv = p.renormalize ? my_s / sum : my_s;
-        p.ids[(size_t)t * p.k + lane] = my_id;
-        p.w[(size_t)t * p.k + lane] = wv * p.routed_scale;
+        const float wv = (p.renormalize ? my_s / sum : my_s) * p.routed_scale;
+        if (store) {
+            p.ids[(size_t)t * p.k + lane] = my_id;
+            p.w[(size_t)t * p.k + lane] = wv;
+        }
+        if (keep) keep[lane] = wv;
     }
 }
 
@@ -140,7 +144,7 @@ __device__ __forceinline__ float dpp_f32(float v) { return __int_as_float(dpp_i3
 // is a wavefront maximum over the lanes' heads.
 //   v    : logits of this lane's experts      lg : LDS [64 NR] scratch, scores out      cs : LDS [64 NR] scratch
 template <int NR>
-__device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR], float *lg, float *cs, int lane, bool store = true)
+__device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR], float *lg, float *cs, int lane, bool store = true, float *keep = nullptr)
 {
     constexpr int kOrderBits = NR <= 4 ? 2 : 3;
     static_assert(NR <= 8, "a lane's order of experts is kept in fields of 2 or 3 bits");
@@ -262,7 +266,69 @@ __device__ __forceinline__ int select_regs(const Pass &p, int t, float (&v)[NR],
         for (int i = 0; i < NR; ++i) c[i] = took ? (i + 1 < NR ? c[i + 1 < NR ? i + 1 : i] : 0u) : c[i];
         order = took ? order >> kOrderBits : order;
     }
-    finish_token(p, t, lane, my_id, lane < p.k && !none ? lg[my_id] : 0.f, store);
+    finish_token(p, t, lane, my_id, lane < p.k && !none ? lg[my_id] : 0.f, store, keep);
+    return my_id;
+}
+
+// The same selection with a token on each group of L = 16 or 32 lanes (gates without groups, at most L experts, an expert per lane; L <= 32): v
+// is the logit of expert `sub` of the lane's token t.  The sums run in select_regs's order, so ids and weights have the same bits; a wavefront selects 64 / L
+// tokens with little more instructions than one.  active: the lane's token exists.
+template <int L>
+__device__ __forceinline__ int select_lanes(const Pass &p, int t, float v, int lane, bool active, bool store, float *keep)
+{
+    static_assert(L == 16 || L == 32, "groups of whole rows of 16 lanes");
+    const int sub = lane & (L - 1);
+    const float NEG = -__builtin_huge_valf();
+    auto sum = [&](float s) {                 // in the group's last lane, from there to all of them
+#define STEP(CTRL, MASK) s += __int_as_float(dpp_i32<CTRL, MASK>(0, __float_as_int(s)));
+        STEP(0x111, 0xf) STEP(0x112, 0xf) STEP(0x114, 0xf) STEP(0x118, 0xf)
+        if (L == 32) { STEP(0x142, 0xa) }
+#undef STEP
+        return __shfl(s, L - 1, L);
+    };
+    auto most = [&](uint32_t m) {             // row_ror 8, 4, 2, 1
+        m = max(m, (uint32_t)dpp_i32<0x128, 0xf>(0, (int)m));
+        m = max(m, (uint32_t)dpp_i32<0x124, 0xf>(0, (int)m));
+        m = max(m, (uint32_t)dpp_i32<0x122, 0xf>(0, (int)m));
+        m = max(m, (uint32_t)dpp_i32<0x121, 0xf>(0, (int)m));
+        if (L == 32) m = max(m, (uint32_t)__shfl_xor((int)m, 16, 64));
+        return m;
+    };
+    const bool is = sub < p.E;
+    if (p.gate == MOE_GATE_SOFTMAX_TOPK) {
+        float m = is ? v : NEG;
+        m = fmaxf(m, dpp_f32<0x128>(m));
+        m = fmaxf(m, dpp_f32<0x124>(m));
+        m = fmaxf(m, dpp_f32<0x122>(m));
+        m = fmaxf(m, dpp_f32<0x121>(m));
+        if (L == 32) m = fmaxf(m, __shfl_xor(m, 16, 64));
+        v = __expf(v - m);
+        v = v / sum(is ? v : 0.f);
+    } else {
+        v = __builtin_amdgcn_rcpf(1.f + __expf(-v));
+    }
+    const float score = v;
+    v = is ? v + (p.select_bias ? p.select_bias[sub] : 0.f) : NEG;
+    uint32_t c = v != NEG ? orderable(v) : 0u;
+    int my_id = 0;
+    bool none = false;
+    for (int j = 0; j < p.k; ++j) {
+        const uint32_t m = most(c);
+        const uint32_t holders = (uint32_t)(__ballot(c == m && m != 0u) >> (lane & (64 - L))) & (uint32_t)((1ull << L) - 1ull);
+        const int win = __ffs((int)holders) - 1;   // equal scores: the lower expert; -1: no candidate left
+        if (sub == j) { my_id = win < 0 ? 0 : win; none = win < 0; }
+        c = sub == win ? 0u : c;
+    }
+    const float got = __shfl(score, my_id, L), my_s = sub < p.k && !none ? got : 0.f;
+    const float total = sum(my_s);
+    if (active && sub < p.k) {
+        const float wv = (p.renormalize ? my_s / total : my_s) * p.routed_scale;
+        if (store) {
+            p.ids[(size_t)t * p.k + sub] = my_id;
+            p.w[(size_t)t * p.k + sub] = wv;
+        }
+        if (keep) keep[sub] = wv;
+    }
     return my_id;
 }
 

@@ -12,6 +12,7 @@
 #include <type_traits>
 
 #include "gate_select.h"
+#include "gate_small.h"
 #include "moe_internal.h"
 #include "wave_ops.h"
 
@@ -39,9 +40,6 @@ constexpr int kThreads = 256;  // 4 wavefronts
 // k_gate_select.  One wavefront per token: scores, group limiting, top-k, weights
 // (select_token in gate_select.h).  Its reductions are latency chains, so it runs as many small
 // workgroups as possible and lets occupancy hide them.
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
 template <typename WT> struct RouterRun;           // the lane's 32 k of one row
 template <> struct RouterRun<uint16_t> { uint4 v[4]; };
 template <> struct RouterRun<float> { uint4 v[8]; };
@@ -80,29 +78,6 @@ __device__ __forceinline__ void widen(const RouterRun<float> &r, float (&f)[32])
 {
 #pragma unroll
     for (int e = 0; e < 32; ++e) f[e] = ((const float *)&r.v[0])[e];
-}
-
-// 8 consecutive elements of a row (zeros past the end)
-template <typename T> struct Run8 { uint4 v[sizeof(T) / 2]; };
-template <typename T>
-__device__ __forceinline__ void load_run8(Run8<T> &r, const T *row, int k, int H)
-{
-#pragma unroll
-    for (int h = 0; h < (int)sizeof(T) / 2; ++h) r.v[h] = k < H ? *(const uint4 *)(row + k + h * (16 / sizeof(T))) : make_uint4(0, 0, 0, 0);
-}
-__device__ __forceinline__ void widen8(const Run8<uint16_t> &r, float (&f)[8])
-{
-    const uint32_t *u = (const uint32_t *)&r.v[0];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        f[2 * e] = __uint_as_float(u[e] << 16);
-        f[2 * e + 1] = __uint_as_float(u[e] & 0xffff0000u);
-    }
-}
-__device__ __forceinline__ void widen8(const Run8<float> &r, float (&f)[8])
-{
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = ((const float *)&r.v[0])[e];
 }
 
 template <typename XT, typename WT>
@@ -387,61 +362,28 @@ __global__ __launch_bounds__(kFusedTokens * 64) __attribute__((amdgpu_waves_per_
 // multiplies expert tile w mod n_et with its share of the contraction, the shares are added in K order.
 // 64 tokens of the 128 x 64 fp32 layer: 8.3 us in two launches -> 5 us.
 // kRank = false: the selection alone (the bookkeeping of the pass is separate).
-constexpr int kSmallExperts = 64, kSmallHidden = 512;
-constexpr int kSmallChunks = kSmallHidden / 32 / (kFusedTokens / (kSmallExperts / 16));   // most chunks of 32 k a wavefront has: 4
 template <typename XT, typename WT, typename Table, bool kRank>
 __global__ __launch_bounds__(kFusedTokens * 64) void k_gate_small(Pass p, int n_blocks, Table tab)
 {
-    constexpr bool kBf16 = sizeof(XT) == 2 && sizeof(WT) == 2;
     __shared__ float part[kFusedTokens * 256];
     __shared__ float lgs[kFusedTokens * 128];
     __shared__ int32_t map[kSmallExperts + 4];
     extern __shared__ uint32_t blkmask[];   // [S]
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = lane & 15, q = lane >> 4;
-    const int E = p.E, H = p.H, t0 = blockIdx.x * kFusedTokens;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, t0 = blockIdx.x * kFusedTokens;
     if (kRank) {
         for (int s = threadIdx.x; s < p.S; s += kFusedTokens * 64) blkmask[s] = 0u;
         stage_table(p, tab, map, kFusedTokens * 64);
     }
-    const int n_et = (E + 15) >> 4, parts = kFusedTokens / n_et, et = wave % n_et, my_part = wave / n_et;
-    const int chunks = (H + 31) / 32, per = (chunks + parts - 1) / parts;
-    const int c0 = min(my_part * per, chunks), c1 = my_part < parts ? min(c0 + per, chunks) : c0;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    const XT *x = (const XT *)p.x + (size_t)min(t0 + n, p.T - 1) * H;
-    const WT *wr = (const WT *)p.router_w + (size_t)min(et * 16 + n, E - 1) * H;
-    Run8<XT> xv[kSmallChunks];
-    Run8<WT> wv[kSmallChunks];
+    const SmallShare sh(p, wave);
+    f32x4 acc[1];
+    small_products<1, XT, WT>(p, t0, sh, lane, acc);
 #pragma unroll
-    for (int i = 0; i < kSmallChunks; ++i) {     // this lane's 8 k of every chunk (H % 8 == 0), all requested together
-        const int k = (c0 + i) * 32 + q * 8, end = c0 + i < c1 ? H : 0;
-        load_run8(xv[i], x, k, end);
-        load_run8(wv[i], wr, k, end);
-    }
-#pragma unroll
-    for (int i = 0; i < kSmallChunks; ++i) {
-        if (c0 + i >= c1) break;
-        if constexpr (kBf16) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&wv[i].v[0], *(bf16x8 *)&xv[i].v[0], acc, 0, 0, 0);
-        } else {
-            float xf[8], wf[8];
-            widen8(xv[i], xf);
-            widen8(wv[i], wf);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[e], xf[e], acc, 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) part[wave * 256 + r * 64 + lane] = acc[r];
+    for (int r = 0; r < 4; ++r) part[wave * 256 + r * 64 + lane] = acc[0][r];
     __syncthreads();
     const int t = t0 + wave;
     int slot = -1;
     if (t < p.T) {
-        float v[1] = {0.f};
-        if (lane < E) {   // expert lane: tile lane / 16, row 4 q' + r of it, token `wave`
-            const int at = (lane & 3) * 64 + ((lane & 15) >> 2) * 16 + wave;
-            for (int i = 0; i < parts; ++i) v[0] += part[(i * n_et + (lane >> 4)) * 256 + at];
-            if (p.logit_bias) v[0] += p.logit_bias[lane];
-        }
+        float v[1] = {small_logit(p, sh, part, wave, lane)};
         const int id = select_regs<1>(p, t, v, lgs + wave * 128, lgs + wave * 128 + 64, lane);
         if (kRank) slot = slot_of_lane(p, map, t, lane, id);
     }

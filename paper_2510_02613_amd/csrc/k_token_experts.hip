@@ -1,5 +1,5 @@
 // Launches saved where a pass is a chain of them: everything behind the gate of a pass of few tokens through a small layer in one
-// launch (k_token_experts), GEMM-2 and combine of a token or two in one (k_gemm2_combine, at the end).
+// launch (k_token_experts), the gate too where all tokens can be selected at once, GEMM-2 and combine of a token or two in one (k_gemm2_combine, at the end).
 //
 // The expert FFN of Sec. 2.1 of the paper and its weighted combine, token by token: a workgroup reads its token's k + n_shared
 // experts (the slot comes from the selection kernel's table of assignments; Sec. 3.2 / 4.6: placement is data), keeps h
@@ -16,6 +16,9 @@
 // instruction, the contractions are too short to fill one.  Sums: a lane's products in order, then the 16 lanes' by halves.
 // Workgroup 0 writes the tables (offsets, permutation, tile list) as in the other kernels that derive their tiles, and h and y go to the
 // workspace too.
+#include <algorithm>
+
+#include "gate_small.h"
 #include "moe_internal.h"
 #include "self_tiles.h"
 #include "wave_ops.h"
@@ -69,52 +72,26 @@ template <typename T> __device__ __forceinline__ float stored(float v);
 template <> __device__ __forceinline__ float stored<float>(float v) { return v; }
 template <> __device__ __forceinline__ float stored<uint16_t>(float v) { return bf16_to_f32(f32_to_bf16(v)); }
 
-template <typename T, bool kSelf>
-__global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_rows)
+// Rows of the slots before s and of s in the blocks of tokens before t's (all lanes of a wavefront, each with its own s)
+__device__ __forceinline__ int rows_before(const Pass &p, int lane, int t, int s, const SelfScan &sc)
 {
-    extern __shared__ float sm[];             // x [H], h [n][I], y [n][H]; or workgroup 0's tables
-    __shared__ int32_t slots[kMaxKK], rows[kMaxKK], n_local;
-    __shared__ float wts[kMaxKK];
-    if (kSelf && blockIdx.x == 0) { self_tables(p, tile_rows, sm); return; }
-    const int t = blockIdx.x - (kSelf ? 1 : 0), H = p.H, I = p.I, tid = threadIdx.x, lane = tid & 63, l = tid & 15, g = tid >> 4;
-    float *x = sm, *h = x + H, *y = h + (size_t)p.kk * I;
-    for (int c = tid; c < H; c += kThreads) x[c] = load_f32<T>((const T *)p.x + (size_t)t * H, c);
-    if (tid < 64) {   // first wavefront: the token's local assignments, compacted, in selection order
-        int slot = -1, row = 0;
-        float wv = 0.f;
-        if (lane < p.kk) {
-            const int a = t * p.kk + lane;
-            wv = lane < p.k ? p.w[(size_t)t * p.k + lane] : 1.0f;
-            if (kSelf) {
-                row = p.slot_rank[a];
-                slot = row >> 12;
-            } else {
-                row = p.inv[a];
-                slot = slot_of(p, a);
-            }
-        }
-        if (kSelf) {   // the row among all rows: those of the slots before, of the slot in earlier blocks of tokens, the rank
-            const SelfScan sc = self_scan(p, lane, (p.T + kFusedTokens - 1) / kFusedTokens, tile_rows);
-            const int s = max(slot, 0), owner = s / sc.spl, mine = s - owner * sc.spl;
-            row = (row & 0xfff) + (__shfl(sc.incl - sc.own, owner, 64) >> 16);
+    const int owner = s / sc.spl, mine = s - owner * sc.spl;
+    int row = __shfl(sc.incl - sc.own, owner, 64) >> 16;
 #pragma unroll
-            for (int i = 0; i < kSelfLaneSlots; ++i) {
-                const uint32_t w = (uint32_t)__shfl((int)sc.w[i], owner, 64);
-                if (i < mine) row += rows_of(w);
-                if (i == mine) row += rows_of(w & ((1u << (8 * (t / kFusedTokens))) - 1u));
-            }
-        }
-        const unsigned long long m = __ballot(slot >= 0);
-        if (slot >= 0) {
-            const int at = __popcll(m & ((1ull << lane) - 1ull));
-            slots[at] = slot;
-            rows[at] = row;
-            wts[at] = wv;
-        }
-        if (lane == 0) n_local = __popcll(m);
+    for (int i = 0; i < kSelfLaneSlots; ++i) {
+        const uint32_t w = (uint32_t)__shfl((int)sc.w[i], owner, 64);
+        if (i < mine) row += rows_of(w);
+        if (i == mine) row += rows_of(w & ((1u << (8 * (t / kFusedTokens))) - 1u));
     }
-    __syncthreads();
-    const int n = n_local;
+    return row;
+}
+
+// A token behind its selection: h and y of its n local experts (slots; x [H], h [n][I], y [n][H] in LDS) and their sum, all threads of the
+// workgroup.  rows: where h and y go in the workspace; written by the first wavefront before it comes here, read behind the first barrier.
+template <typename T>
+__device__ __forceinline__ void token_ffn(const Pass &p, int t, int n, const int32_t *slots, const int32_t *rows, const float *wts, const float *x, float *h, float *y)
+{
+    const int H = p.H, I = p.I, tid = threadIdx.x, l = tid & 15, g = tid >> 4;
     // ---- h = silu(x . Wg) * (x . Wu): a group of lanes takes columns g, g + 64, ... of all experts, two of them together ----
     const size_t s13 = 2 * (size_t)I * H, s2 = (size_t)H * I;
     for (int c0 = g; c0 < n * I; c0 += 2 * kGroups) {
@@ -167,6 +144,127 @@ __global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_row
         for (int j = 0; j < n; ++j) o = fmaf(wts[j], y[(size_t)j * H + c], o);
         store_f32<T>((T *)p.out + (size_t)t * H, c, o);
     }
+}
+
+template <typename T, bool kSelf>
+__global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_rows)
+{
+    extern __shared__ float sm[];             // x [H], h [n][I], y [n][H]; or workgroup 0's tables
+    __shared__ int32_t slots[kMaxKK], rows[kMaxKK], n_local;
+    __shared__ float wts[kMaxKK];
+    if (kSelf && blockIdx.x == 0) { self_tables(p, tile_rows, sm); return; }
+    const int t = blockIdx.x - (kSelf ? 1 : 0), H = p.H, I = p.I, tid = threadIdx.x, lane = tid & 63;
+    float *x = sm, *h = x + H, *y = h + (size_t)p.kk * I;
+    for (int c = tid; c < H; c += kThreads) x[c] = load_f32<T>((const T *)p.x + (size_t)t * H, c);
+    if (tid < 64) {   // first wavefront: the token's local assignments, compacted, in selection order
+        int slot = -1, row = 0;
+        float wv = 0.f;
+        if (lane < p.kk) {
+            const int a = t * p.kk + lane;
+            wv = lane < p.k ? p.w[(size_t)t * p.k + lane] : 1.0f;
+            if (kSelf) {
+                row = p.slot_rank[a];
+                slot = row >> 12;
+            } else {
+                row = p.inv[a];
+                slot = slot_of(p, a);
+            }
+        }
+        if (kSelf) {   // the row among all rows: those of the slots before, of the slot in earlier blocks of tokens, the rank
+            row = (row & 0xfff) + rows_before(p, lane, t, max(slot, 0), self_scan(p, lane, (p.T + kFusedTokens - 1) / kFusedTokens, tile_rows));
+        }
+        const unsigned long long m = __ballot(slot >= 0);
+        if (slot >= 0) {
+            const int at = __popcll(m & ((1ull << lane) - 1ull));
+            slots[at] = slot;
+            rows[at] = row;
+            wts[at] = wv;
+        }
+        if (lane == 0) n_local = __popcll(m);
+    }
+    __syncthreads();
+    token_ffn<T>(p, t, n_local, slots, rows, wts, x, h, y);
+}
+
+// The whole pass of a small layer, the gate too, in one launch (up to 64 tokens; routers as in k_gate_small).  A workgroup per token, and one that writes the tables, ids
+// and weights.  Every one of them multiplies and selects ALL tokens, since where a token's h and y go in the workspace follows from the
+// others' selections, and nothing waits for another workgroup; its own token's experts follow as above.  What bounds it: latency, as above; what it saves is a
+// launch and the round trips of the tables.  NTT tiles of 16 tokens, NTT tokens a wavefront, on 64 / NTT lanes each: a wavefront that selects
+// one after the other takes 1.2 us for each (64 tokens of the 128 x 64 layer 12.1 -> 13.4).
+template <typename T, typename WT, int NTT, typename Table>
+__global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_rows, Table tab)
+{
+    extern __shared__ float sm[];             // x [H]; then partial logits [NTT][wavefronts with a share][256], behind them h [n][I], y [n][H], or the tables and ranks
+    __shared__ uint32_t masks[NTT * kSelfMaxSlots];
+    __shared__ int32_t map[kSmallExperts + 4];
+    __shared__ float scratch[NTT == 1 ? kThreads / 64 * 128 : 1];
+    __shared__ int32_t slots[kMaxKK], rows[kMaxKK], n_local;
+    __shared__ float all_w[kMaxKK], wts[kMaxKK];
+    static_assert(kThreads == 64 * kFusedTokens, "a wavefront per token of a tile");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, t = (int)blockIdx.x - 1, H = p.H;
+    const bool tables = blockIdx.x == 0;
+    float *x = sm, *rest = sm + H;
+    if (!tables)
+        for (int c = tid; c < H; c += kThreads) x[c] = load_f32<T>((const T *)p.x + (size_t)t * H, c);
+    for (int s = tid; s < NTT * kSelfMaxSlots; s += kThreads) masks[s] = 0u;
+    stage_table(p, tab, map, kThreads);
+    const SmallShare sh(p, wave);
+    f32x4 acc[NTT];
+    small_products<NTT, T, WT>(p, 0, sh, lane, acc);
+    if (wave < sh.used) {
+#pragma unroll
+        for (int i = 0; i < NTT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) rest[(i * sh.used + wave) * 256 + r * 64 + lane] = acc[i][r];
+    }
+    __syncthreads();
+    // ---- selection: lanes of a token, its assignment `sub` ----
+    constexpr int L = 64 / NTT;
+    const int sub = lane & (L - 1), tok = wave * NTT + lane / L, tile = tok / kFusedTokens, in_tile = tok % kFusedTokens;
+    const bool own = tok == t;
+    const float logit = small_logit(p, sh, rest + tile * sh.used * 256, in_tile, sub);
+    int slot = -1;
+    if (wave * NTT < p.T) {                                // uniform
+        int id;
+        if constexpr (NTT == 1) {
+            float v[1] = {logit};
+            id = select_regs<1>(p, tok, v, scratch + wave * 128, scratch + wave * 128 + 64, lane, tables, own ? all_w : nullptr);
+        } else {
+            id = select_lanes<L>(p, tok, logit, lane, tok < p.T, tables, own ? all_w : nullptr);
+        }
+        if (tok < p.T) slot = slot_of_lane(p, map, tok, sub, id);
+        if (slot >= 0) atomicOr(&masks[tile * kSelfMaxSlots + slot], 1u << in_tile);
+        wave_sync();
+        const uint64_t here = __ballot(slot >= 0) >> (lane & (64 - L)) & (~0ull >> (64 - L));
+        if (own) {                                         // the local assignments, compacted, in selection order
+            if (slot >= 0) {
+                const int at = __popcll(here & ((1ull << sub) - 1ull));
+                slots[at] = slot;
+                wts[at] = sub < p.k ? all_w[sub] : 1.0f;
+            }
+            if (sub == 0) n_local = __popcll(here);
+        }
+    }
+    __syncthreads();
+    SelfBlocks<NTT> src;
+    src.masks = masks;
+    src.ranks = nullptr;
+    if (tables) {
+        int32_t *ranks = (int32_t *)(rest + kSelfTableBytes / 4);
+        if (tok < p.T && sub < p.kk)
+            ranks[tok * p.kk + sub] = slot >= 0 ? (slot << 12) | __popc(masks[tile * kSelfMaxSlots + slot] & ((1u << in_tile) - 1u)) : -1;
+        src.ranks = ranks;                                // read behind self_tables' barrier
+        self_tables(p, tile_rows, rest, src);
+        return;
+    }
+    const int n = n_local;
+    if (tid < 64) {
+        const int s = lane < n ? slots[lane] : 0, b = t / kFusedTokens;
+        const int before = rows_before(p, lane, t, s, self_scan(p, lane, (p.T + kFusedTokens - 1) / kFusedTokens, tile_rows, src));
+        if (lane < n) rows[lane] = before + __popc(masks[b * kSelfMaxSlots + s] & ((1u << (t % kFusedTokens)) - 1u));
+    }
+    float *h = rest, *y = h + (size_t)p.kk * p.I;
+    token_ffn<T>(p, t, n, slots, rows, wts, x, h, y);
 }
 
 // GEMM-2 and combine of a token or two (bf16): a token's experts share no rows with another token's worth speaking of, so
@@ -235,7 +333,48 @@ __global__ __launch_bounds__(64 * kColWaves) void k_gemm2_combine(Pass p)
     if (lane < kCols) ((uint16_t *)p.out)[(size_t)t * H + n0 + lane] = f32_to_bf16(o);
 }
 
+template <typename T, typename WT, int NTT, typename Table>
+hipError_t launch_pass_t(const Pass &p, int tile_rows, const Table &tab, hipStream_t st)
+{
+    const int n_et = (p.E + 15) / 16, parts = kFusedTokens / n_et, chunks = (p.H + 31) / 32, per = (chunks + parts - 1) / parts;
+    const size_t logits = (size_t)NTT * ((chunks + per - 1) / per * n_et) * 256, ffn = (size_t)p.kk * (p.I + p.H), tables = kSelfTableBytes / 4 + (size_t)p.T * p.kk;
+    const size_t lds = sizeof(float) * (p.H + std::max(logits, std::max(ffn, tables)));
+    if (lds > 48 * 1024) {       // beside the static part
+        const hipError_t e = hipFuncSetAttribute((const void *)k_token_experts<T, WT, NTT, Table>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_token_experts<T, WT, NTT, Table>), dim3(p.T + 1), dim3(kThreads), lds, st, p, tile_rows, tab);
+    return hipGetLastError();
+}
+
+template <typename T, typename WT>
+hipError_t launch_pass(const Pass &p, int tile_rows, hipStream_t st)
+{
+    if (p.T <= 16) return p.host_table ? launch_pass_t<T, WT, 1>(p, tile_rows, fill_table(p), st) : launch_pass_t<T, WT, 1>(p, tile_rows, NoTable{}, st);
+    if (p.T <= 32) return p.host_table ? launch_pass_t<T, WT, 2>(p, tile_rows, fill_table(p), st) : launch_pass_t<T, WT, 2>(p, tile_rows, NoTable{}, st);
+    return p.host_table ? launch_pass_t<T, WT, 4>(p, tile_rows, fill_table(p), st) : launch_pass_t<T, WT, 4>(p, tile_rows, NoTable{}, st);
+}
+
 }  // namespace
+
+// Whether the gate goes into the launch too.  Every workgroup then reads all token rows and the router, which costs it about 30 GB/s worth of time; whole
+// pass, us, gate in a launch of its own (bf16 with more than 4 E assignments: two, bookkeeping) -> in this one, KB of both: 128 x 64 fp32, 8 experts, top-2, 1 token 11.1 -> 7.8, 16 12.1 -> 8.4, 17 (20
+// KB) 12.2 -> 8.4, 64 (36 KB) 12.1 -> 9.4, in bf16 15.8 -> 9.4; 256 x 32, 64 tokens, 16 experts (80 KB) 15.3 -> 13.4, 32, 24 experts (56 KB) 15.3 -> 13.4; 512 x 16 bf16, 32 tokens, 32
+// experts (96 KB) 22.2 -> 21.1; 512 x 8 fp32, 32 of them (128 KB) 21.2 -> 21.5, 64 tokens, 16 experts (160 KB) 19.1 -> 20.2.  With one token tile the gate's own launch reads
+// as much: 512 x 8, 16 tokens, 64 experts (160 KB) 24.9 -> 22.4, 512 x 16 bf16, grouped gate 23.2 -> 20.1.
+bool token_pass_supports(const Pass &p)
+{
+    if (!p.self_tiles || !token_experts_supports(p) || !one_gate_kernel(p)) return false;
+    if (p.T <= 16) return true;
+    const int tiles = p.T <= 32 ? 2 : 4, lanes = 64 / tiles;     // of 16 tokens; that select a token
+    return p.n_group == 1 && p.E <= lanes && p.kk <= lanes && (tiles * 16 * (p.act_bf16 ? 2 : 4) + p.E * (p.router_bf16 ? 2 : 4)) * p.H <= 96 * 1024;
+}
+
+hipError_t launch_token_pass(const Pass &p, int tile_rows, hipStream_t st)
+{
+    if (p.act_bf16) return p.router_bf16 ? launch_pass<uint16_t, uint16_t>(p, tile_rows, st) : launch_pass<uint16_t, float>(p, tile_rows, st);
+    return p.router_bf16 ? launch_pass<float, uint16_t>(p, tile_rows, st) : launch_pass<float, float>(p, tile_rows, st);
+}
 
 // H % 8 == 0 as everywhere
 hipError_t launch_gemm2_combine(const Pass &p, hipStream_t st)

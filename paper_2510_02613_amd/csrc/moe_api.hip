@@ -765,8 +765,9 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     }
 
     const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
-    // few tokens: the weight-streaming GEMM-1 derives its tiles itself and writes the tables beside its stream
-    p.self_tiles = (tiny || f32) && !identity && self_tiles_possible(p);
+    // few tokens: the weight-streaming GEMM-1 (k_token_experts where that is the launch) derives its tiles itself and writes the tables beside its stream
+    p.self_tiles = (tiny || f32 || (whole && !big)) && !identity && self_tiles_possible(p);
+    const bool one_launch = whole && !routed_ids && token_pass_supports(p);   // and the gate too
     // a token to four: it selects the experts too
     p.self_select = (kernels == Kernels::decode || (kernels == Kernels::ring && !ring64)) && !whole && !routed_ids &&
                     gemm1_selects(p, kernels == Kernels::decode ? decode_blocks(p) : ring_blocks(p)) && !one_gate_kernel(p);
@@ -777,7 +778,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const int sel = l->prof_phase;
     auto mark = [&](int j) { if (ev && e == hipSuccess && (sel < 0 || j == sel || j == sel + 1)) e = hipEventRecord(ev[j], st); };
     mark(MOE_PHASE_GATE);
-    if (e == hipSuccess && !routed_ids) e = launch_gate(p, st);
+    if (e == hipSuccess && !routed_ids && !one_launch) e = launch_gate(p, st);
     mark(MOE_PHASE_PERMUTE);
     if (e == hipSuccess && !p.self_tiles) e = launch_permute(p, tile_rows, big, st);   // the large-tile kernels deal a size-ordered list round-robin to the XCDs
     // GEMM-2 and combine in one launch (recorded as GEMM-2): one token, or two where rows are short (whole pass, us, two launches ->
@@ -785,7 +786,7 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     // shape 38.7 -> 33.3, 62.6 -> 57.2, 4 tokens 77.8 -> 80.5; DeepSeek-V3-shaped rank 41.7 -> 40.2, 78.9 -> 79.5, 4 tokens 89.0 -> 91.0)
     const bool fused2 = !whole && !identity && tiny && T <= (p.H <= 4096 ? 2 : 1);
     mark(MOE_PHASE_GEMM1);
-    if (e == hipSuccess) e = whole ? launch_token_experts(p, tile_rows, st) : identity ? launch_identity_experts(p, st) : launch_gemm(0);
+    if (e == hipSuccess) e = one_launch ? launch_token_pass(p, tile_rows, st) : whole ? launch_token_experts(p, tile_rows, st) : identity ? launch_identity_experts(p, st) : launch_gemm(0);
     mark(MOE_PHASE_GEMM2);
     if (e == hipSuccess && !identity && !whole) e = fused2 ? launch_gemm2_combine(p, st) : launch_gemm(1);
     mark(MOE_PHASE_COMBINE);

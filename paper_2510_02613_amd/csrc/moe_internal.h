@@ -87,7 +87,7 @@ struct Pass {
     int32_t max_tiles;
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
     int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 and k_token_experts only: their workgroups derive their tile from the selection kernel's per-block counts and
-                         // masks (self_select: from their own selection) themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
+                         // masks (self_select, and k_token_experts with the gate: from their own selection) themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
     int32_t self_select; // GEMM-1 selects the experts itself from the logits (a token to four): no selection kernel
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
@@ -149,6 +149,8 @@ inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 2
 // everything behind the gate and the bookkeeping in one launch, for few tokens of small layers
 bool token_experts_supports(const Pass &p);
 hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st);
+bool token_pass_supports(const Pass &p);             // and the gate too (self_tiles is set)
+hipError_t launch_token_pass(const Pass &p, int tile_rows, hipStream_t st);
 hipError_t launch_gemm2_combine(const Pass &p, hipStream_t st);   // GEMM-2 and combine of a token or two (bf16)
 hipError_t launch_identity_experts(const Pass &p, hipStream_t st);
 hipError_t launch_combine(const Pass &p, hipStream_t st);

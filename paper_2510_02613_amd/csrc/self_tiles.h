@@ -47,6 +47,21 @@ struct SelfLds {
     __device__ __forceinline__ int slot_rank(const Pass &, int a) const { return ranks[a]; }
 };
 
+// or LDS, for all of up to 64 tokens, where a workgroup has selected them itself:
+template <int NB>
+struct SelfBlocks {
+    const uint32_t *masks;     // [NB][kSelfMaxSlots]
+    const int32_t *ranks;      // per assignment: slot << 12 | rank in the block of 16 tokens, or -1 (the workgroup that writes the tables)
+    __device__ __forceinline__ uint32_t counts(const Pass &, int s, int) const
+    {
+        uint32_t w = 0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w |= (uint32_t)__popc(masks[b * kSelfMaxSlots + s]) << (8 * b);
+        return w;
+    }
+    __device__ __forceinline__ int slot_rank(const Pass &, int a) const { return ranks[a]; }
+};
+
 // Lane l of a wavefront: the count bytes of its slots l * spl + i, i < spl = ceil(S / 64), and the sums over all
 // slots up to and including its own (rows in the high half, tiles of tile_rows in the low one).
 struct SelfScan {
