@@ -82,6 +82,9 @@ constexpr int kXcds = 8;
 constexpr int kMaxPartialSets = 256;        // partial-sum sets the workspace has room for: one round of a 256-unit chip
 constexpr int kTC = kMaxTT / 2;            // token tiles per wavefront
 constexpr int kWT = 4;                     // 16-row weight tiles per wavefront
+// A workgroup's eight wavefronts as WM (token) x 8 / WM (weight): 2 x 4, or 4 x 2 on half an N-slice
+constexpr int pieces_of(int wm) { return kWPieces * 2 / wm; }                // of weight rows per loader and step
+constexpr int acc_tiles(int wm) { return 2 * ((kMaxTT + wm - 1) / wm); }     // 16-row token tiles of a wavefront
 constexpr int kEpiStride1 = 2 * kWT * 8 + 16;  // GEMM-1: 32 h columns per wavefront, bytes per staged row (rows stay 16-byte aligned)
 constexpr int kEpiStride2 = 2 * kWT * 16 + 16;  // GEMM-2: 64 y columns per wavefront
 constexpr int kEpiBytes = 32 * kEpiStride2;     // one token tile of one wavefront
@@ -126,16 +129,18 @@ __device__ __forceinline__ void dma_piece(const void *base, uint32_t byte_off, u
 // out at different moments of a K-step (see k_loop), which one wavefront issuing both could not do
 // without making the token copies wait for the weight copies ahead of them: a wavefront's loads
 // complete in order.
+template <int WM>
 __device__ __forceinline__ void issue_step(const WaveCtx &c, uint32_t slot_addr, int k0)
 {
+    constexpr int WP = pieces_of(WM);
     if (c.wave < 4) {
         const uint16_t *b = c.wbase + k0;
         if (c.stream_w) {
 #pragma unroll
-            for (int i = 0; i < kWPieces; ++i) dma_piece<true>(b, c.off[i], slot_addr + (c.wave * kWPieces + i) * 1024);
+            for (int i = 0; i < WP; ++i) dma_piece<true>(b, c.off[i], slot_addr + (c.wave * WP + i) * 1024);
         } else {
 #pragma unroll
-            for (int i = 0; i < kWPieces; ++i) dma_piece<false>(b, c.off[i], slot_addr + (c.wave * kWPieces + i) * 1024);
+            for (int i = 0; i < WP; ++i) dma_piece<false>(b, c.off[i], slot_addr + (c.wave * WP + i) * 1024);
         }
     } else {
         const uint16_t *b = c.abase + k0;
@@ -170,8 +175,8 @@ __device__ __forceinline__ void wait_loads()
 // weight operands of the next sub-step are requested from LDS before the MFMAs of pair s.  Every other token tile takes
 // its weight tiles backwards, so that an MFMA always has one operand of the one before it (0.6 to 1 % of the whole pass).
 // `mid` is called once, half way through.
-template <int NT, typename Mid>
-__device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x4 (&acc)[kWT][2 * kTC], Mid mid)
+template <int NT, int WM, typename Mid>
+__device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws, const char *Xs, f32x4 (&acc)[kWT][acc_tiles(WM)], Mid mid)
 {
     if constexpr (NT > 0) {
         constexpr int KS = kBK / 32, STEPS = KS * NT, D = 2;
@@ -185,7 +190,7 @@ __device__ __forceinline__ void multiply_stage(const WaveCtx &c, const char *Ws,
         };
         auto fetch_x = [&](int step) {
             const int ks = step / NT, t = step % NT;
-            const uint4 v = *(const uint4 *)(Xs + c.xoff[ks] + (t >> 1) * 64 * 128 + (t & 1) * 16 * 128);
+            const uint4 v = *(const uint4 *)(Xs + c.xoff[ks] + (t >> 1) * WM * 32 * 128 + (t & 1) * 16 * 128);
             xf[step % (D + 1)] = *(const bf16x8 *)&v;
         };
         fetch_w(0);
@@ -241,9 +246,10 @@ using Ring10 = Ring<2, 2, kMaxTT, true>;
 __device__ __forceinline__ int step_at(int i, int first, int KT) { return i + first < KT ? i + first : i + first - KT; }
 
 // KT K-steps of 64 of this wavefront.  The caller issued the first depth - 1 steps of the ring this wavefront loads.
-template <int NT, typename R>
-__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x4 (&acc)[kWT][2 * kTC])
+template <int NT, typename R, int WM>
+__device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int KT, int first, f32x4 (&acc)[kWT][acc_tiles(WM)])
 {
+    constexpr int WP = pieces_of(WM);
     const bool wloader = c.wave < 4;
     const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
     const int depth = wloader ? R::NW : R::NX;
@@ -254,8 +260,8 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
         // one fewer.  The count is an immediate of the instruction; a switch over it was slower (whole pass, us, switch -> here:
         // DeepSeek-V3-shaped, 32 experts, 264 rows 716.5 -> 710, Qwen3 shape 266 rows 348 -> 345, 128 rows 266 -> 265.4, 64 rows 235.6 -> 234.6).
         if (wloader) {
-            if (kt + R::NW - 2 < KT)                  wait_loads<(R::NW - 2) * kWPieces>();
-            else if (R::NW == 4 && kt + 1 < KT)       wait_loads<kWPieces>();
+            if (kt + R::NW - 2 < KT)                  wait_loads<(R::NW - 2) * WP>();
+            else if (R::NW == 4 && kt + 1 < KT)       wait_loads<WP>();
             else                                      wait_loads<0>();
         } else if (R::NX == 2 || kt + 1 >= KT) {
             wait_loads<0>();
@@ -267,11 +273,11 @@ __device__ __forceinline__ void k_loop(const WaveCtx &c, const char *ring, int K
         __syncthreads();   // everyone's share of step kt is in LDS; everyone is done reading step kt-1
         auto issue = [&]() {
             if (kt + depth - 1 >= KT) return;
-            issue_step(c, wloader ? wring + fill * kWStage : xring + fill * R::XStage, step_at(kt + depth - 1, first, KT) * kBK);
+            issue_step<WM>(c, wloader ? wring + fill * kWStage : xring + fill * R::XStage, step_at(kt + depth - 1, first, KT) * kBK);
             fill = fill + 1 == depth ? 0 : fill + 1;
         };
         if (!wloader || !R::kMid) issue();
-        multiply_stage<NT>(c, ring + ws * kWStage, ring + R::XBase + xs * R::XStage, acc, [&]() { if (wloader && R::kMid) issue(); });
+        multiply_stage<NT, WM>(c, ring + ws * kWStage, ring + R::XBase + xs * R::XStage, acc, [&]() { if (wloader && R::kMid) issue(); });
         ws = ws + 1 == R::NW ? 0 : ws + 1;
         xs = xs + 1 == R::NX ? 0 : xs + 1;
     }
@@ -287,7 +293,7 @@ __device__ __forceinline__ float *partial_at(float *set, int wave, int a, int t,
 
 // Epilogue of one 32-row token tile of a wavefront: accumulators (both halves of token tile t of the wavefront, its kWT weight
 // tiles) -> the wavefront's private LDS region [token row][column] -> coalesced rows of h (with SwiGLU) or y.
-template <bool kFirst>
+template <bool kFirst, int WM>
 __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, char *ring, int t,
                                                 const f32x4 (&v)[2][kWT])
 {
@@ -321,7 +327,7 @@ __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c,
 #pragma unroll
     for (int r0 = 0; r0 < 32; r0 += RPI) {
         const int rr = r0 + lr;                       // row inside the token tile
-        const int m = (2 * t + c.wm) * 32 + rr;       // row inside the chunk
+        const int m = (WM * t + c.wm) * 32 + rr;       // row inside the chunk
         const uint4 w = *(const uint4 *)(mine + rr * STRIDE + lc * 2);
         if (m < mt.rows && ncol0 + lc < N)   // N is a multiple of 64: the lane's 8 columns exist together
             *(uint4 *)(O + (size_t)(mt.row_begin + m) * N + ncol0 + lc) = w;
@@ -333,18 +339,18 @@ __device__ __forceinline__ void emit_token_tile(const Pass &p, const WaveCtx &c,
 // p.partials (phase 2, sum_body below, adds them up).
 // (Letting the last of a tile's workgroups to finish do the adding, in the same launch, was
 // measured and is slower: the device-wide fence it needs costs more than the third launch.)
-template <bool kFirst, int NT, int kPhase, typename R>
+template <bool kFirst, int NT, int kPhase, typename R, int WM>
 __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const MTile &mt, int n0, int N, int KT, int first, char *ring,
                                           float *tile_sets, int part)
 {
-    f32x4 acc[kWT][2 * kTC];
+    f32x4 acc[kWT][acc_tiles(WM)];
 #pragma unroll
     for (int a = 0; a < kWT; ++a)
 #pragma unroll
-        for (int t = 0; t < 2 * kTC; ++t)
+        for (int t = 0; t < acc_tiles(WM); ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) acc[a][t][r] = 0.f;
-    k_loop<NT, R>(c, ring, KT, first, acc);
+    k_loop<NT, R, WM>(c, ring, KT, first, acc);
     __syncthreads();  // all operand reads are done: the ring becomes the epilogue staging area
     if (kPhase == 1) {
         float *mine = tile_sets + (size_t)part * kPartialFloats;
@@ -359,7 +365,7 @@ __device__ __forceinline__ void wave_body(const Pass &p, const WaveCtx &c, const
         f32x4 v[2][kWT];
 #pragma unroll
         for (int a = 0; a < kWT; ++a) { v[0][a] = acc[a][2 * t]; v[1][a] = acc[a][2 * t + 1]; }
-        emit_token_tile<kFirst>(p, c, mt, n0, N, ring, t, v);
+        emit_token_tile<kFirst, WM>(p, c, mt, n0, N, ring, t, v);
     }
 }
 
@@ -396,13 +402,16 @@ __device__ __forceinline__ void sum_body(const Pass &p, const WaveCtx &c, const 
                 for (int a = 0; a < kWT; ++a) s[h][a] += v[u][h][a];
         }
     }
-    emit_token_tile<kFirst>(p, c, mt, n0, N, ring, t, s);
+    emit_token_tile<kFirst, 2>(p, c, mt, n0, N, ring, t, s);
 }
 
 // kSpread: units of more than four token tiles start spread over K (the launcher's choice, see `first`).
-template <bool kFirst, int kPhase, bool kSpread = false>
+// kTailWM: 4 or 8 where the N-slices of a last round that fills half or a quarter of the chip run as two or four workgroups each.  An instance
+// of its own: with both kinds in every launch those without such a round were 0.3 to 0.6 % slower (50 instead of 32 spilled scalars).
+template <bool kFirst, int kPhase, bool kSpread = false, int kTailWM = 2>
 __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
 {
+    constexpr int kTailParts = kTailWM / 2;
     const int K = kFirst ? p.H : p.I;
     const int N = kFirst ? p.I : p.H;                  // output columns
     constexpr int BNO = kFirst ? kBN / 2 : kBN;        // output columns per workgroup
@@ -432,11 +441,24 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
         parts = min(parts, min(8, K / kBKW / 8));       // eight weight steps or more per part
         if (parts >= 2) { tail_rows = tr; n_parts = parts; }
     }
-    const int head_blocks = (rows_total - tail_rows) * kXcds;
+    // Where the contraction is not shared out, the last round's N-slices are: kTailParts workgroups each multiply the tile with their part
+    // of the slice's weight rows, their wavefronts as kTailWM (token) x 8 / kTailWM (weight).  Whole output elements, summed as in
+    // a whole slice: the same bits.  The host chooses it (parts_of) from an even load, here it is what the unit list has.
+    int fine_rows = 0, sub = -1;
+    if (kTailParts > 1 && !(p.k_split && rows_total >= rows_round)) {
+        const int tr = rows_total % rows_round;
+        if (kTailParts * tr <= rows_round) fine_rows = tr;
+    }
+    const int head_blocks = (rows_total - tail_rows - fine_rows) * kXcds;
     int b, part = 0;
     if (kPhase == 0) {
         b = blockIdx.x;
-        if (b >= head_blocks) return;
+        if (b >= head_blocks) {
+            const int r = (b - head_blocks) / kXcds;       // the parts of a slice on one XCD, one behind the other
+            if (r >= kTailParts * fine_rows) return;
+            sub = r % kTailParts;
+            b = head_blocks + r / kTailParts * kXcds + b % kXcds;
+        }
     } else if (kPhase == 1) {
         const int tail_blocks = tail_rows * kXcds;
         if (tail_blocks == 0) return;
@@ -453,14 +475,15 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     if (un.rows == 0) return;                          // a hole at the end of this XCD's column
     MTile mt;
     mt.slot = un.slot; mt.row_begin = un.row_begin; mt.rows = un.rows; mt.single = un.info & 1;
-    const int n0 = ((un.info >> 1) + j % spp) * BNO;
+    const int slice = (un.info >> 1) + j % spp, n0 = slice * BNO + (sub > 0 ? sub * (BNO / kTailParts) : 0);
+    if (sub > 0 && n0 >= N) return;
 
     __shared__ __attribute__((aligned(1024))) char ring[kPhase == 2 ? kWaves * kEpiBytes : kLdsBytes];   // phase 2 only stages its epilogue
     WaveCtx c;
     c.lane = threadIdx.x & 63;
     c.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    c.wn = c.wave & 3;
-    c.wm = c.wave >> 2;
+    c.wn = sub < 0 ? c.wave & 3 : c.wave & (8 / kTailWM - 1);
+    c.wm = sub < 0 ? c.wave >> 2 : c.wave / (8 / kTailWM);
     c.n_tt = (mt.rows + 31) >> 5;                      // token tiles that exist
     c.stream_w = mt.single != 0;                       // the slot's rows are one chunk: nobody else reads these weights (known from the tile itself: no further lookup before the first weight copies)
     // pieces w, w + 4, ... that hold rows; up to 128 rows all of a 32-row tile's
@@ -479,7 +502,7 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
 #pragma unroll
         for (int i = 0; i < kWPieces; ++i) {
             // weight piece: rows [8*pc, 8*pc+8) of the weight tile, 128 bytes each
-            const int pc = c.wave * kWPieces + i;
+            const int pc = c.wave * (sub < 0 ? pieces_of(2) : pieces_of(kTailWM)) + i;   // (a part of a slice: its loaders copy the first ones)
             const int row = pc * 8 + (c.lane >> 3);
             const int chunk = (c.lane & 7) ^ swz8(row);
             int g;
@@ -522,22 +545,38 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
     // Tiles with many: their rows are shared through L2 by slices at the same step, so a unit's slices start together and the units are
     // spread by their place in the list (kSpread: launch_experts_mfma8), 5 steps from one to the next (1 and 3: the same within 1 %).
     // Not the chunks of one slot, which share its weights the same way.
-    const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? n0 / BNO * KT / p.n_slices[kFirst ? 0 : 1] : kSpread && mt.single ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
+    const int first = kPhase != 0 ? 0 : c.n_tt <= 4 ? slice * KT / p.n_slices[kFirst ? 0 : 1] : kSpread && mt.single ? ((j / spp) * kXcds + b % kXcds) * 5 % KT : 0;
     // 32-row token tiles this wavefront multiplies: wm, wm+2, ... < n_tt.  The whole rest of the
     // wavefront's work is specialised on their number, above 128 rows on that of their 16-row halves, so that its K loop is straight-line code.
-    const int ntc = (c.n_tt - c.wm + 1) >> 1;
+    const int ntc = sub < 0 ? (c.n_tt - c.wm + 1) >> 1 : (c.n_tt - c.wm + kTailWM - 1) / kTailWM;
     if constexpr (kPhase == 2) {
         // phase 2 is spread over the token tiles too: a workgroup adds up one per wavefront
         if ((int)blockIdx.y < ntc) sum_body<kFirst>(p, c, mt, n0, N, ring, tile_sets, n_parts, (int)blockIdx.y);
     } else {
-        auto run = [&](auto geometry, auto tiles) __attribute__((always_inline)) {
+        auto run_on = [&](auto geometry, auto tiles, auto wm) __attribute__((always_inline)) {
             using R = decltype(geometry);
+            constexpr int WM = decltype(wm)::value;
             const uint32_t wring = lds_addr(ring), xring = wring + R::XBase;
             const int depth = c.wave < 4 ? R::NW : R::NX;
-            for (int s = 0; s < depth - 1 && s < KT; ++s) issue_step(c, c.wave < 4 ? wring + s * kWStage : xring + s * R::XStage, step_at(s, first, KT) * kBK);
-            wave_body<kFirst, decltype(tiles)::value, kPhase, R>(p, c, mt, n0, N, KT, first, ring, tile_sets, part);
+            for (int s = 0; s < depth - 1 && s < KT; ++s) issue_step<WM>(c, c.wave < 4 ? wring + s * kWStage : xring + s * R::XStage, step_at(s, first, KT) * kBK);
+            wave_body<kFirst, decltype(tiles)::value, kPhase, R, WM>(p, c, mt, n0, N, KT, first, ring, tile_sets, part);
         };
         using std::integral_constant;
+        auto run = [&](auto geometry, auto tiles) __attribute__((always_inline)) { run_on(geometry, tiles, integral_constant<int, 2>{}); };
+        if constexpr (kTailParts > 1) {
+            if (sub >= 0) {
+                // whole 32-row tiles: `most` of them where a wavefront has that many, else one fewer
+                auto pick2 = [&](auto geometry, auto most) __attribute__((always_inline)) {
+                    constexpr int m = decltype(most)::value;
+                    if (ntc >= m) run_on(geometry, integral_constant<int, 2 * m>{}, integral_constant<int, kTailWM>{});
+                    else          run_on(geometry, integral_constant<int, 2 * m - 2>{}, integral_constant<int, kTailWM>{}); };
+                if (c.n_tt <= 2)      pick2(Ring2{}, integral_constant<int, 1>{});
+                else if (c.n_tt <= 4) pick2(Ring4{}, integral_constant<int, 1>{});
+                else if (c.n_tt <= 8) pick2(Ring8{}, integral_constant<int, (8 + kTailWM - 1) / kTailWM>{});
+                else                  pick2(Ring10{}, integral_constant<int, (kMaxTT + kTailWM - 1) / kTailWM>{});
+                return;
+            }
+        }
         // the body for nt, n .. most: the numbers of 16-row token tiles that a wavefront of this geometry can have
         auto pick = [&](auto self, auto geometry, auto n, auto most, int nt) __attribute__((always_inline)) {
             constexpr int v = decltype(n)::value;
@@ -552,6 +591,39 @@ __global__ __launch_bounds__(kThreads, 1) void k_expert_gemm_mfma8(Pass p)
         if (c.n_tt <= 8)      pick(pick, Ring8{}, integral_constant<int, 4>{}, integral_constant<int, 8>{}, nt);
         else                  pick(pick, Ring10{}, integral_constant<int, 8>{}, integral_constant<int, 10>{}, nt);
     }
+}
+
+// Into how many workgroups the N-slices of a last round that is not full are to be split (1, 2 or 4), from the tiles of an even load; rows of 8
+// workgroups, `round` of them run at a time.  A launch takes as long as its fullest compute unit: 1.5 rounds cost what two do,
+// and 48 workgroups, a fifth of the chip, what a whole round does.  A part of a slice reads all of the tile's token rows for fewer weight rows, so that it
+// takes more than its share of the time (rows + 128 or rows + 64 of rows + 256): worth it where there are compute units left over.
+// us a pass, whole slices -> in two -> in four.  Under one round: 8 Qwen3 experts, 1000 tokens 67.8 -> 55.3 -> 49.0, 10, 3000 97.0 -> 82.3 -> 78.1,
+// 16, 3000 98.6 -> 86.0 (too many for four), 32, 3000 tokens, 192 workgroups: whole.  More than one: 48, 1500 142.3 -> 132.1 -> 128.6, 3000 170.0 -> 160.9 -> 156.2, 64, 4096
+// 208 -> 205; DeepSeek-V2-Lite shape, 1777 tokens 332.9 -> 328.4 -> 328.4, 16 experts, 1000 127.1 -> 118.2 -> 112.8; DeepSeek-V3-shaped, 16 experts, 6000 505 -> 496 -> 493.
+//  * In four up to 224 rows a tile: above, the token rows that are read four times tell (DeepSeek-V2-Lite shape, 281 rows 294.7 -> 289.3 -> 294.8, DeepSeek-V3-shaped, 250
+//    588 -> 579 -> 584; Qwen3 shape, 231 rows, 10 experts 96.8 -> 79.2 -> 82.3; 281 rows 208.7 -> 198.1 -> 200.5, though on 10 experts 119 -> 104 -> 100).
+//  * Slots with several tiles, whose weights are read out of L2 as it is, only under one round (Qwen3 shape, 6000 tokens, 8 experts 103.4 -> 93.6, 4 101.3 -> 86.8;
+//    32 experts, 1.5 rounds, 189.4 -> 195.4).
+//  * A long contraction of more than a round is shared out instead (k_split).  Under one round it cannot be (DeepSeek-V3-shaped, 4 experts, 4000 tokens 240 -> 201).
+int parts_of(const Pass &p, int n_slices, int round)
+{
+    if (p.tiles_expected <= 0) return 1;
+    const int runs = mfma8_runs(p.tiles_expected, n_slices);
+    const int rows = (p.tiles_expected * runs + kXcds - 1) / kXcds * (n_slices / runs), tail = rows % round;
+    if (tail == 0 || 2 * tail > round || (rows >= round && (p.k_split || p.slot_tiles_expected > 1))) return 1;
+    return 4 * tail > round || p.tile_rows_expected > 224 ? 2 : 4;
+}
+
+template <bool kFirst, int kTailWM>
+void launch_phase0(const Pass &p, bool spread, int grid, hipStream_t st)
+{
+    if (spread) hipLaunchKernelGGL((k_expert_gemm_mfma8<kFirst, 0, true, kTailWM>), dim3(grid), dim3(kThreads), 0, st, p);
+    else        hipLaunchKernelGGL((k_expert_gemm_mfma8<kFirst, 0, false, kTailWM>), dim3(grid), dim3(kThreads), 0, st, p);
+}
+void launch_whole(const Pass &p, bool first, int parts, bool spread, int grid, hipStream_t st)
+{
+    if (first) parts == 1 ? launch_phase0<true, 2>(p, spread, grid, st) : parts == 2 ? launch_phase0<true, 4>(p, spread, grid, st) : launch_phase0<true, 8>(p, spread, grid, st);
+    else       parts == 1 ? launch_phase0<false, 2>(p, spread, grid, st) : parts == 2 ? launch_phase0<false, 4>(p, spread, grid, st) : launch_phase0<false, 8>(p, spread, grid, st);
 }
 
 }  // namespace
@@ -601,7 +673,7 @@ hipError_t launch_experts_mfma8(const Pass &p0, int which, hipStream_t st)
     p.k_split = p.partials != nullptr && K / kBKW >= 64 && tile_list_sorted(p);
     if (!p.units[0] || !p.unit_hdr) return hipErrorInvalidValue;   // the bookkeeping kernel must have been asked for unit lists
     const int nt = p.n_slices[which];
-    const int grid = mfma8_grid_rows(p.max_tiles, nt) * kXcds;
+    int grid = mfma8_grid_rows(p.max_tiles, nt) * kXcds;      // and the parts of a last round's slices
     const int round_blocks = (cus < kMaxPartialSets ? cus : kMaxPartialSets) / kXcds * kXcds;
     // K starts of many-row units spread over K (see the kernel): where rows are a multiple of 4096 bytes, and the order of the tile
     // list does not follow from the slots the experts sit in -- a row's sum would.
@@ -612,17 +684,14 @@ hipError_t launch_experts_mfma8(const Pass &p0, int which, hipStream_t st)
     // A shared expert with several chunks reads the same token rows as everybody: DeepSeek-V2-Lite shape with the whole batch,
     // GEMM-1 of 1000 tokens 166 -> 168, 1777 tokens 194.5 -> 198.6, 3000 tokens 270 -> 259.  There the starts stay together.
     const bool spread = K % 2048 == 0 && tile_list_sorted(p) && !(which == 0 && p.shared_end - p.shared_begin > kBM);
-    if (which == 0) {
-        if (spread) hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 0, true>), dim3(grid), dim3(kThreads), 0, st, p);
-        else        hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 0, false>), dim3(grid), dim3(kThreads), 0, st, p);
-        if (p.k_split) {
+    const int parts = parts_of(p, nt, round_blocks / kXcds);
+    if (parts > 1) grid += (parts - 1) * (round_blocks / kXcds / parts) * kXcds;
+    launch_whole(p, which == 0, parts, spread, grid, st);
+    if (p.k_split) {
+        if (which == 0) {
             hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 1>), dim3(round_blocks), dim3(kThreads), 0, st, p);
             hipLaunchKernelGGL((k_expert_gemm_mfma8<true, 2>), dim3(round_blocks / 2, kTC), dim3(kThreads), 0, st, p);
-        }
-    } else {
-        if (spread) hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 0, true>), dim3(grid), dim3(kThreads), 0, st, p);
-        else        hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 0, false>), dim3(grid), dim3(kThreads), 0, st, p);
-        if (p.k_split) {
+        } else {
             hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 1>), dim3(round_blocks), dim3(kThreads), 0, st, p);
             hipLaunchKernelGGL((k_expert_gemm_mfma8<false, 2>), dim3(round_blocks / 2, kTC), dim3(kThreads), 0, st, p);
         }

@@ -762,6 +762,10 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
         p.unit_cap = (int32_t)l->lay.unit_cap;
         p.n_slices[0] = mfma8_n_slices(p.H, p.I, 0);
         p.n_slices[1] = mfma8_n_slices(p.H, p.I, 1);
+        const int most = mfma8_tile_rows();
+        p.slot_tiles_expected = (int)std::ceil((rows + 2.0 * std::sqrt(rows)) / most);
+        p.tile_rows_expected = p.slot_tiles_expected > 0 ? (int)(rows / p.slot_tiles_expected) : 0;
+        p.tiles_expected = (int)(resident * (1.0 - std::exp(-rows)) + 0.5) * p.slot_tiles_expected + p.n_shared * ((shared_end - shared_begin + most - 1) / most);
     }
 
     const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1

@@ -82,6 +82,7 @@ struct Pass {
     UnitHdr *unit_hdr;   // [2]
     int32_t unit_cap;
     int32_t n_slices[2]; // N-slices of a tile in GEMM-1 and GEMM-2
+    int32_t tiles_expected, slot_tiles_expected, tile_rows_expected;   // large-tile GEMMs, for an even load: tiles in all, of a slot, rows of a tile
     void *h;             // [A,I]
     void *y;             // [A,H]
     int32_t max_tiles;

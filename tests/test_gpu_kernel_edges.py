@@ -44,6 +44,31 @@ def test_large_tile_rings_at_every_token_tile_count(hidden, inter):
     np.testing.assert_array_equal(rows, np.sort(counts))      # the large-tile kernels ran: a tile per slot
 
 
+@pytest.mark.parametrize("hidden,inter,rows,parts", [
+    (64, 192, "few", (8, 8)), (320, 128, "few", (8, 8)), (448, 448, "few", (4, 8)), (4096, 64, "few", (8, 8)),       # 34 workgroups or so, half and quarter slices of 64 columns
+    (64, 192, "many", (4, 4)), (448, 448, "many", (4, 4)),                                                           # more than 224 rows a slot
+    (320, 512, "few", (4, 8)), (64, 1152, "few", (2, 8)), (2304, 64, "few", (8, 2)), (64, 2048, "few", (8, 8)),      # 68, 153 workgroups, a round and 16
+    (64, 2944, "many", (2, 4)), (4096, 2048, "chunks", (4, 4)), (64, 192, "chunks", (8, 8))])                        # a round and 135; several tiles a slot
+def test_last_round_of_the_large_tiles_in_parts(hidden, inter, rows, parts):
+    """N-slices as two or four workgroups (wavefronts 4 x 2 and 8 x 1) and whole ones, at every number of token tiles, on short contractions, and the numbers of workgroups on both sides of the rule; a
+    column slice that ends inside its first, second and third part."""
+    from gpu_util import Case, kernels_of
+    from test_gpu_routed import _check
+    counts = {"few": [1, 32, 33, 64, 65, 97, 128, 129, 160, 161, 193, 225, 256, 257, 288, 289, 320],
+              "many": [193, 224, 225, 239, 240, 241, 255, 256, 257, 272, 273, 288, 289, 304, 305, 319, 320], "chunks": [321, 350, 400, 410]}[rows]
+    tokens = sum(counts)
+    wl = MoEWorkload(name="parts", tokens=tokens, hidden=hidden, inter=inter, n_experts=len(counts), top_k=1, n_slots=len(counts),
+                     n_local=len(counts), act_dtype="bf16", router_dtype="f32", gate="softmax", seed=360 + hidden)
+    g = np.random.Generator(np.random.PCG64(hidden))
+    ids = g.permutation(np.repeat(np.arange(len(counts)), counts)).astype(np.int32)[:, None]
+    case = Case(wl)
+    import torch
+    dev_ids, w, out = torch.from_numpy(ids).to(case.x_dev.device), torch.ones((tokens, 1), device=case.x_dev.device), torch.empty_like(case.x_dev)
+    names = [n for n in kernels_of(lambda s: case.layer.forward_routed(case.x_dev, dev_ids, w, out=out, stream=s)) if n.startswith("k_expert_gemm_mfma8") and ", 0, " in n]
+    assert [int(n.rstrip(">").split(", ")[-1]) for n in names] == list(parts), names
+    _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
+
+
 @pytest.mark.parametrize("hidden,inter", [(64, 192), (320, 128)])
 def test_large_tiles_stage_by_8_rows_and_multiply_by_16(hidden, inter):
     """Slots of more than 128 rows that end just before, at and behind multiples of 8 and 16, in each half of a 32-row tile and
