@@ -40,8 +40,9 @@ constexpr int kSmallChunks = kSmallHidden / 32 / (kFusedTokens / (kSmallExperts 
 // contraction, which is shared out over the wavefronts of an expert tile.
 struct SmallShare {
     int n_et, parts, et, c0, c1;
-    int used;                      // wavefronts with chunks: the first `used` ones
-    __device__ __forceinline__ SmallShare(const Pass &p, int wave)
+    int added;                     // shares that are added up: all of them or, where LDS is short (exact), the first ones, up to the last chunk
+    __device__ __forceinline__ int waves() const { return added * n_et; }
+    __device__ __forceinline__ SmallShare(const Pass &p, int wave, bool exact)
     {
         n_et = (p.E + 15) >> 4;
         parts = kFusedTokens / n_et;
@@ -49,7 +50,7 @@ struct SmallShare {
         const int mine = wave / n_et, chunks = (p.H + 31) / 32, per = (chunks + parts - 1) / parts;
         c0 = min(mine * per, chunks);
         c1 = mine < parts ? min(c0 + per, chunks) : c0;
-        used = (chunks + per - 1) / per * n_et;
+        added = exact ? (chunks + per - 1) / per : parts;
     }
 };
 
@@ -106,7 +107,7 @@ __device__ __forceinline__ float small_logit(const Pass &p, const SmallShare &sh
     float v = 0.f;
     if (e < p.E) {      // tile e / 16, row 4 q' + r of it
         const int at = (e & 3) * 64 + ((e & 15) >> 2) * 16 + token;
-        for (int w = e >> 4; w < sh.used; w += sh.n_et) v += part[w * 256 + at];
+        for (int i = 0; i < sh.added; ++i) v += part[(i * sh.n_et + (e >> 4)) * 256 + at];
         if (p.logit_bias) v += p.logit_bias[e];
     }
     return v;

@@ -374,7 +374,7 @@ __global__ __launch_bounds__(kFusedTokens * 64) void k_gate_small(Pass p, int n_
         for (int s = threadIdx.x; s < p.S; s += kFusedTokens * 64) blkmask[s] = 0u;
         stage_table(p, tab, map, kFusedTokens * 64);
     }
-    const SmallShare sh(p, wave);
+    const SmallShare sh(p, wave, false);
     f32x4 acc[1];
     small_products<1, XT, WT>(p, t0, sh, lane, acc);
 #pragma unroll

@@ -208,21 +208,21 @@ __global__ __launch_bounds__(kThreads) void k_token_experts(Pass p, int tile_row
         for (int c = tid; c < H; c += kThreads) x[c] = load_f32<T>((const T *)p.x + (size_t)t * H, c);
     for (int s = tid; s < NTT * kSelfMaxSlots; s += kThreads) masks[s] = 0u;
     stage_table(p, tab, map, kThreads);
-    const SmallShare sh(p, wave);
+    const SmallShare sh(p, wave, true);
     f32x4 acc[NTT];
     small_products<NTT, T, WT>(p, 0, sh, lane, acc);
-    if (wave < sh.used) {
+    if (wave < sh.waves()) {
 #pragma unroll
         for (int i = 0; i < NTT; ++i)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) rest[(i * sh.used + wave) * 256 + r * 64 + lane] = acc[i][r];
+            for (int r = 0; r < 4; ++r) rest[(i * sh.waves() + wave) * 256 + r * 64 + lane] = acc[i][r];
     }
     __syncthreads();
     // ---- selection: lanes of a token, its assignment `sub` ----
     constexpr int L = 64 / NTT;
     const int sub = lane & (L - 1), tok = wave * NTT + lane / L, tile = tok / kFusedTokens, in_tile = tok % kFusedTokens;
     const bool own = tok == t;
-    const float logit = small_logit(p, sh, rest + tile * sh.used * 256, in_tile, sub);
+    const float logit = small_logit(p, sh, rest + tile * sh.waves() * 256, in_tile, sub);
     int slot = -1;
     if (wave * NTT < p.T) {                                // uniform
         int id;
