@@ -69,10 +69,10 @@ __device__ __forceinline__ void wait_younger(int xlive)
     else                       wait_loads<kSteps * kWPieces>();
 }
 
-// The part of a task behind the tile lookup, for a tile of up to 16 HT rows; tokens, tok0: the tile's rows where GEMM-1 derived
-// them (kSelf).
+// The part of a task behind the tile lookup, for a tile of up to 16 HT rows; tokens, tok0 (kSelf) or tok (LDS, not NULL): the tile's rows where
+// GEMM-1 derived them.
 template <bool kFirst, bool kSelf, int HT>
-__device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int slice, int slices, unsigned long long tokens, int tok0, char *ring)
+__device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int slice, int slices, unsigned long long tokens, int tok0, const int32_t *tok, char *ring)
 {
     constexpr int TT = (HT + 1) / 2;
     using R = Ring<TT>;
@@ -104,7 +104,7 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
         xoff[i] = 0;
         if (i >= xlive) continue;
         const int row = (wave + kWaves * i) * 8 + (lane >> 3), r = min(row, mt.rows - 1);
-        const int src = kSelf ? nth_set_bit(tokens, tok0 + r) : kFirst ? p.perm[mt.row_begin + r] : mt.row_begin + r;
+        const int src = kSelf ? nth_set_bit(tokens, tok0 + r) : !kFirst ? mt.row_begin + r : tok ? tok[r] : p.perm[mt.row_begin + r];
         xoff[i] = ((uint32_t)src * K + ((lane & 7) ^ swz8(row)) * 8) * 2;
     }
     const int KT = K / kBK;
@@ -201,15 +201,29 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... ta
     std::conditional_t<kSelect, SelfLds, SelfTables> src;
     static_assert(sizeof(SelectLds) <= kLds - 16384 && kSelfTableBytes <= 16384, "the selection borrows the ring, the tables are put together in front of it");
     if constexpr (kSelect) src = select_few(p, *(SelectLds *)(ring + 16384), tab...);
-    if (kSelf) {
-        if (task == 0) { self_tables(p, kRows, ring, src); return; }
-        task -= 1;
+    // The tiles of up to 1024 tokens too are derived here (at run time, in the kernel that reads the list otherwise): a launch and its tables' round trips less, for
+    // 1 to 2 us in front of a workgroup's stream (whole pass, us, k_scan_place -> here: 32 Qwen3 experts, 65 tokens 68.2 -> 65.6, 320 75.9 -> 73.1, 128 experts, 100 tokens 207.8 -> 203.0; DeepSeek-V2-Lite
+    // shape 64 tokens 205.0 -> 201.7, 213 224.0 -> 218.1; 16 experts of 512, 1020 tokens 58.6 -> 55.8; no more tokens were measured).
+    const bool many = kFirst && !kSelf && p.table_blocks > 0;
+    if (kSelf || many) {
+        const int tables = many ? p.table_blocks : 1;
+        if (task < tables) {
+            if (many) many_tables(p, kTiles * kRows, task, ring);
+            else      self_tables(p, kRows, ring, src);
+            return;
+        }
+        task -= tables;
     }
     const int tile = task / slices, slice = task - tile * slices;
     MTile mt;
     unsigned long long tokens = 0;
     int tok0 = 0;
-    if (kSelf) {
+    // in the last 8 KB, which the first copies leave alone: a ring of two token tiles ends before them, one of one copies there behind the first barrier
+    int32_t *tok = many ? (int32_t *)(ring + kLds - 8192) + (threadIdx.x >> 6) * (kTiles * kRows) : nullptr;
+    static_assert(3 * Ring<2>::kStage <= kLds - 8192 && 3 * Ring<1>::kStage <= kLds - 8192, "what is copied before that barrier");
+    if (many) {
+        if (!many_tile(p, threadIdx.x & 63, tile, kTiles * kRows, &mt, tok)) return;
+    } else if (kSelf) {
         if (!self_tile(p, threadIdx.x & 63, tile, kRows, &mt, &tokens, &tok0, src)) return;
         if (kSelect) __syncthreads();   // everyone has read the masks: the ring is free
     } else {
@@ -217,22 +231,25 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... ta
         mt = p.tiles[tile];
     }
     if constexpr (kTiles == 2) {
-        if (mt.rows > 48) { task_body<kFirst, kSelf, 4>(p, mt, slice, slices, tokens, tok0, ring); return; }
-        if (mt.rows > 32) { task_body<kFirst, kSelf, 3>(p, mt, slice, slices, tokens, tok0, ring); return; }
+        if (mt.rows > 48) { task_body<kFirst, kSelf, 4>(p, mt, slice, slices, tokens, tok0, tok, ring); return; }
+        if (mt.rows > 32) { task_body<kFirst, kSelf, 3>(p, mt, slice, slices, tokens, tok0, tok, ring); return; }
     }
-    if (mt.rows > 16) task_body<kFirst, kSelf, 2>(p, mt, slice, slices, tokens, tok0, ring);
-    else              task_body<kFirst, kSelf, 1>(p, mt, slice, slices, tokens, tok0, ring);
+    if (mt.rows > 16) task_body<kFirst, kSelf, 2>(p, mt, slice, slices, tokens, tok0, tok, ring);
+    else              task_body<kFirst, kSelf, 1>(p, mt, slice, slices, tokens, tok0, tok, ring);
 }
 
 }  // namespace
 
 int ring_tile_rows(bool large) { return large ? 2 * kRows : kRows; }
 
+// (sums of rows are kept in 15 bits)
+int self_table_blocks(const Pass &p) { return p.fused_hist && p.S <= kSelfMaxSlots && p.T <= kManyBlocks * kFusedTokens && p.T * p.kk < (1 << 15) ? table_blocks(p) : 0; }
+
 int ring_blocks(const Pass &p) { return p.max_tiles * ((p.I + kBN / 2 - 1) / (kBN / 2)); }
 
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st)
 {
-    const dim3 block(kThreads), grid(which == 0 ? ring_blocks(p) + (p.self_tiles && tile_rows <= kRows ? 1 : 0) : p.max_tiles * ((p.H + kBN - 1) / kBN));
+    const dim3 block(kThreads), grid(which == 0 ? ring_blocks(p) + (p.table_blocks > 0 ? p.table_blocks : p.self_tiles ? 1 : 0) : p.max_tiles * ((p.H + kBN - 1) / kBN));
     if (tile_rows > kRows) {
         if (which == 0) hipLaunchKernelGGL((k_expert_ring<true, false, 2>), grid, block, 0, st, p);
         else            hipLaunchKernelGGL((k_expert_ring<false, false, 2>), grid, block, 0, st, p);
@@ -241,7 +258,7 @@ hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStrea
             hipLaunchKernelGGL((k_expert_ring<true, true, 1, TableArg>), grid, block, 0, st, p, fill_table(p));
         } else if (p.self_select) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1, NoTable>), grid, block, 0, st, p, NoTable{});
-        } else if (p.self_tiles) {
+        } else if (p.self_tiles && p.table_blocks == 0) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1>), grid, block, 0, st, p);
         } else {
             hipLaunchKernelGGL((k_expert_ring<true, false, 1>), grid, block, 0, st, p);

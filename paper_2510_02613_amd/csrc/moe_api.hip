@@ -771,6 +771,8 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
     // few tokens: the weight-streaming GEMM-1 (k_token_experts where that is the launch) derives its tiles itself and writes the tables beside its stream
     p.self_tiles = (tiny || f32 || (whole && !big)) && !identity && self_tiles_possible(p);
+    // the ring's GEMM-1 for more tokens too (table_blocks workgroups write the tables then)
+    if (kernels == Kernels::ring && !whole && !identity && !p.self_tiles) { p.table_blocks = self_table_blocks(p); p.self_tiles = p.table_blocks > 0; }
     const bool one_launch = whole && !routed_ids && token_pass_supports(p);   // and the gate too
     // a token to four: it selects the experts too
     p.self_select = (kernels == Kernels::decode || (kernels == Kernels::ring && !ring64)) && !whole && !routed_ids &&

@@ -89,6 +89,7 @@ struct Pass {
     int32_t gate_tiled;  // the LDS-tiled gate logits kernel is forced (testing aid)
     int32_t self_tiles;  // weight-streaming and fp32 GEMM-1 and k_token_experts only: their workgroups derive their tile from the selection kernel's per-block counts and
                          // masks (self_select, and k_token_experts with the gate: from their own selection) themselves, and workgroup 0 of the launch writes the tables (offsets, permutation, tile list) beside them
+    int32_t table_blocks; // self_tiles, k_expert_ring with tiles of 64 rows or more than 64 tokens: as many workgroups write the tables; else 0
     int32_t self_select; // GEMM-1 selects the experts itself from the logits (a token to four): no selection kernel
     int32_t fused_hist;  // the selection kernel also ranks the assignments (blocks of kFusedTokens tokens, blk_hist [S][blocks]
                          // of token masks); the scan-and-place kernel finishes the bookkeeping
@@ -147,6 +148,7 @@ int f32_tile_rows(const Pass &p);
 // GEMM-1 of these can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
 // at most 4 blocks of tokens and 256 slots: no bookkeeping kernel in front of it
 inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 256 && p.T <= 4 * 16; }
+int self_table_blocks(const Pass &p);   // k_expert_ring, up to 64 blocks: workgroups that write the tables, 0: not possible
 // everything behind the gate and the bookkeeping in one launch, for few tokens of small layers
 bool token_experts_supports(const Pass &p);
 hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st);

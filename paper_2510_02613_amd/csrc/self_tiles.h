@@ -174,6 +174,128 @@ __device__ __forceinline__ bool self_tile(const Pass &p, int lane, int tile, int
     return true;
 }
 
+// The same for more tokens (k_expert_ring): up to kManyBlocks blocks of 16.  A slot's count bytes are one 16-byte load per 16 blocks then, lane b has
+// the mask of block b, and the tile's tokens go through LDS.
+constexpr int kManyBlocks = 64;
+static_assert(fused_row_stride(kManyBlocks) == kManyBlocks, "rows of count bytes are one line");
+// rows of slot s in the blocks before b (16-byte words 0 .. n16 - 1 of its count bytes, n16 = 1 .. 4)
+__device__ __forceinline__ int rows_in_blocks(const uint4 (&v)[4], int n16, int b)
+{
+    int sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (j >= n16) continue;                             // uniform
+        const uint32_t w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n = b - 16 * j - 4 * i;               // bytes of the word that count
+            sum += rows_of(n >= 4 ? w[i] : n <= 0 ? 0u : w[i] & ((1u << (8 * n)) - 1u));
+        }
+    }
+    return sum;
+}
+__device__ __forceinline__ void load_counts(const Pass &p, int s, int n16, uint4 (&v)[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (j < n16) v[j] = ((const uint4 *)(p.blk_cnt + (size_t)s * kManyBlocks))[j];
+}
+struct ManyScan { int c[kSelfLaneSlots], own, incl, spl; };   // as SelfScan, with the slots' rows instead of their count bytes
+__device__ __forceinline__ ManyScan many_scan(const Pass &p, int lane, int nb, int tile_rows)
+{
+    ManyScan r;
+    const int n16 = (nb + 15) >> 4;
+    r.spl = (p.S + 63) >> 6;
+    uint4 v[kSelfLaneSlots][4];
+#pragma unroll
+    for (int i = 0; i < kSelfLaneSlots; ++i)
+        if (i < r.spl) load_counts(p, min(lane * r.spl + i, p.S - 1), n16, v[i]);
+    r.own = 0;
+#pragma unroll
+    for (int i = 0; i < kSelfLaneSlots; ++i) {
+        r.c[i] = 0;
+        if (i < r.spl && lane * r.spl + i < p.S) r.c[i] = rows_in_blocks(v[i], n16, nb);
+        r.own += (r.c[i] << 16) | ((r.c[i] + tile_rows - 1) / tile_rows);
+    }
+    r.incl = wave_incl_scan_i32(r.own);
+    return r;
+}
+// As self_tile; tok (LDS, tile_rows entries of the wavefront's own): the tile's tokens
+__device__ __forceinline__ bool many_tile(const Pass &p, int lane, int tile, int tile_rows, MTile *mt, int32_t *tok)
+{
+    const int nb = (p.T + kFusedTokens - 1) / kFusedTokens;
+    const ManyScan sc = many_scan(p, lane, nb, tile_rows);
+    const unsigned long long owners = __ballot((sc.incl & 0xffff) > tile);
+    if (owners == 0) return false;
+    const int l = __ffsll((long long)owners) - 1;
+    int before = __builtin_amdgcn_readlane(sc.incl - sc.own, l), cs = 0, s = l * sc.spl;
+#pragma unroll
+    for (int i = 0; i < kSelfLaneSlots; ++i) {              // which of the lane's slots (uniform)
+        const int c = __builtin_amdgcn_readlane(sc.c[i], l), nt = (c + tile_rows - 1) / tile_rows;
+        if (cs == 0) {
+            if ((before & 0xffff) + nt > tile) { cs = c; s += i; }
+            else before += (c << 16) | nt;
+        }
+    }
+    const int first = (tile - (before & 0xffff)) * tile_rows;
+    mt->slot = s;
+    mt->row_begin = (before >> 16) + first;
+    mt->rows = min(tile_rows, cs - first);
+    mt->single = cs <= tile_rows;
+    uint32_t m = lane < nb ? (uint32_t)p.blk_hist[(size_t)s * kManyBlocks + lane] & 0xffffu : 0u;
+    int at = wave_incl_scan_i32(__popc(m)) - __popc(m) - first;
+    for (; m; m &= m - 1, ++at)
+        if (at >= 0 && at < mt->rows) tok[at] = lane * kFusedTokens + __ffs((int)m) - 1;
+    wave_sync();
+    return true;
+}
+// Workgroup `part` of those that write the tables: the permutation and its inverse for kTableAssign assignments each, the first one everything else
+constexpr int kTableAssign = 1024;
+inline int table_blocks(const Pass &p) { return (p.T * p.kk + kTableAssign - 1) / kTableAssign; }
+__device__ inline void many_tables(const Pass &p, int tile_rows, int part, void *lds)
+{
+    int32_t *s_off = (int32_t *)lds;                         // [kSelfMaxSlots]
+    const int tid = threadIdx.x, nb = (p.T + kFusedTokens - 1) / kFusedTokens, n16 = (nb + 15) >> 4;
+    if (tid < 64) {
+        const ManyScan sc = many_scan(p, tid, nb, tile_rows);
+        int row = (sc.incl - sc.own) >> 16, tl = (sc.incl - sc.own) & 0xffff;
+#pragma unroll
+        for (int i = 0; i < kSelfLaneSlots; ++i) {
+            const int s = tid * sc.spl + i, c = sc.c[i], nt = (c + tile_rows - 1) / tile_rows;
+            if (i >= sc.spl || s >= p.S) continue;
+            s_off[s] = row;
+            if (part == 0) {
+                p.counts[s] = c;
+                p.offs[s] = row;
+                for (int j = 0; j < nt; ++j, ++tl)
+                    if (tl < p.max_tiles) {
+                        MTile mt;
+                        mt.slot = s; mt.row_begin = row + j * tile_rows; mt.rows = min(tile_rows, c - j * tile_rows); mt.single = nt == 1;
+                        p.tiles[tl] = mt;
+                    }
+            }
+            row += c;
+        }
+        if (part == 0 && tid == 63) {
+            p.offs[p.S] = sc.incl >> 16;
+            *p.n_tiles = min(sc.incl & 0xffff, p.max_tiles);
+        }
+    }
+    __syncthreads();
+    for (int a = part * kTableAssign + tid; a < min((part + 1) * kTableAssign, p.T * p.kk); a += blockDim.x) {
+        const int sr = p.slot_rank[a];
+        int row = -1;
+        if (sr >= 0) {
+            const int slot = sr >> 12, t = a / p.kk;
+            uint4 v[4];
+            load_counts(p, slot, n16, v);
+            row = s_off[slot] + (sr & 0xfff) + rows_in_blocks(v, n16, t / kFusedTokens);
+            p.perm[row] = t;
+        }
+        p.inv[a] = row;
+    }
+}
+
 // A token to four behind the logits kernel alone, selected by a GEMM-1's workgroup of four wavefronts, one a token: their masks and (workgroup 0, which
 // also leaves the ids, the weights and what `tab` brings in the workspace) ranks in LDS.
 constexpr int kSelectTokens = 4, kSelectExperts = 128, kSelectKK = 36;   // top_k <= 32 plus <= 4 shared experts

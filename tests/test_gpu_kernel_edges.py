@@ -546,6 +546,43 @@ def test_small_layers_gate_and_experts_in_one_launch(act, router, tokens, expert
     both()
 
 
+@pytest.mark.parametrize("tokens,experts,k,local,shared", [(33, 256, 4, 60, 1), (64, 256, 4, 63, 1), (65, 96, 3, 63, 2), (65, 256, 8, 254, 0), (128, 256, 8, 200, 0), (256, 64, 4, 61, 1), (257, 64, 4, 20, 4),
+                                                           (511, 256, 4, 255, 1), (513, 256, 4, 256, 1), (1024, 256, 4, 129, 1), (1025, 256, 4, 129, 1)])
+def test_ring_kernels_derive_the_tiles_of_many_tokens(tokens, experts, k, local, shared):
+    """The ring's GEMM-1 that derives its tiles for up to 1024 tokens and 256 slots, at the ends of blocks of 16 tokens, of the 16 blocks of a load, of a slot per lane, of a workgroup's share
+    of the tables, and the first sizes past it: several tiles a slot, experts elsewhere, a slot without rows, copies of an expert.  Tables, h, y and output as with separate bookkeeping kernels, bit for bit, on a
+    workspace poisoned before every pass."""
+    from gpu_util import Case, check_bookkeeping, check_output, check_routing
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="many", tokens=tokens, hidden=128, inter=128, n_experts=experts, top_k=k, n_slots=local + shared, n_local=local - 2,
+                     act_dtype="bf16", router_dtype="bf16", gate="softmax", n_shared=shared, shared_range=(0, min(tokens, 300) if shared else 0), seed=2000 + tokens + local)
+    case = Case(wl, expert_map=block_expert_map(experts, 0, local - 2, np.random.Generator(np.random.PCG64(local)).permutation(local)[:local - 2]))
+    names = _kernels(case, tokens, wl.shared_range)
+    assert "k_expert_ring" in names and ("k_scan_place" in names) == (tokens > 1024 or local + shared > 256), names
+    scratch = B.moe_workspace_view(case.layer.handle).topk_ids - case.layer.workspace.data_ptr()
+
+    def both():
+        runs = []
+        for flags in (0, B.MOE_FLAG_PERMUTE_UNFUSED):
+            case.layer.workspace[scratch:].fill_(0xff)
+            runs.append((case.run(flags=flags), case.layer.view(tokens)))
+        np.testing.assert_array_equal(runs[0][0], runs[1][0])
+        for key in ("topk_ids", "topk_w", "counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+            np.testing.assert_array_equal(runs[0][1][key], runs[1][1][key])
+        return runs[0]
+    out, v = both()
+    ids, _, _ = check_routing(case, v["topk_ids"], v["topk_w"])
+    check_bookkeeping(case, v, tokens, wl.shared_range)
+    check_output(case, out, ids)
+    taken = set(int(m) for m in case.expert_map) | set(int(s) for s in case.shared_slots)
+    spare = [s for s in range(wl.n_slots) if s not in taken][:2]
+    case.layer.set_expert_replicas([[int(m)] + (spare if e == 1 else []) if m >= 0 else [] for e, m in enumerate(case.expert_map)], case.shared_slots if shared else None)
+    both()
+    case.layer.set_expert_map(case.expert_map, case.shared_slots if shared else None)
+    case.layer.router_w.zero_()                    # equal scores: every token takes the first k experts, slots with all of them
+    both()
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 3])
 @pytest.mark.parametrize("hidden,inter", [(136, 512), (72, 520), (64, 1024), (104, 1544), (4096, 72), (4104, 72)])
 def test_second_gemm_and_combine_of_a_token_or_two(tokens, hidden, inter):
