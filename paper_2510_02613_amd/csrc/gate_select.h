@@ -333,9 +333,10 @@ __device__ __forceinline__ int select_lanes(const Pass &p, int t, float v, int l
 }
 
 // One token's selection from its logits: the planes (partial sums of the K ranges) are added in K order.  They come
-// from other XCDs' L2s, so PZ planes of all of a lane's experts are requested before anything is added.
-template <int NR, int PZ>
-__device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *lg, float *cs, int lane, bool store = true)
+// from other XCDs' L2s, so PZ planes of all of a lane's experts are requested before anything is added.  `beside` is called behind the
+// first requests: what a workgroup stages for later goes there, in the shadow of that round trip.
+template <int NR, int PZ, typename Beside>
+__device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *lg, float *cs, int lane, bool store, Beside beside)
 {
     const float *src = p.logits + (size_t)t * p.E;
     const size_t plane = (size_t)p.T * p.E;
@@ -350,6 +351,7 @@ __device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *l
 #pragma unroll
                 for (int i = 0; i < NR; ++i) part[z][i] = src[(z0 + z) * plane + min(64 * i + lane, p.E - 1)];
             }
+        if (z0 == 0) beside();
 #pragma unroll
         for (int z = 0; z < PZ; ++z)
             if (z0 + z < p.logit_planes) {
@@ -362,13 +364,14 @@ __device__ __forceinline__ int select_from_planes(const Pass &p, int t, float *l
 // Up to 512 experts in registers: above 256 the LDS form, which re-reads the scores in every round, costs more at every
 // batch size (whole pass, us, LDS -> registers: 384 experts on rows of 7168, 64 tokens 119 -> 104 and 8192 tokens 239 -> 232;
 // 512 experts on rows of 2048, 1 token 30 -> 20 and 30000 tokens 381 -> 339).
-template <int PZ>
-__device__ __forceinline__ int select_one(const Pass &p, int t, float *lg, float *cs, int lane)
+template <int PZ, typename Beside>
+__device__ __forceinline__ int select_one(const Pass &p, int t, float *lg, float *cs, int lane, Beside beside)
 {
-    if (p.E <= 64)  return select_from_planes<1, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 128) return select_from_planes<2, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 256) return select_from_planes<4, PZ>(p, t, lg, cs, lane);
-    if (p.E <= 512) return select_from_planes<8, PZ>(p, t, lg, cs, lane);
+    if (p.E <= 64)  return select_from_planes<1, PZ>(p, t, lg, cs, lane, true, beside);
+    if (p.E <= 128) return select_from_planes<2, PZ>(p, t, lg, cs, lane, true, beside);
+    if (p.E <= 256) return select_from_planes<4, PZ>(p, t, lg, cs, lane, true, beside);
+    if (p.E <= 512) return select_from_planes<8, PZ>(p, t, lg, cs, lane, true, beside);
+    beside();
     const float *src = p.logits + (size_t)t * p.E;
     const size_t plane = (size_t)p.T * p.E;
     for (int e = lane; e < p.E; e += 64) {

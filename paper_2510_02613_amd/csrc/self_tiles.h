@@ -311,12 +311,12 @@ __device__ __forceinline__ SelfLds select_few(const Pass &p, SelectLds &s, const
     const bool first = blockIdx.x == 0;
     for (int i = threadIdx.x; i < kSelfMaxSlots; i += kSelectTokens * 64) s.masks[i] = 0u;
     stage_table(p, tab, s.map, kSelectTokens * 64);
-    __syncthreads();
+    __syncthreads();   // (requesting the logits first, as in the selection kernel, was no faster here: one token of the Qwen3 shape 27.1 -> 27.3)
     int slot = -1;
     if (t < p.T) {
         float *lg = s.scores[t], *cs = lg + kSelectExperts;
-        const int id = p.E <= 64 ? select_from_planes<1, kGatePlanes>(p, t, lg, cs, lane, first)
-                                 : select_from_planes<2, kGatePlanes>(p, t, lg, cs, lane, first);
+        const int id = p.E <= 64 ? select_from_planes<1, kGatePlanes>(p, t, lg, cs, lane, first, [] {})
+                                 : select_from_planes<2, kGatePlanes>(p, t, lg, cs, lane, first, [] {});
         slot = slot_of_lane(p, s.map, t, lane, id);
         if (slot >= 0) atomicOr(&s.masks[slot], 1u << t);
     }
