@@ -35,6 +35,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBK = 64;   // K-step
+constexpr int kChain = 8;   // K-steps that are added up in the matrix cores' accumulators before they go to a sum
 
 __device__ __forceinline__ uint32_t lds_addr(const void *p)
 {
@@ -157,11 +158,18 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
         }
     }
 
-    f32x4 acc[EBT][TBT];
+    // sum: what every kChain K-steps leave, so that a logit's error does not grow with the K-steps of a split
+    f32x4 acc[EBT][TBT], sum[EBT][TBT];
 #pragma unroll
     for (int a = 0; a < EBT; ++a)
 #pragma unroll
-        for (int tb = 0; tb < TBT; ++tb) acc[a][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int tb = 0; tb < TBT; ++tb) acc[a][tb] = sum[a][tb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    auto flush = [&]() {
+#pragma unroll
+        for (int a = 0; a < EBT; ++a)
+#pragma unroll
+            for (int tb = 0; tb < TBT; ++tb) { sum[a][tb] += acc[a][tb]; acc[a][tb] = (f32x4){0.f, 0.f, 0.f, 0.f}; }
+    };
 
     auto multiply = [&](int slot) {
         const char *X = ring + slot * STAGE + wt * TBT * 16 * 128;
@@ -209,6 +217,7 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
         __syncthreads();   // everyone's pieces of step kt have landed; everyone is done reading step kt-1
         if (kt + NS - 1 < kt1) issue(kt + NS - 1, fill);
         multiply(slot);
+        if (((kt - kt0) & (kChain - 1)) == kChain - 1) flush();
         slot = slot + 1 == NS ? 0 : slot + 1;
         fill = fill + 1 == NS ? 0 : fill + 1;
     }
@@ -216,6 +225,7 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     // ---- epilogue: accumulators -> this wavefront's LDS region [token][expert] -> whole row segments ----
     // A lane holds token n of each token tile and experts 4q .. 4q+3 of each of its expert tiles:
     // stored straight from registers every instruction would touch 16 rows, 64 bytes each.
+    flush();
     __syncthreads();   // all operand reads are done: the ring becomes the staging area
     float *plane = p.logits + (size_t)blockIdx.z * p.T * E;
     const float *bias = blockIdx.z == 0 ? p.logit_bias : nullptr;   // added once
@@ -226,7 +236,7 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     for (int a = 0; a < EBT; ++a)
 #pragma unroll
         for (int tb = 0; tb < TBT; ++tb)
-            *(f32x4 *)(stg + (tb * 16 + n) * STRIDE + a * 16 + 4 * q) = acc[a][tb];
+            *(f32x4 *)(stg + (tb * 16 + n) * STRIDE + a * 16 + 4 * q) = sum[a][tb];
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_wave_barrier();
     constexpr int LPR = COLS / 4, RPI = 64 / LPR;        // lanes per row, rows per instruction
@@ -266,15 +276,11 @@ hipError_t launch_t(const Pass &p, int planes, hipStream_t st)
     return hipGetLastError();
 }
 
-// K splits for a tiling with n_tiles output tiles: enough workgroups for the chip, at least 8
-// K-steps each (the ring needs a few steps to reach its depth), at most kGatePlanes
-int splits_for(long long n_tiles, int KT)
-{
-    long long z = (256 + n_tiles - 1) / n_tiles;
-    if (z > kGatePlanes) z = kGatePlanes;
-    if (z > KT / 8) z = KT / 8;
-    return z < 1 ? 1 : (int)z;
-}
+// The tilings: tokens x experts of a workgroup, and the us that one of its K-steps takes (bf16, fp32 router), measured on 150 to 8000 tokens of 64, 128 and 256
+// experts on rows of 2048 and 7168.
+struct Tiling { int tokens, experts[2]; float step[2]; };
+constexpr Tiling kTilings[3] = {{32, {64, 64}, {0.25f, 0.45f}}, {64, {128, 128}, {0.35f, 0.8f}}, {128, {256, 128}, {0.85f, 1.1f}}};
+constexpr float kTileUs = 0.5f, kPlaneBytesPerUs = 5e6f;   // a workgroup's start and end; the planes' way out and back
 
 }  // namespace
 
@@ -287,15 +293,23 @@ bool gate_dma_supports(const Pass &p)
 // Writes *planes partial-sum planes [T,E] to p.logits.
 hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st)
 {
-    // tilings, largest first: tokens x experts per workgroup.  The first one that fills the chip
-    // (with its K splits) and whose expert block is not mostly padding is taken.
-    const int KT = p.H / kBK;
-    auto tiles = [&](int tb, int eb) { return (long long)((p.T + tb - 1) / tb) * ((p.E + eb - 1) / eb); };
-    const int ebL = p.router_bf16 ? 256 : 128;
-    int cfg = 0;
-    if (p.E > ebL / 2 && tiles(128, ebL) * splits_for(tiles(128, ebL), KT) >= 192) cfg = 2;
-    else if (p.E > 64 && tiles(64, 128) * splits_for(tiles(64, 128), KT) >= 192) cfg = 1;
-    const int z = cfg == 2 ? splits_for(tiles(128, ebL), KT) : cfg == 1 ? splits_for(tiles(64, 128), KT) : splits_for(tiles(32, 64), KT);
+    // The tiling and the K split (at most kGatePlanes, at least 4 K-steps each) with the shortest time by that measure: rounds of the 256 compute units, each with one workgroup, times
+    // K-steps, and what the planes cost.  What matters is that a launch is one round: the largest tiling that filled the chip, split into ceil(256 / tiles), was
+    // a little more than one round nearly everywhere.  Gate phase, us, that -> this: 128 experts on rows of 2048 (fp32 router) 333 tokens 15.3 -> 13.7, 1100 21.1 -> 17.2, 2200 28.8 -> 18.7,
+    // 3000 28.7 -> 20.2, 6000 37.4 -> 29.1, where it was one round 4096 22.0 -> 22.0; 256 on rows of 7168 (bf16) 700 tokens 28.0 -> 22.8, 2500 37.1 -> 29.7,
+    // 5000 62.4 -> 45.0, 8000 81.2 -> 61.4, slower 512 20.3 -> 20.8; 64 on rows of 2048 2500 20.4 -> 16.7.  The best of all (tiling, split) pairs is 0.3 % faster on average over 47 such sizes.
+    const int KT = p.H / kBK, f32 = p.router_bf16 ? 0 : 1;
+    int cfg = 0, z = 1;
+    float best = 0.f;
+    for (int c = 0; c < 3; ++c) {
+        const Tiling &t = kTilings[c];
+        if (c > 0 && p.E <= t.experts[f32] / 2) continue;      // mostly padding
+        const long long tiles = (long long)((p.T + t.tokens - 1) / t.tokens) * ((p.E + t.experts[f32] - 1) / t.experts[f32]);
+        for (int n = 1; n <= kGatePlanes && (n == 1 || KT / n >= 4); ++n) {
+            const float us = (float)((tiles * n + 255) / 256) * (kTileUs + (float)((KT + n - 1) / n) * t.step[f32]) + (float)n * (float)p.T * (float)p.E * 8.f / kPlaneBytesPerUs;
+            if ((c == 0 && n == 1) || us < best) { best = us; cfg = c; z = n; }
+        }
+    }
     *planes = z;
     // 128 x 256 (bf16 router) or 128 x 128 (fp32 router) on 8 wavefronts (2 x 4), 64 x 128 on 8, 32 x 64 on 4
     if (p.router_bf16) return cfg == 2 ? launch_t<uint16_t, 4, 4, 3, 8, 2>(p, z, st) : cfg == 1 ? launch_t<uint16_t, 2, 2, 6, 8, 2>(p, z, st) : launch_t<uint16_t, 2, 1, 6, 4, 1>(p, z, st);

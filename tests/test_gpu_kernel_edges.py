@@ -186,6 +186,25 @@ def test_largest_gate_tilings_at_few_steps(hidden, tokens, router, experts):
     check_routing(case, v["topk_ids"], v["topk_w"])
 
 
+@pytest.mark.parametrize("router,experts,hidden,tokens,tiling", [
+    ("f32", 64, 1024, 129, "2, 1, 6, 4, 1"), ("f32", 100, 1088, 600, "2, 1, 6, 4, 1"), ("bf16", 65, 512, 250, "2, 1, 6, 4, 1"),
+    ("f32", 100, 1088, 2600, "4, 1, 4, 8, 1"), ("bf16", 200, 1088, 2600, "2, 2, 6, 8, 2"), ("bf16", 256, 2112, 4100, "2, 2, 6, 8, 2"),
+    ("f32", 128, 1088, 12300, "4, 2, 3, 8, 2"), ("bf16", 200, 1152, 12300, "4, 4, 3, 8, 2"), ("bf16", 129, 1152, 24460, "4, 4, 3, 8, 2")])
+def test_gate_tilings_by_rounds_of_the_chip(router, experts, hidden, tokens, tiling):
+    """The tilings that the rule by rounds and K-steps takes, with splits of 4, of 8 and of more K-steps (which go to a sum every 8) and shares of unequal length.  Routing of every
+    token against the oracle."""
+    from gpu_util import Case, check_routing, kernels_of
+    wl = MoEWorkload(name="gate_rounds", tokens=tokens, hidden=hidden, inter=8, n_experts=experts, top_k=3, n_slots=2, n_local=2,
+                     act_dtype="bf16", router_dtype=router, gate="softmax", seed=60 + hidden + experts)
+    case = Case(wl)
+    spare = case.x_dev.clone()
+    names = kernels_of(lambda s: case.layer.forward(case.x_dev, out=spare, stream=s))
+    assert any(n.startswith("k_gate_logits_dma") and n.rstrip(">").endswith(", " + tiling) for n in names), names
+    case.run()
+    v = case.layer.view(tokens)
+    check_routing(case, v["topk_ids"], v["topk_w"])
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
