@@ -417,10 +417,11 @@ hipError_t launch_logits_bf16(const Pass &p, int *planes, hipStream_t st)
 {
     // Up to a hundred or so tokens there are too few (token, expert) tiles for the LDS-tiled kernels: the
     // K-split kernel reads both operands straight into registers, 16 tokens x 16 experts per workgroup, and
-    // shares the contraction out over its wavefronts and over workgroups.  (Without the direct-to-LDS
+    // shares the contraction out over its wavefronts and over workgroups, until the router, which it reads once per 16 tokens, comes to 16 MB (gate phase, us, this kernel ->
+    // the direct-to-LDS one: DeepSeek-V3-shaped rank 64 tokens, 15 MB, 17.5 -> 18.2, 80, 18 MB, 19.6 -> 18.4, 128, 29 MB, 21.4 -> 18.7; Qwen3 shape 128, 8 MB, 13.1 -> 13.7, 144 13.9 -> 13.9).  (Without the direct-to-LDS
     // kernel -- H not a multiple of 64 -- it stays ahead until the router re-reads reach about 128 MB.)
     const size_t router_rereads = (size_t)((p.T + 15) / 16) * p.E * p.H * (p.router_bf16 ? 2 : 4);
-    const bool small = gate_dma_supports(p) ? p.T <= 128 : (p.T <= kGateFewTokens || router_rereads <= (size_t)128 << 20);
+    const bool small = gate_dma_supports(p) ? p.T <= 128 && router_rereads <= (size_t)16 << 20 : (p.T <= kGateFewTokens || router_rereads <= (size_t)128 << 20);
     *planes = 1;
     if (!p.gate_tiled && small) {
         *planes = few_token_planes(p.T, p.H);
