@@ -209,23 +209,25 @@ __global__ __launch_bounds__(NW * 64) void k_gate_logits_dma(Pass p)
     // ---- K loop: steps kt+1 .. kt+NS-1 are in flight while step kt is multiplied ----
     for (int s = 0; s < NS - 1 && kt0 + s < kt1; ++s) issue(kt0 + s, s);
     int slot = 0, fill = NS - 1;
-    for (int kt = kt0; kt < kt1; ++kt) {
-        // Behind step kt's copies those of NS - 2 steps were issued and may stay on their way; the last steps wait for all.  (Counted down
-        // exactly, by a switch over the immediates of the instruction, it was slower.)
-        if (kt + NS - 2 < kt1) wait_loads<(NS - 2) * PW>();
-        else                   wait_loads<0>();
-        __syncthreads();   // everyone's pieces of step kt have landed; everyone is done reading step kt-1
-        if (kt + NS - 1 < kt1) issue(kt + NS - 1, fill);
-        multiply(slot);
-        if (((kt - kt0) & (kChain - 1)) == kChain - 1) flush();
-        slot = slot + 1 == NS ? 0 : slot + 1;
-        fill = fill + 1 == NS ? 0 : fill + 1;
+    for (int kt = kt0; kt < kt1;) {
+        const int end = min(kt + kChain, kt1);
+        for (; kt < end; ++kt) {
+            // Behind step kt's copies those of NS - 2 steps were issued and may stay on their way; the last steps wait for all.  (Counted down
+            // exactly, by a switch over the immediates of the instruction, it was slower.)
+            if (kt + NS - 2 < kt1) wait_loads<(NS - 2) * PW>();
+            else                   wait_loads<0>();
+            __syncthreads();   // everyone's pieces of step kt have landed; everyone is done reading step kt-1
+            if (kt + NS - 1 < kt1) issue(kt + NS - 1, fill);
+            multiply(slot);
+            slot = slot + 1 == NS ? 0 : slot + 1;
+            fill = fill + 1 == NS ? 0 : fill + 1;
+        }
+        flush();
     }
 
     // ---- epilogue: accumulators -> this wavefront's LDS region [token][expert] -> whole row segments ----
     // A lane holds token n of each token tile and experts 4q .. 4q+3 of each of its expert tiles:
     // stored straight from registers every instruction would touch 16 rows, 64 bytes each.
-    flush();
     __syncthreads();   // all operand reads are done: the ring becomes the staging area
     float *plane = p.logits + (size_t)blockIdx.z * p.T * E;
     const float *bias = blockIdx.z == 0 ? p.logit_bias : nullptr;   // added once
@@ -279,8 +281,8 @@ hipError_t launch_t(const Pass &p, int planes, hipStream_t st)
 // The tilings: tokens x experts of a workgroup, and the us that one of its K-steps takes (bf16, fp32 router), measured on 150 to 8000 tokens of 64, 128 and 256
 // experts on rows of 2048 and 7168.
 struct Tiling { int tokens, experts[2]; float step[2]; };
-constexpr Tiling kTilings[3] = {{32, {64, 64}, {0.25f, 0.45f}}, {64, {128, 128}, {0.35f, 0.8f}}, {128, {256, 128}, {0.85f, 1.1f}}};
-constexpr float kTileUs = 0.5f, kPlaneBytesPerUs = 5e6f;   // a workgroup's start and end; the planes' way out and back
+constexpr Tiling kTilings[3] = {{32, {64, 64}, {0.21f, 0.45f}}, {64, {128, 128}, {0.38f, 0.8f}}, {128, {256, 128}, {0.95f, 1.1f}}};
+constexpr float kTileUs = 0.5f, kPlaneBytesPerUs = 6e6f;   // a workgroup's start and end; the planes' way out and back
 
 }  // namespace
 
@@ -296,8 +298,8 @@ hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st)
     // The tiling and the K split (at most kGatePlanes, at least 4 K-steps each) with the shortest time by that measure: rounds of the 256 compute units, each with one workgroup, times
     // K-steps, and what the planes cost.  What matters is that a launch is one round: the largest tiling that filled the chip, split into ceil(256 / tiles), was
     // a little more than one round nearly everywhere.  Gate phase, us, that -> this: 128 experts on rows of 2048 (fp32 router) 333 tokens 15.3 -> 13.7, 1100 21.1 -> 17.2, 2200 28.8 -> 18.7,
-    // 3000 28.7 -> 20.2, 6000 37.4 -> 29.1, where it was one round 4096 22.0 -> 22.0; 256 on rows of 7168 (bf16) 700 tokens 28.0 -> 22.8, 2500 37.1 -> 29.7,
-    // 5000 62.4 -> 45.0, 8000 81.2 -> 61.4, slower 512 20.3 -> 20.8; 64 on rows of 2048 2500 20.4 -> 16.7.  The best of all (tiling, split) pairs is 0.3 % faster on average over 47 such sizes.
+    // 3000 28.7 -> 20.2, 6000 37.4 -> 29.1, where it was one round 4096 22.0 -> 22.0; 256 on rows of 7168 (bf16) 512 tokens 20.3 -> 20.3, 700 28.0 -> 22.5, 2500 37.1 -> 29.7,
+    // 5000 62.4 -> 45.0, 8000 81.2 -> 61.4; 64 on rows of 2048 2500 20.4 -> 16.7.  The best of all (tiling, split) pairs is 0.3 % faster on average over 47 such sizes.
     const int KT = p.H / kBK, f32 = p.router_bf16 ? 0 : 1;
     int cfg = 0, z = 1;
     float best = 0.f;
