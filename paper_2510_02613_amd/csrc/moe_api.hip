@@ -668,6 +668,8 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     //  * finer tasks and shorter bookkeeping win, the more so the fewer slots there are to fill the chip: Qwen3 shape with 2 local experts,
     //    50 tokens 55 -> 30; 8, 300 tokens 59 -> 46; 32, 140 tokens 96 -> 74; 64, 200 tokens 127 -> 120; 128, 100 tokens 219 -> 214;
     //    24 experts of 1024 x 768, 250 tokens 65 -> 52, of 128 x 128, 40 tokens 24 -> 24;
+    //    (with the large tiles' last round in parts and the tiles derived in ring64's GEMM-1, large -> ring64: 8 experts, 310 tokens 42.9 -> 39.3; 16 50.9 -> 45.6; 24 65.4 -> 66.9; 32 73.2 -> 72.1; 64 123.3 ->
+    //    119.0; 16 of DeepSeek-V2-Lite, 210 tokens 100.5 -> 90.2; past the line below 16 Qwen3 experts, 400 tokens 51.8 -> 48.4, 24 67.3 -> 68.5);
     //  * what it costs: an even load of 200 or 300 tokens on 32 Qwen3 experts 74.5 -> 75, 75.5 -> 77, of 160 on 24 of them 54 -> 58 (a
     //    Zipf(1.2) one, 310 tokens on 32, 98 -> 68);
     //  * rows of 2560, 3072 and 4096 gain as much: 768 wide, 80 to 300 tokens, 8 local experts -27 to -32 %, 16 -17 to -40 %, 32 0 to
