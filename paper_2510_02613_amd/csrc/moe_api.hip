@@ -775,7 +775,10 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
     p.self_tiles = (tiny || f32 || (whole && !big)) && !identity && self_tiles_possible(p);
     // the ring's GEMM-1 for more tokens too (table_blocks workgroups write the tables then)
     if (kernels == Kernels::ring && !whole && !identity && !p.self_tiles) { p.table_blocks = self_table_blocks(p); p.self_tiles = p.table_blocks > 0; }
-    const bool one_launch = whole && !routed_ids && token_pass_supports(p);   // and the gate too
+    // and the gate too, unless out lies on x: its workgroups all read all token rows and write their own row of out, in no order
+    const size_t row_bytes = (size_t)T * p.H * esize(c.act_dtype);
+    const bool apart = (uintptr_t)x + row_bytes <= (uintptr_t)out || (uintptr_t)out + row_bytes <= (uintptr_t)x;
+    const bool one_launch = whole && !routed_ids && apart && token_pass_supports(p);
     // a token to four: it selects the experts too
     p.self_select = (kernels == Kernels::decode || (kernels == Kernels::ring && !ring64)) && !whole && !routed_ids &&
                     gemm1_selects(p, kernels == Kernels::decode ? decode_blocks(p) : ring_blocks(p)) && !one_gate_kernel(p);

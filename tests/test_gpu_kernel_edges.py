@@ -565,6 +565,46 @@ def test_small_layers_gate_and_experts_in_one_launch(act, router, tokens, expert
     both()
 
 
+_ON_X = [   # act, tokens, experts, k, hidden, inter, flags, kernels of the pass with out on x
+    ("f32", 1, 8, 2, 128, 56, 0, ["k_gate_small", "k_token_experts"]), ("f32", 16, 64, 4, 512, 8, 0, ["k_gate_small", "k_token_experts"]),
+    ("f32", 64, 8, 2, 128, 56, 0, ["k_gate_small", "k_token_experts"]), ("bf16", 1, 8, 2, 128, 64, 0, ["k_gate_small", "k_token_experts"]),
+    ("bf16", 32, 17, 3, 136, 24, 0, ["k_gate_small", "k_token_experts"]), ("bf16", 50, 16, 3, 136, 24, 0, ["k_gate_small", "k_token_experts"]),
+    ("f32", 200, 8, 2, 128, 56, 0, "k_token_experts"), ("bf16", 256, 8, 2, 128, 64, 0, "k_token_experts"),
+    ("f32", 20, 40, 4, 264, 264, 0, "k_expert_f32"), ("f32", 600, 40, 4, 264, 264, 0, "k_expert_f32_tile"),
+    ("bf16", 1, 72, 4, 576, 512, 0, "k_expert_decode"), ("bf16", 7, 72, 4, 584, 520, 0, "k_expert_decode"),
+    ("bf16", 4, 96, 8, 576, 512, 0, "k_expert_ring"), ("bf16", 47, 96, 4, 320, 320, 0, "k_expert_ring"), ("bf16", 300, 96, 4, 320, 320, 0, "k_expert_ring"),
+    ("bf16", 700, 16, 4, 136, 200, 0, "k_expert_gemm_mfma"), ("bf16", 900, 16, 4, 64, 192, 0, "k_expert_gemm_mfma8"),
+    ("bf16", 64, 16, 4, 136, 200, 2, "k_expert_gemm_generic"), ("bf16", 64, 16, 4, 136, 200, 1, "k_identity_experts")]
+
+
+@pytest.mark.parametrize("act,tokens,experts,k,hidden,inter,flags,kernels", _ON_X)
+def test_output_on_the_input(act, tokens, experts, k, hidden, inter, flags, kernels):
+    """out = x with every family of expert kernels: output, ids, weights, tables, h and y as with a buffer of its own, bit for bit.  Small layers then have their gate in a launch of its own, in front of
+    the one that writes out."""
+    from gpu_util import Case, kernels_of
+    wl = MoEWorkload(name="on_x", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=k, n_slots=experts, n_local=experts - 2,
+                     act_dtype=act, router_dtype="f32", gate="softmax", n_shared=1, shared_range=(tokens // 3, tokens // 3 + (tokens + 2) // 4), seed=2100 + tokens)
+    case = Case(wl)
+    sr, x = wl.shared_range, case.x_dev
+
+    def forward(inp, out, stream=None):
+        return case.layer.forward(inp, out=out, shared_range=sr, flags=flags, stream=stream)
+    names = [n.split("<")[0] for n in kernels_of(lambda s: forward(x, x, s))]
+    assert names == kernels if isinstance(kernels, list) else kernels in names, names
+    keys = ("topk_ids", "topk_w", "counts", "offsets", "perm", "inv", "tiles", "h", "y")
+    want, v = forward(x, x.clone()), case.layer.view(tokens)
+    own = x.clone()
+    forward(own, own)
+    w = case.layer.view(tokens)
+    np.testing.assert_array_equal(own.cpu().numpy(), want.cpu().numpy())
+    for key in keys:
+        np.testing.assert_array_equal(v[key], w[key])
+    if flags == 0 and tokens <= 64:
+        own = x.clone()
+        case.layer.forward_static(own, out=own, shared_range=sr)
+        np.testing.assert_array_equal(own.cpu().numpy(), want.cpu().numpy())
+
+
 @pytest.mark.parametrize("tokens,experts,k,local,shared", [(33, 256, 4, 60, 1), (64, 256, 4, 63, 1), (65, 96, 3, 63, 2), (65, 256, 8, 254, 0), (128, 256, 8, 200, 0), (256, 64, 4, 61, 1), (257, 64, 4, 20, 4),
                                                            (511, 256, 4, 255, 1), (513, 256, 4, 256, 1), (1024, 256, 4, 129, 1), (1025, 256, 4, 129, 1)])
 def test_ring_kernels_derive_the_tiles_of_many_tokens(tokens, experts, k, local, shared):
