@@ -770,14 +770,16 @@ static moe_status_t forward_pass(moe_layer_t *l, const void *x, int32_t T, const
         p.tiles_expected = (int)(resident * (1.0 - std::exp(-rows)) + 0.5) * p.slot_tiles_expected + p.n_shared * ((shared_end - shared_begin + most - 1) / most);
     }
 
-    const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
+    // Where out lies on x: every pass writes out behind the last launch that reads x, except those that go token by token.  There a workgroup has read its own
+    // row of x before it writes its row of out, but other workgroups may not have read theirs: out may be x itself, and nothing else that meets it.
+    const size_t row_bytes = (size_t)T * p.H * esize(c.act_dtype);
+    const bool apart = (uintptr_t)x + row_bytes <= (uintptr_t)out || (uintptr_t)out + row_bytes <= (uintptr_t)x;
+    const bool whole = !identity && !(flags & MOE_FLAG_FORCE_GENERIC) && (apart || x == out) && token_experts_supports(p);   // GEMM-1, GEMM-2 and combine in one launch, recorded as GEMM-1
     // few tokens: the weight-streaming GEMM-1 (k_token_experts where that is the launch) derives its tiles itself and writes the tables beside its stream
     p.self_tiles = (tiny || f32 || (whole && !big)) && !identity && self_tiles_possible(p);
     // the ring's GEMM-1 for more tokens too (table_blocks workgroups write the tables then)
     if (kernels == Kernels::ring && !whole && !identity && !p.self_tiles) { p.table_blocks = self_table_blocks(p); p.self_tiles = p.table_blocks > 0; }
-    // and the gate too, unless out lies on x: its workgroups all read all token rows and write their own row of out, in no order
-    const size_t row_bytes = (size_t)T * p.H * esize(c.act_dtype);
-    const bool apart = (uintptr_t)x + row_bytes <= (uintptr_t)out || (uintptr_t)out + row_bytes <= (uintptr_t)x;
+    // and the gate too, for which all of its workgroups read all token rows
     const bool one_launch = whole && !routed_ids && apart && token_pass_supports(p);
     // a token to four: it selects the experts too
     p.self_select = (kernels == Kernels::decode || (kernels == Kernels::ring && !ring64)) && !whole && !routed_ids &&

@@ -605,6 +605,41 @@ def test_output_on_the_input(act, tokens, experts, k, hidden, inter, flags, kern
         np.testing.assert_array_equal(own.cpu().numpy(), want.cpu().numpy())
 
 
+@pytest.mark.parametrize("routed", [False, True])
+@pytest.mark.parametrize("act,tokens,experts,k,hidden,inter", [("f32", 2, 8, 2, 128, 56), ("f32", 64, 8, 2, 128, 56), ("bf16", 50, 16, 3, 136, 24), ("f32", 200, 8, 2, 128, 56),
+                                                               ("bf16", 256, 8, 2, 128, 64), ("bf16", 4, 96, 8, 576, 512), ("bf16", 300, 96, 4, 320, 320)])
+def test_output_that_meets_the_input(act, tokens, experts, k, hidden, inter, routed):
+    """out a few rows, or less than one, before or behind x: other kernels than token by token, and the output that a buffer of its own has, to the oracle's bar (bit for bit where the kernels are the same)."""
+    import torch
+    from gpu_util import TOL, Case, kernels_of, rel_err, tensor_to_host, to_f64
+    wl = MoEWorkload(name="meets", tokens=tokens, hidden=hidden, inter=inter, n_experts=experts, top_k=k, n_slots=experts, n_local=experts - 2,
+                     act_dtype=act, router_dtype="f32", gate="softmax", n_shared=1, shared_range=(0, tokens // 2), seed=2200 + tokens)
+    case = Case(wl)
+    sr, x = wl.shared_range, case.x_dev
+    v = case.layer.forward(x, shared_range=sr) is not None and case.layer.view(tokens)
+    ids, w = (torch.from_numpy(np.ascontiguousarray(v[key])).to(x.device) for key in ("topk_ids", "topk_w"))
+
+    def forward(inp, out, stream=None):
+        if routed:
+            return case.layer.forward_routed(inp, ids, w, out=out, shared_range=sr, stream=stream)
+        return case.layer.forward(inp, out=out, shared_range=sr, stream=stream)
+    want = tensor_to_host(forward(x, x.clone()))
+    same = "k_token_experts" not in [n.split("<")[0] for n in kernels_of(lambda s: forward(x, x.clone(), s))]
+    for shift in (8, hidden, 3 * hidden):                       # elements between the two
+        for ahead in (False, True):
+            both = torch.empty(tokens * hidden + shift, dtype=x.dtype, device=x.device)
+            lo, hi = both[:tokens * hidden].view(tokens, hidden), both[shift:].view(tokens, hidden)
+            inp, out = (hi, lo) if ahead else (lo, hi)
+            if shift < tokens * hidden:
+                names = [n.split("<")[0] for n in kernels_of(lambda s: forward(inp, out, s))]
+                assert "k_token_experts" not in names, names
+            inp.copy_(x)
+            got = tensor_to_host(forward(inp, out))
+            if same:
+                np.testing.assert_array_equal(got, want)
+            assert rel_err(to_f64(got), to_f64(want)) <= TOL[act]
+
+
 @pytest.mark.parametrize("tokens,experts,k,local,shared", [(33, 256, 4, 60, 1), (64, 256, 4, 63, 1), (65, 96, 3, 63, 2), (65, 256, 8, 254, 0), (128, 256, 8, 200, 0), (256, 64, 4, 61, 1), (257, 64, 4, 20, 4),
                                                            (511, 256, 4, 255, 1), (513, 256, 4, 256, 1), (1024, 256, 4, 129, 1), (1025, 256, 4, 129, 1)])
 def test_ring_kernels_derive_the_tiles_of_many_tokens(tokens, experts, k, local, shared):
