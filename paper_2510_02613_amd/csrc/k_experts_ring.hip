@@ -183,16 +183,22 @@ __device__ __forceinline__ void task_body(const Pass &p, const MTile &mt, int sl
     }
 }
 
+// GEMM-1 that reads the bookkeeping kernels' tile list: an instance of its own, without the code that derives tiles, which spills 56 scalars (in front of its K loops).
+// One kernel for both cost routed passes 0.3 to 0.7 % (whole pass, us, both in one -> this: DeepSeek-V2-Lite shape, 180 tokens on 32 experts 126.4 -> 125.7, on 16 78.7 -> 78.3, 120 on
+// 32 121.9 -> 121.1, Qwen3 shape 200 on 32 63.1 -> 62.9).
+struct TileList {};
+
 // kTiles: the most token tiles of 32 rows an M-tile has.
-// Table (NoTable or TableArg, or none): GEMM-1 of a token to four selects the experts too (see k_experts_decode.hip).  Whole pass, us, selection kernel -> here: Qwen3
+// How GEMM-1 comes by its tiles: TileList; NoTable or TableArg: a token to four, it selects the experts too (see k_experts_decode.hip); none: kSelf up to 64 tokens, else up
+// to 1024.  Selection, whole pass, us, selection kernel -> here: Qwen3
 // shape two tokens 39.7 -> 36.9, four 63.7 -> 61.0, four on half of its experts 36.0 -> 33.3; DeepSeek-V2-Lite shape three tokens 68.7 -> 66.2, four
 // 75.2 -> 72.5.  The limit on the workgroups is the register kernels', measured for both there.
-template <bool kFirst, bool kSelf, int kTiles, typename... Table>
-__global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... tab)
+template <bool kFirst, bool kSelf, int kTiles, typename... How>
+__global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, How... how)
 {
-    constexpr bool kSelect = sizeof...(Table) == 1;
+    constexpr bool kList = !kFirst || (std::is_same_v<How, TileList> || ...), kSelect = sizeof...(How) == 1 && !kList, kMany = !kSelf && !kList;
     static_assert(!kSelect || (kSelf && kSelectTokens == kWaves), "a GEMM-1 that selects derives its tiles too, a wavefront selects a token");
-    static_assert(!kSelf || kFirst, "only GEMM-1 derives its tiles itself");
+    static_assert(!kSelf || (kFirst && !kList), "only GEMM-1 derives its tiles itself");
     constexpr int BNO = kFirst ? kBN / 2 : kBN;             // output columns per task
     __shared__ __attribute__((aligned(1024))) char ring[kLds];
     const int N = kFirst ? p.I : p.H;
@@ -200,16 +206,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... ta
     int task = blockIdx.x;
     std::conditional_t<kSelect, SelfLds, SelfTables> src;
     static_assert(sizeof(SelectLds) <= kLds - 16384 && kSelfTableBytes <= 16384, "the selection borrows the ring, the tables are put together in front of it");
-    if constexpr (kSelect) src = select_few(p, *(SelectLds *)(ring + 16384), tab...);
-    // The tiles of up to 1024 tokens too are derived here (at run time, in the kernel that reads the list otherwise): a launch and its tables' round trips less, for
+    if constexpr (kSelect) src = select_few(p, *(SelectLds *)(ring + 16384), how...);
+    // The tiles of up to 1024 tokens too are derived here: a launch and its tables' round trips less, for
     // 1 to 2 us in front of a workgroup's stream (whole pass, us, k_scan_place -> here: 32 Qwen3 experts, 65 tokens 68.2 -> 65.6, 320 75.9 -> 73.1, 128 experts, 100 tokens 207.8 -> 203.0; DeepSeek-V2-Lite
     // shape 64 tokens 205.0 -> 201.7, 213 224.0 -> 218.1; 16 experts of 512, 1020 tokens 58.6 -> 55.8; no more tokens were measured).
-    const bool many = kFirst && !kSelf && p.table_blocks > 0;
-    if (kSelf || many) {
-        const int tables = many ? p.table_blocks : 1;
+    if constexpr (!kList) {
+        const int tables = kMany ? p.table_blocks : 1;
         if (task < tables) {
-            if (many) many_tables(p, kTiles * kRows, task, ring);
-            else      self_tables(p, kRows, ring, src);
+            if constexpr (kMany) many_tables(p, kTiles * kRows, task, ring);
+            else                 self_tables(p, kRows, ring, src);
             return;
         }
         task -= tables;
@@ -219,11 +224,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, Table... ta
     unsigned long long tokens = 0;
     int tok0 = 0;
     // in the last 8 KB, which the first copies leave alone: a ring of two token tiles ends before them, one of one copies there behind the first barrier
-    int32_t *tok = many ? (int32_t *)(ring + kLds - 8192) + (threadIdx.x >> 6) * (kTiles * kRows) : nullptr;
+    int32_t *tok = kMany ? (int32_t *)(ring + kLds - 8192) + (threadIdx.x >> 6) * (kTiles * kRows) : nullptr;
     static_assert(3 * Ring<2>::kStage <= kLds - 8192 && 3 * Ring<1>::kStage <= kLds - 8192, "what is copied before that barrier");
-    if (many) {
+    if constexpr (kMany) {
         if (!many_tile(p, threadIdx.x & 63, tile, kTiles * kRows, &mt, tok)) return;
-    } else if (kSelf) {
+    } else if constexpr (kSelf) {
         if (!self_tile(p, threadIdx.x & 63, tile, kRows, &mt, &tokens, &tok0, src)) return;
         if (kSelect) __syncthreads();   // everyone has read the masks: the ring is free
     } else {
@@ -250,18 +255,22 @@ int ring_blocks(const Pass &p) { return p.max_tiles * ((p.I + kBN / 2 - 1) / (kB
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st)
 {
     const dim3 block(kThreads), grid(which == 0 ? ring_blocks(p) + (p.table_blocks > 0 ? p.table_blocks : p.self_tiles ? 1 : 0) : p.max_tiles * ((p.H + kBN - 1) / kBN));
+    const bool many = p.table_blocks > 0;
     if (tile_rows > kRows) {
-        if (which == 0) hipLaunchKernelGGL((k_expert_ring<true, false, 2>), grid, block, 0, st, p);
-        else            hipLaunchKernelGGL((k_expert_ring<false, false, 2>), grid, block, 0, st, p);
+        if (which != 0) hipLaunchKernelGGL((k_expert_ring<false, false, 2>), grid, block, 0, st, p);
+        else if (many)  hipLaunchKernelGGL((k_expert_ring<true, false, 2>), grid, block, 0, st, p);
+        else            hipLaunchKernelGGL((k_expert_ring<true, false, 2, TileList>), grid, block, 0, st, p, TileList{});
     } else if (which == 0) {
         if (p.self_select && p.host_table) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1, TableArg>), grid, block, 0, st, p, fill_table(p));
         } else if (p.self_select) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1, NoTable>), grid, block, 0, st, p, NoTable{});
-        } else if (p.self_tiles && p.table_blocks == 0) {
+        } else if (many) {
+            hipLaunchKernelGGL((k_expert_ring<true, false, 1>), grid, block, 0, st, p);
+        } else if (p.self_tiles) {
             hipLaunchKernelGGL((k_expert_ring<true, true, 1>), grid, block, 0, st, p);
         } else {
-            hipLaunchKernelGGL((k_expert_ring<true, false, 1>), grid, block, 0, st, p);
+            hipLaunchKernelGGL((k_expert_ring<true, false, 1, TileList>), grid, block, 0, st, p, TileList{});
         }
     } else {
         hipLaunchKernelGGL((k_expert_ring<false, false, 1>), grid, block, 0, st, p);

@@ -677,6 +677,26 @@ def test_ring_kernels_derive_the_tiles_of_many_tokens(tokens, experts, k, local,
     both()
 
 
+@pytest.mark.parametrize("tokens,experts,k,routed,flags,tiles", [
+    (300, 64, 4, False, 0, "2"), (300, 64, 4, True, 0, "2, TileList"), (300, 64, 4, False, 8, "2, TileList"), (1024, 256, 4, False, 0, "2"), (1025, 256, 4, False, 0, "2, TileList"),
+    (90, 96, 4, False, 0, "1"), (90, 96, 4, True, 0, "1, TileList"), (47, 96, 4, True, 0, "1, TileList"), (47, 96, 4, False, 8, "1, TileList")])
+def test_ring_kernels_that_read_the_tile_list(tokens, experts, k, routed, flags, tiles):
+    """Which instance of the ring's GEMM-1 a pass launches: the one that reads the list behind every pass with a bookkeeping kernel.  (Nothing runs.)"""
+    import types
+    import torch
+    from gpu_util import kernels_of
+    from paper_2510_02613_amd.layer import MoELayer
+    layer = MoELayer(hidden=320, inter=320, n_experts=experts, top_k=k, n_slots=experts, max_tokens=tokens, act_dtype="bf16", router_dtype="f32",
+                     gate="softmax", router_w=np.zeros((experts, 320), np.float32))
+    layer.set_expert_map(list(range(experts)))
+    x = torch.empty(tokens, 320, dtype=torch.int16, device="cuda:0")
+    ids, w = (torch.zeros((tokens, k), dtype=t, device=x.device) for t in (torch.int32, torch.float32))
+    out = torch.empty_like(x)
+    names = kernels_of(lambda s: layer.forward_routed(x, ids, w, out=out, flags=flags, stream=s) if routed else layer.forward(x, out=out, flags=flags, stream=s))
+    assert f"k_expert_ring<true, false, {tiles}>" in names, names
+    assert any(n.split("<")[0] in ("k_scan_place", "k_hist_place", "k_slot_place", "k_permute_one_block") for n in names) == ("TileList" in tiles), names
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 3])
 @pytest.mark.parametrize("hidden,inter", [(136, 512), (72, 520), (64, 1024), (104, 1544), (4096, 72), (4104, 72)])
 def test_second_gemm_and_combine_of_a_token_or_two(tokens, hidden, inter):

@@ -77,3 +77,15 @@ def test_wavefronts_per_simd(kernels, pattern, waves):
     for name, k in mine.items():
         assert _waves(k) >= waves, (name, k[".vgpr_count"])
         assert k[".private_segment_fixed_size"] == 0 and k[".vgpr_spill_count"] == 0, name
+
+
+def test_scalar_spills_of_the_ring_kernels(kernels):
+    """Kernels that read the tile list (GEMM-2, and GEMM-1 of routed passes, of more than 1024 tokens or 256 slots) hold nothing of the code that derives tiles: no scalar
+    is spilled, GEMM-1 needs the registers that GEMM-2 needs.  That code's own spills lie in front of its K loops."""
+    mine = {n: k for n, k in kernels.items() if n.startswith("k_expert_ring<")}
+    for tiles in (1, 2):
+        first, second = mine.pop(f"k_expert_ring<true, false, {tiles}, TileList>"), mine.pop(f"k_expert_ring<false, false, {tiles}>")
+        assert first[".sgpr_spill_count"] == second[".sgpr_spill_count"] == 0
+        assert first[".vgpr_count"] <= second[".vgpr_count"]
+    for name, k in mine.items():
+        assert k[".sgpr_spill_count"] <= (56 if name in ("k_expert_ring<true, false, 1>", "k_expert_ring<true, false, 2>") else 0), name
