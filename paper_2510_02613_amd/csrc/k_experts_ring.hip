@@ -209,7 +209,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, How... how)
     if constexpr (kSelect) src = select_few(p, *(SelectLds *)(ring + 16384), how...);
     // The tiles of up to 1024 tokens too are derived here: a launch and its tables' round trips less, for
     // 1 to 2 us in front of a workgroup's stream (whole pass, us, k_scan_place -> here: 32 Qwen3 experts, 65 tokens 68.2 -> 65.6, 320 75.9 -> 73.1, 128 experts, 100 tokens 207.8 -> 203.0; DeepSeek-V2-Lite
-    // shape 64 tokens 205.0 -> 201.7, 213 224.0 -> 218.1; 16 experts of 512, 1020 tokens 58.6 -> 55.8; no more tokens were measured).
+    // shape 64 tokens 205.0 -> 201.7, 213 224.0 -> 218.1; 16 experts of 512, 1020 tokens 58.6 -> 55.8; where it costs more than it saves: self_table_blocks).
     if constexpr (!kList) {
         const int tables = kMany ? p.table_blocks : 1;
         if (task < tables) {
@@ -247,10 +247,22 @@ __global__ __launch_bounds__(kThreads, 2) void k_expert_ring(Pass p, How... how)
 
 int ring_tile_rows(bool large) { return large ? 2 * kRows : kRows; }
 
-// (sums of rows are kept in 15 bits)
-int self_table_blocks(const Pass &p) { return p.fused_hist && p.S <= kSelfMaxSlots && p.T <= kManyBlocks * kFusedTokens && p.T * p.kk < (1 << 15) ? table_blocks(p) : 0; }
-
 int ring_blocks(const Pass &p) { return p.max_tiles * ((p.I + kBN / 2 - 1) / (kBN / 2)); }
+
+// Every wavefront of GEMM-1 adds up the count bytes of all slots: 16-byte loads of a lane, one per 64 slots and 256 tokens, in each workgroup.  With rows of 1024 and more they
+// hide behind the weight stream (whole pass, us, k_scan_place -> derived: 256 slots of 2048 x 768, 576 tokens 399 -> 392, of 2048 x 64, 1024 76 -> 73 and 78 -> 77; 250 of 1024 x 192, 700 76.0 -> 74.9,
+// 1024 78.4 -> 78.6).  Shorter rows end too soon for that: up to 5500 loads of all workgroups' lanes derived (256 slots of 128 x 128, 512 tokens, 4600 loads 28.0 -> 26.3, of 512 x 64, 1024, 5100 36.8 -> 36.1; 128 of
+// 320 x 192, 1024, 4600 33.5 -> 31.0), above list (128 slots of 256 x 256, 784 tokens, 5700 loads 31.9 -> 32.4, 640 x 256, 1024, 6100 47.3 -> 48.2; 256 of 128 x 128, 640, 7100 28.1 -> 29.2, 320 x 320, 1024, 25600
+// 56.0 -> 61.8, 256 x 256 43.3 -> 48.9).  What that leaves: up to 512 tokens some would gain further up (256 slots of 192 x 192, 6900 loads 34.8 -> 33.8; 256 x 256, 9200 41.0 -> 42.8).
+constexpr int kLongRow = 1024, kManyLoads = 5500;
+
+// (sums of rows are kept in 15 bits)
+int self_table_blocks(const Pass &p)
+{
+    if (!p.fused_hist || p.S > kSelfMaxSlots || p.T > kManyBlocks * kFusedTokens || p.T * p.kk >= (1 << 15)) return 0;
+    const int loads = (p.S + 63) / 64 * ((p.T + 16 * kFusedTokens - 1) / (16 * kFusedTokens));
+    return p.H >= kLongRow || ring_blocks(p) * loads <= kManyLoads ? table_blocks(p) : 0;
+}
 
 hipError_t launch_experts_ring(const Pass &p, int tile_rows, int which, hipStream_t st)
 {

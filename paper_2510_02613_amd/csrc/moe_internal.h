@@ -148,7 +148,7 @@ int f32_tile_rows(const Pass &p);
 // GEMM-1 of these can derive its tiles itself (Pass::self_tiles) when the selection kernel left per-block masks for
 // at most 4 blocks of tokens and 256 slots: no bookkeeping kernel in front of it
 inline bool self_tiles_possible(const Pass &p) { return p.fused_hist && p.S <= 256 && p.T <= 4 * 16; }
-int self_table_blocks(const Pass &p);   // k_expert_ring, up to 64 blocks: workgroups that write the tables, 0: not possible
+int self_table_blocks(const Pass &p);   // k_expert_ring, up to 64 blocks: workgroups that write the tables, 0: not possible, or slower than the bookkeeping kernel (max_tiles is set)
 // everything behind the gate and the bookkeeping in one launch, for few tokens of small layers
 bool token_experts_supports(const Pass &p);
 hipError_t launch_token_experts(const Pass &p, int tile_rows, hipStream_t st);

@@ -1,5 +1,5 @@
-// Tiles derived by the expert GEMM-1 itself, for passes of at most 64 tokens: shared by the weight-streaming bf16
-// kernels (registers and LDS ring), the fp32 kernel and the token-by-token one.
+// Tiles derived by the expert GEMM-1 itself: for passes of at most 64 tokens, shared by the weight-streaming bf16
+// kernels (registers and LDS ring), the fp32 kernel and the token-by-token one, and for up to 1024 by the LDS ring (many_*, below).
 #pragma once
 #include "gate_select.h"
 #include "moe_internal.h"

@@ -678,7 +678,7 @@ def test_ring_kernels_derive_the_tiles_of_many_tokens(tokens, experts, k, local,
 
 
 @pytest.mark.parametrize("tokens,experts,k,routed,flags,tiles", [
-    (300, 64, 4, False, 0, "2"), (300, 64, 4, True, 0, "2, TileList"), (300, 64, 4, False, 8, "2, TileList"), (1024, 256, 4, False, 0, "2"), (1025, 256, 4, False, 0, "2, TileList"),
+    (300, 64, 4, False, 0, "2"), (300, 64, 4, True, 0, "2, TileList"), (300, 64, 4, False, 8, "2, TileList"), (1024, 256, 4, False, 0, "2, TileList"), (1025, 256, 4, False, 0, "2, TileList"),
     (90, 96, 4, False, 0, "1"), (90, 96, 4, True, 0, "1, TileList"), (47, 96, 4, True, 0, "1, TileList"), (47, 96, 4, False, 8, "1, TileList")])
 def test_ring_kernels_that_read_the_tile_list(tokens, experts, k, routed, flags, tiles):
     """Which instance of the ring's GEMM-1 a pass launches: the one that reads the list behind every pass with a bookkeeping kernel.  (Nothing runs.)"""
@@ -695,6 +695,26 @@ def test_ring_kernels_that_read_the_tile_list(tokens, experts, k, routed, flags,
     names = kernels_of(lambda s: layer.forward_routed(x, ids, w, out=out, flags=flags, stream=s) if routed else layer.forward(x, out=out, flags=flags, stream=s))
     assert f"k_expert_ring<true, false, {tiles}>" in names, names
     assert any(n.split("<")[0] in ("k_scan_place", "k_hist_place", "k_slot_place", "k_permute_one_block") for n in names) == ("TileList" in tiles), names
+
+
+@pytest.mark.parametrize("tokens,slots,hidden,inter,derives", [
+    (1024, 256, 1024, 64, True), (1024, 256, 960, 64, True), (700, 256, 960, 128, False), (256, 256, 320, 256, True), (257, 256, 320, 256, False),
+    (512, 256, 128, 128, True), (513, 256, 128, 128, False), (512, 256, 256, 256, False), (1024, 128, 320, 192, True), (1024, 128, 320, 256, False), (1024, 64, 320, 320, True)])
+def test_ring_kernels_derive_tiles_where_that_is_cheap(tokens, slots, hidden, inter, derives):
+    """GEMM-1 on both sides of the line on its workgroups times what each adds up, short rows and long ones: the pass's launches, and the same bits as with the separate bookkeeping kernels."""
+    from gpu_util import Case, kernels_of
+    from paper_2510_02613_amd import binding as B
+    wl = MoEWorkload(name="cheap", tokens=tokens, hidden=hidden, inter=inter, n_experts=256, top_k=4, n_slots=slots, n_local=slots, act_dtype="bf16", router_dtype="bf16", gate="softmax", seed=2300 + tokens)
+    case = Case(wl)
+    out = case.x_dev.clone()
+    names = kernels_of(lambda s: case.layer.forward(case.x_dev, out=out, stream=s))
+    first = next(n for n in names if n.startswith("k_expert_ring<true"))
+    assert ("TileList" not in first) == derives == (not any(n.startswith("k_scan_place") for n in names)), names
+    out, v = case.run(), case.layer.view(tokens)
+    np.testing.assert_array_equal(case.run(flags=B.MOE_FLAG_PERMUTE_UNFUSED), out)
+    w = case.layer.view(tokens)
+    for key in ("counts", "offsets", "perm", "inv", "tiles", "h", "y"):
+        np.testing.assert_array_equal(v[key], w[key])
 
 
 @pytest.mark.parametrize("tokens", [1, 2, 3])
