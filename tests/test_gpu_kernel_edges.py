@@ -69,6 +69,41 @@ def test_last_round_of_the_large_tiles_in_parts(hidden, inter, rows, parts):
     _check(case, ids, g.uniform(0.5, 1.5, size=ids.shape).astype(np.float32))
 
 
+@pytest.mark.parametrize("hidden,inter,more,big,parts", [(512, 256, 79, False, (8, 8)), (448, 448, 103, False, (4, 8)), (448, 448, 103, True, (4, 4)), (64, 128, 223, False, (8, 8))])
+def test_a_split_last_round_has_the_bits_of_whole_slices(hidden, inter, more, big, parts):
+    """17 experts' tokens alone, whose slices run as two or four workgroups each, and beside `more` other experts, whose launches have a whole round or most of one: the same bits in h and in the output."""
+    import torch
+    from gpu_util import kernels_of
+    from paper_2510_02613_amd.layer import MoELayer
+    counts = [193, 224, 225, 239, 240, 241, 255, 256, 257, 272, 273, 288, 289, 304, 305, 319, 320] if big else [1, 32, 33, 64, 65, 97, 128, 129, 160, 161, 193, 225, 256, 257, 288, 289, 320]
+    experts, dev = len(counts) + more, torch.device("cuda:0")
+    round_rows = torch.cuda.get_device_properties(dev).multi_processor_count // 8
+    gen = torch.Generator(device=dev).manual_seed(380 + hidden)
+    ids = torch.repeat_interleave(torch.arange(experts, device=dev), torch.tensor(counts + [64] * more, device=dev)).to(torch.int32)[:, None].contiguous()
+    x = torch.randn(len(ids), hidden, generator=gen, device=dev).bfloat16().view(torch.int16)
+    weights = [(torch.randn(experts, *s, generator=gen, device=dev) * 0.1).bfloat16().view(torch.int16) for s in ((2 * inter, hidden), (hidden, inter))]
+
+    def run(n, tokens):
+        layer = MoELayer(hidden=hidden, inter=inter, n_experts=n, top_k=1, n_slots=n, max_tokens=tokens, act_dtype="bf16", router_dtype="f32", gate="softmax",
+                         router_w=np.zeros((n, hidden), np.float32))
+        layer.w13.copy_(weights[0][:n])
+        layer.w2.copy_(weights[1][:n])
+        layer.set_expert_map(list(range(n)))
+        w, out = torch.ones((tokens, 1), device=dev), torch.empty_like(x[:tokens])
+        names = kernels_of(lambda s: layer.forward_routed(x[:tokens], ids[:tokens], w, out=out, stream=s))
+        layer.forward_routed(x[:tokens], ids[:tokens], w, out=out)
+        v = layer.view(tokens)
+        return ([int(k.rstrip(">").split(", ")[-1]) for k in names if k.startswith("k_expert_gemm_mfma8") and ", 0, " in k], out.cpu().numpy(), v["h"][v["inv"][:, 0]], v["unit_hdr"][:, 0])
+    own = sum(counts)
+    split, out, h, rows = run(len(counts), own)
+    whole, out_whole, h_whole, rows_whole = run(experts, len(ids))
+    assert split == list(parts) and whole == [2, 2]
+    for r, part in zip(rows, parts):
+        assert 0 < r % round_rows * (part // 2) <= round_rows, rows       # the unit list has such a round
+    np.testing.assert_array_equal(out, out_whole[:own])
+    np.testing.assert_array_equal(h, h_whole[:own])
+
+
 @pytest.mark.parametrize("hidden,inter", [(64, 192), (320, 128)])
 def test_large_tiles_stage_by_8_rows_and_multiply_by_16(hidden, inter):
     """Slots of more than 128 rows that end just before, at and behind multiples of 8 and 16, in each half of a 32-row tile and
