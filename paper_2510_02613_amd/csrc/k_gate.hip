@@ -417,11 +417,18 @@ hipError_t launch_logits_bf16(const Pass &p, int *planes, hipStream_t st)
 {
     // Up to a hundred or so tokens there are too few (token, expert) tiles for the LDS-tiled kernels: the
     // K-split kernel reads both operands straight into registers, 16 tokens x 16 experts per workgroup, and
-    // shares the contraction out over its wavefronts and over workgroups, until the router, which it reads once per 16 tokens, comes to 16 MB (gate phase, us, this kernel ->
-    // the direct-to-LDS one: DeepSeek-V3-shaped rank 64 tokens, 15 MB, 17.5 -> 18.2, 80, 18 MB, 19.6 -> 18.4, 128, 29 MB, 21.4 -> 18.7; Qwen3 shape 128, 8 MB, 13.1 -> 13.7, 144 13.9 -> 13.9).  (Without the direct-to-LDS
-    // kernel -- H not a multiple of 64 -- it stays ahead until the router re-reads reach about 128 MB.)
-    const size_t router_rereads = (size_t)((p.T + 15) / 16) * p.E * p.H * (p.router_bf16 ? 2 : 4);
-    const bool small = gate_dma_supports(p) ? p.T <= 128 && router_rereads <= (size_t)16 << 20 : (p.T <= kGateFewTokens || router_rereads <= (size_t)128 << 20);
+    // shares the contraction out over its wavefronts and over workgroups.  Up to 128 tokens it is ahead of the direct-to-LDS kernel (gate phase, us, this kernel -> that one)
+    //  * for one block of tokens, whatever the router's size (512 experts on rows of 8192, fp32, one token 14.3 -> 18.4, 16 tokens 19.1 -> 22.4; 1024 on rows of 7168, bf16, 1 and 16
+    //    34.6 -> 34.9, 42.6 -> 42.2);
+    //  * while the router, which it reads once per block, comes to 16 MB (256 on rows of 7168, bf16, 32 tokens 14.2 -> 15.2, 64, 15 MB, 15.8 -> 15.4, 80, 18 MB, 17.8 -> 15.4, 128 19.2 -> 15.6; 128 on rows of 2048,
+    //    fp32, 128, 8 MB, 13.1 -> 13.7; 256 on rows of 4096, fp32, 64, 16 MB, 15.8 -> 16.3, 65, 20 MB, 17.3 -> 16.4);
+    //  * with an fp32 router, which the other one splits into three planes, while blocks of tokens times experts come to 1024 at most (rows of 7168, 256 experts, 64 tokens 19.0 -> 19.4, 65 21.6 -> 19.6; 384, 32
+    //    21.1 -> 21.6, 33 23.3 -> 21.9; 128, 96 17.8 -> 18.2; 512 on rows of 8192, 32 22.1 -> 22.8, 33 25.5 -> 23.4).
+    // (Without the direct-to-LDS kernel -- H not a multiple of 64 -- it stays ahead until the router re-reads reach about 128 MB.)
+    const int blocks = (p.T + 15) / 16;
+    const size_t router_rereads = (size_t)blocks * p.E * p.H * (p.router_bf16 ? 2 : 4);
+    const bool few = blocks == 1 || router_rereads <= (size_t)16 << 20 || (!p.router_bf16 && blocks * p.E <= 1024);
+    const bool small = gate_dma_supports(p) ? p.T <= 128 && few : (p.T <= kGateFewTokens || router_rereads <= (size_t)128 << 20);
     *planes = 1;
     if (!p.gate_tiled && small) {
         *planes = few_token_planes(p.T, p.H);

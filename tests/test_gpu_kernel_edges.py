@@ -240,6 +240,24 @@ def test_gate_tilings_by_rounds_of_the_chip(router, experts, hidden, tokens, til
     check_routing(case, v["topk_ids"], v["topk_w"])
 
 
+@pytest.mark.parametrize("router,experts,hidden,tokens,direct", [
+    ("f32", 512, 8256, 1, False), ("f32", 512, 8256, 32, False), ("f32", 512, 8256, 33, True), ("f32", 384, 7168, 32, False), ("f32", 384, 7168, 33, True), ("f32", 256, 7168, 64, False),
+    ("f32", 256, 7168, 65, True), ("f32", 128, 7168, 128, False), ("f32", 128, 7168, 129, True), ("f32", 256, 4096, 64, False), ("f32", 256, 4096, 65, True), ("f32", 256, 2048, 128, False),
+    ("bf16", 1024, 8256, 16, False), ("bf16", 1024, 8256, 17, True), ("bf16", 256, 7168, 64, False), ("bf16", 256, 7168, 65, True)])
+def test_gate_of_few_tokens_by_the_router_s_size(router, experts, hidden, tokens, direct):
+    """The logits kernel on both sides of the lines on blocks of tokens, bytes of router and experts (direct: the one with direct copies to LDS).  Routing of every token against the oracle."""
+    from gpu_util import Case, check_routing, kernels_of
+    wl = MoEWorkload(name="gate_few", tokens=tokens, hidden=hidden, inter=8, n_experts=experts, top_k=3, n_slots=2, n_local=2,
+                     act_dtype="bf16", router_dtype=router, gate="softmax", seed=70 + experts)
+    case = Case(wl)
+    spare = case.x_dev.clone()
+    names = [n.split("<")[0] for n in kernels_of(lambda s: case.layer.forward(case.x_dev, out=spare, stream=s))]
+    assert ("k_gate_logits_dma" in names) == direct == ("k_gate_logits" not in names), names
+    case.run()
+    v = case.layer.view(tokens)
+    check_routing(case, v["topk_ids"], v["topk_w"])
+
+
 @pytest.mark.parametrize("tokens", [1, 2, 15, 32, 47, 64, 90])
 @pytest.mark.parametrize("hidden,inter", [(64, 64), (128, 448), (192, 64), (320, 128), (768, 1024)])
 def test_decode_ring_kernels(tokens, hidden, inter):
