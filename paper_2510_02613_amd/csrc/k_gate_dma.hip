@@ -279,9 +279,11 @@ hipError_t launch_t(const Pass &p, int planes, hipStream_t st)
 }
 
 // The tilings: tokens x experts of a workgroup, and the us that one of its K-steps takes (bf16, fp32 router), measured on 150 to 8000 tokens of 64, 128 and 256
-// experts on rows of 2048 and 7168.
+// experts on rows of 2048 and 7168.  Two workgroups of the first one with a bf16 router have their LDS on a compute unit (72 KB each; of all others one): alone one takes 0.16 us a step, two
+// together 0.30.  Its 0.21 stands for both, and a launch of it that is counted as two rounds is in truth one of pairs.
 struct Tiling { int tokens, experts[2]; float step[2]; };
 constexpr Tiling kTilings[3] = {{32, {64, 64}, {0.21f, 0.45f}}, {64, {128, 128}, {0.38f, 0.8f}}, {128, {256, 128}, {0.95f, 1.1f}}};
+constexpr int kChipUnits = 256;                            // the step times are of a whole chip; on a part of one only the choice would be another
 constexpr float kTileUs = 0.5f, kPlaneBytesPerUs = 6e6f;   // a workgroup's start and end; the planes' way out and back
 
 }  // namespace
@@ -295,11 +297,13 @@ bool gate_dma_supports(const Pass &p)
 // Writes *planes partial-sum planes [T,E] to p.logits.
 hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st)
 {
-    // The tiling and the K split (at most kGatePlanes, at least 4 K-steps each) with the shortest time by that measure: rounds of the 256 compute units, each with one workgroup, times
+    // The tiling and the K split (at most kGatePlanes, at least 4 K-steps each) with the shortest time by that measure: rounds of the chip's compute units, each with one workgroup, times
     // K-steps, and what the planes cost.  What matters is that a launch is one round: the largest tiling that filled the chip, split into ceil(256 / tiles), was
     // a little more than one round nearly everywhere.  Gate phase, us, that -> this: 128 experts on rows of 2048 (fp32 router) 333 tokens 15.3 -> 13.7, 1100 21.1 -> 17.2, 2200 28.8 -> 18.7,
     // 3000 28.7 -> 20.2, 6000 37.4 -> 29.1, where it was one round 4096 22.0 -> 22.0; 256 on rows of 7168 (bf16) 512 tokens 20.3 -> 20.3, 700 28.0 -> 22.5, 2500 37.1 -> 29.7,
-    // 5000 62.4 -> 45.0, 8000 81.2 -> 61.4; 64 on rows of 2048 2500 20.4 -> 16.7.  The best of all (tiling, split) pairs is 0.3 % faster on average over 47 such sizes.
+    // 5000 62.4 -> 45.0, 8000 81.2 -> 61.4; 64 on rows of 2048 2500 20.4 -> 16.7.  The best of all (tiling, split) pairs is 0.3 % faster on average over 47 such sizes,
+    // and 0.7 % over 168: 130 to 8000 tokens of 14 routers, 60 to 512 experts on rows of 1024 to 7168 (at worst 11 %, 128 experts on rows of 2048, bf16, 2200 tokens 17.6 us -> 15.9).  Counting the pairs above
+    // (0.16, 0.30) comes to 0.6 %, six of seven changed choices 1 to 10 % faster, but 384 experts on rows of 7168, 333 tokens 23.3 -> 25.3: not taken.
     const int KT = p.H / kBK, f32 = p.router_bf16 ? 0 : 1;
     int cfg = 0, z = 1;
     float best = 0.f;
@@ -308,7 +312,7 @@ hipError_t launch_gate_logits_dma(const Pass &p, int *planes, hipStream_t st)
         if (c > 0 && p.E <= t.experts[f32] / 2) continue;      // mostly padding
         const long long tiles = (long long)((p.T + t.tokens - 1) / t.tokens) * ((p.E + t.experts[f32] - 1) / t.experts[f32]);
         for (int n = 1; n <= kGatePlanes && (n == 1 || KT / n >= 4); ++n) {
-            const float us = (float)((tiles * n + 255) / 256) * (kTileUs + (float)((KT + n - 1) / n) * t.step[f32]) + (float)n * (float)p.T * (float)p.E * 8.f / kPlaneBytesPerUs;
+            const float us = (float)((tiles * n + kChipUnits - 1) / kChipUnits) * (kTileUs + (float)((KT + n - 1) / n) * t.step[f32]) + (float)n * (float)p.T * (float)p.E * 8.f / kPlaneBytesPerUs;
             if ((c == 0 && n == 1) || us < best) { best = us; cfg = c; z = n; }
         }
     }
